@@ -368,6 +368,14 @@ extern "C" int kv_pool_write(hkv_pool *pool, const int32_t *page_ids, int32_t fi
             return fail(HKV_ERANGE, "kv_pool_write: page id %d (entry %lld) outside pool of %d pages", page_ids[i],
                         (long long)i, pool->d.num_pages);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (n_pg <= kMaxInlineWrite && pool->d.dtype != HKV_FP32) {  // the ids travel in the kernel arguments: one launch, no staging
+        int32_t ids[kMaxInlineWrite];
+        for (int64_t b = b0; b <= b1; ++b) ids[b - b0] = page_ids[b / S] * S + (int32_t)(b % S);
+        const PoolWriteLaunch a{pool->d.k_pages, pool->d.v_pages, pool->d.k_scale, pool->d.v_scale, pool->d.num_kv_heads, pool->d.dtype,
+                                nullptr, (int32_t)n_pg, first_slot % HKV_PAGE_SIZE, n_tokens, k_src, v_src, nullptr, ids};
+        HKV_HIP(launch_pool_write(a, s));
+        return HKV_OK;
+    }
     if (int rc = ensure_write_staging(pool)) return rc;
     const int slot = pool->next_slot;
     pool->next_slot = (slot + 1) % hkv_pool::kWriteSlots;
@@ -378,7 +386,7 @@ extern "C" int kv_pool_write(hkv_pool *pool, const int32_t *page_ids, int32_t fi
     // a copy kernel on the stream reads the pinned slot (a DMA copy between kernels of one stream costs more)
     HKV_HIP(launch_upload(pool->hd_ids + (size_t)slot * hkv_pool::kMaxWritePages, d, align_up(sizeof(int32_t) * (size_t)n_pg, 16), s));
     PoolWriteLaunch a{pool->d.k_pages, pool->d.v_pages, pool->d.k_scale, pool->d.v_scale, pool->d.num_kv_heads,
-                      pool->d.dtype, d, (int32_t)n_pg, first_slot % HKV_PAGE_SIZE, n_tokens, k_src, v_src, nullptr};
+                      pool->d.dtype, d, (int32_t)n_pg, first_slot % HKV_PAGE_SIZE, n_tokens, k_src, v_src, nullptr, nullptr};
     if (pool->d.dtype == HKV_FP32)
         HKV_HIP(launch_pool_write_fp32(a, s));
     else
@@ -419,7 +427,7 @@ extern "C" int kv_pool_append(hkv_pool *pool, const int32_t *page_ids, const int
     if (n <= kMaxInlineAppend) {  // the usual decode batch: everything travels in the kernel arguments
         PoolAppendInline a{};
         a.base = PoolWriteLaunch{pool->d.k_pages, pool->d.v_pages, pool->d.k_scale, pool->d.v_scale, pool->d.num_kv_heads,
-                                 pool->d.dtype, nullptr, n, 0, n, k_src, v_src, nullptr};
+                                 pool->d.dtype, nullptr, n, 0, n, k_src, v_src, nullptr, nullptr};
         for (int i = 0; i < n; ++i) {
             a.block[i] = page_ids[i] * S + slots[i] / HKV_PAGE_SIZE;
             a.slot[i] = (uint8_t)(slots[i] % HKV_PAGE_SIZE);
@@ -439,7 +447,7 @@ extern "C" int kv_pool_append(hkv_pool *pool, const int32_t *page_ids, const int
     }
     HKV_HIP(launch_upload(pool->hd_ids + (size_t)slot * hkv_pool::kMaxWritePages, d, align_up(sizeof(int32_t) * 2 * (size_t)n, 16), s));
     PoolWriteLaunch a{pool->d.k_pages, pool->d.v_pages, pool->d.k_scale, pool->d.v_scale, pool->d.num_kv_heads,
-                      pool->d.dtype, d, n, 0, n, k_src, v_src, d + n};
+                      pool->d.dtype, d, n, 0, n, k_src, v_src, d + n, nullptr};
     HKV_HIP(launch_pool_write(a, s));
     HKV_HIP(hipEventRecord(pool->slot_free[slot], s));
     pool->slot_in_flight[slot] = true;
@@ -1197,7 +1205,7 @@ static int plan_append(hkv_decode_plan *plan, const int32_t *new_page_ids, const
         g.n_req = plan->n_req;
         if (with_tokens) {  // the same launch stores the tokens
             w.base = PoolWriteLaunch{pool->d.k_pages, pool->d.v_pages, pool->d.k_scale, pool->d.v_scale, Hkv, pool->d.dtype,
-                                     nullptr, plan->n_req, 0, plan->n_req, k_src, v_src, nullptr};
+                                     nullptr, plan->n_req, 0, plan->n_req, k_src, v_src, nullptr, nullptr};
             HKV_HIP(launch_decode_step_append(w, g, s));
         } else {
             HKV_HIP(launch_plan_grow_inline(g, s));

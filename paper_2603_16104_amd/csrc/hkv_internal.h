@@ -111,7 +111,11 @@ struct PoolWriteLaunch {
     // (i, head) stores source row i at slot slots[i] (0..15) of block page_ids[i]; first_slot and
     // n_tokens are not used.
     const int32_t *slots;        // device
+    // The block ids on the host (null: page_ids above): up to kMaxInlineWrite of them travel in the kernel's
+    // arguments; page_ids is then not read.  bf16 and fp8 pools, runs of tokens only.
+    const int32_t *host_ids;
 };
+constexpr int kMaxInlineWrite = 960;  // with the rest of the arguments below 4 KiB
 
 // One token for each of up to kMaxInlineAppend sequences, ids and slots by value.
 constexpr int kMaxInlineAppend = 256;
