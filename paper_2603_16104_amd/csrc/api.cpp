@@ -4,6 +4,7 @@
 #include "hkv_internal.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -100,6 +101,7 @@ struct hkv_decode_plan {
     DecodeItem *d_items = nullptr, *d_tile_items = nullptr;
     int32_t n_single = 0;  // items [0, n_single) run one per workgroup, the rest four per workgroup
     int32_t n_stages = 3;  // LDS stages of 16 KiB per workgroup of the per-node kernel
+    bool has_shared = false;  // some item of `items` is shared by more than 16 query rows
     bool fp8_matrix = false;  // fp8 pools: both products on the fp8 matrix instruction (HKV_PLAN_FP8_MATRIX)
     hkv_decode_plan_params opt{};  // the planner's settings (0 = the library's choice)
     int32_t *d_pages = nullptr, *d_node_req_idx = nullptr, *d_part_count = nullptr;
@@ -636,7 +638,6 @@ static void plan_items(hkv_decode_plan &pl) {
     // fewer (node, head) units than workgroups fit on the chip at once; then they are cut, but not
     // below 256 tokens.  Nodes shared by more rows run one row tile per wavefront over all tokens
     // of the item, so their chunks are kept near the typical leaf-type item to finish together.
-    const int kResidentGroups = chip.n_cu * (pl.pool->d.dtype == HKV_FP8_E4M3 ? 2 : 3);  // workgroups the chip holds at once
     // Nodes shared by many rows go to the 256-row tile kernel (not with per-row visibility, which that kernel
     // does not know, and not when the caller asked for the fp8 matrix instruction).
     const int tile_min_rows = or_default(opt.tile_min_rows, 128);
@@ -657,6 +658,13 @@ static void plan_items(hkv_decode_plan &pl) {
         return tiles_pay && !pl.no_tiles && !pl.fp8_matrix && pl.nodes[v].n_tokens > 0 &&
                R * G >= std::max(tile_min_rows, kMinTileItemRows);
     };
+    bool any_shared = false;  // nodes for shared::body (or, with the fp8 matrix instruction, its forerunner)
+    for (int v = 0; v < n_nodes; ++v) {
+        const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
+        any_shared = any_shared || (pl.nodes[v].n_tokens > 0 && R * G > 16 && !tiled(v));
+    }
+    // workgroups the chip holds at once: two per compute unit with fp8 pools or with shared::body in the launch, else three
+    const int kResidentGroups = chip.n_cu * (pl.pool->d.dtype == HKV_FP8_E4M3 || any_shared ? 2 : 3);
     int64_t leaf_units = 0, leaf_tokens = 0, shared_units = 0;
     for (int v = 0; v < n_nodes; ++v) {
         int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
@@ -680,9 +688,9 @@ static void plan_items(hkv_decode_plan &pl) {
     // every item a start-up, while a long item is the last to finish; measured on forests with 2k to 9k
     // shared tokens the best chunk is about a sixth of the path, between 512 and 1024 tokens.  Beyond
     // 16k shared tokens the chunks grow further so that a row collects about 16 partials at most.
+    int64_t longest = 0;  // most shared tokens on one path
     {
         std::vector<int64_t> shared_above(n_nodes, 0);
-        int64_t longest = 0;
         for (int v = 0; v < n_nodes; ++v) {
             const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
             const int64_t up = pl.nodes[v].parent >= 0 ? shared_above[pl.nodes[v].parent] : 0;
@@ -717,6 +725,81 @@ static void plan_items(hkv_decode_plan &pl) {
             units += (int64_t)Hkv * (cut_for_packing(T) ? (T + pack_tokens - 1) / pack_tokens : 1);
         }
         cut_leaves = any && (pack_mode == 3 || units > kResidentGroups);
+    }
+    // Items of more than 16 rows: how long a chunk?  Such an item costs a start-up, a hand-over between its wavefronts and
+    // a partial per row (6 us together) beside 0.8 us per 64 tokens alone and 1.1 to 2.9 us on a full chip (from L2 / from
+    // HBM); two run on a compute unit, dispatched in front of the others, which fill what they leave free.  So a chunk
+    // that puts a few items into a second round, or leaves the others no room beside the first, costs a whole further
+    // item: 4096 tokens x 512 rows + 8 x 1024 x 64 + 128 private leaves, bf16, takes 47 us cut into 768 tokens (512 such
+    // items), 31 us at 1024 (320), 36 us at 1376 (256).  From the length above up to the longest there is, the one with
+    // the shortest estimated step is taken.
+    int piece_tokens = pack_tokens;
+    if (any_shared && !pl.fp8_matrix && opt.shared_chunk == 0 && opt.leaf_chunk == 0) {
+        const bool fp8 = pl.pool->d.dtype == HKV_FP8_E4M3;
+        const int64_t slots = kResidentGroups;
+        double through = 0, unique = 0, other_steps = 0;  // tokens through workgroups, tokens read from HBM; steps of the other items
+        int64_t other_units = 0, rows_below = 0;
+        for (int v = 0; v < n_nodes; ++v) {
+            const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
+            if (pl.nodes[v].n_tokens == 0 || R == 0 || tiled(v)) continue;
+            if (R * G > 16) {
+                through += (double)pl.nodes[v].n_tokens * ((R + max_req_per_item - 1) / max_req_per_item);
+                unique += pl.nodes[v].n_tokens;
+                rows_below = std::max<int64_t>(rows_below, (int64_t)R * pl.num_q_heads);
+            } else {
+                const int pieces = cut_leaves && cut_for_packing(pl.nodes[v].n_tokens) ? (pl.nodes[v].n_tokens + pack_tokens - 1) / pack_tokens : 1;
+                other_units += (int64_t)pieces * Hkv;
+                other_steps += (double)Hkv * ((pl.nodes[v].n_tokens + step_tokens - 1) / step_tokens);
+            }
+        }
+        const double us_alone = 0.8, us_full = std::max(fp8 ? 1.25 : 1.1, (fp8 ? 1.54 : 2.9) * unique / through);  // per 64 tokens
+        const bool packs = pack_mode == 3 || (pack_mode == 2 && other_units + shared_units > kResidentGroups);
+        const int64_t other_wgs = packs ? (other_units + 3) / 4 : other_units;
+        const double other_us = other_units ? 5.0 + other_steps / other_units / (packs ? 1 : 4) : 1.0;
+        int best = shared_chunk;
+        double best_us = 1e30;
+        int64_t best_n = 0;  // such items at the chunk taken
+        for (int ch = shared_chunk; ch <= kMaxSharedItemTokens; ch += 64) {
+            int64_t n = 0, longest_blocks = 0;
+            for (int v = 0; v < n_nodes; ++v) {
+                const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
+                if (pl.nodes[v].n_tokens == 0 || R * G <= 16 || tiled(v)) continue;
+                const int64_t chunks = (pl.nodes[v].n_tokens + ch - 1) / ch;
+                n += (int64_t)((R + max_req_per_item - 1) / max_req_per_item) * Hkv * chunks;
+                longest_blocks = std::max<int64_t>(longest_blocks, (pl.nodes[v].n_tokens + 64 * chunks - 1) / (64 * chunks));
+            }
+            const int64_t full = n / slots, rest = n % slots;
+            const double last = rest ? 6.0 + longest_blocks * (us_alone + std::max(0.0, us_full - us_alone) * rest / slots) : 0.0;
+            double us = full * (6.0 + longest_blocks * us_full) + last;
+            if (other_wgs > 0) {  // in the slots left free, then in all of them
+                const int64_t beside = rest ? (slots - rest) * std::max<int64_t>(1, (int64_t)(last / other_us)) : 0;
+                us = other_wgs <= beside ? std::max(us, other_us) : us + other_us * std::ceil((double)(other_wgs - beside) / slots);
+            }
+            us += rows_below * 264.0 * 2 / 4e6 * ((longest + ch - 1) / ch);  // the partials, written and read at about 4 TB/s
+            if (us < best_us - 1e-9) {
+                best_us = us;
+                best = ch;
+                best_n = n;
+            }
+        }
+        shared_chunk = best;
+        // Where both kinds together leave workgroup slots empty, the pieces of the packed nodes shrink until they fill them
+        // (a wavefront that streams its piece alone is the longest chain of such a launch; below 160 resp. 256 tokens its
+        // start-up takes over).  2048 tokens x 64 requests + 64 x 512 private ones: 3 pieces instead of 2 take the step
+        // from 30.1 to 28.1 us (bf16), 2 instead of 1 from 23.1 to 21.3 us (fp8); one block too many and it is 10 % slower.
+        if (packs && best_n + other_wgs < slots)
+            for (int piece = std::max(160, 4 * step_tokens); piece < pack_tokens; piece += 16) {
+                int64_t units = 0;
+                for (int v = 0; v < n_nodes; ++v) {
+                    const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
+                    const int T = pl.nodes[v].n_tokens;
+                    if (T > 0 && R > 0 && R * G <= 16 && !tiled(v)) units += (int64_t)Hkv * (3 * T < 8 * pack_tokens ? (T + piece - 1) / piece : 4);
+                }
+                if (best_n + (units + 3) / 4 <= slots) {
+                    piece_tokens = piece;
+                    break;
+                }
+            }
     }
     // The tile kernel's share of the chip: its persistent workgroups hold one compute unit each for as long as
     // the other kernel streams its bytes, so their number follows from the two amounts of work (matrix
@@ -786,13 +869,17 @@ static void plan_items(hkv_decode_plan &pl) {
             continue;
         }
         int chunk = std::max(16, R * G > 16 ? shared_chunk : leaf_chunk);
-        if (R * G <= 16 && cut_leaves && cut_for_packing(nd.n_tokens)) chunk = pack_tokens;  // equal pieces below
+        if (R * G <= 16 && ((cut_leaves && cut_for_packing(nd.n_tokens)) || (piece_tokens < pack_tokens && 3 * nd.n_tokens < 8 * pack_tokens)))
+            chunk = piece_tokens;  // equal pieces below
         // equal chunks of whole pages
         int n_chunks = (nd.n_tokens + chunk - 1) / chunk;
         int pages_per_chunk = (nd.n_pages + n_chunks - 1) / n_chunks;
         node_chunks[v] = (nd.n_pages + pages_per_chunk - 1) / pages_per_chunk;
-        for (int r0 = 0; r0 < R; r0 += max_req_per_item) {
-            int nr = std::min(max_req_per_item, R - r0);
+        // equal request groups (64 + 4 rows would leave a long item of few rows that is listed behind the others)
+        const int n_groups = (R + max_req_per_item - 1) / max_req_per_item;
+        const int req_per_group = (R + n_groups - 1) / n_groups;
+        for (int r0 = 0; r0 < R; r0 += req_per_group) {
+            int nr = std::min(req_per_group, R - r0);
             for (int pg = 0, ci = 0; pg < nd.n_pages; pg += pages_per_chunk, ++ci) {
                 int tb = pg * 16;
                 int nt = std::min(pages_per_chunk * 16, nd.n_tokens - tb);
@@ -856,7 +943,10 @@ static void plan_items(hkv_decode_plan &pl) {
     }
     // LDS stages per workgroup.  The fp8 kernel runs two workgroups per CU (registers), so each may own
     // half of the CU's 160 KiB: five stages, four steps of a shared item in flight instead of two.
-    pl.n_stages = or_default(opt.stages, pl.pool->d.dtype == HKV_FP8_E4M3 ? 5 : 3);
+    pl.has_shared = false;
+    for (const DecodeItem &it : pl.items) pl.has_shared = pl.has_shared || it.n_req * G > 16;
+    pl.n_stages = or_default(opt.stages, pl.pool->d.dtype == HKV_FP8_E4M3 || pl.has_shared ? 5 : 3);
+    if (pl.has_shared && !pl.fp8_matrix) pl.n_stages = std::max(pl.n_stages, 4);  // shared::body's ring holds two half-blocks in use and two on their way
     pl.part_count.assign(pl.n_req, 0);
     pl.max_parts = 1;
     for (int r = 0; r < pl.n_req; ++r) {
@@ -1452,7 +1542,7 @@ static int run_decode_plan(hkv_decode_plan *plan, const void *q, float scale, vo
     const DecodeLaunch a{view_of(plan->pool), q, plan->d_items, plan->d_pages, plan->d_node_req_idx, o_parts, lse_parts,
                          down_parts, (int32_t)plan->items.size(), plan->num_q_heads, plan->max_parts, scale,
                          plan->d_row_leaf, plan->d_row_limit, plan->d_row_mask, plan->n_single, plan->n_stages,
-                         plan->fp8_matrix ? 1 : 0, plan->d_q_rows};
+                         plan->fp8_matrix ? 1 : 0, plan->d_q_rows, plan->has_shared ? 1 : 0};
     if (plan->fused) {
         HKV_HIP(launch_decode_fused(a, t, s, prof ? plan->ev[0] : nullptr, prof ? plan->ev[1] : nullptr));
     } else if (tiles) {

@@ -17,10 +17,12 @@ using rows::kMaxStages;
 using rows::kMinStages;
 using rows::kStageBytes;
 
-template <int DT>
-__global__ __launch_bounds__(rows::kThreads, DT == 0 ? 3 : 2) void decode_node_kernel(DecodeLaunch a) {
+// SHARED: the launch holds items of more than 16 query rows.  bf16 pools without such items keep three workgroups on a
+// compute unit; shared::body needs the registers of two.
+template <int DT, bool SHARED>
+__global__ __launch_bounds__(rows::kThreads, SHARED || DT != 0 ? 2 : 3) void decode_node_kernel(DecodeLaunch a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];  // a.n_stages * kStageBytes
-    rows::body<DT, false>(a, smem, (int)blockIdx.x, (int)threadIdx.x);
+    rows::body<DT, false, SHARED>(a, smem, (int)blockIdx.x, (int)threadIdx.x);
 }
 
 // Workgroups [0, n_tile_wgs) are the persistent workgroups of the tile items (all 512 threads); each
@@ -34,7 +36,7 @@ __global__ __launch_bounds__(tile::kThreads, 2) void decode_fused_kernel(DecodeL
         tile::body<true, FP8>(t, smem, (int)blockIdx.x, n_tile_wgs);
     } else {
         const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);  // wavefront-uniform: keeps the item in scalar registers
-        rows::body<FP8 ? 1 : 0, true>(r, smem + half * rows::kCombineBytes, 2 * ((int)blockIdx.x - n_tile_wgs) + half,
+        rows::body<FP8 ? 1 : 0, true, false>(r, smem + half * rows::kCombineBytes, 2 * ((int)blockIdx.x - n_tile_wgs) + half,
                                       (int)threadIdx.x & 255);
     }
 }
@@ -65,9 +67,9 @@ static __device__ __align__(256) unsigned char scratch[hkv::kStaticWorkspaceByte
 namespace hkv {
 
 static hipError_t setup_device(DeviceSetup &st) {
-    const void *fns[3] = {reinterpret_cast<const void *>(decode_node_kernel<0>),
-                          reinterpret_cast<const void *>(decode_node_kernel<1>),
-                          reinterpret_cast<const void *>(decode_node_kernel<2>)};
+    const void *fns[5] = {reinterpret_cast<const void *>(decode_node_kernel<0, false>), reinterpret_cast<const void *>(decode_node_kernel<0, true>),
+                          reinterpret_cast<const void *>(decode_node_kernel<1, false>), reinterpret_cast<const void *>(decode_node_kernel<1, true>),
+                          reinterpret_cast<const void *>(decode_node_kernel<2, true>)};
     for (const void *fn : fns)
         if (hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxStages * kStageBytes);
             e != hipSuccess)
@@ -96,16 +98,17 @@ hipError_t prepare_decode_device(void **static_ws) {
 hipError_t launch_decode(const DecodeLaunch &a, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end) {
     if (a.n_items <= 0) return hipSuccess;
     if (a.n_stages < kMinStages || a.n_stages > kMaxStages) return hipErrorInvalidValue;
-    const int variant = a.pool.dtype == 0 ? 0 : a.fp8_matrix ? 2 : 1;
+    if (a.has_shared && !a.fp8_matrix && a.n_stages < 4) return hipErrorInvalidValue;  // shared::body's ring
     if (hipError_t e = prepare_decode_device(nullptr); e != hipSuccess) return e;
     const dim3 grid(a.n_single + (a.n_items - a.n_single + rows::kWaves - 1) / rows::kWaves);
     const unsigned lds = (unsigned)a.n_stages * kStageBytes;
-    if (variant == 0)
-        hipExtLaunchKernelGGL(decode_node_kernel<0>, grid, dim3(rows::kThreads), lds, s, ev_begin, ev_end, 0, a);
-    else if (variant == 1)
-        hipExtLaunchKernelGGL(decode_node_kernel<1>, grid, dim3(rows::kThreads), lds, s, ev_begin, ev_end, 0, a);
+    auto go = [&](auto kernel) { hipExtLaunchKernelGGL(kernel, grid, dim3(rows::kThreads), lds, s, ev_begin, ev_end, 0, a); };
+    if (a.pool.dtype != 0 && a.fp8_matrix)
+        go(decode_node_kernel<2, true>);
+    else if (a.pool.dtype == 0)
+        a.has_shared ? go(decode_node_kernel<0, true>) : go(decode_node_kernel<0, false>);
     else
-        hipExtLaunchKernelGGL(decode_node_kernel<2>, grid, dim3(rows::kThreads), lds, s, ev_begin, ev_end, 0, a);
+        a.has_shared ? go(decode_node_kernel<1, true>) : go(decode_node_kernel<1, false>);
     return hipGetLastError();
 }
 

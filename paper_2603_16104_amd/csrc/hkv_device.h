@@ -26,6 +26,26 @@ __device__ __forceinline__ u32x4 ld16_stream(const void *p) {
     return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
 }
 
+#ifndef HKV_LDS_PTR
+#define HKV_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
+#endif
+
+// LDS-direct load of 16 bytes per lane: lane l's piece lands at LDS byte lds_base + 16*l.  Issued as
+// inline assembly on purpose: the compiler makes every LDS read wait for ALL outstanding loads of
+// this kind that it knows of (it cannot tell the stages apart), which would drain the prefetch queue
+// at the top of every iteration.  Completion is tracked by hand (vmcnt waits + barriers) instead.
+__device__ __forceinline__ void load_to_lds16(const void *gptr, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_base) : "memory");
+}
+// The same from a wavefront-uniform base plus a 32-bit offset per lane: the address arithmetic of the uniform
+// part stays on the scalar unit.
+__device__ __forceinline__ void load_to_lds16(const void *uniform_base, uint32_t lane_offset, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 ::"v"(lane_offset), "s"(uniform_base), "s"(lds_base)
+                 : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const void *p) { return (uint32_t)(size_t)HKV_LDS_PTR(p); }
+
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // float -> bf16 bits, round to nearest even (inputs here are finite or +-inf, never NaN payloads
@@ -89,6 +109,17 @@ __device__ __forceinline__ float rows_sum(float v) {
     x = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
     const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x16 zero16() {
+    f32x16 z;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) z[i] = 0.f;
+    return z;
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }

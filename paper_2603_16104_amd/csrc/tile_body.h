@@ -68,38 +68,8 @@ constexpr int kParts = 16 / kWaves;            // (page, quarter) pairs of a blo
 constexpr int kLoadsPerBlock = 2 * kParts;     // LDS-direct loads each wavefront issues per iteration
 static_assert(kMaxTileItemTokens <= kScaleSlots * kPage && kMaxTileItemTokens <= kIdSlots * kPage, "decode item limit");
 
-#ifndef HKV_LDS_PTR
-#define HKV_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
-#endif
 // s_waitcnt immediate that waits for vmcnt <= n only (gfx9 encoding)
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
-
-// LDS-direct load of 16 bytes per lane: lane l's piece lands at LDS byte lds_base + 16*l.  Issued as
-// inline assembly on purpose: the compiler makes every LDS read wait for ALL outstanding loads of
-// this kind that it knows of (it cannot tell the stages apart), which would drain the prefetch queue
-// at the top of every iteration.  Completion is tracked by hand (vmcnt waits + barriers) instead.
-__device__ __forceinline__ void load_to_lds16(const void *gptr, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_base) : "memory");
-}
-// The same from a wavefront-uniform base plus a 32-bit offset per lane: the address arithmetic of the uniform
-// part stays on the scalar unit.
-__device__ __forceinline__ void load_to_lds16(const void *uniform_base, uint32_t lane_offset, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 ::"v"(lane_offset), "s"(uniform_base), "s"(lds_base)
-                 : "memory");
-}
-__device__ __forceinline__ uint32_t lds_address(const void *p) { return (uint32_t)(size_t)HKV_LDS_PTR(p); }
-
-__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ f32x16 zero16() {
-    f32x16 z;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) z[i] = 0.f;
-    return z;
-}
 
 // What the two roles hand the kernel.
 struct TileArgs {

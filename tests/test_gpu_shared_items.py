@@ -1,0 +1,85 @@
+"""Decode items shared by 17 to 64 query rows (two 32-row tiles x two token halves per workgroup): the edges of row tiles, of
+token halves and of the 64-token block, scores that rise far above the first block's (the lazily moved softmax reference),
+rows that see nothing of a chunk, and the split of more than 64 rows into equal groups, against the oracle."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2603_16104_amd import workloads as wl
+
+from test_gpu_parity import both_pools, check_close, check_lse, gpu  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@dataclasses.dataclass
+class Rising(wl.Workload):
+    """Keys that grow with the token: the largest scores of a node lie in its last blocks."""
+    gain: float = 1.0
+
+    def node_kv(self, node):
+        k, v = super().node_kv(node)
+        up = (1.0 + self.gain * np.arange(k.shape[0]) / max(1, k.shape[0])).astype(np.float32)[:, None, None]
+        return wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(k) * up), v
+
+
+def workload(kv_dtype, hq, hk, n_req, root, gain=0.0):
+    parent, ntok = [-1] + [0] * n_req, [root] + [1 + 3 * r % 40 for r in range(n_req)]
+    n_used = sum((t + 15) // 16 for t in ntok)
+    pages = np.random.default_rng([n_req, root]).permutation(n_used + 5).astype(np.int32)
+    f = wl.make_forest(parent, ntok, list(range(1, n_req + 1)), pages)
+    return Rising(name=f"root{root}_x{n_req}_{hq}_{hk}", num_q_heads=hq, num_kv_heads=hk, kv_dtype=kv_dtype, num_pages=n_used + 5,
+                  seed=root + n_req, forest=f, mode="decode", gain=gain)
+
+
+def run(gpu, oracle, w, T=1, **settings):  # noqa: F811
+    import torch
+    from paper_2603_16104_amd import binding as hkv
+    hp, dp = both_pools(gpu, oracle, w)
+    f = w.forest
+    q = wl.f32_to_bf16_bits(np.random.default_rng(w.seed).standard_normal((f.n_req * T, w.num_q_heads, 128)).astype(np.float32))
+    masks = np.tile(np.asarray([(1 << (t + 1)) - 1 for t in range(T)], dtype=np.uint64), f.n_req)
+    exp_o, exp_l = oracle.attn_decode_tree(hp, q, f.nodes, f.node_pages, np.repeat(f.req_leaf, T), float(w.scale),
+                                           tail_len=T if T > 1 else 0, tail_mask=masks if T > 1 else None)
+    plan = hkv.hkv_decode_plan_create_ex(dp.handle, f.nodes, f.node_pages, f.req_leaf, w.num_q_heads, tokens_per_req=T,
+                                         visible=masks if T > 16 else None, **settings)
+    items = hkv.hkv_decode_plan_items(plan)
+    G = w.num_q_heads // w.num_kv_heads
+    assert (items[:, 4] * G > 16).any() and (items[:, 4] * G <= 64).all()
+    nb = hkv.hkv_decode_plan_workspace_bytes(plan)
+    ws = torch.empty(max(nb, 256), dtype=torch.uint8, device="cuda")
+    out = torch.zeros((f.n_req * T, w.num_q_heads, 128), dtype=torch.int16, device="cuda")
+    lse = torch.zeros((f.n_req * T, w.num_q_heads), dtype=torch.float32, device="cuda")
+    hkv.attn_decode_plan_run(plan, gpu.to_device_bits(q), float(w.scale), out, lse, ws, nb)
+    torch.cuda.synchronize()
+    hkv.hkv_decode_plan_destroy(plan)
+    dp.close()
+    check_close(gpu.bf16_tensor_to_f64(out), exp_o, w.name)
+    check_lse(lse.cpu().numpy(), exp_l, w.name)
+
+
+@pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
+@pytest.mark.parametrize("hq, hk, n_req", [(17, 1, 1), (8, 2, 5), (8, 2, 8), (11, 1, 3), (16, 2, 8), (10, 2, 13), (4, 1, 17), (8, 1, 25)])
+def test_row_tiles_and_token_edges(gpu, oracle, kv_dtype, hq, hk, n_req):  # noqa: F811
+    if hq // hk > 16:
+        hq, n_req = 9, 2               # 18 rows
+    for root in (1, 16, 17, 31, 33, 64, 65, 96, 97, 130, 700):
+        run(gpu, oracle, workload(kv_dtype, hq, hk, n_req, root))
+
+
+@pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
+@pytest.mark.parametrize("settings", [{}, {"shared_chunk": 64}, {"shared_chunk": 2048, "stages": 3}, {"shared_chunk": 2048, "stages": 4}])
+def test_rising_scores_and_ring_sizes(gpu, oracle, kv_dtype, settings):  # noqa: F811
+    run(gpu, oracle, workload(kv_dtype, 8, 2, 16, 2048 + 33, gain=15.0), **settings)
+
+
+@pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
+@pytest.mark.parametrize("T, leaf_chunk", [(8, 0), (16, 16), (40, 32)])
+def test_drafted_rows_of_one_leaf(gpu, oracle, kv_dtype, T, leaf_chunk):  # noqa: F811
+    """T x 4 rows of one leaf: causal limits inside the item, and (short chunks) rows that see nothing of one."""
+    parent, ntok = [-1, 0, 0], [128, T + 37, T]
+    n_used = sum((t + 15) // 16 for t in ntok)
+    f = wl.make_forest(parent, ntok, [1, 2], np.random.default_rng(T).permutation(n_used + 3).astype(np.int32))
+    w = wl.Workload(name=f"draft{T}", num_q_heads=8, num_kv_heads=2, kv_dtype=kv_dtype, num_pages=n_used + 3, seed=T, forest=f, mode="decode")
+    run(gpu, oracle, w, T, **({"leaf_chunk": leaf_chunk, "shared_chunk": leaf_chunk} if leaf_chunk else {}))
