@@ -357,7 +357,9 @@ typedef struct {
                                  groups of this size (default 8); -1: one class after the other */
     int32_t tile_min_rows;    /* nodes shared by this many query rows or more may go to the 256-row tile kernel
                                  (default 128, at least 65) ... */
-    int32_t tile_min_gflop;   /* ... if the forest holds this much such work (default 40); -1: whatever the amount */
+    int32_t tile_min_gflop;   /* ... if the forest holds this much such work (default 40); -1: whatever the amount.  With
+                                 several query tokens per request only nodes that are no request's last node, beside
+                                 last nodes of more than 16 rows, from 30 on (the default and -1) or this amount */
     int32_t tile_workgroups;  /* persistent workgroups of the tile kernel (default: from the two amounts of work) */
     int32_t tile_chunk;       /* tokens per item of the tile kernel; multiple of 16, at most 8192 */
     int32_t large_batch_updates; /* growing plans: 1 = apply appends as for more than 256 requests (work list re-sent

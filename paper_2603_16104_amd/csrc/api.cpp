@@ -90,7 +90,8 @@ struct hkv_decode_plan {
     // that runs `items` (or in front of it on the caller's stream when concurrent is false).
     std::vector<DecodeItem> tile_items;
     int32_t tile_workgroups = 0;
-    bool no_tiles = false, concurrent = true;
+    bool row_visibility = false;  // several query tokens per request: rows see their last node in part
+    bool concurrent = true;
     bool fused = false;  // both kinds of items go out as one launch (no item of `items` has more than 16 rows)
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -101,7 +102,7 @@ struct hkv_decode_plan {
     DecodeItem *d_items = nullptr, *d_tile_items = nullptr;
     int32_t n_single = 0;  // items [0, n_single) run one per workgroup, the rest four per workgroup
     int32_t n_stages = 3;  // LDS stages of 16 KiB per workgroup of the per-node kernel
-    bool has_shared = false;  // some item of `items` is shared by more than 16 query rows
+    bool has_shared = false;  // items of `items` shared by more than 16 query rows are run by shared::body
     bool fp8_matrix = false;  // fp8 pools: both products on the fp8 matrix instruction (HKV_PLAN_FP8_MATRIX)
     hkv_decode_plan_params opt{};  // the planner's settings (0 = the library's choice)
     int32_t *d_pages = nullptr, *d_node_req_idx = nullptr, *d_part_count = nullptr;
@@ -638,33 +639,64 @@ static void plan_items(hkv_decode_plan &pl) {
     // fewer (node, head) units than workgroups fit on the chip at once; then they are cut, but not
     // below 256 tokens.  Nodes shared by more rows run one row tile per wavefront over all tokens
     // of the item, so their chunks are kept near the typical leaf-type item to finish together.
-    // Nodes shared by many rows go to the 256-row tile kernel (not with per-row visibility, which that kernel
-    // does not know, and not when the caller asked for the fp8 matrix instruction).
+    // Nodes shared by many rows go to the 256-row tile kernel (not when the caller asked for the fp8 matrix instruction).
     const int tile_min_rows = or_default(opt.tile_min_rows, 128);
     // The second kernel, its stream and the two events pay only when that share of the step is large (measured:
     // c2 and c3, 2 and 9 GFLOP of such work in steps of 30 to 50 us, lose; c5, 137 GFLOP in 0.5 ms, gains 11 %).
+    // Plans with several query tokens per request: the tile kernel knows no per-row visibility, but only the requests'
+    // last nodes need it; every other node is seen whole by all rows below it.  There the tiles run in front of the other
+    // items' kernel on all compute units (64 requests x 21 drafted tokens x 4 heads over 2048 shared tokens, 45 GFLOP, step
+    // 125.5 -> 105.7 us bf16, 120 -> 109 us fp8: the root in 84 groups of 64 rows read its K/V 84 times from L2); with
+    // 8 drafted tokens, 17 GFLOP, the second kernel's ramp costs more than the tiles save (64.8 -> 70.2 us, 51.8 -> 57.4).
+    // Only beside last nodes of more than 16 rows: in one launch with smaller ones (4 tokens x 4 heads, 17 GFLOP) it lost too
+    // (39.0 -> 46.2 us).
+    std::vector<char> row_node(n_nodes, 0);  // nodes whose tokens some rows see in part
+    bool wide_row_node = false;
+    if (pl.row_visibility)
+        for (int r = 0; r < pl.n_req; ++r) {
+            const int v = pl.req_leaf[r];
+            row_node[v] = 1;
+            wide_row_node = wide_row_node || (pl.node_req_indptr[v + 1] - pl.node_req_indptr[v]) * G > 16;
+        }
     bool tiles_pay = false;
     {
         double flop = 0;
         for (int v = 0; v < n_nodes; ++v) {
             const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
-            if (R * G >= std::max(tile_min_rows, kMinTileItemRows))
+            if (!row_node[v] && R * G >= std::max(tile_min_rows, kMinTileItemRows))
                 flop += 4.0 * HKV_HEAD_DIM * pl.nodes[v].n_tokens * (double)R * pl.num_q_heads;
         }
-        tiles_pay = opt.tile_min_gflop < 0 || flop >= 1e9 * or_default(opt.tile_min_gflop, 40);
+        if (pl.row_visibility)
+            tiles_pay = wide_row_node && flop >= 1e9 * (opt.tile_min_gflop > 0 ? opt.tile_min_gflop : 30);
+        else
+            tiles_pay = opt.tile_min_gflop < 0 || flop >= 1e9 * or_default(opt.tile_min_gflop, 40);
     }
     auto tiled = [&](int v) {
         const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
-        return tiles_pay && !pl.no_tiles && !pl.fp8_matrix && pl.nodes[v].n_tokens > 0 &&
+        return tiles_pay && !row_node[v] && !pl.fp8_matrix && pl.nodes[v].n_tokens > 0 &&
                R * G >= std::max(tile_min_rows, kMinTileItemRows);
     };
-    bool any_shared = false;  // nodes for shared::body (or, with the fp8 matrix instruction, its forerunner)
+    bool any_shared = false;
+    double through = 0, unique = 0, other_tokens = 0;  // K/V tokens: of shared nodes through workgroups / from HBM, of the others
     for (int v = 0; v < n_nodes; ++v) {
         const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
-        any_shared = any_shared || (pl.nodes[v].n_tokens > 0 && R * G > 16 && !tiled(v));
+        if (pl.nodes[v].n_tokens == 0 || R == 0 || tiled(v)) continue;
+        if (R * G > 16) {
+            any_shared = true;
+            through += (double)pl.nodes[v].n_tokens * ((R + max_req_per_item - 1) / max_req_per_item);
+            unique += pl.nodes[v].n_tokens;
+        } else {
+            other_tokens += pl.nodes[v].n_tokens;
+        }
     }
+    // Shared nodes go to shared::body, except (bf16) beside three times as many tokens of private nodes in a step of more
+    // than 80 MB: such a step is bound by streaming those, and the 16-row tiles with three workgroups per compute unit
+    // disturb them less (64 requests of 512 private tokens below 512 / 1024 / 2048 shared ones: 29.8 / 29.5 / 29.2 us
+    // against 30.4 / 30.5 / 30.1; below 4096, 31.2 against 31.0).
+    const bool fp8_pool = pl.pool->d.dtype == HKV_FP8_E4M3;
+    pl.has_shared = any_shared && (fp8_pool || other_tokens < 3 * through || other_tokens * 4 * HKV_HEAD_DIM * Hkv < 80e6);
     // workgroups the chip holds at once: two per compute unit with fp8 pools or with shared::body in the launch, else three
-    const int kResidentGroups = chip.n_cu * (pl.pool->d.dtype == HKV_FP8_E4M3 || any_shared ? 2 : 3);
+    const int kResidentGroups = chip.n_cu * (fp8_pool || pl.has_shared ? 2 : 3);
     int64_t leaf_units = 0, leaf_tokens = 0, shared_units = 0;
     for (int v = 0; v < n_nodes; ++v) {
         int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
@@ -734,17 +766,15 @@ static void plan_items(hkv_decode_plan &pl) {
     // items), 31 us at 1024 (320), 36 us at 1376 (256).  From the length above up to the longest there is, the one with
     // the shortest estimated step is taken.
     int piece_tokens = pack_tokens;
-    if (any_shared && !pl.fp8_matrix && opt.shared_chunk == 0 && opt.leaf_chunk == 0) {
-        const bool fp8 = pl.pool->d.dtype == HKV_FP8_E4M3;
+    if (pl.has_shared && !pl.fp8_matrix && opt.shared_chunk == 0 && opt.leaf_chunk == 0) {
+        const bool fp8 = fp8_pool;
         const int64_t slots = kResidentGroups;
-        double through = 0, unique = 0, other_steps = 0;  // tokens through workgroups, tokens read from HBM; steps of the other items
+        double other_steps = 0;
         int64_t other_units = 0, rows_below = 0;
         for (int v = 0; v < n_nodes; ++v) {
             const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
             if (pl.nodes[v].n_tokens == 0 || R == 0 || tiled(v)) continue;
             if (R * G > 16) {
-                through += (double)pl.nodes[v].n_tokens * ((R + max_req_per_item - 1) / max_req_per_item);
-                unique += pl.nodes[v].n_tokens;
                 rows_below = std::max<int64_t>(rows_below, (int64_t)R * pl.num_q_heads);
             } else {
                 const int pieces = cut_leaves && cut_for_packing(pl.nodes[v].n_tokens) ? (pl.nodes[v].n_tokens + pack_tokens - 1) / pack_tokens : 1;
@@ -783,17 +813,17 @@ static void plan_items(hkv_decode_plan &pl) {
             }
         }
         shared_chunk = best;
-        // Where both kinds together leave workgroup slots empty, the pieces of the packed nodes shrink until they fill them
-        // (a wavefront that streams its piece alone is the longest chain of such a launch; below 160 resp. 256 tokens its
-        // start-up takes over).  2048 tokens x 64 requests + 64 x 512 private ones: 3 pieces instead of 2 take the step
-        // from 30.1 to 28.1 us (bf16), 2 instead of 1 from 23.1 to 21.3 us (fp8); one block too many and it is 10 % slower.
-        if (packs && best_n + other_wgs < slots)
+        // Where both kinds together leave workgroup slots empty, packed nodes that are whole so far are cut until they fill
+        // them (a wavefront that streams a node alone is the longest chain of such a launch; below 160 resp. 256 tokens its
+        // start-up takes over).  64 requests of 512 private tokens below 4096 shared ones, fp8: 28.9 us whole, 22.8 us as
+        // 2 x 256; a few blocks too many and it is 10 % slower.
+        if (packs && !cut_leaves && best_n + other_wgs < slots)
             for (int piece = std::max(160, 4 * step_tokens); piece < pack_tokens; piece += 16) {
                 int64_t units = 0;
                 for (int v = 0; v < n_nodes; ++v) {
                     const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
                     const int T = pl.nodes[v].n_tokens;
-                    if (T > 0 && R > 0 && R * G <= 16 && !tiled(v)) units += (int64_t)Hkv * (3 * T < 8 * pack_tokens ? (T + piece - 1) / piece : 4);
+                    if (T > 0 && R > 0 && R * G <= 16 && !tiled(v)) units += (int64_t)Hkv * (T <= pack_tokens ? (T + piece - 1) / piece : 4);
                 }
                 if (best_n + (units + 3) / 4 <= slots) {
                     piece_tokens = piece;
@@ -805,6 +835,8 @@ static void plan_items(hkv_decode_plan &pl) {
     // the other kernel streams its bytes, so their number follows from the two amounts of work (matrix
     // arithmetic at about 3.5 TFLOP/s per compute unit against bytes at about 5.5 TB/s for the chip).
     const int req_per_tile = std::max(1, 256 / G);
+    const bool tiles_first = pl.row_visibility;
+    if (tiles_first) pl.concurrent = false;
     pl.tile_items.clear();
     pl.tile_workgroups = 0;
     int tile_chunk = kMaxTileItemTokens;
@@ -834,11 +866,23 @@ static void plan_items(hkv_decode_plan &pl) {
                 wgs = (int)(tile_flop / (3.5e12 * t_other) + 0.999);
                 wgs = std::min(n_cu - 64, std::max(8, (wgs + 7) / 8 * 8));  // whole groups of 8: one per XCD
             }
+            if (tiles_first) wgs = n_cu;
             wgs = std::min(n_cu, or_default(opt.tile_workgroups, wgs));
             pl.tile_workgroups = wgs;
             // chunks: about one item per workgroup (a workgroup that is done gives its compute unit to the other
             // items, and every chunk costs every row below the node a partial), more where the nodes are few
-            const int64_t n_chunks = std::max<int64_t>(1, std::min<int64_t>((wgs + tile_units / 2) / tile_units, tile_tokens_max / 256));
+            int64_t n_chunks = std::max<int64_t>(1, std::min<int64_t>((wgs + tile_units / 2) / tile_units, tile_tokens_max / 256));
+            if (tiles_first) {  // rounds of items at 1.45 us per 64 tokens and 4 us each, and what the partials cost
+                double best_us = 1e30;
+                for (int64_t n = (tile_tokens_max + kMaxTileItemTokens - 1) / kMaxTileItemTokens; n <= 8; ++n) {
+                    const int64_t blocks = (tile_tokens_max + 64 * n - 1) / (64 * n);
+                    const double us = (double)((tile_units * n + wgs - 1) / wgs) * (4.0 + 1.45 * blocks) + (double)n * pl.n_req * pl.num_q_heads * 264 * 2 / 4e6;
+                    if (us < best_us) {
+                        best_us = us;
+                        n_chunks = n;
+                    }
+                }
+            }
             int64_t ch = ((tile_tokens_max + n_chunks - 1) / n_chunks + 63) / 64 * 64;
             tile_chunk = (int)std::min<int64_t>(kMaxTileItemTokens, std::max<int64_t>(256, ch));
             tile_chunk = std::min(kMaxTileItemTokens, or_default(opt.tile_chunk, tile_chunk)) / 16 * 16;
@@ -869,7 +913,7 @@ static void plan_items(hkv_decode_plan &pl) {
             continue;
         }
         int chunk = std::max(16, R * G > 16 ? shared_chunk : leaf_chunk);
-        if (R * G <= 16 && ((cut_leaves && cut_for_packing(nd.n_tokens)) || (piece_tokens < pack_tokens && 3 * nd.n_tokens < 8 * pack_tokens)))
+        if (R * G <= 16 && ((cut_leaves && cut_for_packing(nd.n_tokens)) || (piece_tokens < pack_tokens && nd.n_tokens <= pack_tokens)))
             chunk = piece_tokens;  // equal pieces below
         // equal chunks of whole pages
         int n_chunks = (nd.n_tokens + chunk - 1) / chunk;
@@ -926,7 +970,7 @@ static void plan_items(hkv_decode_plan &pl) {
     // compute unit), in whole groups of 8 (one per XCD).  The items then hold few compute units for the whole
     // step instead of many for a part of it, which the streaming items use better (c5: 64 workgroups of two
     // items against 128 of one, step -2 %); a chain that outlasts the step would lengthen it, hence the margin.
-    if (opt.tile_workgroups == 0 && !pl.tile_items.empty() && (int)pl.tile_items.size() <= chip.n_cu - 64) {
+    if (!tiles_first && opt.tile_workgroups == 0 && !pl.tile_items.empty() && (int)pl.tile_items.size() <= chip.n_cu - 64) {
         const int n_items = (int)pl.tile_items.size();
         double item_seconds = 0;
         for (const DecodeItem &it : pl.tile_items)
@@ -943,9 +987,7 @@ static void plan_items(hkv_decode_plan &pl) {
     }
     // LDS stages per workgroup.  The fp8 kernel runs two workgroups per CU (registers), so each may own
     // half of the CU's 160 KiB: five stages, four steps of a shared item in flight instead of two.
-    pl.has_shared = false;
-    for (const DecodeItem &it : pl.items) pl.has_shared = pl.has_shared || it.n_req * G > 16;
-    pl.n_stages = or_default(opt.stages, pl.pool->d.dtype == HKV_FP8_E4M3 || pl.has_shared ? 5 : 3);
+    pl.n_stages = or_default(opt.stages, fp8_pool || pl.has_shared ? 5 : 3);
     if (pl.has_shared && !pl.fp8_matrix) pl.n_stages = std::max(pl.n_stages, 4);  // shared::body's ring holds two half-blocks in use and two on their way
     pl.part_count.assign(pl.n_req, 0);
     pl.max_parts = 1;
@@ -1041,8 +1083,8 @@ static int build_fp32_rows(hkv_decode_plan &pl, bool upload) {
     return HKV_OK;
 }
 
-// internal flag: no item may go to the 256-row tile kernel (plans with per-row visibility)
-constexpr uint32_t kPlanNoTiles = 0x40000000u;
+// internal flag: plans with per-row visibility
+constexpr uint32_t kPlanRowVisibility = 0x40000000u;
 
 // the planner's settings, each 0 (the library's choice) or inside its documented range
 static int check_plan_settings(const hkv_decode_plan_params *o) {
@@ -1111,7 +1153,7 @@ static int create_decode_plan(hkv_pool *pool, const hkv_node *nodes, int32_t n_n
         pl->opt.q_rows = nullptr;  // the caller's array is not kept
     }
     pl->opt.visible = nullptr;
-    pl->no_tiles = (flags & kPlanNoTiles) != 0;
+    pl->row_visibility = (flags & kPlanRowVisibility) != 0;
     pl->concurrent = !(flags & HKV_PLAN_ONE_STREAM);
     if (int rc = build_node_req_csr(nodes, n_nodes, req_leaf, n_req, pl->node_req_indptr, pl->node_req_idx,
                                     "hkv_decode_plan_create")) {
@@ -1186,7 +1228,7 @@ extern "C" int hkv_decode_plan_create(hkv_pool *pool, const hkv_node *nodes, int
                                       const int32_t *node_pages, int32_t n_node_pages, const int32_t *req_leaf,
                                       int32_t n_req, int32_t num_q_heads, uint32_t flags, hkv_decode_plan **out) {
     return create_decode_plan(pool, nodes, n_nodes, node_pages, n_node_pages, req_leaf, n_req, num_q_heads,
-                              flags & ~kPlanNoTiles, 0, nullptr, out);
+                              flags & ~kPlanRowVisibility, 0, nullptr, out);
 }
 
 static int create_growing_plan(hkv_pool *pool, const hkv_node *nodes, int32_t n_nodes, const int32_t *node_pages,
@@ -1217,7 +1259,7 @@ static int create_growing_plan(hkv_pool *pool, const hkv_node *nodes, int32_t n_
             return fail(HKV_ETREE, "hkv_decode_plan_create_growing: the leaf of request %d holds no token", r);
     }
     return create_decode_plan(pool, nodes, n_nodes, node_pages, n_node_pages, req_leaf, n_req, num_q_heads,
-                              flags & ~kPlanNoTiles, reserve_tokens, opt, out);
+                              flags & ~kPlanRowVisibility, reserve_tokens, opt, out);
 }
 
 extern "C" int hkv_decode_plan_create_growing(hkv_pool *pool, const hkv_node *nodes, int32_t n_nodes,
@@ -1344,7 +1386,7 @@ static int create_rows_plan(hkv_pool *pool, const hkv_node *nodes, int32_t n_nod
     for (int r = 0; r < n_req; ++r)
         for (int t = 0; t < T; ++t) rows[(size_t)r * T + t] = req_leaf[r];
     hkv_decode_plan *pl = nullptr;
-    const uint32_t rows_flags = (flags & ~kPlanNoTiles) | ((T > 1 || masks) ? kPlanNoTiles : 0u);
+    const uint32_t rows_flags = (flags & ~kPlanRowVisibility) | ((T > 1 || masks) ? kPlanRowVisibility : 0u);
     if (int rc = create_decode_plan(pool, nodes, n_nodes, node_pages, n_node_pages, rows.data(), n_req * T, num_q_heads,
                                     rows_flags, 0, opt, &pl))
         return rc;
@@ -1446,7 +1488,7 @@ extern "C" int hkv_decode_plan_create_ex(hkv_pool *pool, const hkv_node *nodes, 
         return create_growing_plan(pool, nodes, n_nodes, node_pages, n_node_pages, req_leaf, n_req, num_q_heads, reserve,
                                    flags, params, out);
     return create_decode_plan(pool, nodes, n_nodes, node_pages, n_node_pages, req_leaf, n_req, num_q_heads,
-                              flags & ~kPlanNoTiles, 0, params, out);
+                              flags & ~kPlanRowVisibility, 0, params, out);
 }
 
 extern "C" int hkv_decode_plan_destroy(hkv_decode_plan *plan) {

@@ -17,8 +17,8 @@ using rows::kMaxStages;
 using rows::kMinStages;
 using rows::kStageBytes;
 
-// SHARED: the launch holds items of more than 16 query rows.  bf16 pools without such items keep three workgroups on a
-// compute unit; shared::body needs the registers of two.
+// SHARED: items of more than 16 query rows are run by shared::body, which needs the registers of two workgroups per
+// compute unit; bf16 launches without it keep three.
 template <int DT, bool SHARED>
 __global__ __launch_bounds__(rows::kThreads, SHARED || DT != 0 ? 2 : 3) void decode_node_kernel(DecodeLaunch a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];  // a.n_stages * kStageBytes

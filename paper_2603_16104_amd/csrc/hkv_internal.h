@@ -79,7 +79,7 @@ struct DecodeLaunch {
     int32_t fp8_matrix;
     // Row r of the plan reads row q_rows[r] of q (device; null: row r).  Partials stay indexed by r.
     const int32_t *q_rows;
-    int32_t has_shared;          // some item is shared by more than 16 query rows
+    int32_t has_shared;          // items shared by more than 16 query rows are run by shared::body
 };
 
 struct PrefillLaunch {

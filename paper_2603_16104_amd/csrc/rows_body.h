@@ -142,7 +142,7 @@ __device__ __forceinline__ T pick(const T (&v)[4], int sel) {
 
 // One workgroup's (FUSED: one half-workgroup's) share of the launch: virtual block `vblock` of the grid of
 // n_single + ceil((n_items - n_single) / 4) blocks, run by the 256 threads `tid` = 0..255 with `smem` as their LDS.
-// SHARED: the launch holds items of more than 16 query rows.
+// SHARED: items of more than 16 query rows are run by shared_body.h.
 // FUSED: the 256 threads are one half of a 512-thread workgroup whose other half runs another block (or
 // none: vblock beyond the grid); every half executes exactly one workgroup barrier, so the launch must hold
 // no item shared by more than 16 query rows (those synchronise once per step).
@@ -179,15 +179,16 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
     const int G = a.num_q_heads / Hkv;
     const int rows = it.n_req * G;
     // Up to 16 rows: the four wavefronts split the tokens and read K/V straight into registers.
-    // More rows: shared_body.h; on the fp8 matrix instruction (DT == 2) each wavefront owns a 16-row tile, all
-    // tokens, and K/V are staged once in LDS.
+    // More rows: shared_body.h; without it (the fp8 matrix instruction; bf16 plans bound by streaming their private
+    // nodes) each wavefront owns a 16-row tile, all tokens, and K/V are staged once in LDS.
     if constexpr (SHARED && DT != 2) {
         if (!packed && rows > 16) {  // wavefront-uniform, the same for the whole workgroup
             shared::body<DT == 1>(a, it, smem, wave, lane);
             return;
         }
     }
-    const bool shared = SHARED && DT == 2 && !packed && rows > 16;
+    constexpr bool kOwnTiles = !FUSED && (DT == 2 || (DT == 0 && !SHARED));
+    const bool shared = kOwnTiles && !packed && rows > 16;
     const int n_rt = shared ? kWaves : 1;
     const int n_ts = packed ? 1 : kWaves / n_rt;
     const int rt = packed ? 0 : wave % n_rt, ts = packed ? 0 : wave / n_rt;
@@ -502,7 +503,7 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
         }
     };
 
-    if constexpr (SHARED && DT == 2) if (shared) {
+    if constexpr (kOwnTiles) if (shared) {
         // ---- K/V staged in LDS, fetched once for all row tiles of the item (LDS-direct loads: the
         // data in flight occupies no registers, so n_stages - 1 steps are kept in flight: a step of
         // such an item takes about a memory round trip divided by that number).  A stage
@@ -517,8 +518,10 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
 #pragma unroll
         for (int r = 0; r < kIdRegs; ++r) {
             id_lane[r] = a.pages[it.page_off + min(lane + 64 * r, last_page)];
-            ksc_lane[r] = a.pool.k_scale[(size_t)id_lane[r] * Hkv + it.kv_head];
-            vsc_lane[r] = a.pool.v_scale[(size_t)id_lane[r] * Hkv + it.kv_head];
+            if constexpr (DT != 0) {
+                ksc_lane[r] = a.pool.k_scale[(size_t)id_lane[r] * Hkv + it.kv_head];
+                vsc_lane[r] = a.pool.v_scale[(size_t)id_lane[r] * Hkv + it.kv_head];
+            }
         }
         auto step_pages = [&](StepPages<DT> &sp, int blk) {
 #pragma unroll
@@ -535,8 +538,10 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
                         vv = vsc_lane[r];
                     }
                 sp.id[i] = __builtin_amdgcn_readlane(idv, lo);
-                sp.ksc[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, kv), lo));
-                sp.vsc[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, vv), lo));
+                if constexpr (DT != 0) {
+                    sp.ksc[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, kv), lo));
+                    sp.vsc[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, vv), lo));
+                }
             }
         };
         const int n_stages = a.n_stages, n_ahead = n_stages - 1;
@@ -551,13 +556,13 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int f = 4 * j + wave;
-                const int koff = (f & 1) * 1024 + (f >> 1) * 256;
+                const int koff = (DT == 0) ? (f & 3) * 1024 + (f >> 2) * 256 : (f & 1) * 1024 + (f >> 1) * 256;
                 __builtin_amdgcn_global_load_lds(HKV_GLOBAL_PTR(pk + koff), HKV_LDS_PTR(stage + f * 1024), 16, 0, 0);
             }
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int dt = 4 * j + wave;
-                __builtin_amdgcn_global_load_lds(HKV_GLOBAL_PTR(pv + dt * 256),
+                __builtin_amdgcn_global_load_lds(HKV_GLOBAL_PTR(pv + dt * ((DT == 0) ? 512 : 256)),
                                                  HKV_LDS_PTR(stage + (8 + dt) * 1024), 16, 0, 0);
             }
         };

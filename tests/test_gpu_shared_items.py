@@ -33,7 +33,7 @@ def workload(kv_dtype, hq, hk, n_req, root, gain=0.0):
                   seed=root + n_req, forest=f, mode="decode", gain=gain)
 
 
-def run(gpu, oracle, w, T=1, **settings):  # noqa: F811
+def run(gpu, oracle, w, T=1, tiles=(False, False), **settings):  # noqa: F811
     import torch
     from paper_2603_16104_amd import binding as hkv
     hp, dp = both_pools(gpu, oracle, w)
@@ -46,7 +46,10 @@ def run(gpu, oracle, w, T=1, **settings):  # noqa: F811
                                          visible=masks if T > 16 else None, **settings)
     items = hkv.hkv_decode_plan_items(plan)
     G = w.num_q_heads // w.num_kv_heads
-    assert (items[:, 4] * G > 16).any() and (items[:, 4] * G <= 64).all()
+    n_tiles, fused = hkv.hkv_decode_plan_num_tile_items(plan), bool(hkv.hkv_decode_plan_is_fused(plan))
+    assert (n_tiles > 0, fused) == tiles
+    if not n_tiles:
+        assert (items[:, 4] * G > 16).any() and (items[:, 4] * G <= 64).all()
     nb = hkv.hkv_decode_plan_workspace_bytes(plan)
     ws = torch.empty(max(nb, 256), dtype=torch.uint8, device="cuda")
     out = torch.zeros((f.n_req * T, w.num_q_heads, 128), dtype=torch.int16, device="cuda")
@@ -83,3 +86,15 @@ def test_drafted_rows_of_one_leaf(gpu, oracle, kv_dtype, T, leaf_chunk):  # noqa
     f = wl.make_forest(parent, ntok, [1, 2], np.random.default_rng(T).permutation(n_used + 3).astype(np.int32))
     w = wl.Workload(name=f"draft{T}", num_q_heads=8, num_kv_heads=2, kv_dtype=kv_dtype, num_pages=n_used + 3, seed=T, forest=f, mode="decode")
     run(gpu, oracle, w, T, **({"leaf_chunk": leaf_chunk, "shared_chunk": leaf_chunk} if leaf_chunk else {}))
+
+
+@pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
+@pytest.mark.parametrize("T, n_req", [(8, 48), (4, 84)])
+def test_tiles_above_drafted_rows(gpu, oracle, kv_dtype, T, n_req):  # noqa: F811
+    """Several query tokens per request over a root shared by more than 256 rows: the root goes to the 256-row tile, the
+    leaves with their causal limits to the other items' kernel behind it; not beside leaves of 16 rows."""
+    parent, ntok = [-1] + [0] * n_req, [1040] + [T + 5 * r % 50 for r in range(n_req)]
+    n_used = sum((t + 15) // 16 for t in ntok)
+    f = wl.make_forest(parent, ntok, list(range(1, n_req + 1)), np.random.default_rng(T).permutation(n_used + 3).astype(np.int32))
+    w = wl.Workload(name=f"tiles{T}", num_q_heads=8, num_kv_heads=2, kv_dtype=kv_dtype, num_pages=n_used + 3, seed=T, forest=f, mode="decode")
+    run(gpu, oracle, w, T, tiles=(T == 8, False), tile_min_gflop=1)
