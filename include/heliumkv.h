@@ -468,6 +468,8 @@ size_t attn_decode_workspace_bytes(hkv_pool *pool, const hkv_node *nodes, int32_
  *   block_table beyond ceil(kv_len/16) are ignored.  ERANGE if a used page id is outside the pool.
  * ESHAPE unless num_q_heads is a multiple of num_kv_heads with a ratio G of at most 16 (a
  * workgroup's 256 rows hold floor(256/G) tokens x G heads; at most G - 1 rows stay unused).
+ * A plan over few tiles splits them along their keys; the fp32 partial results lie in device memory of the plan's own (up
+ * to 140 MB, taken at creation; where it cannot be had the tiles stay whole), so its runs belong on one stream or in order.
  */
 int hkv_prefill_plan_create(hkv_pool *pool, const int32_t *cu_q, const int32_t *block_table, int32_t max_pages,
                             const int32_t *kv_len, int32_t n_req, int32_t num_q_heads, uint32_t flags,

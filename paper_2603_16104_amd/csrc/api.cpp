@@ -150,6 +150,15 @@ struct hkv_prefill_plan {
     std::vector<int32_t> src_pages;
     int32_t *d_src_pages = nullptr;
     unsigned int *d_fallback = nullptr;  // tiles that repeated with a running maximum, over all runs of the plan
+    // tiles split along their keys (empty: a workgroup per tile); the partials lie in the plan's own allocation
+    std::vector<PrefillSegment> segments;
+    std::vector<int32_t> seg_begin;
+    std::vector<PrefillSplitTile> split;
+    int32_t n_parts = 0;
+    PrefillSegment *d_segments = nullptr;
+    int32_t *d_seg_begin = nullptr, *d_part_bail = nullptr;
+    PrefillSplitTile *d_split = nullptr;
+    float *d_part_data = nullptr;
 };
 
 struct hkv_pool {
@@ -1750,6 +1759,116 @@ extern "C" size_t attn_decode_workspace_bytes(hkv_pool *pool, const hkv_node *no
 // prefill planning
 // cu_q: request r's new tokens are rows cu_q[r] .. cu_q[r + 1] - 1 of q / out / lse.  q_row_begin (may be null):
 // they are rows q_row_begin[r] .. q_row_begin[r] + (cu_q[r + 1] - cu_q[r]) - 1 instead.
+//
+// The tiles of a small batch, cut along their keys into equal shares of one persistent workgroup per compute unit.  All
+// KV heads have the same tiles, so one head's are laid out over its n_cu / Hkv workers (workgroup index = worker * Hkv +
+// head: a head stays on its XCD): whole tiles, longest first, while whole rounds of them remain, then what is left end to
+// end, cut where a worker's share is full.  Taken where the estimate says so (in key blocks of 64 tokens, 1.4 us each on a
+// full chip, a little less on one that is not): a tile or segment costs 4 blocks beside its own, the partials 135 KB each
+// on their way through memory and the second kernel 3 more.  Against a workgroup per tile, 32 / 8 heads, one request:
+// 64 / 256 / 1024 new tokens over 8192 cached ones 154 / 159 / 174 -> 53 / 59 / 145 us, 700 over 4096 95.5 -> 66.3,
+// 128 over 1024 29.9 -> 27.6; six requests of 256 to 512 over 2048 113.9 -> 108.  Where the estimate gains less than 13 %
+// it was a loss as often as not (three of 1024 over 8192: estimate 0.89, measured 1.01).
+static void split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<PrefillTile> &head_tiles, int n_cu) {
+    const int Hkv = pl.pool->d.num_kv_heads;
+    const int n = (int)head_tiles.size(), workers = n_cu / Hkv;
+    if (n == 0 || workers < 2 || n > 4 * workers) return;
+    constexpr double kOver = 4.0;
+    std::vector<int> blocks(n);
+    int64_t total = 0;
+    for (int i = 0; i < n; ++i) {
+        const PrefillTile &t = head_tiles[i];
+        blocks[i] = (t.prefix_len + t.q_begin + t.n_q + 63) / 64;
+        total += blocks[i];
+    }
+    // whole: dispatched in order, each to the workgroup that is free first
+    std::vector<double> load(workers, 0.0);
+    for (int i = 0; i < n; ++i) *std::min_element(load.begin(), load.end()) += blocks[i] + kOver;
+    const double whole_cost = *std::max_element(load.begin(), load.end());
+
+    const int n_whole = n / workers * workers;
+    std::vector<std::vector<int>> own(workers);
+    std::fill(load.begin(), load.end(), 0.0);
+    for (int i = 0; i < n_whole; ++i) {
+        const int w = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+        own[w].push_back(i);
+        load[w] += blocks[i] + kOver;
+    }
+    if (n_whole == n) return;  // whole rounds: nothing to gain
+    int64_t rest = 0;
+    for (int i = n_whole; i < n; ++i) rest += blocks[i];
+    // the level up to which the rest fills the workers (a worker whose whole tiles reach it gets none), each paying one more segment
+    double level = 0;
+    for (double l : load) level += l;
+    level = (level + rest + 1.5 * kOver * workers) / workers;
+    if (level - *std::min_element(load.begin(), load.end()) < 3 * kOver) {  // shares too short: fewer, longer ones
+        level = *std::min_element(load.begin(), load.end()) + 3 * kOver;
+    }
+    struct Cut { int tile, b0, b1; };
+    std::vector<std::vector<Cut>> cuts(workers);
+    int tile = n_whole, at = 0, w = 0, n_cuts = 0;
+    double worst = *std::max_element(load.begin(), load.end());
+    while (tile < n) {
+        const bool last = w == workers - 1;
+        int room = last ? 1 << 28 : (int)std::floor(level - load[w] - kOver);
+        while (tile < n && (room >= 4 || room >= blocks[tile] - at)) {  // no segment below four blocks but a tile's end
+            int take = std::min(room, blocks[tile] - at);
+            if (blocks[tile] - at - take < 4) take = blocks[tile] - at;
+            cuts[w].push_back({tile, at, at + take});
+            ++n_cuts;
+            load[w] += take + kOver;
+            room -= take + (int)kOver;
+            at += take;
+            if (at == blocks[tile]) {
+                ++tile;
+                at = 0;
+            }
+        }
+        worst = std::max(worst, load[w]);
+        if (last) break;
+        ++w;
+    }
+    const double split_cost = worst + 3.0 + n_cuts * (double)Hkv * kSplitPartFloats * 4 / 5e6 / 1.4;
+    if (split_cost > 0.87 * whole_cost || (int64_t)n_cuts * Hkv > 1024) return;
+
+    std::vector<int> pieces(n, 0);
+    for (auto &c : cuts)
+        for (const Cut &x : c) ++pieces[x.tile];
+    std::vector<int32_t> part0((size_t)n * Hkv, -1), used((size_t)n * Hkv, 0);
+    int32_t parts = 0;
+    for (int i = n_whole; i < n; ++i)
+        if (pieces[i] > 1)
+            for (int h = 0; h < Hkv; ++h) {
+                part0[(size_t)i * Hkv + h] = parts;
+                PrefillTile t = head_tiles[i];
+                t.kv_head = h;
+                pl.split.push_back(PrefillSplitTile{t, parts, pieces[i]});
+                parts += pieces[i];
+            }
+    pl.n_parts = parts;
+    pl.seg_begin.push_back(0);
+    for (int k = 0; k < workers; ++k)
+        for (int h = 0; h < Hkv; ++h) {
+            for (int i : own[k]) {
+                PrefillTile t = head_tiles[i];
+                t.kv_head = h;
+                pl.segments.push_back(PrefillSegment{t, t.prefix_len + t.q_begin + t.n_q, -1});
+            }
+            for (const Cut &x : cuts[k]) {
+                PrefillTile t = head_tiles[x.tile];
+                const int end = t.prefix_len + t.q_begin + t.n_q;
+                t.kv_head = h;
+                t.prefix_len -= 64 * x.b0;  // (new tokens in front of the segment get negative positions: they see nothing of it)
+                t.kv_len -= 64 * x.b0;
+                t.bt_off += 4 * x.b0;
+                const size_t th = (size_t)x.tile * Hkv + h;
+                const int32_t part = part0[th] < 0 ? -1 : part0[th] + used[th]++;
+                pl.segments.push_back(PrefillSegment{t, std::min(end, 64 * x.b1) - 64 * x.b0, part});
+            }
+            pl.seg_begin.push_back((int32_t)pl.segments.size());
+        }
+}
+
 static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_t *q_row_begin, const int32_t *block_table,
                                int32_t max_pages, const int32_t *kv_len, int32_t n_req, int32_t num_q_heads,
                                uint32_t flags, hkv_prefill_plan **out) {
@@ -1816,6 +1935,11 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
             pl->tiles.push_back(PrefillTile{p.req, p.q_begin, p.n_q, h, (q_row_begin ? q_row_begin[p.req] : cu_q[p.req]) + p.q_begin, kv_len[p.req] - s,
                                             kv_len[p.req], p.req * max_blocks});
         }
+    if (pool->d.dtype != HKV_FP32) {
+        std::vector<PrefillTile> head_tiles;
+        for (size_t i = 0; i < pl->tiles.size(); i += Hkv) head_tiles.push_back(pl->tiles[i]);
+        split_prefill_tiles(*pl, head_tiles, chip_shape().n_cu);
+    }
     // fp8 pools: number the pages this batch reads (first use first) and point the device table at them
     std::vector<int32_t> remapped;
     if (pool->d.dtype == HKV_FP8_E4M3) {
@@ -1840,8 +1964,30 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
         size_t off_bt = align_up(sizeof(PrefillTile) * pl->tiles.size(), 256);
         size_t off_src = off_bt + align_up(sizeof(int32_t) * dev_table.size(), 256);
         size_t off_fb = off_src + align_up(sizeof(int32_t) * pl->src_pages.size(), 256);
-        size_t total = off_fb + 256;
-        hipError_t e = hipMalloc(&pl->dev, total);
+        const size_t off_seg = off_fb + 256, off_sb = off_seg + align_up(sizeof(PrefillSegment) * pl->segments.size(), 256);
+        const size_t off_split = off_sb + align_up(sizeof(int32_t) * pl->seg_begin.size(), 256);
+        const size_t off_bail = off_split + align_up(sizeof(PrefillSplitTile) * pl->split.size(), 256);
+        const size_t off_part = off_bail + align_up(sizeof(int32_t) * pl->n_parts, 256);
+        hipError_t e = hipMalloc(&pl->dev, off_part + sizeof(float) * kSplitPartFloats * pl->n_parts);
+        if (e == hipErrorOutOfMemory && !pl->segments.empty()) {  // no room for partials: a workgroup per tile needs none
+            (void)hipGetLastError();
+            pl->segments.clear();
+            pl->dev = nullptr;
+            e = hipMalloc(&pl->dev, off_fb + 256);
+        }
+        if (e == hipSuccess && !pl->segments.empty()) {
+            char *base = static_cast<char *>(pl->dev);
+            pl->d_segments = reinterpret_cast<PrefillSegment *>(base + off_seg);
+            pl->d_seg_begin = reinterpret_cast<int32_t *>(base + off_sb);
+            pl->d_split = reinterpret_cast<PrefillSplitTile *>(base + off_split);
+            pl->d_part_bail = reinterpret_cast<int32_t *>(base + off_bail);
+            pl->d_part_data = reinterpret_cast<float *>(base + off_part);
+            std::vector<char> image(off_bail - off_seg, 0);
+            memcpy(image.data(), pl->segments.data(), sizeof(PrefillSegment) * pl->segments.size());
+            memcpy(image.data() + (off_sb - off_seg), pl->seg_begin.data(), sizeof(int32_t) * pl->seg_begin.size());
+            if (!pl->split.empty()) memcpy(image.data() + (off_split - off_seg), pl->split.data(), sizeof(PrefillSplitTile) * pl->split.size());
+            e = hipMemcpy(base + off_seg, image.data(), image.size(), hipMemcpyHostToDevice);
+        }
         if (e == hipSuccess) {
             pl->d_fallback = reinterpret_cast<unsigned int *>(static_cast<char *>(pl->dev) + off_fb);
             e = hipMemset(pl->d_fallback, 0, 256);
@@ -1974,7 +2120,9 @@ extern "C" int attn_prefill_plan_run_ws(hkv_prefill_plan *plan, const void *q, f
         view = PoolView{k_dst, v_dst, nullptr, nullptr, view.num_kv_heads, HKV_BF16};
     }
     PrefillLaunch a{view, q, plan->d_tiles, plan->d_block_table, out, lse_out,
-                    (int32_t)plan->tiles.size(), plan->num_q_heads, scale, plan->d_fallback};
+                    (int32_t)plan->tiles.size(), plan->num_q_heads, scale, plan->d_fallback,
+                    plan->d_segments, plan->d_seg_begin, plan->d_split, plan->d_part_data, plan->d_part_bail,
+                    plan->d_segments ? (int32_t)plan->seg_begin.size() - 1 : 0, (int32_t)plan->split.size()};
     HKV_HIP(launch_prefill(a, static_cast<hipStream_t>(stream)));
     return HKV_OK;
 }

@@ -38,6 +38,22 @@ struct PrefillTile {
     int32_t bt_off;     // offset of the request's row in the uploaded block table
 };
 
+// A run of a prefill tile's 64-token key blocks, one workgroup's work where tiles are split along their keys.
+struct PrefillSegment {
+    PrefillTile t;      // the tile, its positions, lengths and table offset moved to the segment's first key
+    int32_t kv_end;     // keys of the segment (a multiple of 64 unless it is the tile's last)
+    int32_t part;       // partial result it writes; -1: the segment is the whole tile and writes the output itself
+};
+// A tile cut into segments: its partials are part0 .. part0 + n_parts - 1.
+struct PrefillSplitTile {
+    PrefillTile t;
+    int32_t part0;
+    int32_t n_parts;
+};
+// One partial of a split tile: 256 rows of unnormalised fp32 o in the accumulators' register order, then per row the
+// softmax reference and the row sum, then whether the running-maximum path was taken.
+constexpr size_t kSplitPartFloats = 256 * kHeadDim + 2 * 256;
+
 struct PoolView {
     const void *k_pages;
     const void *v_pages;
@@ -93,6 +109,15 @@ struct PrefillLaunch {
     int32_t num_q_heads;
     float scale;
     unsigned int *fallback_tiles;  // device, may be null: counts the tiles that had to repeat with a running maximum
+    // Tiles split along their keys (n_workers > 0): worker w runs the segments seg_begin[w] .. seg_begin[w + 1] - 1, then a
+    // second kernel combines the partials of the n_split cut tiles.
+    const PrefillSegment *segments;     // device
+    const int32_t *seg_begin;           // device [n_workers + 1]
+    const PrefillSplitTile *split;      // device
+    float *part_data;                   // device, kSplitPartFloats per partial
+    int32_t *part_bail;                 // device, one per partial
+    int32_t n_workers;
+    int32_t n_split;
 };
 
 struct PoolWriteLaunch {

@@ -89,16 +89,22 @@ struct TileArgs {
     int32_t max_parts;
     const int32_t *q_rows;       // decode items, may be null: row r of the plan reads row q_rows[r] of q
     unsigned int *fallback_tiles;  // may be null: incremented once per tile that takes the running-maximum path
+    const int32_t *seg_begin;      // split prefill: tiles is PrefillSegment[], workgroup w runs seg_begin[w] .. seg_begin[w + 1] - 1
+    float *part_data;              // split prefill: kSplitPartFloats per partial
+    int32_t *part_bail;            // split prefill: whether a partial took the running-maximum path
 };
 
 // DECODE: decode work items (persistent workgroups, partial results) instead of prefill tiles.
+// SPLIT: segments of prefill tiles (a run of a tile's key blocks), several per workgroup; a segment that is not the whole
+// tile writes a partial result (unnormalised o, reference, row sum, all fp32) for prefill_merge_kernel.
 // FP8: the pool holds e4m3 codes with a scale per 16-token block and head (decode items only).
 // lds: kLdsBytes of the workgroup's LDS, 16-byte aligned.  The workgroup (kThreads threads, thread index
 // threadIdx.x) runs tiles first, first + stride, ... (prefill runs one: stride is not used).
 constexpr int kLdsBytes = 2 * kStages * kTileBytes + kIdSlots * 4 + kScaleSlots * 16 + 16;
 
-template <bool DECODE, bool FP8>
+template <bool DECODE, bool FP8, bool SPLIT = false>
 __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, int stride) {
+    static_assert(!SPLIT || !DECODE, "segments are cut from prefill tiles");
     static_assert(DECODE || !FP8, "prefill reads fp8 pools through the dequantising pre-pass");
     char(*sK)[kTileBytes] = reinterpret_cast<char(*)[kTileBytes]>(lds);
     char(*sV)[kTileBytes] = reinterpret_cast<char(*)[kTileBytes]>(lds + kStages * kTileBytes);
@@ -151,12 +157,14 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     const int va_base = n * 32 + ((h ^ ((n >> 3) & 1)) << 4);
 
     // prefill: one tile per workgroup; decode items: workgroup w runs items w, w + grid, ...
-    for (int ti = first; ti < a.n_tiles; ti += stride) {
-    if (DECODE && ti != first) __syncthreads();  // everyone has left the last item's LDS
+    const int begin = SPLIT ? a.seg_begin[first] : first, end = SPLIT ? a.seg_begin[first + 1] : a.n_tiles;
+    for (int ti = begin; ti < end; ti += SPLIT ? 1 : stride) {
+    if ((DECODE || SPLIT) && ti != begin) __syncthreads();  // everyone has left the last item's LDS
 
     // ---- the tile: kv_head, n_slots tokens (requests) x G heads, keys 0 .. kv_end-1 of the page list bt
     int kv_head, n_slots, kv_len, kv_end, pos_first;
     const int32_t *bt;
+    int part = -1;  // SPLIT: the partial this segment writes
     PrefillTile tl{};
     DecodeItem it{};
     if constexpr (DECODE) {
@@ -167,11 +175,18 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
         pos_first = it.n_tokens - 1;  // every row sees every token of the item
         bt = a.ids + it.page_off;
     } else {
-        tl = static_cast<const PrefillTile *>(a.tiles)[ti];
+        if constexpr (SPLIT) {
+            const PrefillSegment sg = static_cast<const PrefillSegment *>(a.tiles)[ti];
+            tl = sg.t;
+            kv_end = sg.kv_end;
+            part = sg.part;
+        } else {
+            tl = static_cast<const PrefillTile *>(a.tiles)[ti];
+            kv_end = tl.prefix_len + tl.q_begin + tl.n_q;  // keys any row of the tile can see
+        }
         kv_head = tl.kv_head;
         n_slots = tl.n_q;
         kv_len = tl.kv_len;
-        kv_end = tl.prefix_len + tl.q_begin + tl.n_q;  // keys any row of the tile can see
         pos_first = tl.prefix_len + tl.q_begin;
         bt = a.ids + tl.bt_off;
     }
@@ -407,6 +422,8 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
 #pragma unroll
         for (int i = 1; i < 16; ++i) mx = fmaxf(mx, sa[i] * s0.ck[i >> 3]);
         mc = fmaxf(mx, __shfl_xor(mx, 32));
+        // a row that lies in front of the whole segment sees nothing of it: exp2(-inf - 0) = 0 throughout
+        if (SPLIT && mc == -INFINITY) mc = 0.f;
     }
 
     // One phase, written in issue order and fenced so that the compiler keeps it.  Operands live in
@@ -551,7 +568,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     if (__builtin_amdgcn_ballot_w64(!(l_run < kSumLimit))) sBail = 1;
     __syncthreads();
     const bool bail = sBail != 0;
-    if (bail && tid == 0 && a.fallback_tiles) atomicAdd(a.fallback_tiles, 1u);
+    if (bail && tid == 0 && a.fallback_tiles && (!SPLIT || part < 0)) atomicAdd(a.fallback_tiles, 1u);
     float m_fin = mc;
 
     // =========================================================================================
@@ -597,7 +614,8 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
 #pragma unroll
                 for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i] * sc.ck[i >> 3]);
                 mx = fmaxf(mx, __shfl_xor(mx, 32));
-                const float m_new = fmaxf(m_run, mx);
+                const float m_top = fmaxf(m_run, mx);
+                const float m_new = SPLIT && m_top == -INFINITY ? 0.f : m_top;  // (nothing seen so far)
                 const float alpha = fast_exp2(m_run - m_new);
                 float p[16];
                 float sum0 = 0.f, sum1 = 0.f;
@@ -612,7 +630,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
                 u32x4 w[2];
                 pack_probs(w, p);
                 l_run = l_run * alpha + sum0 * sc.iv[0] + sum1 * sc.iv[1];
-                m_run = m_new;
+                m_run = m_top;
 #pragma unroll
                 for (int dm = 0; dm < 4; ++dm)
 #pragma unroll
@@ -627,6 +645,20 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
 
     // ---- normalise and store; lane (n, h) holds dims 32*dm + 8*(i/4) + 4*h + i%4 of its row
     const float l_tot = l_run + __shfl_xor(l_run, 32);
+    if (SPLIT && part >= 0) {  // the partial, in register order: every store is a whole KiB per wavefront
+        float *pd = a.part_data + (size_t)part * kSplitPartFloats;
+        f32x4 *po = reinterpret_cast<f32x4 *>(pd) + wave * (16 * 64) + lane;
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            po[64 * k] = f32x4{o[k >> 2][4 * (k & 3)], o[k >> 2][4 * (k & 3) + 1], o[k >> 2][4 * (k & 3) + 2], o[k >> 2][4 * (k & 3) + 3]};
+        if (h == 0) {
+            float *pm = pd + 256 * kHeadDim + 64 * wave + n;
+            pm[0] = l_tot > 0.f ? m_fin : -INFINITY;
+            pm[32] = l_tot;
+        }
+        if (tid == 0) a.part_bail[part] = bail ? 1 : 0;
+        continue;
+    }
     float up = 1.f, down = 1.f;
     if constexpr (DECODE) {  // the partial goes out as fp16 times a power of two that puts the row's largest value near 2^14
         float amax = 0.f;
@@ -668,7 +700,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
             if (a.lse_out && h == 0) a.lse_out[io_row] = (m_fin + fast_log2(l_tot)) * kLn2;
         }
     }
-    if constexpr (!DECODE) break;
+    if constexpr (!DECODE && !SPLIT) break;
     }  // tiles of this workgroup
 }
 

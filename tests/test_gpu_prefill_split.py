@@ -1,0 +1,100 @@
+"""Suffix prefill of batches small enough to be split along their keys: one to a few requests over a long cached prefix, so that
+a tile's key blocks go to several workgroups and a second kernel combines their results.  Segments that end inside the causal
+part (rows that see nothing of one), ragged ends with NaN behind them, pages of several blocks, a dominant key inside one
+segment (running-maximum path, counted once per tile), whole tiles in front of cut ones, against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2603_16104_amd import workloads as wl
+
+from test_gpu_parity import LSE_ABS_FP8_PREFILL, both_pools, check_close, check_lse, gpu  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def workload(hq, hk, prefix, new, kv_dtype=wl.KV_BF16, page_size=16, cls=wl.Workload):
+    parent, ntok = [-1] + [0] * len(new), [prefix] + list(new)
+    n_used = sum((t + page_size - 1) // page_size for t in ntok)
+    pages = np.random.default_rng([prefix, *new]).permutation(n_used + 5).astype(np.int32)
+    f = wl.make_forest(parent, ntok, list(range(1, len(new) + 1)), pages, page_size)
+    return cls(name=f"{hq}_{hk}_{prefix}_{new}", num_q_heads=hq, num_kv_heads=hk, kv_dtype=kv_dtype, num_pages=n_used + 5, seed=prefix + sum(new),
+               forest=f, mode="prefill", q_len=np.asarray(new, dtype=np.int32))
+
+
+def run(gpu, oracle, w, runs=1):  # noqa: F811
+    import torch
+    from paper_2603_16104_amd import binding as hkv
+    hp, dp = both_pools(gpu, oracle, w)
+    exp_o, exp_l = oracle.run_workload(w, hp)
+    r = gpu.PrefillRunner(dp, w)
+    for _ in range(runs):
+        r.out.fill_(0x7FC0)
+        r.lse.fill_(float("nan"))
+        r.run()
+    torch.cuda.synchronize()
+    got_o, got_l = gpu.bf16_tensor_to_f64(r.out), r.lse.cpu().numpy()
+    fallback = hkv.hkv_prefill_plan_fallback_tiles(r.plan)
+    n_tiles = len(hkv.hkv_prefill_plan_tiles(r.plan))
+    r.close()
+    dp.close()
+    check_close(got_o, exp_o, w.name)
+    check_lse(got_l, exp_l, w.name, tol=LSE_ABS_FP8_PREFILL if w.kv_dtype == wl.KV_FP8_E4M3 else 2e-3 + 1e-6 * np.abs(exp_l).max())
+    return fallback, n_tiles
+
+
+@pytest.mark.parametrize("hq, hk, prefix, new", [
+    (8, 2, 2048, (1,)), (8, 2, 2048, (64,)), (8, 2, 2064, (65, 3)), (8, 2, 4112, (200,)),
+    (2, 2, 1040, (255,)), (2, 2, 1040, (257, 300)), (4, 2, 1104, (700,)),       # 256 resp. 128 tokens per tile: segments cut the diagonal
+    (5, 1, 1500 // 16 * 16, (51, 52, 103)), (16, 1, 1600, (16, 17, 1)), (3, 3, 1024, (86, 400)),
+    (8, 8, 1008, (256 * 9 + 1,)),                                              
+])
+def test_split_prefill(gpu, oracle, hq, hk, prefix, new):  # noqa: F811
+    assert run(gpu, oracle, workload(hq, hk, prefix, new), runs=2)[0] == 0
+
+
+@pytest.mark.parametrize("kv_dtype, page_size", [(wl.KV_FP8_E4M3, 16), (wl.KV_BF16, 64), (wl.KV_FP8_E4M3, 32)])
+def test_split_prefill_pools_and_pages(gpu, oracle, kv_dtype, page_size):  # noqa: F811
+    run(gpu, oracle, workload(8, 2, 2048, (77, 130), kv_dtype, page_size))
+
+
+class Loud(wl.Workload):
+    """One token in the middle of the prefix whose key dwarfs the others."""
+
+    def node_kv(self, node):
+        k, v = super().node_kv(node)
+        if node == 0:
+            k = wl.bf16_bits_to_f32(k).copy()
+            k[1500] = 60.0 * np.sign(k[1500])
+            k = wl.f32_to_bf16_bits(k)
+        return k, v
+
+
+def test_split_prefill_running_maximum(gpu, oracle):  # noqa: F811
+    fallback, n_tiles = run(gpu, oracle, workload(8, 2, 3072, (130,), cls=Loud))
+    assert 0 < fallback <= n_tiles
+
+
+def test_split_prefill_under_graph_replay(gpu):  # noqa: F811
+    """Two kernels over the plan's own partials: every replay gives the eager result's bits."""
+    import torch
+    w = workload(8, 2, 2048, (130, 40))
+    dp = gpu.DevicePool(w.num_pages, w.num_kv_heads, w.kv_dtype)
+    dp.fill_from(w)
+    r = gpu.PrefillRunner(dp, w)
+    r.run()
+    torch.cuda.synchronize()
+    ref_o, ref_l = r.out.clone(), r.lse.clone()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        r.run()
+    for _ in range(3):
+        r.out.fill_(7)
+        r.lse.fill_(3.0)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(r.out, ref_o) and torch.equal(r.lse, ref_l)
+        r.run()                                        # eager work on the same partials between replays
+    del g
+    r.close()
+    dp.close()
