@@ -2101,7 +2101,7 @@ extern "C" int attn_prefill_plan_run_ws(hkv_prefill_plan *plan, const void *q, f
     if ((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(out)) & 15)
         return fail(HKV_EINVAL, "attn_prefill_plan_run: q and out must be 16-byte aligned");
     if (!plan->dev) return fail(HKV_EINVAL, "attn_prefill_plan_run: plan was built host-only");
-    if (plan->pool->d.dtype == HKV_FP32) {  // full-precision path: one wavefront per (new token, head)
+    if (plan->pool->d.dtype == HKV_FP32) {  // full-precision path
         RowsLaunch r{view_of(plan->pool), static_cast<const float *>(q), plan->d_block_table, plan->d_rows_req, plan->d_rows_len,
                      static_cast<float *>(out), lse_out, plan->total_q, plan->num_q_heads, plan->max_pages, scale};
         HKV_HIP(launch_rows_fp32(r, static_cast<hipStream_t>(stream)));

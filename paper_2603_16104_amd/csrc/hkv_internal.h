@@ -184,7 +184,7 @@ struct PoolDequantLaunch {
     void *v_dst;
 };
 
-// fp32 pools: one wavefront per (query token, query head), no sharing (rows_fp32.hip).
+// fp32 pools: a workgroup per (query token, KV head, pair of its query heads), no sharing between requests (rows_fp32.hip).
 struct RowsLaunch {
     PoolView pool;
     const float *q;              // [n_q_tokens][Hq][128] fp32

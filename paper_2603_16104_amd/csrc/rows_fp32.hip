@@ -1,107 +1,183 @@
 // Full-precision path for fp32 pools: plain softmax attention of every query row over its request's
 // block table, all arithmetic in fp32 on the vector ALUs (no matrix cores, no bf16 rounding anywhere),
-// so that fp32 inputs meet the 1e-4 bound.  One wavefront per (query token, query head); nothing is
-// shared between requests here: this path is for checking and for callers that need the precision,
-// not a throughput path.  (Same definition as everywhere: Section 2, "Scope": the result equals plain
-// attention over the request's whole key/value sequence.)
+// so that fp32 inputs meet the 1e-4 bound.  Nothing is shared between requests here: this path is for
+// checking and for callers that need the precision.  (Same definition as everywhere: Section 2, "Scope":
+// the result equals plain attention over the request's whole key/value sequence.)
 //
 // fp32 block format: K in 64-byte dimension chunks of 16 floats, chunk-major then slot
 // ((d / 16) * 256 + slot * 16 + d % 16); V dimension-major (d * 16 + slot).
+#include <algorithm>
+
 #include "hkv_device.h"
 
 namespace hkv {
 
 namespace {
 
-constexpr int kRowWaves = 4;
+// One workgroup per (query token, KV head, up to kRows of its query heads): its wavefronts take turns at steps of two
+// pages and combine in LDS.  Bound by the latency of a chain of steps per wavefront (K of the next step is requested
+// behind the first product, V behind the second), then by K/V from L2.  Every load is one KiB a wavefront: lane = (slot,
+// quarter of a 16-dimension chunk) for K, (dimension, quarter of the slots) for V, so a dot product is 32 multiply-adds in a
+// lane and two adds over its quad.  A wavefront per (token, head) with a lane per key read 64-byte pieces, walked all keys
+// alone and took 118 us for 16 requests x 32 heads over 1024 + 256 tokens on half of the chip; this takes 20.5 us (512 new
+// tokens over 2048: 3.02 -> 0.77 ms), with a third of the rounding error, the dot products being shorter chains.
+constexpr int kRowWaves = 8;  // at most; fewer for short sequences (the launch decides)
+constexpr int kStepPages = 2;
+constexpr int kStepKeys = kStepPages * kPage;
 
-__device__ __forceinline__ float wave_max_f(float v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
+// the value of lane (lane & ~3) + i of the same quad ...
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
 }
-__device__ __forceinline__ float wave_sum_f(float v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRor4 = 0x124, kRor8 = 0x128;
+__device__ __forceinline__ float quad_sum(float v) {
+    v += dpp<kQuadXor1>(v);
+    return v + dpp<kQuadXor2>(v);
 }
 
-__global__ __launch_bounds__(64 * kRowWaves) void rows_fp32_kernel(RowsLaunch a) {
-    __shared__ float sQ[kRowWaves][kHeadDim];
-    __shared__ float sP[kRowWaves][64];
-    __shared__ int sPage[kRowWaves][4];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const long row = (long)blockIdx.x * kRowWaves + wave;
-    const bool live = row < (long)a.n_q_tokens * a.num_q_heads;
-    const int tq = live ? (int)(row / a.num_q_heads) : 0, h = live ? (int)(row % a.num_q_heads) : 0;
-    const int G = a.num_q_heads / a.pool.num_kv_heads, kvh = h / G;
-    const int req = a.row_req[tq];
-    const int len = live ? a.row_len[tq] : 0;  // keys this query token sees
-    const int32_t *bt = a.block_table + (size_t)req * a.max_pages;
-    const float *K = static_cast<const float *>(a.pool.k_pages), *V = static_cast<const float *>(a.pool.v_pages);
-    const float *qp = a.q + ((size_t)tq * a.num_q_heads + h) * kHeadDim;
-    sQ[wave][lane] = live ? qp[lane] : 0.f;
-    sQ[wave][64 + lane] = live ? qp[64 + lane] : 0.f;
-    __syncthreads();
-    float m = -INFINITY, l = 0.f, acc0 = 0.f, acc1 = 0.f;  // this lane owns dims 2*lane, 2*lane + 1
-    // The trip count differs between the wavefronts of a workgroup, so nothing below synchronises across
-    // them: sP and sPage are per wavefront, and LDS operations of one wavefront execute in order.
-    for (int t0 = 0; t0 < len; t0 += 64) {
-        const int t = t0 + lane;
-        const bool valid = t < len;
-        float s = -INFINITY;
-        if (valid) {
-            const size_t blk = ((size_t)bt[t >> 4] * a.pool.num_kv_heads + kvh) * kBlockElems;
-            const float *kp = K + blk + (t & 15) * 16;
-            float dot = 0.f;
+template <int kRows>
+__global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch a) {
+    static_assert(kRows == 1 || kRows == 2, "a lane of a quad stands for one row and page of a step");
+    __shared__ float sP[kRowWaves][kRows][kStepKeys];
+    __shared__ float sO[kRowWaves][kRows][kHeadDim];
+    __shared__ float sM[kRowWaves][kRows], sL[kRowWaves][kRows];
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int Hkv = a.pool.num_kv_heads, G = a.num_q_heads / Hkv, groups = (G + kRows - 1) / kRows;
+    const int kvh = (int)(blockIdx.x % Hkv);  // a head stays on its XCD where there are eight
+    const int rest = (int)(blockIdx.x / Hkv), h0 = rest % groups * kRows, tq = rest / groups;
+    const int len = a.row_len[tq];  // keys this query token sees
+    const int32_t *bt = a.block_table + (size_t)a.row_req[tq] * a.max_pages;
+    const float *K = static_cast<const float *>(a.pool.k_pages) + (size_t)kvh * kBlockElems + 4 * lane;
+    const float *V = static_cast<const float *>(a.pool.v_pages) + (size_t)kvh * kBlockElems + 4 * lane;
+    const size_t page_stride = (size_t)Hkv * kBlockElems;
+    const int slot = lane >> 2, quarter = lane & 3, n_waves = (int)blockDim.x >> 6;
+    // in a quad every lane owns one (page of the step, row): its exponentials and row sums
+    const int own_page = kRows == 2 ? quarter >> 1 : quarter & 1, own_row = kRows == 2 ? quarter & 1 : 0;
+    const bool counts = kRows == 2 || quarter < 2;  // (one row: the upper two lanes repeat the lower two)
+    const float c = a.scale * kLog2e;
+
+    f32x4 qf[kRows][8];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
+    for (int r = 0; r < kRows; ++r) {
+        const float *qp = a.q + ((size_t)tq * a.num_q_heads + kvh * G + min(h0 + r, G - 1)) * kHeadDim + 4 * quarter;
 #pragma unroll
-                for (int j4 = 0; j4 < 4; ++j4) {
-                    const f32x4 kv = *reinterpret_cast<const f32x4 *>(kp + c * 256 + 4 * j4);
+        for (int i = 0; i < 8; ++i) qf[r][i] = *reinterpret_cast<const f32x4 *>(qp + 16 * i);
+    }
+    const int n_steps = (len + kStepKeys - 1) / kStepKeys, last_page = max(len - 1, 0) >> 4;
+    f32x4 kf[kStepPages][8], vf[kStepPages][8];
+    auto fetch = [&](f32x4 (&f)[kStepPages][8], const float *base, int step) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) dot = __builtin_fmaf(sQ[wave][c * 16 + 4 * j4 + j], kv[j], dot);
-                }
-            }
-            s = dot * a.scale;
+        for (int g = 0; g < kStepPages; ++g) {
+            const float *p = base + (size_t)bt[min(step * kStepPages + g, last_page)] * page_stride;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) f[g][i] = *reinterpret_cast<const f32x4 *>(p + 256 * i);
         }
-        const float m_new = fmaxf(m, wave_max_f(s));  // finite: the step holds at least one valid key
-        const float p = valid ? __expf(s - m_new) : 0.f;
-        const float alpha = __expf(m - m_new);         // 0 on the first step (m = -inf)
-        l = l * alpha + wave_sum_f(p);
-        acc0 *= alpha;
-        acc1 *= alpha;
+    };
+    float m = -INFINITY, l = 0.f;  // of the own row: running maximum (times scale * log2 e), this lane's share of the row sum
+    f32x4 acc[kRows][2];           // dims 16 i + slot of row r, this lane's quarter of the slots: element i % 4 of acc[r][i / 4]
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) acc[r][0] = acc[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (wave < n_steps) {
+        fetch(kf, K, wave);
+        fetch(vf, V, wave);
+    }
+    for (int step = wave; step < n_steps; step += n_waves) {
+        float s[kStepPages][kRows];
+#pragma unroll
+        for (int g = 0; g < kStepPages; ++g)
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                float dot = 0.f;
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) dot = __builtin_fmaf(qf[r][i][j], kf[g][i][j], dot);
+                s[g][r] = quad_sum(dot);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(kf, K, step + n_waves);  // the K registers are free (behind the last step: its page again, in bounds)
+        __builtin_amdgcn_sched_barrier(0);
+        float x = kRows == 2 ? (own_row ? (own_page ? s[1][kRows - 1] : s[0][kRows - 1]) : (own_page ? s[1][0] : s[0][0])) : (own_page ? s[1][0] : s[0][0]);
+        x = (step * kStepPages + own_page) * kPage + slot < len ? x * c : -INFINITY;
+        float mx = fmaxf(x, dpp<kRor4>(x));  // over the lanes of the own row: slots ...
+        mx = fmaxf(mx, dpp<kRor8>(mx));
+        mx = rows_max(mx);
+        mx = fmaxf(mx, kRows == 2 ? dpp<kQuadXor2>(mx) : dpp<kQuadXor1>(mx));  // ... and pages
+        const float m_new = fmaxf(m, mx);     // finite: the step holds at least one valid key
+        const float alpha = fast_exp2(m - m_new);  // 0 on the first step (m = -inf)
+        const float p = fast_exp2(x - m_new);
+        l = l * alpha + p;
         m = m_new;
-        sP[wave][lane] = p;
-        if (lane < 4) sPage[wave][lane] = (t0 + 16 * lane < len) ? bt[(t0 >> 4) + lane] : -1;
-        __builtin_amdgcn_wave_barrier();
+        if (counts) sP[wave][own_row][own_page * kPage + slot] = p;
+        __builtin_amdgcn_wave_barrier();  // (LDS operations of one wavefront execute in order)
+        const bool tail = (step + 1) * kStepKeys > len;
 #pragma unroll
-        for (int pg = 0; pg < 4; ++pg) {
-            const int page = sPage[wave][pg];
-            if (page < 0) continue;  // uniform
-            const float *vp = V + ((size_t)page * a.pool.num_kv_heads + kvh) * kBlockElems + (2 * lane) * 16;
+        for (int r = 0; r < kRows; ++r) {
+            const float al = kRows == 2 ? (r ? dpp<0x55>(alpha) : dpp<0x00>(alpha)) : alpha;  // the row's factor from its lane of the quad
+            acc[r][0] *= al;
+            acc[r][1] *= al;
+        }
 #pragma unroll
-            for (int j4 = 0; j4 < 4; ++j4) {
-                const f32x4 v0 = *reinterpret_cast<const f32x4 *>(vp + 4 * j4);
-                const f32x4 v1 = *reinterpret_cast<const f32x4 *>(vp + 16 + 4 * j4);
+        for (int g = 0; g < kStepPages; ++g) {
+            if (tail) {  // slots past the sequence end may hold anything (NaN included)
+                const int left = len - (step * kStepPages + g) * kPage - 4 * quarter;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float pj = sP[wave][pg * 16 + 4 * j4 + j];
-                    if (pj != 0.f) {  // slots past the sequence end may hold anything (NaN included)
-                        acc0 = __builtin_fmaf(pj, v0[j], acc0);
-                        acc1 = __builtin_fmaf(pj, v1[j], acc1);
-                    }
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) vf[g][i][j] = j < left ? vf[g][i][j] : 0.f;
+            }
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const f32x4 pr = *reinterpret_cast<const f32x4 *>(&sP[wave][r][g * kPage + 4 * quarter]);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    float o = acc[r][i >> 2][i & 3];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) o = __builtin_fmaf(pr[j], vf[g][i][j], o);
+                    acc[r][i >> 2][i & 3] = o;
                 }
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(vf, V, step + n_waves);
+        __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_wave_barrier();
     }
-    if (!live) return;
-    float *op = a.out + ((size_t)tq * a.num_q_heads + h) * kHeadDim;
-    const float inv = l > 0.f ? 1.0f / l : 0.f;  // a row without keys gives out = 0, lse = -inf
-    op[2 * lane] = acc0 * inv;
-    op[2 * lane + 1] = acc1 * inv;
-    if (a.lse_out && lane == 0) a.lse_out[(size_t)tq * a.num_q_heads + h] = l > 0.f ? m + __logf(l) : -INFINITY;
+    // the own row's sum over its lanes, the dims over the quads; then the wavefronts
+    float lt = l + dpp<kRor4>(l);
+    lt += dpp<kRor8>(lt);
+    lt = rows_sum(lt);
+    lt += kRows == 2 ? dpp<kQuadXor2>(lt) : dpp<kQuadXor1>(lt);
+    if (lane < kRows) {  // lanes 0 and 1 own rows 0 and 1
+        sM[wave][lane] = m;
+        sL[wave][lane] = lt;
+    }
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float o = quad_sum(acc[r][i >> 2][i & 3]);
+            if (quarter == (i & 3)) sO[wave][r][16 * i + slot] = o;
+        }
+    __syncthreads();
+    for (int t = threadIdx.x; t < kRows * kHeadDim; t += blockDim.x) {
+        const int r = t / kHeadDim, d = t % kHeadDim;
+        if (h0 + r >= G) return;
+        float M = -INFINITY;
+        for (int w = 0; w < n_waves; ++w) M = fmaxf(M, sM[w][r]);
+        float L = 0.f, out = 0.f;
+        if (M != -INFINITY) {
+            for (int w = 0; w < n_waves; ++w) {
+                const float f = fast_exp2(sM[w][r] - M);  // 0 for a wavefront without a step
+                L = __builtin_fmaf(sL[w][r], f, L);
+                out = __builtin_fmaf(sO[w][r][d], f, out);
+            }
+        }
+        const size_t row = (size_t)tq * a.num_q_heads + kvh * G + h0 + r;
+        a.out[row * kHeadDim + d] = L > 0.f ? out / L : 0.f;  // a row without keys gives out = 0, lse = -inf
+        if (a.lse_out && d == 0) a.lse_out[row] = L > 0.f ? (M + fast_log2(L)) * kLn2 : -INFINITY;
+    }
 }
 
 // fp32 source tokens -> fp32 block format, one thread per element
@@ -119,10 +195,29 @@ __global__ __launch_bounds__(256) void pool_write_fp32_kernel(PoolWriteLaunch a)
 }  // namespace
 
 hipError_t launch_rows_fp32(const RowsLaunch &a, hipStream_t s) {
-    const long rows = (long)a.n_q_tokens * a.num_q_heads;
-    if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(rows_fp32_kernel, dim3((unsigned)((rows + kRowWaves - 1) / kRowWaves)), dim3(64 * kRowWaves), 0, s, a);
-    return hipGetLastError();
+    const int Hkv = a.pool.num_kv_heads, G = a.num_q_heads / Hkv;
+    // a step is 32 keys: sequences that never reach four steps a wavefront would pay for wavefronts without one (128 query
+    // tokens of 17 to 32 keys, 32 heads: 24.2 us with eight, 12.5 us with two)
+    const int waves = a.max_pages > 16 ? kRowWaves : a.max_pages > 8 ? 4 : 2;
+    // two query heads of a KV head per workgroup: they share its K/V reads
+    const size_t per_token = (size_t)Hkv * (G == 1 ? 1 : (G + 1) / 2);
+    const size_t most = std::max<size_t>(1, ((size_t)1 << 31) / (per_token * 64 * waves));  // query tokens of a launch: below 2^32 threads
+    for (size_t t0 = 0; t0 < (size_t)std::max(a.n_q_tokens, 0); t0 += most) {
+        RowsLaunch b = a;
+        b.n_q_tokens = (int32_t)std::min(most, (size_t)a.n_q_tokens - t0);
+        b.q += t0 * a.num_q_heads * kHeadDim;
+        b.out += t0 * a.num_q_heads * kHeadDim;
+        if (b.lse_out) b.lse_out += t0 * a.num_q_heads;
+        b.row_req += t0;
+        b.row_len += t0;
+        const dim3 grid((unsigned)(b.n_q_tokens * per_token)), block(64 * waves);
+        if (G == 1)
+            hipLaunchKernelGGL(rows_fp32_kernel<1>, grid, block, 0, s, b);
+        else
+            hipLaunchKernelGGL(rows_fp32_kernel<2>, grid, block, 0, s, b);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_pool_write_fp32(const PoolWriteLaunch &a, hipStream_t s) {
