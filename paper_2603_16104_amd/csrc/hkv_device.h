@@ -103,6 +103,12 @@ __device__ __forceinline__ float rows_max(float v) {
     const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
     return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
+// A lane's value from another lane of its row of 16 (DPP control), in the vector ALU.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRor4 = 0x124, kRor8 = 0x128;
 __device__ __forceinline__ float rows_sum(float v) {
     uint32_t x = __float_as_uint(v);
     const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);

@@ -25,12 +25,6 @@ constexpr int kRowWaves = 8;  // at most; fewer for short sequences (the launch 
 constexpr int kStepPages = 2;
 constexpr int kStepKeys = kStepPages * kPage;
 
-// the value of lane (lane & ~3) + i of the same quad ...
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRor4 = 0x124, kRor8 = 0x128;
 __device__ __forceinline__ float quad_sum(float v) {
     v += dpp<kQuadXor1>(v);
     return v + dpp<kQuadXor2>(v);
