@@ -1766,8 +1766,8 @@ extern "C" size_t attn_decode_workspace_bytes(hkv_pool *pool, const hkv_node *no
 // end, cut where a worker's share is full.  Taken where the estimate says so (in key blocks of 64 tokens, 1.4 us each on a
 // full chip, a little less on one that is not): a tile or segment costs 4 blocks beside its own, the partials 135 KB each
 // on their way through memory and the second kernel 3 more.  Against a workgroup per tile, 32 / 8 heads, one request:
-// 64 / 256 / 1024 new tokens over 8192 cached ones 154 / 159 / 174 -> 53 / 59 / 145 us, 700 over 4096 95.5 -> 66.3,
-// 128 over 1024 29.9 -> 27.6; six requests of 256 to 512 over 2048 113.9 -> 108.  Where the estimate gains less than 13 %
+// 64 / 256 / 1024 new tokens over 8192 cached ones 154 / 159 / 174 -> 33 / 51 / 147 us, 700 over 4096 95.5 -> 64.3,
+// 128 over 1024 29.9 -> 22.4; six requests of 256 to 512 over 2048 113.9 -> 104.3.  Where the estimate gains less than 13 %
 // it was a loss as often as not (three of 1024 over 8192: estimate 0.89, measured 1.01).
 static void split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<PrefillTile> &head_tiles, int n_cu) {
     const int Hkv = pl.pool->d.num_kv_heads;

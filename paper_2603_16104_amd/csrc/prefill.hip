@@ -20,53 +20,58 @@ __global__ __launch_bounds__(kThreads, 2) void attn_tile_kernel(TileArgs a) {
 // Prefill tiles split along their keys: a persistent workgroup per compute unit runs an equal share of all key blocks.
 // Bound by the matrix cores like the tile itself; a batch of fewer tiles than compute units (or a little more than a
 // whole number of rounds) leaves the rest of the chip idle otherwise.  700 new tokens over 4096 cached ones, 88 tiles:
-// 95.5 us a workgroup per tile (0.53 PFLOP/s), 66.3 us split, both kernels (0.77).
+// 95.5 us a workgroup per tile (0.53 PFLOP/s), 64.3 us split, both kernels (0.79).
 __global__ __launch_bounds__(kThreads, 2) void prefill_split_kernel(TileArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[kLdsBytes];
     body<false, false, true>(a, lds, (int)blockIdx.x, 1);
 }
 
-// Combines the partials of the cut tiles: a wavefront per 32-row tile in the accumulators' register order, so that every
-// load is a whole KiB; log-sum-exp weights from the references and row sums.
+// Combines the partials of the cut tiles: a workgroup per 32 rows of a tile, a wavefront per quarter of their 128 dims, in
+// the accumulators' register order, so that every load is a whole KiB; log-sum-exp weights from the references and row sums.
+// Bound by the partials' bytes once enough wavefronts have loads in flight: 88 tiles in 256 shares (45 MB)
+// 12.4 -> 8.9 us (5 TB/s) against a wavefront per 32 whole rows; 64 new tokens over 8192 cached ones, 8 tiles of one
+// 32-row part each in 256 shares, 53 -> 33 us with the tiles.
 __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillLaunch p) {
-    const PrefillSplitTile st = p.split[blockIdx.x >> 1];
+    const PrefillSplitTile st = p.split[blockIdx.x];
     const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
-    const int wave = (int)(blockIdx.x & 1) * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int rt = (int)blockIdx.y, quarter = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int G = p.num_q_heads / p.pool.num_kv_heads;
-    const int r_tile = 32 * wave + n, tok = r_tile / G;
-    if (blockIdx.x % 2 == 0 && threadIdx.x == 0 && p.fallback_tiles) {
+    const int r_tile = 32 * rt + n, tok = r_tile / G;
+    if (rt == 0 && threadIdx.x == 0 && p.fallback_tiles) {
         int any = 0;
         for (int k = 0; k < st.n_parts; ++k) any |= p.part_bail[st.part0 + k];
         if (any) atomicAdd(p.fallback_tiles, 1u);
     }
-    if (32 * wave / G >= st.t.n_q) return;  // (wavefront-uniform) no row of this tile exists
+    if (32 * rt / G >= st.t.n_q) return;  // (workgroup-uniform) no row of these exists
     const float *pd = p.part_data + (size_t)st.part0 * kSplitPartFloats;
-    const float *pm = pd + 256 * kHeadDim + 64 * wave + n;
+    const float *pm = pd + 256 * kHeadDim + 64 * rt + n;
     float M = -INFINITY;
+#pragma unroll 4
     for (int k = 0; k < st.n_parts; ++k) M = fmaxf(M, pm[k * kSplitPartFloats]);
-    f32x4 acc[16];
+    f32x4 acc[4];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     float L = 0.f;
+#pragma unroll 4
     for (int k = 0; k < st.n_parts; ++k) {
         const float w = fast_exp2(pm[k * kSplitPartFloats] - M);  // (a row sees its own key at least: M is finite)
         L += w * pm[k * kSplitPartFloats + 32];
-        const f32x4 *po = reinterpret_cast<const f32x4 *>(pd + k * kSplitPartFloats) + wave * (16 * 64) + lane;
+        const f32x4 *po = reinterpret_cast<const f32x4 *>(pd + k * kSplitPartFloats) + rt * (16 * 64) + quarter * (4 * 64) + lane;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] += po[64 * i] * w;
+        for (int i = 0; i < 4; ++i) acc[i] += po[64 * i] * w;
     }
     if (tok >= st.t.n_q) return;
     const float inv = 1.0f / L;
     const uint32_t io_row = (uint32_t)(st.t.q_row0 + tok) * p.num_q_heads + st.t.kv_head * G + r_tile % G;
-    uint16_t *op = static_cast<uint16_t *>(p.out) + (size_t)io_row * kHeadDim;
+    uint16_t *op = static_cast<uint16_t *>(p.out) + (size_t)io_row * kHeadDim + 32 * quarter;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < 4; ++i) {
         u32x2 w;
         w[0] = pack_bf16(acc[i][0] * inv, acc[i][1] * inv);
         w[1] = pack_bf16(acc[i][2] * inv, acc[i][3] * inv);
         *reinterpret_cast<u32x2 *>(op + 8 * i + 4 * h) = w;
     }
-    if (p.lse_out && h == 0) p.lse_out[io_row] = (M + fast_log2(L)) * kLn2;
+    if (p.lse_out && quarter == 0 && h == 0) p.lse_out[io_row] = (M + fast_log2(L)) * kLn2;
 }
 
 }  // namespace
@@ -92,7 +97,7 @@ hipError_t launch_prefill(const PrefillLaunch &p, hipStream_t s) {
         a.part_data = p.part_data;
         a.part_bail = p.part_bail;
         hipLaunchKernelGGL(prefill_split_kernel, dim3(p.n_workers), dim3(kThreads), 0, s, a);
-        if (p.n_split > 0) hipLaunchKernelGGL(prefill_merge_kernel, dim3(2 * p.n_split), dim3(256), 0, s, p);
+        if (p.n_split > 0) hipLaunchKernelGGL(prefill_merge_kernel, dim3(p.n_split, 8), dim3(256), 0, s, p);
         return hipGetLastError();
     }
     hipLaunchKernelGGL((attn_tile_kernel<false, false>), dim3(p.n_tiles), dim3(kThreads), 0, s, a);
