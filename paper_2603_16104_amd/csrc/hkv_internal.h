@@ -87,8 +87,8 @@ struct DecodeLaunch {
     // Items [0, n_single) get a workgroup each; the items behind them (short, at most 16 rows) are run
     // four to a workgroup, one per wavefront.
     int32_t n_single;
-    // LDS stages of 16 KiB a workgroup owns (3..5): items shared by more than 16 query rows keep
-    // n_stages - 1 steps in flight.  The launch reserves n_stages * 16 KiB of LDS per workgroup.
+    // LDS stages of 16 KiB a workgroup owns (3..5; at least 4 where has_shared): the ring of items shared by more than
+    // 16 query rows.  The launch reserves n_stages * 16 KiB of LDS per workgroup.
     int32_t n_stages;
     // fp8 pools: run both products on the fp8 matrix instruction (codes of K and V as they are, query
     // and probabilities as two e4m3 terms each) instead of widening the codes to bf16.
