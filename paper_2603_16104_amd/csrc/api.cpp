@@ -1975,33 +1975,31 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
             pl->dev = nullptr;
             e = hipMalloc(&pl->dev, off_fb + 256);
         }
-        if (e == hipSuccess && !pl->segments.empty()) {
+        if (e == hipSuccess) {
             char *base = static_cast<char *>(pl->dev);
-            pl->d_segments = reinterpret_cast<PrefillSegment *>(base + off_seg);
-            pl->d_seg_begin = reinterpret_cast<int32_t *>(base + off_sb);
-            pl->d_split = reinterpret_cast<PrefillSplitTile *>(base + off_split);
-            pl->d_part_bail = reinterpret_cast<int32_t *>(base + off_bail);
-            pl->d_part_data = reinterpret_cast<float *>(base + off_part);
-            std::vector<char> image(off_bail - off_seg, 0);
-            memcpy(image.data(), pl->segments.data(), sizeof(PrefillSegment) * pl->segments.size());
-            memcpy(image.data() + (off_sb - off_seg), pl->seg_begin.data(), sizeof(int32_t) * pl->seg_begin.size());
-            if (!pl->split.empty()) memcpy(image.data() + (off_split - off_seg), pl->split.data(), sizeof(PrefillSplitTile) * pl->split.size());
-            e = hipMemcpy(base + off_seg, image.data(), image.size(), hipMemcpyHostToDevice);
-        }
-        if (e == hipSuccess) {
-            pl->d_fallback = reinterpret_cast<unsigned int *>(static_cast<char *>(pl->dev) + off_fb);
-            e = hipMemset(pl->d_fallback, 0, 256);
-        }
-        if (e == hipSuccess) {
             pl->d_tiles = static_cast<PrefillTile *>(pl->dev);
-            pl->d_block_table = reinterpret_cast<int32_t *>(static_cast<char *>(pl->dev) + off_bt);
-            pl->d_src_pages = reinterpret_cast<int32_t *>(static_cast<char *>(pl->dev) + off_src);
-            e = hipMemcpy(pl->d_tiles, pl->tiles.data(), sizeof(PrefillTile) * pl->tiles.size(), hipMemcpyHostToDevice);
+            pl->d_block_table = reinterpret_cast<int32_t *>(base + off_bt);
+            pl->d_src_pages = reinterpret_cast<int32_t *>(base + off_src);
+            pl->d_fallback = reinterpret_cast<unsigned int *>(base + off_fb);
+            // one image, one copy: with a blocking copy or fill for each part a plan over split tiles took 75-89 us to create,
+            // 30-38 this way, and a plan made for a single run has to gain that back
+            std::vector<char> image(pl->segments.empty() ? off_seg : off_bail, 0);
+            auto put = [&](size_t off, const auto &v) { if (!v.empty()) memcpy(image.data() + off, v.data(), sizeof(v[0]) * v.size()); };
+            put(0, pl->tiles);
+            put(off_bt, dev_table);
+            put(off_src, pl->src_pages);
+            if (!pl->segments.empty()) {
+                pl->d_segments = reinterpret_cast<PrefillSegment *>(base + off_seg);
+                pl->d_seg_begin = reinterpret_cast<int32_t *>(base + off_sb);
+                pl->d_split = reinterpret_cast<PrefillSplitTile *>(base + off_split);
+                pl->d_part_bail = reinterpret_cast<int32_t *>(base + off_bail);
+                pl->d_part_data = reinterpret_cast<float *>(base + off_part);
+                put(off_seg, pl->segments);
+                put(off_sb, pl->seg_begin);
+                put(off_split, pl->split);
+            }
+            e = hipMemcpy(pl->dev, image.data(), image.size(), hipMemcpyHostToDevice);
         }
-        if (e == hipSuccess)
-            e = hipMemcpy(pl->d_block_table, dev_table.data(), sizeof(int32_t) * dev_table.size(), hipMemcpyHostToDevice);
-        if (e == hipSuccess && !pl->src_pages.empty())
-            e = hipMemcpy(pl->d_src_pages, pl->src_pages.data(), sizeof(int32_t) * pl->src_pages.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess && pool->d.dtype == HKV_FP32 && pl->total_q > 0) {
             std::vector<int32_t> rr(2 * (size_t)pl->total_q);
             for (int r = 0; r < n_req; ++r)
