@@ -169,7 +169,8 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
             }
         }
         const size_t row = (size_t)tq * a.num_q_heads + kvh * G + h0 + r;
-        a.out[row * kHeadDim + d] = L > 0.f ? out / L : 0.f;  // a row without keys gives out = 0, lse = -inf
+        // a row without keys gives out = 0, lse = -inf; one whose scores hold a NaN or +inf, or only -inf, gives NaN
+        a.out[row * kHeadDim + d] = L > 0.f ? out / L : len > 0 ? __builtin_nanf("") : 0.f;
         if (a.lse_out && d == 0) a.lse_out[row] = L > 0.f ? (M + fast_log2(L)) * kLn2 : -INFINITY;
     }
 }

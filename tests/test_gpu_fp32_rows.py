@@ -30,3 +30,59 @@ def test_fp32_rows_edges(gpu, oracle, hq, hk, lens):  # noqa: F811
         check_lse(r.lse.cpu().numpy(), exp_l, w.name, tol=1e-4)
         r.close()
         dp.close()
+
+
+def one_row(gpu, K, V, q, q_heads, decode=True):  # noqa: F811
+    """out, lse of one request's newest token over K / V [tokens][kv_heads][128], fp32, through a decode or a prefill plan."""
+    import torch
+    from paper_2603_16104_amd import binding as hkv
+    n, H = K.shape[0], K.shape[1]
+    dp = gpu.DevicePool((n + 15) // 16, H, wl.KV_FP32)
+    pages = np.arange((n + 15) // 16, dtype=np.int32)
+    dp.write(pages, 0, torch.from_numpy(K).cuda(), torch.from_numpy(V).cuda())
+    out = torch.full((1, q_heads, 128), 7.0, dtype=torch.float32, device="cuda")
+    lse = torch.full((1, q_heads), 7.0, dtype=torch.float32, device="cuda")
+    qd = torch.from_numpy(q).cuda()
+    if decode:
+        f = wl.make_forest([-1], [n], [0], pages)
+        plan = hkv.hkv_decode_plan_create(dp.handle, f.nodes, f.node_pages, f.req_leaf, q_heads)
+        hkv.attn_decode_plan_run(plan, qd, 1.0, out, lse, torch.empty(256, dtype=torch.uint8, device="cuda"), 256)
+    else:
+        plan = hkv.hkv_prefill_plan_create(dp.handle, np.asarray([0, 1]), pages[None], np.asarray([n]), q_heads)
+        hkv.attn_prefill_plan_run(plan, qd, 1.0, out, lse)
+    torch.cuda.synchronize()
+    (hkv.hkv_decode_plan_destroy if decode else hkv.hkv_prefill_plan_destroy)(plan)
+    dp.close()
+    return out[0].cpu().numpy().astype(np.float64), lse[0].cpu().numpy().astype(np.float64)
+
+
+def exact_row(K, V, q, q_heads, keep):
+    """The same in float64 over the tokens `keep`."""
+    o, ls = np.zeros((q_heads, 128)), np.zeros(q_heads)
+    for h in range(q_heads):
+        kvh = h // (q_heads // K.shape[1])
+        s = K[keep, kvh].astype(np.float64) @ q[0, h].astype(np.float64)
+        ls[h] = s.max() + np.log(np.exp(s - s.max()).sum())
+        o[h] = np.exp(s - ls[h]) @ V[keep, kvh].astype(np.float64)
+    return o, ls
+
+
+def row_inputs(n, q_heads, kv_heads):
+    rng = np.random.default_rng([n, q_heads])
+    K = (0.1 * rng.standard_normal((n, kv_heads, 128))).astype(np.float32)
+    V = rng.standard_normal((n, kv_heads, 128)).astype(np.float32)
+    q = rng.standard_normal((1, q_heads, 128)).astype(np.float32)
+    q[:, :, 0] = 1.0
+    return K, V, q
+
+
+@pytest.mark.parametrize("value, tokens", [(np.nan, [5]), (np.nan, [150]), (np.nan, range(300)), (np.inf, [150]), (-np.inf, range(300))])
+def test_scores_without_a_softmax_give_nan(gpu, value, tokens):  # noqa: F811
+    """A NaN or +inf among a row's scores, or nothing but -inf: out is NaN and lse -inf, never a finite number."""
+    K, V, q = row_inputs(300, 4, 2)
+    K[list(tokens), 0, 0] = value                       # of KV head 0 only
+    got_o, got_l = one_row(gpu, K, V, q, 4)
+    exp_o, exp_l = exact_row(K[:, 1:], V[:, 1:], q[:, 2:], 2, range(300))
+    assert np.isnan(got_o[:2]).all() and np.isneginf(got_l[:2]).all()
+    check_close_fp32(got_o[2:], exp_o, "the other head")
+    check_lse(got_l[2:], exp_l, "the other head", tol=1e-4)
