@@ -98,9 +98,10 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
         mx = fmaxf(mx, dpp<kRor8>(mx));
         mx = rows_max(mx);
         mx = fmaxf(mx, kRows == 2 ? dpp<kQuadXor2>(mx) : dpp<kQuadXor1>(mx));  // ... and pages
-        const float m_new = fmaxf(m, mx);     // finite: the step holds at least one valid key
-        const float alpha = fast_exp2(m - m_new);  // 0 on the first step (m = -inf)
-        const float p = fast_exp2(x - m_new);
+        const float m_new = fmaxf(m, mx);
+        const float ref = m_new == -INFINITY ? 0.f : m_new;  // every score so far is -inf: their weights are 0, not exp(inf - inf)
+        const float alpha = fast_exp2(m - ref);              // 0 on the first step (m = -inf)
+        const float p = fast_exp2(x - ref);
         l = l * alpha + p;
         m = m_new;
         if (counts) sP[wave][own_row][own_page * kPage + slot] = p;

@@ -76,6 +76,18 @@ def row_inputs(n, q_heads, kv_heads):
     return K, V, q
 
 
+@pytest.mark.parametrize("n, quiet", [(100, range(32, 64)), (600, range(32, 64)), (600, range(0, 32)), (600, range(96, 600))])
+def test_keys_that_score_minus_infinity(gpu, n, quiet):  # noqa: F811
+    """A wavefront's first keys, or all of its keys, score -inf: their weight is zero, the rest is plain attention."""
+    K, V, q = row_inputs(n, 4, 2)
+    K[list(quiet), :, 0] = -np.inf
+    keep = [t for t in range(n) if t not in quiet]
+    exp_o, exp_l = exact_row(K, V, q, 4, keep)
+    got_o, got_l = one_row(gpu, K, V, q, 4)
+    check_close_fp32(got_o, exp_o, "-inf scores")
+    check_lse(got_l, exp_l, "-inf scores", tol=1e-4)
+
+
 @pytest.mark.parametrize("value, tokens", [(np.nan, [5]), (np.nan, [150]), (np.nan, range(300)), (np.inf, [150]), (-np.inf, range(300))])
 def test_scores_without_a_softmax_give_nan(gpu, value, tokens):  # noqa: F811
     """A NaN or +inf among a row's scores, or nothing but -inf: out is NaN and lse -inf, never a finite number."""
