@@ -68,8 +68,15 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
             for (int i = 0; i < 8; ++i) f[g][i] = *reinterpret_cast<const f32x4 *>(p + 256 * i);
         }
     };
-    float m = -INFINITY, l = 0.f;  // of the own row: running maximum (times scale * log2 e), this lane's share of the row sum
-    f32x4 acc[kRows][2];           // dims 16 i + slot of row r, this lane's quarter of the slots: element i % 4 of acc[r][i / 4]
+    float m, l;           // of the own row: running maximum (times scale * log2 e), this lane's share of the row sum
+    f32x4 acc[kRows][2];  // dims 16 i + slot of row r, this lane's quarter of the slots: element i % 4 of acc[r][i / 4]
+    // A value whose weight underflows to zero takes no part, whatever it is (0 * inf would be NaN).  Asking for that at every
+    // product would double the vector instructions, and infinities stay in a sum once they are there: a wavefront that ends
+    // with one in its sums walks its keys a second time, asking.
+    bool careful = false;
+  walk:
+    m = -INFINITY;
+    l = 0.f;
 #pragma unroll
     for (int r = 0; r < kRows; ++r) acc[r][0] = acc[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (wave < n_steps) {
@@ -112,6 +119,7 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
             const float al = kRows == 2 ? (r ? dpp<0x55>(alpha) : dpp<0x00>(alpha)) : alpha;  // the row's factor from its lane of the quad
             acc[r][0] *= al;
             acc[r][1] *= al;
+            if (careful && al == 0.f) acc[r][0] = acc[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
         for (int g = 0; g < kStepPages; ++g) {
@@ -125,6 +133,14 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
 #pragma unroll
             for (int r = 0; r < kRows; ++r) {
                 const f32x4 pr = *reinterpret_cast<const f32x4 *>(&sP[wave][r][g * kPage + 4 * quarter]);
+                if (careful) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (pr[j] != 0.f) acc[r][i >> 2][i & 3] = __builtin_fmaf(pr[j], vf[g][i][j], acc[r][i >> 2][i & 3]);
+                    continue;
+                }
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     float o = acc[r][i >> 2][i & 3];
@@ -138,6 +154,17 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
         fetch(vf, V, step + n_waves);
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_wave_barrier();
+    }
+    if (!careful) {
+        bool finite = true;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) finite = finite && fabsf(acc[r][i >> 2][i & 3]) < INFINITY;
+        if (__builtin_amdgcn_ballot_w64(!finite)) {
+            careful = true;
+            goto walk;
+        }
     }
     // the own row's sum over its lanes, the dims over the quads; then the wavefronts
     float lt = l + dpp<kRor4>(l);
@@ -166,7 +193,7 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
             for (int w = 0; w < n_waves; ++w) {
                 const float f = fast_exp2(sM[w][r] - M);  // 0 for a wavefront without a step
                 L = __builtin_fmaf(sL[w][r], f, L);
-                out = __builtin_fmaf(sO[w][r][d], f, out);
+                if (f != 0.f) out = __builtin_fmaf(sO[w][r][d], f, out);
             }
         }
         const size_t row = (size_t)tq * a.num_q_heads + kvh * G + h0 + r;

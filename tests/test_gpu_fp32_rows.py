@@ -76,6 +76,24 @@ def row_inputs(n, q_heads, kv_heads):
     return K, V, q
 
 
+@pytest.mark.parametrize("decode", [True, False])
+@pytest.mark.parametrize("hq, hk", [(2, 2), (4, 2), (3, 1)])
+@pytest.mark.parametrize("n, loud, where", [(30, 3, (7, 25)), (200, 60, (3, 61, 66, 199)), (700, 1, (0, 31, 32, 640)), (700, 690, (0, 40, 170, 300))])
+def test_values_of_no_weight_take_no_part(gpu, decode, hq, hk, n, loud, where):  # noqa: F811
+    """One key whose score passes the others by 500: their weights are zero in fp32, and infinities and NaN among their values
+    (in the same 32-key step, in another step of the same wavefront behind or in front of it, in other wavefronts) do not show."""
+    K, V, q = row_inputs(n, hq, hk)
+    K[:, :, 0] = 0.0
+    K[loud, :, 0] = 500.0
+    keep = [t for t in range(n) if t not in where]
+    exp_o, exp_l = exact_row(K, V, q, hq, keep)
+    for i, t in enumerate(where):
+        V[t, :, i::2] = (np.inf, -np.inf, np.nan)[i % 3]
+    got_o, got_l = one_row(gpu, K, V, q, hq, decode)
+    check_close_fp32(got_o, exp_o, "infinite values")
+    check_lse(got_l, exp_l, "infinite values", tol=2e-3)   # a score of 500 in 32 additions: 32 * 500 * 2^-24 = 1e-3
+
+
 @pytest.mark.parametrize("n, quiet", [(100, range(32, 64)), (600, range(32, 64)), (600, range(0, 32)), (600, range(96, 600))])
 def test_keys_that_score_minus_infinity(gpu, n, quiet):  # noqa: F811
     """A wavefront's first keys, or all of its keys, score -inf: their weight is zero, the rest is plain attention."""
