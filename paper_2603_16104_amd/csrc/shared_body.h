@@ -13,9 +13,12 @@
 // cycles; the vector instructions of a block (and, for fp8 pools, the widening of its codes to bf16) have to stay
 // below that.  With a 16-row tile per wavefront over all tokens they did not: every wavefront read every K/V operand
 // from LDS and widened it for 16 rows only, about 24 vector instructions per score and lane.  Here an operand
-// serves 32 rows, each wavefront touches half of the tokens, and the running maximum is lazy: the reference of a
-// row moves only when a score exceeds it by more than 8 powers of two (p <= 2^8; softmax does not depend on the
-// reference, and bf16 / fp32 keep their relative precision), so the accumulators are rescaled once or twice per item.
+// serves 32 rows and each wavefront touches half of the tokens.  bf16 pools: the reference is the running maximum.  The
+// probabilities are rounded to bf16, whose relative error is smallest just below a power of two (and nil at it): with the
+// maximum as reference that is where a row's heaviest weights lie, with any other they fall anywhere in the binade and the
+// error of a result grows by 6 % (0.00219 -> 0.00232 with references up to 8 powers of two behind, 0.00216 this way).
+// fp8 pools: a probability is multiplied by its block's V scale before it is rounded, so there is no such place; the
+// reference moves only when a score passes it by 8 powers of two, and the accumulators are rescaled once or twice per item.
 //
 // Latency, not issue rate, is what the first form of this loop ran into (3900 cycles per block with a fifth of them
 // busy): an LDS read takes about 200 cycles, so a phase reads its operands in bulk, runs S(j+1) = K(j+1) Q^T beside
@@ -33,7 +36,6 @@ namespace shared {
 
 constexpr int kWaves = 4;
 constexpr int kBlockTokens = 64;   // one half-step: K or V of four pages
-constexpr float kLazy = 8.0f;      // a reference moves when a score passes it by this many powers of two
 
 // Waits until at most n vector-memory operations of this wavefront are outstanding (and every LDS read has
 // returned, so that the slot it read may be overwritten behind the barrier that follows).
@@ -72,6 +74,7 @@ template <bool FP8>
 __device__ __forceinline__ void body(const DecodeLaunch &a, const DecodeItem &it, char *smem, const int wave, const int lane) {
     constexpr int kPageBytes = kBlockElems * (FP8 ? 1 : 2);
     constexpr int kSlotBytes = 4 * kPageBytes;
+    constexpr float kLazy = FP8 ? 8.0f : 0.0f;      // a reference moves when a score passes it by this many powers of two
     constexpr int kLoads = kPageBytes / 1024;       // LDS-direct loads per wavefront and half-step (wavefront w: page w)
     constexpr int kKReads = FP8 ? 4 : 8;            // 16-byte K operand reads per 32-token unit and lane
     const int Hkv = a.pool.num_kv_heads, G = a.num_q_heads / Hkv;

@@ -98,3 +98,55 @@ def test_tiles_above_drafted_rows(gpu, oracle, kv_dtype, T, n_req):  # noqa: F81
     f = wl.make_forest(parent, ntok, list(range(1, n_req + 1)), np.random.default_rng(T).permutation(n_used + 3).astype(np.int32))
     w = wl.Workload(name=f"tiles{T}", num_q_heads=8, num_kv_heads=2, kv_dtype=kv_dtype, num_pages=n_used + 3, seed=T, forest=f, mode="decode")
     run(gpu, oracle, w, T, tiles=(T == 8, False), tile_min_gflop=1)
+
+
+def weight_of_one_key(gpu, n_req, T, root, where, tiles=False, hq=8, hk=2, **settings):  # noqa: F811
+    """Rows over `root` shared tokens (bf16) in which one key, token `where`, scores 0.3 to 7.7 powers of two above two keys of
+    the first block whose values are zero; nothing else has weight.  Returns each row's relative error of that key's weight,
+    the factor by which its result is the key's value."""
+    import torch
+    from paper_2603_16104_amd import binding as hkv
+    parent, ntok = [-1] + [0] * n_req, [root] + [T + r % 3 for r in range(n_req)]
+    n_used = sum((t + 15) // 16 for t in ntok)
+    f = wl.make_forest(parent, ntok, list(range(1, n_req + 1)), np.random.default_rng(root).permutation(n_used).astype(np.int32))
+    rng = np.random.default_rng([n_req, T, root])
+    bits, back = wl.f32_to_bf16_bits, wl.bf16_bits_to_f32
+    dp = gpu.DevicePool(n_used, hk, wl.KV_BF16)
+    for v in range(len(ntok)):
+        K, V = np.zeros((ntok[v], hk, 128), dtype=np.float32), np.zeros((ntok[v], hk, 128), dtype=np.float32)
+        K[:, :, 1] = -60.0
+        if v == 0:
+            K[[0, 40, where], :, 1] = 0.0
+            K[where, :, 0] = 1.0
+            V[where] = rng.standard_normal((hk, 128))
+            value = back(bits(V[where])).astype(np.float64)
+        dp.write(f.node_pages[f.page_begin[v]: f.page_begin[v] + f.n_pages[v]], 0, gpu.to_device_bits(bits(K)), gpu.to_device_bits(bits(V)))
+    q = np.zeros((n_req * T, hq, 128), dtype=np.float32)
+    q[:, :, 0] = rng.uniform(0.3, 7.7, (n_req * T, hq))
+    q[:, :, 1] = 1.0
+    q = bits(q)
+    masks = np.tile(np.asarray([(1 << (t + 1)) - 1 for t in range(T)], dtype=np.uint64), n_req) if T > 16 else None
+    plan = hkv.hkv_decode_plan_create_ex(dp.handle, f.nodes, f.node_pages, f.req_leaf, hq, tokens_per_req=T, visible=masks, **settings)
+    assert (hkv.hkv_decode_plan_num_tile_items(plan) > 0) == tiles
+    nb = hkv.hkv_decode_plan_workspace_bytes(plan)
+    out = torch.zeros((n_req * T, hq, 128), dtype=torch.int16, device="cuda")
+    hkv.attn_decode_plan_run(plan, gpu.to_device_bits(q), float(np.log(2.0)), out, None, torch.empty(nb, dtype=torch.uint8, device="cuda"), nb)
+    torch.cuda.synchronize()
+    hkv.hkv_decode_plan_destroy(plan)
+    dp.close()
+    got, value = gpu.bf16_tensor_to_f64(out), np.repeat(value, hq // hk, axis=0)
+    factor = (got * value).sum(axis=2) / (value * value).sum(axis=1)
+    p = np.exp2(back(q)[:, :, 0].astype(np.float64))
+    return factor / (p / (2.0 + p)) - 1.0
+
+
+# With the row's maximum as reference that weight is exp2(0) = 1, exact in bf16, and what is left is the rounding of the 128 results:
+# 2^-8 / sqrt(3) * 0.72 = 1.6e-3 rms each (0.72: mean place in a binade), times sqrt(sum v^4) / sum v^2 = sqrt(3 / 128): 2.5e-4.  With
+# another reference the weight itself is rounded, 1.6e-3 rms.  The line between them is their geometric mean.
+WEIGHT_RMS = 6.4e-4
+
+
+@pytest.mark.parametrize("n_req, where", [(5, 69), (8, 145), (16, 256 + 31), (16, 500), (13, 64), (16, 96)])
+def test_heaviest_weight_is_exact(gpu, n_req, where):  # noqa: F811
+    err = weight_of_one_key(gpu, n_req, 1, 640, where)
+    assert np.sqrt((err ** 2).mean()) < WEIGHT_RMS
