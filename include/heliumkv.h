@@ -359,7 +359,8 @@ typedef struct {
                                  (default 128, at least 65) ... */
     int32_t tile_min_gflop;   /* ... if the forest holds this much such work (default 40); -1: whatever the amount.  With
                                  several query tokens per request only nodes that are no request's last node, beside
-                                 last nodes of more than 16 rows, from 30 on (the default and -1) or this amount */
+                                 last nodes of more than 16 rows, from this amount on; 0 and -1 there: from 30 on for
+                                 fp8 pools, never for bf16 pools (their results would be 6 % further off) */
     int32_t tile_workgroups;  /* persistent workgroups of the tile kernel (default: from the two amounts of work) */
     int32_t tile_chunk;       /* tokens per item of the tile kernel; multiple of 16, at most 8192 */
     int32_t large_batch_updates; /* growing plans: 1 = apply appends as for more than 256 requests (work list re-sent

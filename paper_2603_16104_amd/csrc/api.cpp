@@ -654,11 +654,17 @@ static void plan_items(hkv_decode_plan &pl) {
     // c2 and c3, 2 and 9 GFLOP of such work in steps of 30 to 50 us, lose; c5, 137 GFLOP in 0.5 ms, gains 11 %).
     // Plans with several query tokens per request: the tile kernel knows no per-row visibility, but only the requests'
     // last nodes need it; every other node is seen whole by all rows below it.  There the tiles run in front of the other
-    // items' kernel on all compute units (64 requests x 21 drafted tokens x 4 heads over 2048 shared tokens, 45 GFLOP, step
-    // 125.5 -> 105.7 us bf16, 120 -> 109 us fp8: the root in 84 groups of 64 rows read its K/V 84 times from L2); with
-    // 8 drafted tokens, 17 GFLOP, the second kernel's ramp costs more than the tiles save (64.8 -> 70.2 us, 51.8 -> 57.4).
-    // Only beside last nodes of more than 16 rows: in one launch with smaller ones (4 tokens x 4 heads, 17 GFLOP) it lost too
-    // (39.0 -> 46.2 us).
+    // items' kernel on all compute units; without them a root of 64 requests x 21 drafted tokens x 4 heads reads its K/V
+    // from L2 84 times, once per 64 rows.  fp8 pools, tokens of the shared node x requests x drafted tokens, work of the
+    // tiles, step without -> with them: 1024 x 64 x 21, 23 GFLOP, 86.4 -> 79.5 us; 2048 x 64 x 8, 17 GFLOP, 52.3 -> 58.5 (the
+    // second kernel's ramp); 4096 x 64 x 8, 34 GFLOP, 75.2 -> 72.2; 8192 x 32 x 8, 34 GFLOP, 62.4 -> 63.3; 2048 x 64 x 21,
+    // 45 GFLOP, 114.7 -> 100.4; 8192 x 64 x 4 x 8 heads, 69 GFLOP, 119 -> 100.6.  Below 30 GFLOP the shapes that lose lose more
+    // than the others gain.  Only beside last nodes of more than 16 rows: in one launch with smaller ones (4 tokens x 4
+    // heads, 17 GFLOP) it lost too (39.0 -> 46.2 us).
+    // bf16 pools only if the caller asks (tile_min_gflop): the tile keeps one reference per row, so that the heaviest
+    // probabilities lie anywhere in their binade when they are rounded to bf16, and the error against 64 bits grows from
+    // 0.00217 to 0.00231 (64 x 21 over 2048 + 512 tokens, 123.0 -> 97.4 us).  With fp8 pools the V scale comes in before that
+    // rounding, whatever the reference, and the error is the same (0.00236).
     std::vector<char> row_node(n_nodes, 0);  // nodes whose tokens some rows see in part
     bool wide_row_node = false;
     if (pl.row_visibility)
@@ -676,7 +682,7 @@ static void plan_items(hkv_decode_plan &pl) {
                 flop += 4.0 * HKV_HEAD_DIM * pl.nodes[v].n_tokens * (double)R * pl.num_q_heads;
         }
         if (pl.row_visibility)
-            tiles_pay = wide_row_node && flop >= 1e9 * (opt.tile_min_gflop > 0 ? opt.tile_min_gflop : 30);
+            tiles_pay = wide_row_node && (opt.tile_min_gflop > 0 ? flop >= 1e9 * opt.tile_min_gflop : pl.pool->d.dtype == HKV_FP8_E4M3 && flop >= 30e9);
         else
             tiles_pay = opt.tile_min_gflop < 0 || flop >= 1e9 * or_default(opt.tile_min_gflop, 40);
     }

@@ -150,3 +150,9 @@ WEIGHT_RMS = 6.4e-4
 def test_heaviest_weight_is_exact(gpu, n_req, where):  # noqa: F811
     err = weight_of_one_key(gpu, n_req, 1, 640, where)
     assert np.sqrt((err ** 2).mean()) < WEIGHT_RMS
+
+
+def test_heaviest_weight_of_drafted_rows_is_exact(gpu):  # noqa: F811
+    """64 requests x 21 drafted tokens over 2048 shared tokens: 45 GFLOP above the last nodes, not on the one-reference tile."""
+    err = weight_of_one_key(gpu, 64, 21, 2048, 1500, hq=32, hk=8)
+    assert np.sqrt((err ** 2).mean()) < WEIGHT_RMS
