@@ -469,8 +469,8 @@ size_t attn_decode_workspace_bytes(hkv_pool *pool, const hkv_node *nodes, int32_
  *   block_table beyond ceil(kv_len/16) are ignored.  ERANGE if a used page id is outside the pool.
  * ESHAPE unless num_q_heads is a multiple of num_kv_heads with a ratio G of at most 16 (a
  * workgroup's 256 rows hold floor(256/G) tokens x G heads; at most G - 1 rows stay unused).
- * A plan over few tiles splits them along their keys; the fp32 partial results lie in device memory of the plan's own (up
- * to 140 MB, taken at creation; where it cannot be had the tiles stay whole), so its runs belong on one stream or in order.
+ * A plan over few tiles can split them along their keys: a run with a workspace (attn_prefill_plan_run_ws) then spreads a
+ * tile's keys over several workgroups, which leave fp32 partial results there for a second kernel.
  */
 int hkv_prefill_plan_create(hkv_pool *pool, const int32_t *cu_q, const int32_t *block_table, int32_t max_pages,
                             const int32_t *kv_len, int32_t n_req, int32_t num_q_heads, uint32_t flags,
@@ -484,8 +484,10 @@ int hkv_prefill_plan_create_rows(hkv_pool *pool, const int32_t *q_row_begin, con
                                  const int32_t *block_table, int32_t max_pages, const int32_t *kv_len, int32_t n_req,
                                  int32_t num_q_heads, uint32_t flags, hkv_prefill_plan **out);
 int hkv_prefill_plan_destroy(hkv_prefill_plan *plan);
-/* Number of (request, query tile, kv head) workgroups the plan launches. */
+/* Number of (request, query tile, kv head) tiles of the plan: a workgroup each, or, where a run splits them along their
+ * keys, hkv_prefill_plan_num_segments pieces of work for one workgroup per compute unit (0: the plan splits nothing). */
 int32_t hkv_prefill_plan_num_tiles(const hkv_prefill_plan *plan);
+int32_t hkv_prefill_plan_num_segments(const hkv_prefill_plan *plan);
 /* The prefill kernel keeps one softmax reference per row (the maximum of its first 32 scores); a tile in which a
  * later score exceeds it by more than the exponent range allows repeats with a running maximum, at about
  * twice the cost.  count (host): how many tiles did so over all runs of this plan so far (the call waits for
@@ -493,6 +495,10 @@ int32_t hkv_prefill_plan_num_tiles(const hkv_prefill_plan *plan);
 int hkv_prefill_plan_fallback_tiles(hkv_prefill_plan *plan, int64_t *count);
 /* Tile layout for tests, 8 int32 each: (req, q_begin, n_q, kv_head, q_row0, prefix_len, kv_len, bt_off). */
 int hkv_prefill_plan_tiles(const hkv_prefill_plan *plan, int32_t *tiles_out);
+/* Segment layout for tests, 12 int32 each, in the order the workers run them: the tile's eight fields with prefix_len, kv_len
+ * and bt_off moved to the segment's first key, the segment's keys, the partial it writes (-1: it is the whole tile and
+ * writes the output), its worker, and its tile's index. */
+int hkv_prefill_plan_segments(const hkv_prefill_plan *plan, int32_t *segments_out);
 
 /* q: device [cu_q[n_req]][num_q_heads][128] bf16; out: device, same shape, bf16; lse_out: device
  * [cu_q[n_req]][num_q_heads] float or NULL. */
@@ -500,19 +506,23 @@ int attn_prefill_plan_run(hkv_prefill_plan *plan, const void *q, float scale, vo
                           void *stream);
 /* fp8 pools: the matrix-core kernel reads bf16, so the pages the batch reads (each once, however
  * many requests share it) are first dequantised (code * scale, rounded to bf16) into a scratch pool
- * in the caller's workspace: hkv_prefill_plan_workspace_bytes(plan) bytes (8 KiB per distinct page
- * and KV head; 0 for bf16 and fp32 pools), device memory, 256-byte aligned, scratch.  The pre-pass
+ * in the caller's workspace (8 KiB per distinct page and KV head), 256-byte aligned device memory.  The pre-pass
  * moves 3 bytes per cached element against 512 flop per (query, key) pair: well below 1 % of the
- * kernel at the sizes prefill runs at.  attn_prefill_plan_run is the same call without a workspace.
- * EINVAL (fp8 pool and no / unaligned workspace), ENOMEM (too small). */
+ * kernel at the sizes prefill runs at.
+ * bf16 and fp8 pools: a plan that splits its tiles keeps their partial results in the workspace too, behind those pages (133 KB
+ * per partial, 140 MB at most).  hkv_prefill_plan_workspace_bytes is what both take together, 0 where neither is needed;
+ * with less (the pages alone, or none for a bf16 pool) the tiles stay whole, which is slower but gives the same
+ * results up to the order of the sums.  The workspace is scratch and belongs to one run at a time: runs on different
+ * streams take one each.  attn_prefill_plan_run is the same call without a workspace.
+ * EINVAL (fp8 pool and no / unaligned workspace), ENOMEM (too small for an fp8 pool's pages). */
 size_t hkv_prefill_plan_workspace_bytes(const hkv_prefill_plan *plan);
 int attn_prefill_plan_run_ws(hkv_prefill_plan *plan, const void *q, float scale, void *out, float *lse_out,
                              void *workspace, size_t workspace_bytes, void *stream);
 
-/* One-shot form; workspace may be NULL for bf16 and fp32 pools (a query tile reads its whole key
- * range itself; attn_prefill_workspace_bytes is 0); an fp8 pool needs what
- * hkv_prefill_plan_workspace_bytes reports for the same batch (the error text of a too small
- * workspace names the size). */
+/* One-shot form; workspace may be NULL for bf16 and fp32 pools (attn_prefill_workspace_bytes is 0: tiles then stay whole); an
+ * fp8 pool needs its pages' part of what hkv_prefill_plan_workspace_bytes reports for the same batch (the error text of a
+ * too small workspace names the size).  With all of it the call splits tiles as a plan's run does; calls on
+ * different streams take a workspace each. */
 int attn_prefill_with_prefix(hkv_pool *pool, const void *q, const int32_t *cu_q, const int32_t *block_table,
                              int32_t max_pages, const int32_t *kv_len, int32_t n_req, int32_t num_q_heads,
                              float scale, void *out, float *lse_out, void *workspace, size_t workspace_bytes,

@@ -34,7 +34,7 @@ EXPORTS = [
     "hkv_decode_plan_set_profiling", "hkv_decode_plan_elapsed_ms", "hkv_decode_plan_elapsed_kernels_ms",
     "hkv_decode_plan_num_tile_items", "hkv_decode_plan_tile_workgroups", "hkv_decode_plan_is_fused",
     "attn_decode_prefix_tree", "attn_decode_workspace_bytes", "hkv_prefill_plan_create", "hkv_prefill_plan_destroy",
-    "hkv_prefill_plan_num_tiles", "hkv_prefill_plan_tiles", "attn_prefill_plan_run", "attn_prefill_plan_run_ws", "hkv_prefill_plan_workspace_bytes", "attn_prefill_with_prefix",
+    "hkv_prefill_plan_num_tiles", "hkv_prefill_plan_tiles", "hkv_prefill_plan_num_segments", "hkv_prefill_plan_segments", "attn_prefill_plan_run", "attn_prefill_plan_run_ws", "hkv_prefill_plan_workspace_bytes", "attn_prefill_with_prefix",
     "attn_prefill_workspace_bytes",
     "kv_cache_create", "kv_cache_destroy", "kv_cache_acquire", "kv_cache_release", "kv_cache_unpin", "kv_cache_stats",
     "trt_build", "trt_destroy", "trt_num_nodes", "trt_num_syms", "trt_num_calls", "trt_nodes", "trt_prefill_usage",
@@ -457,9 +457,18 @@ def hkv_prefill_plan_tiles(plan) -> np.ndarray:
     return tiles
 
 
+def hkv_prefill_plan_segments(plan) -> np.ndarray:
+    """[n][12]: tile fields moved to the segment's first key, its keys, partial or -1, worker, tile; empty: nothing is split."""
+    n = _check(lib().hkv_prefill_plan_num_segments(plan))
+    segments = np.empty((n, 12), dtype=np.int32)
+    _check(lib().hkv_prefill_plan_segments(plan, _hp(segments)))
+    return segments
+
+
 def attn_prefill_plan_run(plan, q, scale: float, out, lse_out=None, stream=None, workspace=None,
                           workspace_bytes: int = 0) -> None:
-    """workspace: device scratch of hkv_prefill_plan_workspace_bytes(plan) bytes (fp8 pools only)."""
+    """workspace: device scratch of hkv_prefill_plan_workspace_bytes(plan) bytes, one per stream (needed for an fp8 pool's pages;
+    without room for the partial results of split tiles they stay whole)."""
     _check(lib().attn_prefill_plan_run_ws(plan, _dev(q), C.c_float(scale), _dev(out), _dev(lse_out), _dev(workspace),
                                           C.c_size_t(workspace_bytes), _stream(stream)))
 

@@ -150,15 +150,14 @@ struct hkv_prefill_plan {
     std::vector<int32_t> src_pages;
     int32_t *d_src_pages = nullptr;
     unsigned int *d_fallback = nullptr;  // tiles that repeated with a running maximum, over all runs of the plan
-    // tiles split along their keys (empty: a workgroup per tile); the partials lie in the plan's own allocation
+    // tiles split along their keys (empty: a workgroup per tile); the partials go to the caller's workspace
     std::vector<PrefillSegment> segments;
-    std::vector<int32_t> seg_begin;
+    std::vector<int32_t> seg_begin, seg_tile;  // first segment of every worker; the tile a segment was cut from
     std::vector<PrefillSplitTile> split;
     int32_t n_parts = 0;
     PrefillSegment *d_segments = nullptr;
-    int32_t *d_seg_begin = nullptr, *d_part_bail = nullptr;
+    int32_t *d_seg_begin = nullptr;
     PrefillSplitTile *d_split = nullptr;
-    float *d_part_data = nullptr;
 };
 
 struct hkv_pool {
@@ -1859,6 +1858,7 @@ static void split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<PrefillT
                 PrefillTile t = head_tiles[i];
                 t.kv_head = h;
                 pl.segments.push_back(PrefillSegment{t, t.prefix_len + t.q_begin + t.n_q, -1});
+                pl.seg_tile.push_back(i * Hkv + h);
             }
             for (const Cut &x : cuts[k]) {
                 PrefillTile t = head_tiles[x.tile];
@@ -1870,6 +1870,7 @@ static void split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<PrefillT
                 const size_t th = (size_t)x.tile * Hkv + h;
                 const int32_t part = part0[th] < 0 ? -1 : part0[th] + used[th]++;
                 pl.segments.push_back(PrefillSegment{t, std::min(end, 64 * x.b1) - 64 * x.b0, part});
+                pl.seg_tile.push_back((int32_t)th);
             }
             pl.seg_begin.push_back((int32_t)pl.segments.size());
         }
@@ -1972,15 +1973,8 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
         size_t off_fb = off_src + align_up(sizeof(int32_t) * pl->src_pages.size(), 256);
         const size_t off_seg = off_fb + 256, off_sb = off_seg + align_up(sizeof(PrefillSegment) * pl->segments.size(), 256);
         const size_t off_split = off_sb + align_up(sizeof(int32_t) * pl->seg_begin.size(), 256);
-        const size_t off_bail = off_split + align_up(sizeof(PrefillSplitTile) * pl->split.size(), 256);
-        const size_t off_part = off_bail + align_up(sizeof(int32_t) * pl->n_parts, 256);
-        hipError_t e = hipMalloc(&pl->dev, off_part + sizeof(float) * kSplitPartFloats * pl->n_parts);
-        if (e == hipErrorOutOfMemory && !pl->segments.empty()) {  // no room for partials: a workgroup per tile needs none
-            (void)hipGetLastError();
-            pl->segments.clear();
-            pl->dev = nullptr;
-            e = hipMalloc(&pl->dev, off_fb + 256);
-        }
+        const size_t total = off_split + align_up(sizeof(PrefillSplitTile) * pl->split.size(), 256);
+        hipError_t e = hipMalloc(&pl->dev, total);
         if (e == hipSuccess) {
             char *base = static_cast<char *>(pl->dev);
             pl->d_tiles = static_cast<PrefillTile *>(pl->dev);
@@ -1989,7 +1983,7 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
             pl->d_fallback = reinterpret_cast<unsigned int *>(base + off_fb);
             // one image, one copy: with a blocking copy or fill for each part a plan over split tiles took 75-89 us to create,
             // 30-38 this way, and a plan made for a single run has to gain that back
-            std::vector<char> image(pl->segments.empty() ? off_seg : off_bail, 0);
+            std::vector<char> image(total, 0);
             auto put = [&](size_t off, const auto &v) { if (!v.empty()) memcpy(image.data() + off, v.data(), sizeof(v[0]) * v.size()); };
             put(0, pl->tiles);
             put(off_bt, dev_table);
@@ -1998,8 +1992,6 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
                 pl->d_segments = reinterpret_cast<PrefillSegment *>(base + off_seg);
                 pl->d_seg_begin = reinterpret_cast<int32_t *>(base + off_sb);
                 pl->d_split = reinterpret_cast<PrefillSplitTile *>(base + off_split);
-                pl->d_part_bail = reinterpret_cast<int32_t *>(base + off_bail);
-                pl->d_part_data = reinterpret_cast<float *>(base + off_part);
                 put(off_seg, pl->segments);
                 put(off_sb, pl->seg_begin);
                 put(off_split, pl->split);
@@ -2087,9 +2079,31 @@ extern "C" int hkv_prefill_plan_fallback_tiles(hkv_prefill_plan *plan, int64_t *
     return HKV_OK;
 }
 
+extern "C" int32_t hkv_prefill_plan_num_segments(const hkv_prefill_plan *plan) {
+    return plan ? (int32_t)plan->segments.size() : fail(HKV_EINVAL, "null plan");
+}
+
+extern "C" int hkv_prefill_plan_segments(const hkv_prefill_plan *plan, int32_t *segments_out) {
+    if (!plan || !segments_out) return fail(HKV_EINVAL, "hkv_prefill_plan_segments: null argument");
+    static_assert(sizeof(PrefillSegment) == 40, "segment layout is part of the introspection contract");
+    for (size_t w = 0; w + 1 < plan->seg_begin.size(); ++w)
+        for (int32_t i = plan->seg_begin[w]; i < plan->seg_begin[w + 1]; ++i) {
+            int32_t *o = segments_out + (size_t)i * 12;
+            memcpy(o, &plan->segments[i], sizeof(PrefillSegment));
+            o[10] = (int32_t)w;
+            o[11] = plan->seg_tile[i];
+        }
+    return HKV_OK;
+}
+
+// The workspace: fp8 pools first the batch's pages as bf16 (K, then V), then the partials of split tiles and their flags.
+static size_t prefill_pages_bytes(const hkv_prefill_plan *plan) {
+    return 2 * plan->src_pages.size() * (size_t)plan->pool->d.num_kv_heads * HKV_PAGE_SIZE * HKV_HEAD_DIM * sizeof(uint16_t);
+}
+
 extern "C" size_t hkv_prefill_plan_workspace_bytes(const hkv_prefill_plan *plan) {
     if (!plan) return 0;
-    return 2 * plan->src_pages.size() * (size_t)plan->pool->d.num_kv_heads * HKV_PAGE_SIZE * HKV_HEAD_DIM * sizeof(uint16_t);
+    return prefill_pages_bytes(plan) + (size_t)plan->n_parts * (kSplitPartFloats * sizeof(float)) + align_up(sizeof(int32_t) * plan->n_parts, 256);
 }
 
 extern "C" int attn_prefill_plan_run(hkv_prefill_plan *plan, const void *q, float scale, void *out, float *lse_out,
@@ -2113,7 +2127,7 @@ extern "C" int attn_prefill_plan_run_ws(hkv_prefill_plan *plan, const void *q, f
     }
     PoolView view = view_of(plan->pool);
     if (plan->pool->d.dtype == HKV_FP8_E4M3) {  // dequantise the pages of this batch, then read the scratch pool
-        const size_t need = hkv_prefill_plan_workspace_bytes(plan);
+        const size_t need = prefill_pages_bytes(plan);
         if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255))
             return fail(HKV_EINVAL, "attn_prefill_plan_run: an fp8 pool needs a 256-byte aligned workspace of %zu bytes", need);
         if (workspace_bytes < need)
@@ -2125,8 +2139,16 @@ extern "C" int attn_prefill_plan_run_ws(hkv_prefill_plan *plan, const void *q, f
     }
     PrefillLaunch a{view, q, plan->d_tiles, plan->d_block_table, out, lse_out,
                     (int32_t)plan->tiles.size(), plan->num_q_heads, scale, plan->d_fallback,
-                    plan->d_segments, plan->d_seg_begin, plan->d_split, plan->d_part_data, plan->d_part_bail,
-                    plan->d_segments ? (int32_t)plan->seg_begin.size() - 1 : 0, (int32_t)plan->split.size()};
+                    plan->d_segments, plan->d_seg_begin, plan->d_split, nullptr, nullptr, 0, 0};
+    // Split tiles need room for their partials; a caller that brings none, or only an fp8 pool's pages, gets whole tiles.
+    // The room is the caller's, so that runs on different streams (of the one-shot form's cached plan too) share nothing.
+    if (plan->d_segments && workspace && (reinterpret_cast<uintptr_t>(workspace) & 255) == 0 &&
+        workspace_bytes >= hkv_prefill_plan_workspace_bytes(plan)) {
+        a.part_data = reinterpret_cast<float *>(static_cast<char *>(workspace) + prefill_pages_bytes(plan));
+        a.part_bail = reinterpret_cast<int32_t *>(a.part_data + (size_t)plan->n_parts * kSplitPartFloats);
+        a.n_workers = (int32_t)plan->seg_begin.size() - 1;
+        a.n_split = (int32_t)plan->split.size();
+    }
     HKV_HIP(launch_prefill(a, static_cast<hipStream_t>(stream)));
     return HKV_OK;
 }

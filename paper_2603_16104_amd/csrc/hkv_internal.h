@@ -50,8 +50,9 @@ struct PrefillSplitTile {
     int32_t part0;
     int32_t n_parts;
 };
-// One partial of a split tile: 256 rows of unnormalised fp32 o in the accumulators' register order, then per row the
-// softmax reference and the row sum, then whether the running-maximum path was taken.
+// One partial of a split tile: 256 rows of unnormalised fp32 o in the accumulators' register order, then for each of the eight
+// 32-row tiles the softmax references of its rows and their row sums.  (Whether the running-maximum path was taken is kept apart,
+// in PrefillLaunch::part_bail.)
 constexpr size_t kSplitPartFloats = 256 * kHeadDim + 2 * 256;
 
 struct PoolView {

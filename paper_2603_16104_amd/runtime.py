@@ -157,7 +157,7 @@ class PrefillRunner:
         self.out = torch.zeros((tq, workload.num_q_heads, hkv.HEAD_DIM), dtype=odt, device=dev)
         self.lse = torch.zeros((tq, workload.num_q_heads), dtype=torch.float32, device=dev)
         self.scale = float(workload.scale)
-        self.ws_bytes = hkv.hkv_prefill_plan_workspace_bytes(self.plan)      # fp8 pools: scratch for dequantised pages
+        self.ws_bytes = hkv.hkv_prefill_plan_workspace_bytes(self.plan)      # dequantised pages, partials of split tiles
         self.ws = torch.empty(max(self.ws_bytes, 256), dtype=torch.uint8, device=dev) if self.ws_bytes else None
 
     def run(self, stream=None) -> None:
@@ -202,7 +202,7 @@ class MixedStepRunner:
             bt, kv_len, *_ = hkv.prefix_tree_flatten(f.nodes, f.node_pages, f.req_leaf[self.pre_req], mp,
                                                      f.page_size)
             self.pre_plan = hkv.hkv_prefill_plan_create_rows(pool.handle, cu[self.pre_req], ql[self.pre_req], bt, kv_len, Hq)
-            self.pws_bytes = hkv.hkv_prefill_plan_workspace_bytes(self.pre_plan)     # fp8 pools only
+            self.pws_bytes = hkv.hkv_prefill_plan_workspace_bytes(self.pre_plan)
             self.pws = torch.empty(max(self.pws_bytes, 256), dtype=torch.uint8, device=dev) if self.pws_bytes else None
 
     def run(self, stream=None) -> None:
@@ -219,6 +219,12 @@ class MixedStepRunner:
         if self.pre_plan is not None:
             hkv.hkv_prefill_plan_destroy(self.pre_plan)
             self.pre_plan = None
+
+
+def _prefill_workspace(steps, device):
+    """One workspace for prefill plans that run one after the other on one stream: the largest that any of them takes."""
+    n = max((hkv.hkv_prefill_plan_workspace_bytes(st["plan"]) for st in steps if st["plan"] is not None), default=0)
+    return (torch.empty(n, dtype=torch.uint8, device=device) if n else None), n
 
 
 class WorkflowRunner:
@@ -292,6 +298,7 @@ class WorkflowRunner:
             self.steps.append(step)
         for v in list(resident):
             hkv.kv_pool_release(self.pool.handle, resident.pop(v))
+        self.ws, self.ws_bytes = _prefill_workspace(self.steps, self.device)
         return usage
 
     def run(self, stream=None) -> None:
@@ -300,7 +307,7 @@ class WorkflowRunner:
                 k, vv, _ = self._node_tensors(v)
                 self.pool.write(st["pages"][v], 0, k, vv, stream)
             if st["plan"] is not None:
-                hkv.attn_prefill_plan_run(st["plan"], st["q"], self.scale, st["out"], None, stream)
+                hkv.attn_prefill_plan_run(st["plan"], st["q"], self.scale, st["out"], None, stream, self.ws, self.ws_bytes)
 
     def release_steps(self) -> None:
         for st in self.steps:
@@ -359,6 +366,7 @@ class PrefixCacheRunner:
                 step["plan"] = hkv.hkv_prefill_plan_create(self.pool.handle, np.array([0, new], dtype=np.int32),
                                                            step["pages"][None, :], np.array([n], dtype=np.int32), self.Hq)
             self.steps.append(step)
+        self.ws, self.ws_bytes = _prefill_workspace(self.steps, self.device)
         st = hkv.kv_cache_stats(self.cache)
         return {"hit_rate": hit / max(total, 1), "prompt_tokens": total, "evictions": st["evictions"]}
 
@@ -367,7 +375,7 @@ class PrefixCacheRunner:
             if st["plan"] is None:
                 continue
             self.pool.write(st["pages"][st["cached"] // hkv.PAGE_SIZE:], 0, st["k"], st["v"], stream)
-            hkv.attn_prefill_plan_run(st["plan"], st["q"], self.scale, st["out"], st["lse"], stream)
+            hkv.attn_prefill_plan_run(st["plan"], st["q"], self.scale, st["out"], st["lse"], stream, self.ws, self.ws_bytes)
 
     def close(self) -> None:
         for st in self.steps:

@@ -98,3 +98,82 @@ def test_split_prefill_under_graph_replay(gpu):  # noqa: F811
     del g
     r.close()
     dp.close()
+
+
+@pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
+def test_room_for_partials_is_the_callers(gpu, oracle, kv_dtype):  # noqa: F811
+    """With the whole workspace the tiles are split and nothing behind it is touched; with an fp8 pool's pages only, with none, or
+    with one that is not aligned (bf16 pools ignored it before there were partials) they stay whole and the results agree."""
+    import torch
+    from paper_2603_16104_amd import binding as hkv
+    w = workload(8, 2, 2048, (130, 40), kv_dtype)
+    hp, dp = both_pools(gpu, oracle, w)
+    exp_o, exp_l = oracle.run_workload(w, hp)
+    r = gpu.PrefillRunner(dp, w)
+    need = hkv.hkv_prefill_plan_workspace_bytes(r.plan)
+    blocks = sum(int(n) for n in w.forest.n_pages)
+    pages = blocks * 2 * 8192 if kv_dtype == wl.KV_FP8_E4M3 else 0
+    assert need > pages
+    ws = torch.full((need + 512,), 0x5A, dtype=torch.uint8, device="cuda")
+
+    def run_with(buffer, nbytes):
+        r.out.fill_(0x7FC0)
+        r.lse.fill_(float("nan"))
+        hkv.attn_prefill_plan_run(r.plan, r.q, r.scale, r.out, r.lse, None, buffer, nbytes)
+        torch.cuda.synchronize()
+        check_close(gpu.bf16_tensor_to_f64(r.out), exp_o, w.name)
+        check_lse(r.lse.cpu().numpy(), exp_l, w.name, tol=LSE_ABS_FP8_PREFILL)
+        return r.out.clone(), r.lse.clone()
+
+    split = run_with(ws, need)
+    assert (ws[need:] == 0x5A).all() and (ws[pages:need] != 0x5A).any()
+    ws[pages:] = 0x5A
+    whole = run_with(ws, need - 1)
+    assert (ws[pages:] == 0x5A).all()
+    assert not torch.equal(whole[1], split[1])          # another order of the sums
+    others = [run_with(ws, pages)] if pages else [run_with(None, 0), run_with(ws[1:], need + 511)]
+    for o, ls in others:
+        assert torch.equal(o, whole[0]) and torch.equal(ls, whole[1])
+    assert (ws[pages:] == 0x5A).all()
+    r.close()
+    dp.close()
+
+
+@pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
+def test_one_shot_calls_on_two_streams(gpu, kv_dtype):  # noqa: F811
+    """The one-shot form keeps its plan in the pool.  Calls over the same tables on two streams, each with its own queries, results
+    and workspace, share nothing that either writes: both give the bits they give alone."""
+    import torch
+    from paper_2603_16104_amd import binding as hkv
+    w = workload(8, 2, 4096, (200, 150), kv_dtype)
+    dp = gpu.DevicePool(w.num_pages, w.num_kv_heads, w.kv_dtype)
+    dp.fill_from(w)
+    r = gpu.PrefillRunner(dp, w)
+    side = [torch.cuda.Stream(), torch.cuda.Stream()]
+    q = [r.q, r.q.flip(0).contiguous()]
+    out, lse = [torch.zeros_like(r.out) for _ in q], [torch.zeros_like(r.lse) for _ in q]
+    ws = [torch.empty(r.ws_bytes, dtype=torch.uint8, device="cuda") for _ in q]
+
+    def call(i, stream):
+        hkv.attn_prefill_with_prefix(dp.handle, q[i], r.cu_q, r.block_table, r.kv_len, w.num_q_heads, r.scale, out[i], lse[i], ws[i], r.ws_bytes,
+                                     stream)
+
+    alone = []
+    for i in range(2):
+        call(i, side[i].cuda_stream)
+        torch.cuda.synchronize()
+        alone.append((out[i].clone(), lse[i].clone()))
+    assert not torch.equal(alone[0][0], alone[1][0])
+    for _ in range(20):
+        for i in range(2):
+            out[i].fill_(7)
+            lse[i].fill_(7.0)
+        torch.cuda.synchronize()
+        for _ in range(4):
+            for i in range(2):
+                call(i, side[i].cuda_stream)
+        torch.cuda.synchronize()
+        for i in range(2):
+            assert torch.equal(out[i], alone[i][0]) and torch.equal(lse[i], alone[i][1])
+    r.close()
+    dp.close()

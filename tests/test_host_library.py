@@ -598,6 +598,23 @@ def test_prefill_plan_error_codes():
     hkv.kv_pool_destroy(p8)
 
 
+@pytest.mark.parametrize("dtype", [hkv.BF16, hkv.FP8_E4M3])
+def test_prefill_workspace_holds_the_partials_of_split_tiles(dtype):
+    """Whole tiles: an fp8 pool's pages only.  Tiles split along their keys: 256 rows of 128 + 2 floats per partial and a flag each
+    on top, in the caller's workspace and not in the plan."""
+    pool = fake_pool(300, 2, dtype=dtype)
+    bt = np.arange(300, dtype=np.int32)[None]
+    for kv_len, new in [(60, 20), (4800, 100)]:
+        plan = hkv.hkv_prefill_plan_create(pool, [0, new], bt, [kv_len], 8, hkv.PLAN_HOST_ONLY)
+        seg = hkv.hkv_prefill_plan_segments(plan)
+        n_parts = int((seg[:, 9] >= 0).sum())
+        assert (n_parts > 0) == (kv_len == 4800)
+        pages = -(-kv_len // 16) * 2 * 8192 if dtype == hkv.FP8_E4M3 else 0
+        assert hkv.hkv_prefill_plan_workspace_bytes(plan) == pages + n_parts * 256 * 130 * 4 + -(-4 * n_parts // 256) * 256
+        hkv.hkv_prefill_plan_destroy(plan)
+    hkv.kv_pool_destroy(pool)
+
+
 def test_merge_argument_validation():
     with pytest.raises(hkv.HkvError) as e:
         hkv.lse_merge(0x1000, 0x2000, 0x3000, 0x4000, 4, 0x5000, 7, stream=0)
