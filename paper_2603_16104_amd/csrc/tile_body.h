@@ -422,8 +422,9 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
 #pragma unroll
         for (int i = 1; i < 16; ++i) mx = fmaxf(mx, sa[i] * s0.ck[i >> 3]);
         mc = fmaxf(mx, __shfl_xor(mx, 32));
-        // a row that lies in front of the whole segment sees nothing of it: exp2(-inf - 0) = 0 throughout
-        if (SPLIT && mc == -INFINITY) mc = 0.f;
+        // A row that lies in front of the whole segment sees nothing of it: exp2(-inf - 0) = 0 throughout.  (A row that sees it
+        // and whose first scores are all -inf ends up with a sum that is no number, and so in the running-maximum loop.)
+        if (SPLIT && pos < 0) mc = 0.f;
     }
 
     // One phase, written in issue order and fenced so that the compiler keeps it.  Operands live in

@@ -177,3 +177,48 @@ def test_one_shot_calls_on_two_streams(gpu, kv_dtype):  # noqa: F811
             assert torch.equal(out[i], alone[i][0]) and torch.equal(lse[i], alone[i][1])
     r.close()
     dp.close()
+
+
+def test_segment_that_begins_with_keys_of_score_minus_infinity(gpu):  # noqa: F811
+    """The first 32 keys of a segment score -inf and all others about -300 powers of two: a segment has no reference from its
+    first scores then, and one that is not its rows' own would make all their weights underflow."""
+    import torch
+    from paper_2603_16104_amd import binding as hkv
+    prefix, new, hq, hk = 2048, 64, 8, 2
+    w = workload(hq, hk, prefix, (new,))
+    dp = gpu.DevicePool(w.num_pages, hk, w.kv_dtype)
+    r = gpu.PrefillRunner(dp, w)
+    seg = hkv.hkv_prefill_plan_segments(r.plan)
+    first = prefix - seg[(seg[:, 3] == 0) & (seg[:, 5] < prefix)][1, 5]          # of some segment behind the first one
+    assert 0 < first < prefix - 32
+    rng = np.random.default_rng(9)
+    bits, back = wl.f32_to_bf16_bits, wl.bf16_bits_to_f32
+    K = rng.standard_normal((prefix + new, hk, 128)).astype(np.float32)
+    K[:, :, 0], K[:, :, 1] = 0.0, -300.0
+    K[first: first + 32, :, 0] = -np.inf
+    V = rng.standard_normal((prefix + new, hk, 128)).astype(np.float32)
+    q = 0.1 * rng.standard_normal((new, hq, 128)).astype(np.float32)
+    q[:, :, :2] = 1.0
+    K, V, q = back(bits(K)), back(bits(V)), back(bits(q))
+    for node, part in ((0, slice(0, prefix)), (1, slice(prefix, prefix + new))):
+        f = w.forest
+        pages = f.node_pages[f.page_begin[node]: f.page_begin[node] + f.n_pages[node]]
+        dp.write(pages, 0, gpu.to_device_bits(bits(K[part])), gpu.to_device_bits(bits(V[part])))
+    out = torch.zeros((new, hq, 128), dtype=torch.int16, device="cuda")
+    lse = torch.zeros((new, hq), dtype=torch.float32, device="cuda")
+    scale = float(np.log(2.0))
+    hkv.attn_prefill_plan_run(r.plan, gpu.to_device_bits(bits(q)), scale, out, lse, None, r.ws, r.ws_bytes)
+    torch.cuda.synchronize()
+    exp_o, exp_l = np.zeros((new, hq, 128)), np.zeros((new, hq))
+    keep = np.ones(prefix + new, dtype=bool)
+    keep[first: first + 32] = False
+    for i in range(new):
+        seen = keep & (np.arange(prefix + new) <= prefix + i)
+        for h in range(hq):
+            s = K[seen, h // (hq // hk)].astype(np.float64) @ q[i, h].astype(np.float64) * scale
+            exp_l[i, h] = s.max() + np.log(np.exp(s - s.max()).sum())
+            exp_o[i, h] = np.exp(s - exp_l[i, h]) @ V[seen, h // (hq // hk)]
+    check_close(gpu.bf16_tensor_to_f64(out), exp_o, "-inf at a segment's start")
+    check_lse(lse.cpu().numpy(), exp_l, "-inf at a segment's start", tol=2e-3 + 1e-6 * np.abs(exp_l).max())
+    r.close()
+    dp.close()
