@@ -396,10 +396,13 @@ int32_t hkv_decode_plan_num_items(const hkv_decode_plan *plan);
  * to 256 / G requests each, at most 8192 tokens): they are run by code built like the prefill kernel (256-row
  * tiles) on hkv_decode_plan_tile_workgroups persistent workgroups.  hkv_decode_plan_is_fused: 1 if those
  * workgroups and the workgroups of the other items go out as one launch (possible when none of the other
- * items is shared by more than 16 query rows), 0 if they are two kernels on two streams. */
+ * items is shared by more than 16 query rows), 0 if they are two kernels: on two streams, or one in front of the other
+ * (HKV_PLAN_ONE_STREAM, and several query tokens per request).  hkv_decode_plan_has_stream: 1 if the plan holds a
+ * stream and two events for that. */
 int32_t hkv_decode_plan_num_tile_items(const hkv_decode_plan *plan);
 int32_t hkv_decode_plan_tile_workgroups(const hkv_decode_plan *plan);
 int32_t hkv_decode_plan_is_fused(const hkv_decode_plan *plan);
+int32_t hkv_decode_plan_has_stream(const hkv_decode_plan *plan);
 /* Workgroups of the per-node kernel: one per item, except that in forests with more items than the
  * chip holds at once the short items of at most 16 query rows (listed last) share a workgroup four
  * at a time, one item per wavefront. */

@@ -1017,6 +1017,9 @@ static void plan_items(hkv_decode_plan &pl) {
     for (const DecodeItem &it : pl.items) pl.fused = pl.fused && it.n_req * G <= 16;
 }
 
+// Whether runs queue the two kinds of items side by side, on the caller's stream and on the plan's own.
+static bool forks(const hkv_decode_plan &pl) { return !pl.tile_items.empty() && !pl.items.empty() && pl.concurrent && !pl.fused; }
+
 static int upload_decode_plan(hkv_decode_plan &pl) {
     size_t off_items = 0;
     size_t off_pages = align_up(off_items + sizeof(DecodeItem) * pl.items.size(), 256);
@@ -1055,7 +1058,7 @@ static int upload_decode_plan(hkv_decode_plan &pl) {
         memset(pl.h_grow, 0, pl.grow_bytes * hkv_decode_plan::kGrowSlots);
         for (hipEvent_t &e : pl.grow_free) HKV_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     }
-    if (!pl.tile_items.empty() && !pl.fused) {  // the tile kernel's own stream and the two events that fork to it and join it
+    if (forks(pl)) {  // the second kernel's own stream and the two events that fork to it and join it
         HKV_HIP(hipStreamCreateWithFlags(&pl.side, hipStreamNonBlocking));
         HKV_HIP(hipEventCreateWithFlags(&pl.ev_fork, hipEventDisableTiming));
         HKV_HIP(hipEventCreateWithFlags(&pl.ev_join, hipEventDisableTiming));
@@ -1538,6 +1541,9 @@ extern "C" int32_t hkv_decode_plan_num_tile_items(const hkv_decode_plan *plan) {
 extern "C" int32_t hkv_decode_plan_is_fused(const hkv_decode_plan *plan) {
     return plan ? (plan->fused ? 1 : 0) : fail(HKV_EINVAL, "null plan");
 }
+extern "C" int32_t hkv_decode_plan_has_stream(const hkv_decode_plan *plan) {
+    return plan ? (plan->side ? 1 : 0) : fail(HKV_EINVAL, "null plan");
+}
 extern "C" int32_t hkv_decode_plan_tile_workgroups(const hkv_decode_plan *plan) {
     return plan ? plan->tile_workgroups : fail(HKV_EINVAL, "null plan");
 }
@@ -1583,7 +1589,7 @@ static int run_decode_plan(hkv_decode_plan *plan, const void *q, float scale, vo
     float *down_parts = lse_parts + align_up((size_t)plan->n_parts * sizeof(float), 256) / sizeof(float);
     const bool prof = plan->profiling;
     const bool tiles = !plan->tile_items.empty();
-    const bool fork = tiles && plan->concurrent && !plan->items.empty() && !plan->fused;
+    const bool fork = forks(*plan);
     // The tile kernel goes first and stays on the caller's stream, so that its persistent workgroups, which need
     // a whole compute unit each, take theirs before the other kernel's many small workgroups fill the chip; that
     // kernel follows on the plan's own stream (behind an event that marks the same point of the caller's stream)

@@ -156,3 +156,22 @@ def test_heaviest_weight_of_drafted_rows_is_exact(gpu):  # noqa: F811
     """64 requests x 21 drafted tokens over 2048 shared tokens: 45 GFLOP above the last nodes, not on the one-reference tile."""
     err = weight_of_one_key(gpu, 64, 21, 2048, 1500, hq=32, hk=8)
     assert np.sqrt((err ** 2).mean()) < WEIGHT_RMS
+
+
+@pytest.mark.parametrize("T, flags, settings, forks", [
+    (1, 0, {"tile_min_gflop": -1, "fused": -1}, True), (1, 4, {"tile_min_gflop": -1, "fused": -1}, False),   # HKV_PLAN_ONE_STREAM
+    (1, 0, {"tile_min_gflop": -1}, False),                                                              # one launch
+    (8, 0, {"tile_min_gflop": 1}, False)])                                                               # tiles in front of the rest
+def test_a_plan_holds_a_stream_only_if_its_runs_fork(gpu, T, flags, settings, forks):  # noqa: F811
+    from paper_2603_16104_amd import binding as hkv
+    n_req = 48 if T == 8 else 80
+    parent, ntok = [-1] + [0] * n_req, [1040] + [T + 20] * n_req
+    n_used = sum((t + 15) // 16 for t in ntok)
+    f = wl.make_forest(parent, ntok, list(range(1, n_req + 1)), np.arange(n_used, dtype=np.int32))
+    dp = gpu.DevicePool(n_used, 2, wl.KV_FP8_E4M3)
+    plan = hkv.hkv_decode_plan_create_ex(dp.handle, f.nodes, f.node_pages, f.req_leaf, 8, flags, tokens_per_req=T, **settings)
+    assert hkv.hkv_decode_plan_num_tile_items(plan) > 0
+    assert hkv.hkv_decode_plan_is_fused(plan) == ("fused" not in settings and T == 1)
+    assert hkv.hkv_decode_plan_has_stream(plan) == forks
+    hkv.hkv_decode_plan_destroy(plan)
+    dp.close()
