@@ -635,7 +635,9 @@ extern "C" int lse_merge_dense(const float *o_parts, const float *lse_parts, con
 // chunks of a node get the same positions k in the partial lists of all those requests, and row
 // (r, h) keeps its partials at (r*Hq + h)*max_parts + k.  The merge then needs no index lists,
 // only the number of partials per request.
-static void plan_items(hkv_decode_plan &pl) {
+//
+// cut_more: nodes of few rows may be cut only to fill workgroup slots.  Returns whether some were.
+static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     const int G = pl.group;
     const int Hkv = pl.pool->d.num_kv_heads;
     const int n_nodes = (int)pl.nodes.size();
@@ -770,7 +772,7 @@ static void plan_items(hkv_decode_plan &pl) {
             any |= cut_for_packing(T);
             units += (int64_t)Hkv * (cut_for_packing(T) ? (T + pack_tokens - 1) / pack_tokens : 1);
         }
-        cut_leaves = any && (pack_mode == 3 || units > kResidentGroups);
+        cut_leaves = any && (pack_mode == 3 || units > (cut_more ? kResidentGroups : chip.n_cu * (fp8_pool ? 2 : 3)));
     }
     // Items of more than 16 rows: how long a chunk?  Such an item costs a start-up, a hand-over between its wavefronts and
     // a partial per row (6 us together) beside 0.8 us per 64 tokens alone and 1.1 to 2.9 us on a full chip (from L2 / from
@@ -831,7 +833,7 @@ static void plan_items(hkv_decode_plan &pl) {
         // them (a wavefront that streams a node alone is the longest chain of such a launch; below 160 resp. 256 tokens its
         // start-up takes over).  64 requests of 512 private tokens below 4096 shared ones, fp8: 28.9 us whole, 22.8 us as
         // 2 x 256; a few blocks too many and it is 10 % slower.
-        if (packs && !cut_leaves && best_n + other_wgs < slots)
+        if (cut_more && packs && !cut_leaves && best_n + other_wgs < slots)
             for (int piece = std::max(160, 4 * step_tokens); piece < pack_tokens; piece += 16) {
                 int64_t units = 0;
                 for (int v = 0; v < n_nodes; ++v) {
@@ -1015,6 +1017,16 @@ static void plan_items(hkv_decode_plan &pl) {
     // blocks side by side, which works as long as no item synchronises per step (more than 16 query rows).
     pl.fused = !pl.tile_items.empty() && !pl.items.empty() && opt.fused >= 0 && !pl.fp8_matrix;
     for (const DecodeItem &it : pl.items) pl.fused = pl.fused && it.n_req * G <= 16;
+    return cut_leaves || piece_tokens < pack_tokens;
+}
+
+// A piece more on one path is a partial more for every row of the batch.  Where that alone would take the partials beyond the
+// static workspace (a batch of many heads in which few paths are long: 234 requests x 128 heads, 30 MB whole, 53 MB cut), the
+// nodes stay whole, so that attn_decode_plan_run_static takes the plan.
+static void plan_items(hkv_decode_plan &pl) {
+    if (!plan_items(pl, true) || hkv_decode_plan_workspace_bytes(&pl) <= kStaticWorkspaceBytes) return;
+    plan_items(pl, false);
+    if (hkv_decode_plan_workspace_bytes(&pl) > kStaticWorkspaceBytes) plan_items(pl, true);
 }
 
 // Whether runs queue the two kinds of items side by side, on the caller's stream and on the plan's own.

@@ -615,6 +615,26 @@ def test_prefill_workspace_holds_the_partials_of_split_tiles(dtype):
     hkv.kv_pool_destroy(pool)
 
 
+@pytest.mark.parametrize("dtype", [hkv.BF16, hkv.FP8_E4M3])
+@pytest.mark.parametrize("n_req, shared, private", [(234, 512, (300, 300, 300)), (200, 512, (380, 380, 380))])
+def test_cutting_nodes_keeps_a_plan_within_the_static_workspace(dtype, n_req, shared, private):
+    """One long path in a batch of short ones: four partials per row fit the static workspace, one per piece of its nodes would not."""
+    parent, ntok, leaves = [-1, 0, 1, 2], [shared, *private], [3]
+    parent, ntok, leaves = parent + [0], ntok + [16], leaves + [4]
+    for _ in range(n_req - 2):
+        leaves.append(len(parent))
+        parent.append(-1)
+        ntok.append(16)
+    n_pages = sum(-(-t // 16) for t in ntok)
+    f = wl.make_forest(parent, ntok, leaves, np.arange(n_pages, dtype=np.int32))
+    pool = fake_pool(n_pages, 8, dtype=dtype)
+    plan = hkv.hkv_decode_plan_create(pool, f.nodes, f.node_pages, f.req_leaf, 128, hkv.PLAN_HOST_ONLY)
+    assert hkv.hkv_decode_plan_max_parts(plan) == 4
+    assert hkv.hkv_decode_plan_workspace_bytes(plan) <= hkv.hkv_static_workspace_bytes()
+    hkv.hkv_decode_plan_destroy(plan)
+    hkv.kv_pool_destroy(pool)
+
+
 def test_merge_argument_validation():
     with pytest.raises(hkv.HkvError) as e:
         hkv.lse_merge(0x1000, 0x2000, 0x3000, 0x4000, 4, 0x5000, 7, stream=0)
