@@ -761,7 +761,7 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     const int pack_tokens = or_default(opt.pack_tokens, 12 * step_tokens);
     const int pack_mode = or_default(opt.pack, 2);  // 1: never, 2: when the items exceed the resident workgroups, 3: always
     auto cut_for_packing = [&](int n_tokens) { return n_tokens > pack_tokens && 3 * n_tokens < 8 * pack_tokens; };
-    bool cut_leaves = false;
+    bool cut_leaves = false, cut_to_fill = false;
     if (leaf_split == 1 && pack_mode != 1 && opt.leaf_chunk == 0) {
         int64_t units = shared_units;
         bool any = false;
@@ -772,7 +772,9 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
             any |= cut_for_packing(T);
             units += (int64_t)Hkv * (cut_for_packing(T) ? (T + pack_tokens - 1) / pack_tokens : 1);
         }
-        cut_leaves = any && (pack_mode == 3 || units > (cut_more ? kResidentGroups : chip.n_cu * (fp8_pool ? 2 : 3)));
+        const bool beyond_chip = pack_mode == 3 || units > chip.n_cu * (fp8_pool ? 2 : 3);
+        cut_leaves = any && (beyond_chip || (cut_more && units > kResidentGroups));
+        cut_to_fill = cut_leaves && !beyond_chip;
     }
     // Items of more than 16 rows: how long a chunk?  Such an item costs a start-up, a hand-over between its wavefronts and
     // a partial per row (6 us together) beside 0.8 us per 64 tokens alone and 1.1 to 2.9 us on a full chip (from L2 / from
@@ -787,16 +789,36 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
         const int64_t slots = kResidentGroups;
         double other_steps = 0;
         int64_t other_units = 0, rows_below = 0;
-        for (int v = 0; v < n_nodes; ++v) {
-            const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
-            if (pl.nodes[v].n_tokens == 0 || R == 0 || tiled(v)) continue;
-            if (R * G > 16) {
-                rows_below = std::max<int64_t>(rows_below, (int64_t)R * pl.num_q_heads);
-            } else {
-                const int pieces = cut_leaves && cut_for_packing(pl.nodes[v].n_tokens) ? (pl.nodes[v].n_tokens + pack_tokens - 1) / pack_tokens : 1;
-                other_units += (int64_t)pieces * Hkv;
-                other_steps += (double)Hkv * ((pl.nodes[v].n_tokens + step_tokens - 1) / step_tokens);
+        // The searches below look at each length once, however many nodes have it (a walk over all nodes for every candidate
+        // made plans of a few hundred nodes take twice as long to create): items a shared node of so many tokens has per
+        // chunk, summed; few-row nodes of so many tokens.
+        std::vector<std::pair<int32_t, int64_t>> shared_lengths;
+        std::vector<int32_t> few_lengths(pack_tokens + 1, 0);
+        int64_t few_longer = 0;
+        {
+            std::vector<int64_t> by_length(kMaxSharedItemTokens + 1, 0);
+            for (int v = 0; v < n_nodes; ++v) {
+                const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v], T = pl.nodes[v].n_tokens;
+                if (T == 0 || R == 0 || tiled(v)) continue;
+                if (R * G > 16) {
+                    rows_below = std::max<int64_t>(rows_below, (int64_t)R * pl.num_q_heads);
+                    const int64_t items = (int64_t)((R + max_req_per_item - 1) / max_req_per_item) * Hkv;
+                    if (T <= kMaxSharedItemTokens)
+                        by_length[T] += items;
+                    else
+                        shared_lengths.push_back({T, items});
+                } else {
+                    const int pieces = cut_leaves && cut_for_packing(T) ? (T + pack_tokens - 1) / pack_tokens : 1;
+                    other_units += (int64_t)pieces * Hkv;
+                    other_steps += (double)Hkv * ((T + step_tokens - 1) / step_tokens);
+                    if (T <= pack_tokens)
+                        ++few_lengths[T];
+                    else
+                        ++few_longer;
+                }
             }
+            for (int T = 1; T <= kMaxSharedItemTokens; ++T)
+                if (by_length[T]) shared_lengths.push_back({T, by_length[T]});
         }
         const double us_alone = 0.8, us_full = std::max(fp8 ? 1.25 : 1.1, (fp8 ? 1.54 : 2.9) * unique / through);  // per 64 tokens
         const bool packs = pack_mode == 3 || (pack_mode == 2 && other_units + shared_units > kResidentGroups);
@@ -807,12 +829,10 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
         int64_t best_n = 0;  // such items at the chunk taken
         for (int ch = shared_chunk; ch <= kMaxSharedItemTokens; ch += 64) {
             int64_t n = 0, longest_blocks = 0;
-            for (int v = 0; v < n_nodes; ++v) {
-                const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
-                if (pl.nodes[v].n_tokens == 0 || R * G <= 16 || tiled(v)) continue;
-                const int64_t chunks = (pl.nodes[v].n_tokens + ch - 1) / ch;
-                n += (int64_t)((R + max_req_per_item - 1) / max_req_per_item) * Hkv * chunks;
-                longest_blocks = std::max<int64_t>(longest_blocks, (pl.nodes[v].n_tokens + 64 * chunks - 1) / (64 * chunks));
+            for (const auto &[T, items] : shared_lengths) {
+                const int chunks = T <= ch ? 1 : (T + ch - 1) / ch;
+                n += items * chunks;
+                longest_blocks = std::max<int64_t>(longest_blocks, chunks == 1 ? (T + 63) / 64 : (T + 64 * chunks - 1) / (64 * chunks));
             }
             const int64_t full = n / slots, rest = n % slots;
             const double last = rest ? 6.0 + longest_blocks * (us_alone + std::max(0.0, us_full - us_alone) * rest / slots) : 0.0;
@@ -835,12 +855,10 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
         // 2 x 256; a few blocks too many and it is 10 % slower.
         if (cut_more && packs && !cut_leaves && best_n + other_wgs < slots)
             for (int piece = std::max(160, 4 * step_tokens); piece < pack_tokens; piece += 16) {
-                int64_t units = 0;
-                for (int v = 0; v < n_nodes; ++v) {
-                    const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
-                    const int T = pl.nodes[v].n_tokens;
-                    if (T > 0 && R > 0 && R * G <= 16 && !tiled(v)) units += (int64_t)Hkv * (T <= pack_tokens ? (T + piece - 1) / piece : 4);
-                }
+                int64_t units = 4 * few_longer;
+                for (int T = 1; T <= pack_tokens; ++T)
+                    if (few_lengths[T]) units += (int64_t)few_lengths[T] * ((T + piece - 1) / piece);
+                units *= Hkv;
                 if (best_n + (units + 3) / 4 <= slots) {
                     piece_tokens = piece;
                     break;
@@ -1017,7 +1035,7 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     // blocks side by side, which works as long as no item synchronises per step (more than 16 query rows).
     pl.fused = !pl.tile_items.empty() && !pl.items.empty() && opt.fused >= 0 && !pl.fp8_matrix;
     for (const DecodeItem &it : pl.items) pl.fused = pl.fused && it.n_req * G <= 16;
-    return cut_leaves || piece_tokens < pack_tokens;
+    return cut_to_fill || piece_tokens < pack_tokens;
 }
 
 // A piece more on one path is a partial more for every row of the batch.  Where that alone would take the partials beyond the
