@@ -276,7 +276,11 @@ enum {
      * event forks to it, one joins it before the merge; both are ordered after everything queued earlier on
      * the caller's stream, and the call is safe under stream capture).  With this flag everything is queued
      * on the caller's stream, one kernel after the other. */
-    HKV_PLAN_ONE_STREAM = 4
+    HKV_PLAN_ONE_STREAM = 4,
+    /* Decode plans over bf16 pools (no effect on others): items of 17 to 64 query rows run as 16-row tiles, a wavefront each
+     * over all their tokens, instead of 32-row tiles x token halves.  The library takes these by itself where a plan is
+     * bound by streaming its private nodes; the flag is for tests and comparisons (hkv_decode_plan_has_wide_tiles). */
+    HKV_PLAN_NARROW_TILES = 8
 };
 
 /* nodes, node_pages, req_leaf: host.  Validates the forest (ETREE/ERANGE, page ids against the
@@ -352,7 +356,7 @@ typedef struct {
     int32_t pack;             /* four short items per workgroup, one per wavefront: 1 never, 2 when the forest has
                                  more items than the chip holds at once (the default), 3 always */
     int32_t pack_tokens;      /* longest item of that mode, tokens */
-    int32_t stages;           /* 16 KiB LDS stages a workgroup owns: 3..5 */
+    int32_t stages;           /* 16 KiB LDS stages a workgroup owns: 3..5 (3 counts as 4 where items run as 32-row tiles) */
     int32_t interleave;       /* items shared by many rows and items of few rows are listed side by side in
                                  groups of this size (default 8); -1: one class after the other */
     int32_t tile_min_rows;    /* nodes shared by this many query rows or more may go to the 256-row tile kernel
@@ -403,6 +407,8 @@ int32_t hkv_decode_plan_num_tile_items(const hkv_decode_plan *plan);
 int32_t hkv_decode_plan_tile_workgroups(const hkv_decode_plan *plan);
 int32_t hkv_decode_plan_is_fused(const hkv_decode_plan *plan);
 int32_t hkv_decode_plan_has_stream(const hkv_decode_plan *plan);
+/* 1 if the plan holds items of 17 to 64 query rows and runs them as 32-row tiles x token halves, else 0. */
+int32_t hkv_decode_plan_has_wide_tiles(const hkv_decode_plan *plan);
 /* Workgroups of the per-node kernel: one per item, except that in forests with more items than the
  * chip holds at once the short items of at most 16 query rows (listed last) share a workgroup four
  * at a time, one item per wavefront. */

@@ -103,6 +103,7 @@ struct hkv_decode_plan {
     int32_t n_single = 0;  // items [0, n_single) run one per workgroup, the rest four per workgroup
     int32_t n_stages = 3;  // LDS stages of 16 KiB per workgroup of the per-node kernel
     bool has_shared = false;  // items of `items` shared by more than 16 query rows are run by shared::body
+    bool narrow_tiles = false;  // bf16 pools: never shared::body (HKV_PLAN_NARROW_TILES)
     bool fp8_matrix = false;  // fp8 pools: both products on the fp8 matrix instruction (HKV_PLAN_FP8_MATRIX)
     hkv_decode_plan_params opt{};  // the planner's settings (0 = the library's choice)
     int32_t *d_pages = nullptr, *d_node_req_idx = nullptr, *d_part_count = nullptr;
@@ -710,7 +711,7 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     // disturb them less (64 requests of 512 private tokens below 512 / 1024 / 2048 shared ones: 29.8 / 29.5 / 29.2 us
     // against 30.4 / 30.5 / 30.1; below 4096, 31.2 against 31.0).
     const bool fp8_pool = pl.pool->d.dtype == HKV_FP8_E4M3;
-    pl.has_shared = any_shared && (fp8_pool || other_tokens < 3 * through || other_tokens * 4 * HKV_HEAD_DIM * Hkv < 80e6);
+    pl.has_shared = any_shared && !pl.narrow_tiles && (fp8_pool || other_tokens < 3 * through || other_tokens * 4 * HKV_HEAD_DIM * Hkv < 80e6);
     // workgroups the chip holds at once: two per compute unit with fp8 pools or with shared::body in the launch, else three
     const int kResidentGroups = chip.n_cu * (fp8_pool || pl.has_shared ? 2 : 3);
     int64_t leaf_units = 0, leaf_tokens = 0, shared_units = 0;
@@ -1179,6 +1180,7 @@ static int create_decode_plan(hkv_pool *pool, const hkv_node *nodes, int32_t n_n
         }
     hkv_decode_plan *pl = new (std::nothrow) hkv_decode_plan;
     if (!pl) return fail(HKV_ENOMEM, "hkv_decode_plan_create: out of host memory");
+    pl->narrow_tiles = pool->d.dtype == HKV_BF16 && (flags & HKV_PLAN_NARROW_TILES);
     pl->pool = pool;
     pl->n_req = n_req;
     pl->num_q_heads = num_q_heads;
@@ -1573,6 +1575,9 @@ extern "C" int32_t hkv_decode_plan_is_fused(const hkv_decode_plan *plan) {
 }
 extern "C" int32_t hkv_decode_plan_has_stream(const hkv_decode_plan *plan) {
     return plan ? (plan->side ? 1 : 0) : fail(HKV_EINVAL, "null plan");
+}
+extern "C" int32_t hkv_decode_plan_has_wide_tiles(const hkv_decode_plan *plan) {
+    return plan ? (plan->has_shared && !plan->fp8_matrix ? 1 : 0) : fail(HKV_EINVAL, "null plan");
 }
 extern "C" int32_t hkv_decode_plan_tile_workgroups(const hkv_decode_plan *plan) {
     return plan ? plan->tile_workgroups : fail(HKV_EINVAL, "null plan");

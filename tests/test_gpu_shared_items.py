@@ -1,6 +1,7 @@
-"""Decode items shared by 17 to 64 query rows (two 32-row tiles x two token halves per workgroup): the edges of row tiles, of
-token halves and of the 64-token block, scores that rise far above the first block's (the lazily moved softmax reference),
-rows that see nothing of a chunk, and the split of more than 64 rows into equal groups, against the oracle."""
+"""Decode items shared by 17 to 64 query rows, in both forms (two 32-row tiles x two token halves per workgroup; for bf16 pools
+also four 16-row tiles): the edges of row tiles, of token halves and of the 64-token block, scores that rise far above the first
+block's (where the softmax reference moves), rows that see nothing of a chunk, scores of -inf and NaN, and the split of more than 64
+rows into equal groups, against the oracle."""
 import dataclasses
 
 import numpy as np
@@ -50,6 +51,7 @@ def run(gpu, oracle, w, T=1, tiles=(False, False), **settings):  # noqa: F811
     assert (n_tiles > 0, fused) == tiles
     if not n_tiles:
         assert (items[:, 4] * G > 16).any() and (items[:, 4] * G <= 64).all()
+        assert hkv.hkv_decode_plan_has_wide_tiles(plan) == (settings.get("flags", 0) != hkv.PLAN_NARROW_TILES)
     nb = hkv.hkv_decode_plan_workspace_bytes(plan)
     ws = torch.empty(max(nb, 256), dtype=torch.uint8, device="cuda")
     out = torch.zeros((f.n_req * T, w.num_q_heads, 128), dtype=torch.int16, device="cuda")
@@ -62,30 +64,86 @@ def run(gpu, oracle, w, T=1, tiles=(False, False), **settings):  # noqa: F811
     check_lse(lse.cpu().numpy(), exp_l, w.name)
 
 
-@pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
-@pytest.mark.parametrize("hq, hk, n_req", [(17, 1, 1), (8, 2, 5), (8, 2, 8), (11, 1, 3), (16, 2, 8), (10, 2, 13), (4, 1, 17), (8, 1, 25)])
-def test_row_tiles_and_token_edges(gpu, oracle, kv_dtype, hq, hk, n_req):  # noqa: F811
-    if hq // hk > 16:
-        hq, n_req = 9, 2               # 18 rows
+NARROW = 8                             # HKV_PLAN_NARROW_TILES: 16-row tiles
+FORMS = [(wl.KV_BF16, 0), (wl.KV_FP8_E4M3, 0), (wl.KV_BF16, NARROW)]
+
+
+@pytest.mark.parametrize("kv_dtype, flags", FORMS)
+@pytest.mark.parametrize("hq, hk, n_req", [(9, 1, 2), (8, 2, 5), (8, 2, 8), (11, 1, 3), (16, 2, 8), (10, 2, 13), (4, 1, 17), (8, 1, 25)])
+def test_row_tiles_and_token_edges(gpu, oracle, kv_dtype, flags, hq, hk, n_req):  # noqa: F811
     for root in (1, 16, 17, 31, 33, 64, 65, 96, 97, 130, 700):
-        run(gpu, oracle, workload(kv_dtype, hq, hk, n_req, root))
+        run(gpu, oracle, workload(kv_dtype, hq, hk, n_req, root), flags=flags)
 
 
-@pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
-@pytest.mark.parametrize("settings", [{}, {"shared_chunk": 64}, {"shared_chunk": 2048, "stages": 3}, {"shared_chunk": 2048, "stages": 4}])
-def test_rising_scores_and_ring_sizes(gpu, oracle, kv_dtype, settings):  # noqa: F811
-    run(gpu, oracle, workload(kv_dtype, 8, 2, 16, 2048 + 33, gain=15.0), **settings)
+@pytest.mark.parametrize("kv_dtype, flags", FORMS)
+@pytest.mark.parametrize("settings", [{}, {"shared_chunk": 64}, {"shared_chunk": 2048, "stages": 4}, {"shared_chunk": 2048, "stages": 5},
+                                      {"shared_chunk": 2048, "stages": 3}])       # 3: four stages for 32-row tiles, three for 16-row tiles
+def test_rising_scores_and_ring_sizes(gpu, oracle, kv_dtype, flags, settings):  # noqa: F811
+    run(gpu, oracle, workload(kv_dtype, 8, 2, 16, 2048 + 33, gain=15.0), flags=flags, **settings)
 
 
-@pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
+@pytest.mark.parametrize("kv_dtype, flags", FORMS)
 @pytest.mark.parametrize("T, leaf_chunk", [(8, 0), (16, 16), (40, 32)])
-def test_drafted_rows_of_one_leaf(gpu, oracle, kv_dtype, T, leaf_chunk):  # noqa: F811
+def test_drafted_rows_of_one_leaf(gpu, oracle, kv_dtype, flags, T, leaf_chunk):  # noqa: F811
     """T x 4 rows of one leaf: causal limits inside the item, and (short chunks) rows that see nothing of one."""
     parent, ntok = [-1, 0, 0], [128, T + 37, T]
     n_used = sum((t + 15) // 16 for t in ntok)
     f = wl.make_forest(parent, ntok, [1, 2], np.random.default_rng(T).permutation(n_used + 3).astype(np.int32))
     w = wl.Workload(name=f"draft{T}", num_q_heads=8, num_kv_heads=2, kv_dtype=kv_dtype, num_pages=n_used + 3, seed=T, forest=f, mode="decode")
-    run(gpu, oracle, w, T, **({"leaf_chunk": leaf_chunk, "shared_chunk": leaf_chunk} if leaf_chunk else {}))
+    run(gpu, oracle, w, T, flags=flags, **({"leaf_chunk": leaf_chunk, "shared_chunk": leaf_chunk} if leaf_chunk else {}))
+
+
+@pytest.mark.parametrize("flags", [0, NARROW])
+@pytest.mark.parametrize("quiet", [range(0, 64), range(32, 160), range(0, 400), range(7, 400)])
+def test_scores_of_minus_infinity_and_nan(gpu, oracle, flags, quiet):  # noqa: F811
+    """Tokens `quiet` of the root score -inf (whole blocks, a wavefront's first ones, the whole item): the rest is plain attention.
+    A NaN among the keys of one head stays with that head."""
+    import torch
+    from paper_2603_16104_amd import binding as hkv
+    w = workload(wl.KV_BF16, 8, 2, 8, 400)
+    f, n_req = w.forest, w.forest.n_req
+    dp = gpu.DevicePool(w.num_pages, 2, wl.KV_BF16)
+    bits, back = wl.f32_to_bf16_bits, wl.bf16_bits_to_f32
+    q = back(w.q()).copy()
+    q[:, :, 0] = 1.0
+    kv = []
+    for v in range(f.n_nodes):
+        K, V = (back(x).copy() for x in w.node_kv(v))
+        K[:, :, 0] = 0.0
+        if v == 0:
+            K[list(quiet), :, 0] = -np.inf
+        kv.append((K, V))
+        dp.write(f.node_pages[f.page_begin[v]: f.page_begin[v] + f.n_pages[v]], 0, gpu.to_device_bits(bits(K)), gpu.to_device_bits(bits(V)))
+    plan = hkv.hkv_decode_plan_create_ex(dp.handle, f.nodes, f.node_pages, f.req_leaf, 8, flags)
+    assert hkv.hkv_decode_plan_has_wide_tiles(plan) == (flags == 0)
+    nb = hkv.hkv_decode_plan_workspace_bytes(plan)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    out = torch.zeros((n_req, 8, 128), dtype=torch.int16, device="cuda")
+    lse = torch.zeros((n_req, 8), dtype=torch.float32, device="cuda")
+
+    def step():
+        hkv.attn_decode_plan_run(plan, gpu.to_device_bits(bits(q)), float(w.scale), out, lse, ws, nb)
+        torch.cuda.synchronize()
+        return gpu.bf16_tensor_to_f64(out), lse.cpu().numpy()
+
+    exp_o, exp_l = np.zeros((n_req, 8, 128)), np.zeros((n_req, 8))
+    for r in range(n_req):
+        keep = [t for t in range(400) if t not in quiet]
+        K, V = (np.concatenate([kv[0][i][keep], kv[f.req_leaf[r]][i]]).astype(np.float64) for i in (0, 1))
+        for h in range(8):
+            s = K[:, h // 4] @ q[r, h].astype(np.float64) * float(w.scale)
+            exp_l[r, h] = s.max() + np.log(np.exp(s - s.max()).sum())
+            exp_o[r, h] = np.exp(s - exp_l[r, h]) @ V[:, h // 4]
+    got_o, got_l = step()
+    check_close(got_o, exp_o, "-inf scores")
+    check_lse(got_l, exp_l, "-inf scores")
+    K = kv[0][0]
+    K[70, 0, 5] = np.nan
+    dp.write(f.node_pages[f.page_begin[0]: f.page_begin[0] + f.n_pages[0]], 0, gpu.to_device_bits(bits(K)), gpu.to_device_bits(bits(kv[0][1])))
+    nan_o, nan_l = step()
+    assert np.array_equal(nan_o[:, 4:], got_o[:, 4:]) and np.array_equal(nan_l[:, 4:], got_l[:, 4:])
+    hkv.hkv_decode_plan_destroy(plan)
+    dp.close()
 
 
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
@@ -146,9 +204,10 @@ def weight_of_one_key(gpu, n_req, T, root, where, tiles=False, hq=8, hk=2, **set
 WEIGHT_RMS = 6.4e-4
 
 
+@pytest.mark.parametrize("flags", [0, NARROW])
 @pytest.mark.parametrize("n_req, where", [(5, 69), (8, 145), (16, 256 + 31), (16, 500), (13, 64), (16, 96)])
-def test_heaviest_weight_is_exact(gpu, n_req, where):  # noqa: F811
-    err = weight_of_one_key(gpu, n_req, 1, 640, where)
+def test_heaviest_weight_is_exact(gpu, flags, n_req, where):  # noqa: F811
+    err = weight_of_one_key(gpu, n_req, 1, 640, where, flags=flags)
     assert np.sqrt((err ** 2).mean()) < WEIGHT_RMS
 
 
