@@ -305,7 +305,8 @@ def test_pool_write_largest_single_call(gpu, oracle, kv_dtype):
 def test_very_long_shared_prefix(gpu, oracle):
     """A 65 536-token prefix shared by 24 requests: decode (the prefix is cut into many LDS-staged chunks and
     every row collects 30+ partials) element by element, prefill of 150-250 new tokens per request on
-    sampled query tokens (the page-id window of the prefill kernel is refilled hundreds of times)."""
+    sampled query tokens, split along their keys and as whole tiles (which refill the prefill kernel's page-id window
+    hundreds of times)."""
     import torch
     rng = np.random.default_rng(5)
     n_req, Hq, Hkv, root = 24, 4, 1, 65536
@@ -328,10 +329,13 @@ def test_very_long_shared_prefix(gpu, oracle):
     r.close()
     wp = wl.Workload(name="long_prefix_prefill", mode="prefill", q_len=np.asarray(s, dtype=np.int32), **common)
     pr = gpu.PrefillRunner(dp, wp)
-    pr.run()
-    torch.cuda.synchronize()
-    got_o, got_l = gpu.bf16_tensor_to_f64(pr.out), pr.lse.cpu().numpy()
-    assert np.isfinite(got_o).all()
+    got = []
+    for ws in (pr.ws, None):      # without a workspace the tiles stay whole
+        pr.out.fill_(0x7FC0)
+        hkv.attn_prefill_plan_run(pr.plan, pr.q, pr.scale, pr.out, pr.lse, None, ws, pr.ws_bytes if ws is not None else 0)
+        torch.cuda.synchronize()
+        got.append((gpu.bf16_tensor_to_f64(pr.out), pr.lse.cpu().numpy()))
+        assert np.isfinite(got[-1][0]).all()
     obt, okv, *_ = oracle.flatten_workload(wp)
     cu, q = wp.cu_q(), wp.q()
     rows, qs, bts, lens = [], [], [], []
@@ -343,8 +347,9 @@ def test_very_long_shared_prefix(gpu, oracle):
         bts.append(obt[req])
         lens.append(okv[req] - s[req] + i + 1)
     e_o, e_l = oracle.attn_decode(hp, np.stack(qs), np.stack(bts), np.array(lens, dtype=np.int32), float(wp.scale))
-    res = check_close(got_o[rows], e_o, wp.name)
-    check_lse(got_l[rows], e_l, wp.name)
-    print(f"{wp.name}: sampled {len(rows)} query tokens: max_abs {res[0]:.3e} rel_l2 {res[1]:.3e}")
+    for got_o, got_l in got:
+        res = check_close(got_o[rows], e_o, wp.name)
+        check_lse(got_l[rows], e_l, wp.name)
+        print(f"{wp.name}: sampled {len(rows)} query tokens: max_abs {res[0]:.3e} rel_l2 {res[1]:.3e}")
     pr.close()
     dp.close()

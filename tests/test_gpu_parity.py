@@ -977,9 +977,10 @@ def test_decode_and_prefill_runs_are_graph_capturable(gpu, oracle):
 @pytest.mark.parametrize("late_key", [False, True])
 def test_prefill_prefix_longer_than_the_page_id_window(gpu, oracle, late_key):
     """A cached prefix of 33 400 tokens (2 088 pages): the kernel keeps 2 048 page ids in LDS at a time and
-    must refill that window on the way; with late_key a dominant key sits behind the refill point, so the
-    running-maximum fallback crosses it as well."""
+    must refill that window on the way where the tiles stay whole (a run without a workspace); with late_key a dominant
+    key sits behind the refill point, so the running-maximum fallback crosses it as well.  The same split along the keys."""
     import torch
+    from paper_2603_16104_amd import binding as hkv
     n_prefix, n_new = 33400 // 16 * 16, 70
     n_pages = (n_prefix + n_new + 15) // 16 + 3
     f = wl.make_forest([-1, 0], [n_prefix, n_new], [1], np.random.default_rng(6).permutation(n_pages).astype(np.int32))
@@ -1001,13 +1002,16 @@ def test_prefill_prefix_longer_than_the_page_id_window(gpu, oracle, late_key):
     hp, dp = both_pools(gpu, oracle, w)
     exp_o, exp_l = oracle.run_workload(w, hp)
     r = gpu.PrefillRunner(dp, w)
-    r.run()
-    torch.cuda.synchronize()
-    got_o, got_l = gpu.bf16_tensor_to_f64(r.out), r.lse.cpu().numpy()
+    for ws in (None, r.ws):
+        r.out.fill_(0x7FC0)
+        hkv.attn_prefill_plan_run(r.plan, r.q, r.scale, r.out, r.lse, None, ws, r.ws_bytes if ws is not None else 0)
+        torch.cuda.synchronize()
+        got_o, got_l = gpu.bf16_tensor_to_f64(r.out), r.lse.cpu().numpy()
+        check_close(got_o, exp_o, w.name)
+        assert np.abs(got_l - exp_l).max() <= 2e-3 + 1e-6 * np.abs(exp_l).max()
+        assert (hkv.hkv_prefill_plan_fallback_tiles(r.plan) > 0) == late_key
     r.close()
     dp.close()
-    check_close(got_o, exp_o, w.name)
-    assert np.abs(got_l - exp_l).max() <= 2e-3 + 1e-6 * np.abs(exp_l).max()
 
 
 # ------------------------------------------------------------------------------ fp32 pools (full-precision path)

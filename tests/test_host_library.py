@@ -615,6 +615,46 @@ def test_prefill_workspace_holds_the_partials_of_split_tiles(dtype):
     hkv.kv_pool_destroy(pool)
 
 
+@pytest.mark.parametrize("hq, hk, prefix, new, whole", [
+    (8, 2, 2048, (1,), 0), (8, 2, 2064, (65, 3), 0), (2, 2, 1040, (257, 300), 0), (5, 1, 1488, (51, 52, 103), 0), (3, 3, 1024, (86, 400), 0),
+    (8, 8, 1008, (2305,), 0), (32, 8, 2048, (256, 300, 350, 400, 450, 512), 256), (32, 8, 4096, (512,) * 5, 256), (32, 8, 4096, (290,) * 7, 256),
+    (8, 8, 65536, (100,) * 24, 0), (32, 8, 2048, (300,) * 6, None), (32, 8, 1024, (512,) * 7, None)])
+def test_split_prefill_covers_every_key_block_once(hq, hk, prefix, new, whole):
+    """The segments of a split prefill plan: every key of every tile in exactly one segment, segments of whole 64-token blocks but for a
+    tile's last, positions and table offsets moved to the segment's first key, whole tiles without a partial and first on their
+    worker, the partials of a tile one after the other, heads by worker.  whole: how many of them are whole tiles; None: no split."""
+    parent, ntok = [-1] + [0] * len(new), [prefix] + list(new)
+    n_pages = sum(-(-t // 16) for t in ntok)
+    f = wl.make_forest(parent, ntok, list(range(1, len(new) + 1)), np.arange(n_pages, dtype=np.int32))
+    pool = fake_pool(n_pages, hk)
+    bt, kv_len, *_ = hkv.prefix_tree_flatten(f.nodes, f.node_pages, f.req_leaf, f.max_pages_per_req(), 16)
+    plan = hkv.hkv_prefill_plan_create(pool, np.concatenate([[0], np.cumsum(new)]), bt, kv_len, hq, hkv.PLAN_HOST_ONLY)
+    tiles, seg = hkv.hkv_prefill_plan_tiles(plan), hkv.hkv_prefill_plan_segments(plan)
+    if whole is None:
+        assert len(seg) == 0 and hkv.hkv_prefill_plan_workspace_bytes(plan) == 0
+        tiles = tiles[:0]
+    else:
+        assert (seg[:, 9] < 0).sum() == whole
+        assert np.array_equal(np.sort(seg[seg[:, 9] >= 0, 9]), np.arange((seg[:, 9] >= 0).sum()))
+        assert (np.diff(seg[:, 10]) >= 0).all() and (seg[:, 3] == seg[:, 10] % hk).all()
+        for w in np.unique(seg[:, 10]):
+            assert (np.diff((seg[seg[:, 10] == w, 9] >= 0).astype(int)) >= 0).all()
+    for i, t in enumerate(tiles):
+        own = seg[seg[:, 11] == i]
+        first = t[5] - own[:, 5]
+        own, first = own[np.argsort(first)], np.sort(first)
+        end = t[5] + t[1] + t[2]
+        assert first[0] == 0 and (first % 64 == 0).all() and np.array_equal(first[1:], (first + own[:, 8])[:-1]) and first[-1] + own[-1, 8] == end
+        assert np.array_equal(own[:, 6], t[6] - first) and np.array_equal(own[:, 7], t[7] + first // 16)
+        assert (own[:, [0, 1, 2, 3, 4]] == t[[0, 1, 2, 3, 4]]).all()
+        if len(own) == 1:
+            assert own[0, 9] == -1
+        else:
+            assert np.array_equal(own[:, 9], own[0, 9] + np.arange(len(own)))
+    hkv.hkv_prefill_plan_destroy(plan)
+    hkv.kv_pool_destroy(pool)
+
+
 @pytest.mark.parametrize("dtype", [hkv.BF16, hkv.FP8_E4M3])
 @pytest.mark.parametrize("n_req, shared, private", [(234, 512, (300, 300, 300)), (200, 512, (380, 380, 380))])
 def test_cutting_nodes_keeps_a_plan_within_the_static_workspace(dtype, n_req, shared, private):
