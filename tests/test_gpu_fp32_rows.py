@@ -116,3 +116,30 @@ def test_scores_without_a_softmax_give_nan(gpu, value, tokens):  # noqa: F811
     assert np.isnan(got_o[:2]).all() and np.isneginf(got_l[:2]).all()
     check_close_fp32(got_o[2:], exp_o, "the other head")
     check_lse(got_l[2:], exp_l, "the other head", tol=1e-4)
+
+
+def test_fp32_launch_of_more_than_two_to_the_31_threads(gpu):  # noqa: F811
+    """131 075 queries x 128 heads over one page: a launch takes 131 072 of them, the rest goes out as a second one."""
+    import torch
+    from paper_2603_16104_amd import binding as hkv
+    n, H = (1 << 31) // (128 * 64 * 2) + 3, 128
+    dp = gpu.DevicePool(1, H, wl.KV_FP32)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    K, V = (torch.randn((16, H, 128), device="cuda", generator=gen) for _ in range(2))
+    dp.write(np.zeros(1, dtype=np.int32), 0, K, V)
+    q = torch.randn((n, H, 128), device="cuda", generator=gen)
+    out, lse = torch.full_like(q, float("nan")), torch.full((n, H), float("nan"), device="cuda")
+    f = wl.make_forest([-1], [16], [0] * n, np.zeros(1, dtype=np.int32))
+    plan = hkv.hkv_decode_plan_create(dp.handle, f.nodes, f.node_pages, f.req_leaf, H)
+    hkv.attn_decode_plan_run(plan, q, 0.1, out, lse, torch.empty(256, dtype=torch.uint8, device="cuda"), 256)
+    torch.cuda.synchronize()
+    hkv.hkv_decode_plan_destroy(plan)
+    assert not torch.isnan(lse).any() and not any(torch.isnan(out[a: a + 8192]).any() for a in range(0, n, 8192))
+    rows = [0, 1, 70000, n - 5, n - 4, n - 3, n - 2, n - 1]
+    s = (q[rows].double()[:, :, None, :] @ K.double().permute(1, 2, 0).contiguous()[None])[:, :, 0] * 0.1
+    l = torch.logsumexp(s, dim=2)
+    o = (torch.exp(s - l[:, :, None])[:, :, None, :] @ V.double().permute(1, 0, 2).contiguous()[None])[:, :, 0]
+    check_close_fp32(out[rows].cpu().numpy().astype(np.float64), o.cpu().numpy(), "rows on both sides of the cut")
+    check_lse(lse[rows].cpu().numpy(), l.cpu().numpy(), "rows on both sides of the cut", tol=1e-4)
+    dp.close()
