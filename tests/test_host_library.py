@@ -675,6 +675,25 @@ def test_cutting_nodes_keeps_a_plan_within_the_static_workspace(dtype, n_req, sh
     hkv.kv_pool_destroy(pool)
 
 
+def items_of(parent, ntok, leaves, hq, hk, dtype=hkv.BF16, T=1, flags=0):
+    """Work items of a host-only plan over a forest in page order, and whether shared ones run as 32-row tiles."""
+    f = wl.make_forest(parent, ntok, leaves, np.arange(sum((t + 15) // 16 for t in ntok), dtype=np.int32))
+    pool = fake_pool(len(f.node_pages), hk, dtype)
+    plan = hkv.hkv_decode_plan_create_ex(pool, f.nodes, f.node_pages, f.req_leaf, hq, hkv.PLAN_HOST_ONLY | flags, tokens_per_req=T)
+    items, wide = hkv.hkv_decode_plan_items(plan), hkv.hkv_decode_plan_has_wide_tiles(plan)
+    hkv.hkv_decode_plan_destroy(plan)
+    hkv.kv_pool_destroy(pool)
+    return items, wide
+
+
+@pytest.mark.parametrize("G, n_req, narrow, wide", [(8, 18, {8, 2}, {6}), (4, 36, {16, 4}, {12}), (4, 21, {11, 10}, {11, 10}), (1, 65, {64, 1}, {33, 32})])
+def test_request_groups_of_shared_nodes(G, n_req, narrow, wide):
+    """16-row tiles take full groups of 64 rows and leave a remainder of up to 16 to the form for few rows; else the groups are equal."""
+    for flags, dtype, sizes in ((hkv.PLAN_NARROW_TILES, hkv.BF16, narrow), (0, hkv.BF16, wide), (0, hkv.FP8_E4M3, wide)):
+        items, _ = items_of([-1] + [0] * n_req, [640] + [16] * n_req, list(range(1, n_req + 1)), 2 * G, 2, dtype, flags=flags)
+        assert set(items[items[:, 7] == 0, 4].tolist()) == sizes
+
+
 def test_merge_argument_validation():
     with pytest.raises(hkv.HkvError) as e:
         hkv.lse_merge(0x1000, 0x2000, 0x3000, 0x4000, 4, 0x5000, 7, stream=0)
