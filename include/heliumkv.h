@@ -278,9 +278,10 @@ enum {
      * on the caller's stream, one kernel after the other. */
     HKV_PLAN_ONE_STREAM = 4,
     /* Decode plans over bf16 pools (no effect on others): items of 17 to 64 query rows run as 16-row tiles, a wavefront each
-     * over all their tokens, instead of 32-row tiles x token halves.  The library takes these by itself where a plan is
-     * bound by streaming its private nodes; the flag is for tests and comparisons (hkv_decode_plan_has_wide_tiles). */
-    HKV_PLAN_NARROW_TILES = 8
+     * over all their tokens, or as 32-row tiles x token halves.  The library takes the form it estimates the shorter step
+     * for (hkv_decode_plan_has_wide_tiles); the flags are for tests and comparisons, NARROW wins over WIDE. */
+    HKV_PLAN_NARROW_TILES = 8,
+    HKV_PLAN_WIDE_TILES = 16
 };
 
 /* nodes, node_pages, req_leaf: host.  Validates the forest (ETREE/ERANGE, page ids against the

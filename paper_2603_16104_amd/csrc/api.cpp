@@ -103,7 +103,7 @@ struct hkv_decode_plan {
     int32_t n_single = 0;  // items [0, n_single) run one per workgroup, the rest four per workgroup
     int32_t n_stages = 3;  // LDS stages of 16 KiB per workgroup of the per-node kernel
     bool has_shared = false;  // items of `items` shared by more than 16 query rows are run by shared::body
-    bool narrow_tiles = false;  // bf16 pools: never shared::body (HKV_PLAN_NARROW_TILES)
+    int tile_form = 0;  // bf16 pools: -1 never, 1 always shared::body (HKV_PLAN_NARROW_TILES, HKV_PLAN_WIDE_TILES)
     bool fp8_matrix = false;  // fp8 pools: both products on the fp8 matrix instruction (HKV_PLAN_FP8_MATRIX)
     hkv_decode_plan_params opt{};  // the planner's settings (0 = the library's choice)
     int32_t *d_pages = nullptr, *d_node_req_idx = nullptr, *d_part_count = nullptr;
@@ -693,8 +693,9 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
         return tiles_pay && !row_node[v] && !pl.fp8_matrix && pl.nodes[v].n_tokens > 0 &&
                R * G >= std::max(tile_min_rows, kMinTileItemRows);
     };
+    const bool fp8_pool = pl.pool->d.dtype == HKV_FP8_E4M3;
     bool any_shared = false;
-    double through = 0, unique = 0, other_tokens = 0;  // K/V tokens: of shared nodes through workgroups / from HBM, of the others
+    double through = 0, unique = 0, few_tokens = 0;  // K/V tokens: of shared nodes through workgroups / from HBM, of the others
     for (int v = 0; v < n_nodes; ++v) {
         const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
         if (pl.nodes[v].n_tokens == 0 || R == 0 || tiled(v)) continue;
@@ -703,17 +704,10 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
             through += (double)pl.nodes[v].n_tokens * ((R + max_req_per_item - 1) / max_req_per_item);
             unique += pl.nodes[v].n_tokens;
         } else {
-            other_tokens += pl.nodes[v].n_tokens;
+            few_tokens += pl.nodes[v].n_tokens;
         }
     }
-    // Shared nodes go to shared::body, except (bf16) beside three times as many tokens of private nodes in a step of more
-    // than 80 MB: such a step is bound by streaming those, and the 16-row tiles with three workgroups per compute unit
-    // disturb them less (64 requests of 512 private tokens below 512 / 1024 / 2048 shared ones: 29.8 / 29.5 / 29.2 us
-    // against 30.4 / 30.5 / 30.1; below 4096, 31.2 against 31.0).
-    const bool fp8_pool = pl.pool->d.dtype == HKV_FP8_E4M3;
-    pl.has_shared = any_shared && !pl.narrow_tiles && (fp8_pool || other_tokens < 3 * through || other_tokens * 4 * HKV_HEAD_DIM * Hkv < 80e6);
-    // workgroups the chip holds at once: two per compute unit with fp8 pools or with shared::body in the launch, else three
-    const int kResidentGroups = chip.n_cu * (fp8_pool || pl.has_shared ? 2 : 3);
+    const int kNodeGroups = chip.n_cu * (fp8_pool ? 2 : 3);  // workgroups the chip holds at once without shared::body (with it: two per compute unit)
     int64_t leaf_units = 0, leaf_tokens = 0, shared_units = 0;
     for (int v = 0; v < n_nodes; ++v) {
         int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
@@ -727,12 +721,12 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
         }
     }
     int leaf_split = 1;
-    if (leaf_units > 0 && leaf_units + shared_units < kResidentGroups / 2)
-        leaf_split = (int)((kResidentGroups / 2 + leaf_units - 1) / leaf_units);
+    if (leaf_units > 0 && leaf_units + shared_units < kNodeGroups / 2)
+        leaf_split = (int)((kNodeGroups / 2 + leaf_units - 1) / leaf_units);
     const int mean_leaf = leaf_units ? (int)(leaf_tokens * Hkv / leaf_units) : 512;
     int leaf_chunk = std::max(256, (mean_leaf / leaf_split + 15) / 16 * 16);
     if (leaf_split == 1) leaf_chunk = 1 << 30;  // whole nodes
-    int shared_chunk = std::min(kMaxSharedItemTokens, std::max(512, std::min(mean_leaf, leaf_chunk) / 16 * 16));
+    int base_chunk = std::min(kMaxSharedItemTokens, std::max(512, std::min(mean_leaf, leaf_chunk) / 16 * 16));
     // Long shared paths: every chunk costs each row below it one partial (written once, read once) and
     // every item a start-up, while a long item is the last to finish; measured on forests with 2k to 9k
     // shared tokens the best chunk is about a sixth of the path, between 512 and 1024 tokens.  Beyond
@@ -748,10 +742,10 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
         }
         int64_t by_path = std::min<int64_t>(1024, (longest / 6 + 128) / 256 * 256);
         if (longest > 16 * by_path) by_path = std::min<int64_t>(kMaxSharedItemTokens, (longest / 16 + 255) / 256 * 256);
-        shared_chunk = std::max(shared_chunk, (int)by_path);
+        base_chunk = std::max(base_chunk, (int)by_path);
     }
     leaf_chunk = or_default(opt.leaf_chunk, leaf_chunk) / 16 * 16;
-    shared_chunk = std::min(kMaxSharedItemTokens, or_default(opt.shared_chunk, shared_chunk)) / 16 * 16;
+    base_chunk = std::min(kMaxSharedItemTokens, or_default(opt.shared_chunk, base_chunk)) / 16 * 16;
     // Few-row nodes a little longer than what one wavefront takes alone (pack_tokens): run whole, their
     // four wavefronts get only a few steps each and pay a start-up and a combine through LDS for them.
     // When cutting them into pieces of at most pack_tokens makes the forest large enough for the
@@ -762,110 +756,196 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     const int pack_tokens = or_default(opt.pack_tokens, 12 * step_tokens);
     const int pack_mode = or_default(opt.pack, 2);  // 1: never, 2: when the items exceed the resident workgroups, 3: always
     auto cut_for_packing = [&](int n_tokens) { return n_tokens > pack_tokens && 3 * n_tokens < 8 * pack_tokens; };
-    bool cut_leaves = false, cut_to_fill = false;
-    if (leaf_split == 1 && pack_mode != 1 && opt.leaf_chunk == 0) {
-        int64_t units = shared_units;
-        bool any = false;
-        for (int v = 0; v < n_nodes; ++v) {
-            const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
-            const int T = pl.nodes[v].n_tokens;
-            if (T == 0 || R == 0 || R * G > 16) continue;
-            any |= cut_for_packing(T);
-            units += (int64_t)Hkv * (cut_for_packing(T) ? (T + pack_tokens - 1) / pack_tokens : 1);
-        }
-        const bool beyond_chip = pack_mode == 3 || units > chip.n_cu * (fp8_pool ? 2 : 3);
-        cut_leaves = any && (beyond_chip || (cut_more && units > kResidentGroups));
-        cut_to_fill = cut_leaves && !beyond_chip;
-    }
-    // Items of more than 16 rows: how long a chunk?  Such an item costs a start-up, a hand-over between its wavefronts and
-    // a partial per row (6 us together) beside 0.8 us per 64 tokens alone and 1.1 to 2.9 us on a full chip (from L2 / from
-    // HBM); two run on a compute unit, dispatched in front of the others, which fill what they leave free.  So a chunk
-    // that puts a few items into a second round, or leaves the others no room beside the first, costs a whole further
-    // item: 4096 tokens x 512 rows + 8 x 1024 x 64 + 128 private leaves, bf16, takes 47 us cut into 768 tokens (512 such
-    // items), 31 us at 1024 (320), 36 us at 1376 (256).  From the length above up to the longest there is, the one with
-    // the shortest estimated step is taken.
-    int piece_tokens = pack_tokens;
-    if (pl.has_shared && !pl.fp8_matrix && opt.shared_chunk == 0 && opt.leaf_chunk == 0) {
-        const bool fp8 = fp8_pool;
-        const int64_t slots = kResidentGroups;
-        double other_steps = 0;
-        int64_t other_units = 0, rows_below = 0;
-        // The searches below look at each length once, however many nodes have it (a walk over all nodes for every candidate
-        // made plans of a few hundred nodes take twice as long to create): items a shared node of so many tokens has per
-        // chunk, summed; few-row nodes of so many tokens.
-        std::vector<std::pair<int32_t, int64_t>> shared_lengths;
-        std::vector<int32_t> few_lengths(pack_tokens + 1, 0);
-        int64_t few_longer = 0;
-        {
-            std::vector<int64_t> by_length(kMaxSharedItemTokens + 1, 0);
+    // What depends on whether shared nodes run in shared::body (`wide`) or as 16-row tiles.
+    struct Layout {
+        bool wide;
+        int slots;                     // workgroups the chip holds at once
+        bool cut_leaves, cut_to_fill;  // few-row nodes cut for packing; only to fill slots
+        int shared_chunk, piece_tokens;
+    };
+    auto lay_out = [&](const bool wide) {
+        Layout lay{wide, wide ? 2 * chip.n_cu : kNodeGroups, false, false, base_chunk, pack_tokens};
+        if (leaf_split == 1 && pack_mode != 1 && opt.leaf_chunk == 0) {
+            int64_t units = shared_units;
+            bool any = false;
             for (int v = 0; v < n_nodes; ++v) {
-                const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v], T = pl.nodes[v].n_tokens;
-                if (T == 0 || R == 0 || tiled(v)) continue;
-                if (R * G > 16) {
-                    rows_below = std::max<int64_t>(rows_below, (int64_t)R * pl.num_q_heads);
-                    const int64_t items = (int64_t)((R + max_req_per_item - 1) / max_req_per_item) * Hkv;
-                    if (T <= kMaxSharedItemTokens)
-                        by_length[T] += items;
-                    else
-                        shared_lengths.push_back({T, items});
-                } else {
-                    const int pieces = cut_leaves && cut_for_packing(T) ? (T + pack_tokens - 1) / pack_tokens : 1;
-                    other_units += (int64_t)pieces * Hkv;
-                    other_steps += (double)Hkv * ((T + step_tokens - 1) / step_tokens);
-                    if (T <= pack_tokens)
-                        ++few_lengths[T];
-                    else
-                        ++few_longer;
+                const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
+                const int T = pl.nodes[v].n_tokens;
+                if (T == 0 || R == 0 || R * G > 16) continue;
+                any |= cut_for_packing(T);
+                units += (int64_t)Hkv * (cut_for_packing(T) ? (T + pack_tokens - 1) / pack_tokens : 1);
+            }
+            const bool beyond_chip = pack_mode == 3 || units > kNodeGroups;
+            lay.cut_leaves = any && (beyond_chip || (cut_more && units > lay.slots));
+            lay.cut_to_fill = lay.cut_leaves && !beyond_chip;
+        }
+        // Items of more than 16 rows: how long a chunk?  Such an item costs a start-up, a hand-over between its wavefronts and
+        // a partial per row (6 us together) beside 0.8 us per 64 tokens alone and 1.1 to 2.9 us on a full chip (from L2 / from
+        // HBM); two run on a compute unit, dispatched in front of the others, which fill what they leave free.  So a chunk
+        // that puts a few items into a second round, or leaves the others no room beside the first, costs a whole further
+        // item: 4096 tokens x 512 rows + 8 x 1024 x 64 + 128 private leaves, bf16, takes 47 us cut into 768 tokens (512 such
+        // items), 31 us at 1024 (320), 36 us at 1376 (256).  From the length above up to the longest there is, the one with
+        // the shortest estimated step is taken.
+        if (wide && !pl.fp8_matrix && opt.shared_chunk == 0 && opt.leaf_chunk == 0) {
+            const bool fp8 = fp8_pool;
+            const int64_t slots = lay.slots;
+            double other_steps = 0;
+            int64_t other_units = 0, rows_below = 0;
+            // The searches below look at each length once, however many nodes have it (a walk over all nodes for every candidate
+            // made plans of a few hundred nodes take twice as long to create): items a shared node of so many tokens has per
+            // chunk, summed; few-row nodes of so many tokens.
+            std::vector<std::pair<int32_t, int64_t>> shared_lengths;
+            std::vector<int32_t> few_lengths(pack_tokens + 1, 0);
+            int64_t few_longer = 0;
+            {
+                std::vector<int64_t> by_length(kMaxSharedItemTokens + 1, 0);
+                for (int v = 0; v < n_nodes; ++v) {
+                    const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v], T = pl.nodes[v].n_tokens;
+                    if (T == 0 || R == 0 || tiled(v)) continue;
+                    if (R * G > 16) {
+                        rows_below = std::max<int64_t>(rows_below, (int64_t)R * pl.num_q_heads);
+                        const int64_t items = (int64_t)((R + max_req_per_item - 1) / max_req_per_item) * Hkv;
+                        if (T <= kMaxSharedItemTokens)
+                            by_length[T] += items;
+                        else
+                            shared_lengths.push_back({T, items});
+                    } else {
+                        const int pieces = lay.cut_leaves && cut_for_packing(T) ? (T + pack_tokens - 1) / pack_tokens : 1;
+                        other_units += (int64_t)pieces * Hkv;
+                        other_steps += (double)Hkv * ((T + step_tokens - 1) / step_tokens);
+                        if (T <= pack_tokens)
+                            ++few_lengths[T];
+                        else
+                            ++few_longer;
+                    }
+                }
+                for (int T = 1; T <= kMaxSharedItemTokens; ++T)
+                    if (by_length[T]) shared_lengths.push_back({T, by_length[T]});
+            }
+            const double us_alone = 0.8, us_full = std::max(fp8 ? 1.25 : 1.1, (fp8 ? 1.54 : 2.9) * unique / through);  // per 64 tokens
+            const bool packs = pack_mode == 3 || (pack_mode == 2 && other_units + shared_units > lay.slots);
+            const int64_t other_wgs = packs ? (other_units + 3) / 4 : other_units;
+            const double other_us = other_units ? 5.0 + other_steps / other_units / (packs ? 1 : 4) : 1.0;
+            int best = lay.shared_chunk;
+            double best_us = 1e30;
+            int64_t best_n = 0;  // such items at the chunk taken
+            for (int ch = lay.shared_chunk; ch <= kMaxSharedItemTokens; ch += 64) {
+                int64_t n = 0, longest_blocks = 0;
+                for (const auto &[T, items] : shared_lengths) {
+                    const int chunks = T <= ch ? 1 : (T + ch - 1) / ch;
+                    n += items * chunks;
+                    longest_blocks = std::max<int64_t>(longest_blocks, chunks == 1 ? (T + 63) / 64 : (T + 64 * chunks - 1) / (64 * chunks));
+                }
+                const int64_t full = n / slots, rest = n % slots;
+                const double last = rest ? 6.0 + longest_blocks * (us_alone + std::max(0.0, us_full - us_alone) * rest / slots) : 0.0;
+                double us = full * (6.0 + longest_blocks * us_full) + last;
+                if (other_wgs > 0) {  // in the slots left free, then in all of them
+                    const int64_t beside = rest ? (slots - rest) * std::max<int64_t>(1, (int64_t)(last / other_us)) : 0;
+                    us = other_wgs <= beside ? std::max(us, other_us) : us + other_us * std::ceil((double)(other_wgs - beside) / slots);
+                }
+                us += rows_below * 264.0 * 2 / 4e6 * ((longest + ch - 1) / ch);  // the partials, written and read at about 4 TB/s
+                if (us < best_us - 1e-9) {
+                    best_us = us;
+                    best = ch;
+                    best_n = n;
                 }
             }
-            for (int T = 1; T <= kMaxSharedItemTokens; ++T)
-                if (by_length[T]) shared_lengths.push_back({T, by_length[T]});
-        }
-        const double us_alone = 0.8, us_full = std::max(fp8 ? 1.25 : 1.1, (fp8 ? 1.54 : 2.9) * unique / through);  // per 64 tokens
-        const bool packs = pack_mode == 3 || (pack_mode == 2 && other_units + shared_units > kResidentGroups);
-        const int64_t other_wgs = packs ? (other_units + 3) / 4 : other_units;
-        const double other_us = other_units ? 5.0 + other_steps / other_units / (packs ? 1 : 4) : 1.0;
-        int best = shared_chunk;
-        double best_us = 1e30;
-        int64_t best_n = 0;  // such items at the chunk taken
-        for (int ch = shared_chunk; ch <= kMaxSharedItemTokens; ch += 64) {
-            int64_t n = 0, longest_blocks = 0;
-            for (const auto &[T, items] : shared_lengths) {
-                const int chunks = T <= ch ? 1 : (T + ch - 1) / ch;
-                n += items * chunks;
-                longest_blocks = std::max<int64_t>(longest_blocks, chunks == 1 ? (T + 63) / 64 : (T + 64 * chunks - 1) / (64 * chunks));
-            }
-            const int64_t full = n / slots, rest = n % slots;
-            const double last = rest ? 6.0 + longest_blocks * (us_alone + std::max(0.0, us_full - us_alone) * rest / slots) : 0.0;
-            double us = full * (6.0 + longest_blocks * us_full) + last;
-            if (other_wgs > 0) {  // in the slots left free, then in all of them
-                const int64_t beside = rest ? (slots - rest) * std::max<int64_t>(1, (int64_t)(last / other_us)) : 0;
-                us = other_wgs <= beside ? std::max(us, other_us) : us + other_us * std::ceil((double)(other_wgs - beside) / slots);
-            }
-            us += rows_below * 264.0 * 2 / 4e6 * ((longest + ch - 1) / ch);  // the partials, written and read at about 4 TB/s
-            if (us < best_us - 1e-9) {
-                best_us = us;
-                best = ch;
-                best_n = n;
-            }
-        }
-        shared_chunk = best;
-        // Where both kinds together leave workgroup slots empty, packed nodes that are whole so far are cut until they fill
-        // them (a wavefront that streams a node alone is the longest chain of such a launch; below 160 resp. 256 tokens its
-        // start-up takes over).  64 requests of 512 private tokens below 4096 shared ones, fp8: 28.9 us whole, 22.8 us as
-        // 2 x 256; a few blocks too many and it is 10 % slower.
-        if (cut_more && packs && !cut_leaves && best_n + other_wgs < slots)
-            for (int piece = std::max(160, 4 * step_tokens); piece < pack_tokens; piece += 16) {
-                int64_t units = 4 * few_longer;
-                for (int T = 1; T <= pack_tokens; ++T)
-                    if (few_lengths[T]) units += (int64_t)few_lengths[T] * ((T + piece - 1) / piece);
-                units *= Hkv;
-                if (best_n + (units + 3) / 4 <= slots) {
-                    piece_tokens = piece;
-                    break;
+            lay.shared_chunk = best;
+            // Where both kinds together leave workgroup slots empty, packed nodes that are whole so far are cut until they fill
+            // them (a wavefront that streams a node alone is the longest chain of such a launch; below 160 resp. 256 tokens its
+            // start-up takes over).  64 requests of 512 private tokens below 4096 shared ones, fp8: 28.9 us whole, 22.8 us as
+            // 2 x 256; a few blocks too many and it is 10 % slower.
+            if (cut_more && packs && !lay.cut_leaves && best_n + other_wgs < slots)
+                for (int piece = std::max(160, 4 * step_tokens); piece < pack_tokens; piece += 16) {
+                    int64_t units = 4 * few_longer;
+                    for (int T = 1; T <= pack_tokens; ++T)
+                        if (few_lengths[T]) units += (int64_t)few_lengths[T] * ((T + piece - 1) / piece);
+                    units *= Hkv;
+                    if (best_n + (units + 3) / 4 <= slots) {
+                        lay.piece_tokens = piece;
+                        break;
+                    }
                 }
+        }
+        return lay;
+    };
+    // A plan's step in one form or the other, bf16 pools, us: three times that run beside each other (as a 3-norm), and the
+    // partials.  Latency: the workgroups, longest first, on the chip's slots; alone one takes 1.6 + 0.82 per 64 tokens as
+    // 32-row tiles, 1.0 + 0.53 per 32 as 16-row tiles, 2.5 + 0.86 per 128 for few rows, and on a full chip 1.4 to 1.5 times that.
+    // Issue, per compute unit: per 64 tokens of an item and per workgroup.  Memory: shared nodes at 5.5 TB/s, the others at 7.1
+    // beside 16-row tiles (three workgroups per compute unit) and 6.5 beside 32-row tiles.  (Fitted to 1376 decode and
+    // verification plans, most of them random, timed in both forms; 8 % rms.)
+    auto step_us = [&](const Layout &lay) {
+        struct Items {
+            int32_t tokens;  // of one
+            float n;
+            bool many;
+        };
+        std::vector<Items> list;
+        list.reserve(n_nodes);
+        std::vector<int32_t> chunks_to(n_nodes);
+        double n_items = 0;
+        int32_t parts = 1;
+        for (int v = 0; v < n_nodes; ++v) {
+            const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v], T = pl.nodes[v].n_tokens, n_pages = pl.nodes[v].n_pages;
+            chunks_to[v] = pl.nodes[v].parent >= 0 ? chunks_to[pl.nodes[v].parent] : 0;
+            if (T == 0 || R == 0 || tiled(v)) continue;
+            const bool many = R * G > 16;
+            int chunk = std::max(16, many ? lay.shared_chunk : leaf_chunk), n_chunks = 1, per_chunk = n_pages;
+            if (!many && ((lay.cut_leaves && cut_for_packing(T)) || (lay.piece_tokens < pack_tokens && T <= pack_tokens))) chunk = lay.piece_tokens;
+            if (T > chunk) {  // as the items are cut below
+                per_chunk = (n_pages + (T - 1) / chunk) / ((T - 1) / chunk + 1);
+                n_chunks = (n_pages + per_chunk - 1) / per_chunk;
             }
-    }
+            chunks_to[v] += n_chunks;
+            parts = std::max(parts, chunks_to[v]);
+            const int64_t n = (int64_t)n_chunks * Hkv * (many ? (R + max_req_per_item - 1) / max_req_per_item : 1);
+            list.push_back({std::min(T, per_chunk * 16), (float)n, many});
+            n_items += n;
+        }
+        const bool packs = pack_mode == 3 || (pack_mode == 2 && n_items > lay.slots);
+        constexpr int kBins = 256;  // durations in steps of 0.25 us
+        double bins[kBins] = {}, n_wgs = 0, work = 0, longest_us = 0, issue = 0;
+        int top = 0;
+        for (const Items &it : list) {
+            const bool packed = packs && !it.many && it.tokens <= pack_tokens;
+            const int blocks = (it.tokens + 63) / 64;
+            const double us = packed     ? (lay.wide ? 2.78 + 0.24 * ((it.tokens + 31) / 32) : 0.01 + 0.31 * ((it.tokens + 31) / 32))
+                              : !it.many ? 2.48 + 0.86 * ((it.tokens + 127) / 128)
+                              : lay.wide ? 1.60 + 0.82 * blocks
+                                         : 0.98 + 0.53 * ((it.tokens + 31) / 32);
+            issue += it.n * blocks * (it.many ? (lay.wide ? 0.52 : 0.55) : (lay.wide ? 0.36 : 0.68));
+            const double wgs = packed ? 0.25 * it.n : it.n;
+            n_wgs += wgs;
+            work += wgs * us;
+            longest_us = std::max(longest_us, us);
+            const int bin = std::min(kBins - 1, (int)(us * 4));
+            bins[bin] += wgs;
+            top = std::max(top, bin);
+        }
+        double span = std::max(longest_us, work / lay.slots), seen = 0;
+        for (int b = top, round = 0; b >= 0; --b) {  // workgroup number k * slots runs as the k + 1st on some slot at the earliest
+            for (seen += bins[b]; seen > (double)round * lay.slots; ++round) span = std::max(span, (round + 1) * 0.25 * (b + 0.5));
+        }
+        span *= 1.0 + (lay.wide ? 0.40 : 0.54) * std::min(1.0, n_wgs / lay.slots);
+        issue = (issue + (lay.wide ? 2.65 : 1.42) * n_wgs) / chip.n_cu;
+        const double stream = (unique / 5.5e6 + few_tokens / (lay.wide ? 6.5e6 : 7.07e6)) * 4 * HKV_HEAD_DIM * Hkv;
+        return 7.5 + std::cbrt(span * span * span + issue * issue * issue + stream * stream * stream) + 0.16e-6 * 264 * 2 * (double)pl.n_req * pl.num_q_heads * parts;
+    };
+    // bf16 pools: shared::body where that estimate is 2 % shorter with it.  It takes two thirds as long for an item alone, but two
+    // workgroups fill a compute unit where three with 16-row tiles do, so that on a full chip the two come to the same and
+    // how the items fill it decides.  Both forms timed (us, 16-row / 32-row tiles): one root of 512 tokens over 64 leaves of
+    // 128 / 320 / 512 / 1024 tokens 22.3 / 17.3, 26.5 / 24.7, 30.1 / 30.8, 52.6 / 52.6; 8192 over 64 x 1024 63.4 / 73.5; 64 requests
+    // x 4 drafted tokens x 5 heads over 133 + 31 tokens 15.7 / 20.8.  Of 1320 random plans 32-row tiles everywhere gain 2.4 % in the
+    // mean and lose up to 38 %, the shorter of the two would gain 4.4 %; this choice gains 3.5 %, loses more than 3 % in 22 plans (most
+    // of them short) and misses a tenth in 27 (shared nodes of several thousand tokens above many rows).
+    const bool either = any_shared && !fp8_pool && pl.tile_form == 0;
+    Layout lay = lay_out(any_shared && (fp8_pool || pl.tile_form > 0));
+    if (either)
+        if (const Layout wide = lay_out(true); step_us(wide) < 0.98 * step_us(lay)) lay = wide;
+    pl.has_shared = lay.wide;
+    const int shared_chunk = lay.shared_chunk, piece_tokens = lay.piece_tokens;
+    const bool cut_leaves = lay.cut_leaves, cut_to_fill = lay.cut_to_fill;
     // The tile kernel's share of the chip: its persistent workgroups hold one compute unit each for as long as
     // the other kernel streams its bytes, so their number follows from the two amounts of work (matrix
     // arithmetic at about 3.5 TFLOP/s per compute unit against bytes at about 5.5 TB/s for the chip).
@@ -976,7 +1056,7 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     // Forests with more items than the chip holds at once: the short items of at most 16 rows are run four
     // to a workgroup, one per wavefront (a workgroup's start-up then serves four items, and such a
     // wavefront streams its whole item with one step in flight); they are listed behind the others.
-    const bool pack = pack_mode == 3 || (pack_mode == 2 && (int64_t)protos.size() > kResidentGroups);
+    const bool pack = pack_mode == 3 || (pack_mode == 2 && (int64_t)protos.size() > lay.slots);
     auto packable = [&](const Proto &p) { return pack && p.it.n_req * G <= 16 && p.it.n_tokens <= pack_tokens; };
     // one item per workgroup first, heavy before light in both classes: a single integer key per item
     for (Proto &p : protos) p.cost = (packable(p) ? 0 : (int64_t)1 << 56) + p.cost;
@@ -1183,7 +1263,7 @@ static int create_decode_plan(hkv_pool *pool, const hkv_node *nodes, int32_t n_n
         }
     hkv_decode_plan *pl = new (std::nothrow) hkv_decode_plan;
     if (!pl) return fail(HKV_ENOMEM, "hkv_decode_plan_create: out of host memory");
-    pl->narrow_tiles = pool->d.dtype == HKV_BF16 && (flags & HKV_PLAN_NARROW_TILES);
+    if (pool->d.dtype == HKV_BF16) pl->tile_form = flags & HKV_PLAN_NARROW_TILES ? -1 : flags & HKV_PLAN_WIDE_TILES ? 1 : 0;
     pl->pool = pool;
     pl->n_req = n_req;
     pl->num_q_heads = num_q_heads;

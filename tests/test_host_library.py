@@ -689,9 +689,35 @@ def items_of(parent, ntok, leaves, hq, hk, dtype=hkv.BF16, T=1, flags=0):
 @pytest.mark.parametrize("G, n_req, narrow, wide", [(8, 18, {8, 2}, {6}), (4, 36, {16, 4}, {12}), (4, 21, {11, 10}, {11, 10}), (1, 65, {64, 1}, {33, 32})])
 def test_request_groups_of_shared_nodes(G, n_req, narrow, wide):
     """16-row tiles take full groups of 64 rows and leave a remainder of up to 16 to the form for few rows; else the groups are equal."""
-    for flags, dtype, sizes in ((hkv.PLAN_NARROW_TILES, hkv.BF16, narrow), (0, hkv.BF16, wide), (0, hkv.FP8_E4M3, wide)):
+    for flags, dtype, sizes in ((hkv.PLAN_NARROW_TILES, hkv.BF16, narrow), (hkv.PLAN_WIDE_TILES, hkv.BF16, wide), (0, hkv.FP8_E4M3, wide)):
         items, _ = items_of([-1] + [0] * n_req, [640] + [16] * n_req, list(range(1, n_req + 1)), 2 * G, 2, dtype, flags=flags)
         assert set(items[items[:, 7] == 0, 4].tolist()) == sizes
+
+
+@pytest.mark.parametrize("tokens, fan, heads, T, wide", [
+    ((512, 128), (1, 64), (32, 8), 1, True), ((512, 320), (1, 64), (32, 8), 1, True), ((2048, 256), (1, 64), (32, 8), 1, True),   # items of both kinds
+    ((512, 1024), (1, 32), (32, 8), 1, False), ((2048, 512), (1, 64), (32, 8), 1, False),                 # bound by streaming private nodes
+    ((8192, 1024), (1, 64), (32, 8), 1, False), ((2048, 512), (1, 64), (32, 8), 4, False),
+    ((133, 31), (1, 64), (40, 8), 4, False), ((146, 100, 62), (1, 12, 11), (64, 8), 4, False),             # one round of short items against two
+])
+def test_form_of_shared_items_is_the_one_that_measured_shorter(tokens, fan, heads, T, wide):
+    """bf16 pools, at points where the two forms' times differ by 3 % or more."""
+    parent, ntok, level = [], [], [-1]
+    for t, n in zip(tokens, fan):
+        parent += [p for p in level for _ in range(n)]
+        level = list(range(len(ntok), len(parent)))
+        ntok += [t] * len(level)
+    assert items_of(parent, ntok, level, *heads, T=T)[1] == wide
+    for flags in (hkv.PLAN_NARROW_TILES, hkv.PLAN_WIDE_TILES):
+        assert items_of(parent, ntok, level, *heads, T=T, flags=flags)[1] == (flags == hkv.PLAN_WIDE_TILES)
+
+
+@pytest.mark.parametrize("flags", [hkv.PLAN_NARROW_TILES, hkv.PLAN_WIDE_TILES])
+def test_few_long_nodes_are_cut_in_both_forms(flags):
+    """12 nodes of 3222 tokens x 16 rows and 24 of 16 tokens: 296 (node, head) units leave half of the chip idle, whatever runs the root."""
+    parent = [-1] + [0] * 12 + [1 + i // 2 for i in range(24)]
+    items, _ = items_of(parent, [226] + [3222] * 12 + [16] * 24, list(range(13, 37)), 32, 8, T=2, flags=flags)
+    assert items[:, 1].max() <= 1104
 
 
 def test_merge_argument_validation():
