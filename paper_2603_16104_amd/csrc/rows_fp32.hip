@@ -7,6 +7,7 @@
 // fp32 block format: K in 64-byte dimension chunks of 16 floats, chunk-major then slot
 // ((d / 16) * 256 + slot * 16 + d % 16); V dimension-major (d * 16 + slot).
 #include <algorithm>
+#include <type_traits>
 
 #include "hkv_device.h"
 
@@ -68,104 +69,104 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
             for (int i = 0; i < 8; ++i) f[g][i] = *reinterpret_cast<const f32x4 *>(p + 256 * i);
         }
     };
-    float m, l;           // of the own row: running maximum (times scale * log2 e), this lane's share of the row sum
+    // Of the own row: running maximum (times scale * log2 e), this lane's share of the row sum.  It begins at the lowest finite
+    // number: scores of -inf have weight 0 against that, not exp2(inf - inf), however many come first.
+    constexpr float kLowest = -3.40282347e38f;
+    float m, l;
     f32x4 acc[kRows][2];  // dims 16 i + slot of row r, this lane's quarter of the slots: element i % 4 of acc[r][i / 4]
     // A value whose weight underflows to zero takes no part, whatever it is (0 * inf would be NaN).  Asking for that at every
     // product would double the vector instructions, and infinities stay in a sum once they are there: a wavefront that ends
-    // with one in its sums walks its keys a second time, asking.
-    bool careful = false;
-  walk:
-    m = -INFINITY;
-    l = 0.f;
+    // with one in its sums walks its keys a second time, asking.  (Two loops: one with a flag took 256 registers
+    // instead of 241; 23 x 84 new tokens x 32 heads over 240, 753 -> 683 us.)
+    auto walk = [&](auto careful_tag) {
+        constexpr bool kCareful = decltype(careful_tag)::value;
+        m = kLowest;
+        l = 0.f;
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) acc[r][0] = acc[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (wave < n_steps) {
-        fetch(kf, K, wave);
-        fetch(vf, V, wave);
-    }
-    for (int step = wave; step < n_steps; step += n_waves) {
-        float s[kStepPages][kRows];
-#pragma unroll
-        for (int g = 0; g < kStepPages; ++g)
-#pragma unroll
-            for (int r = 0; r < kRows; ++r) {
-                float dot = 0.f;
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) dot = __builtin_fmaf(qf[r][i][j], kf[g][i][j], dot);
-                s[g][r] = quad_sum(dot);
-            }
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(kf, K, step + n_waves);  // the K registers are free (behind the last step: its page again, in bounds)
-        __builtin_amdgcn_sched_barrier(0);
-        float x = kRows == 2 ? (own_row ? (own_page ? s[1][kRows - 1] : s[0][kRows - 1]) : (own_page ? s[1][0] : s[0][0])) : (own_page ? s[1][0] : s[0][0]);
-        x = (step * kStepPages + own_page) * kPage + slot < len ? x * c : -INFINITY;
-        float mx = fmaxf(x, dpp<kRor4>(x));  // over the lanes of the own row: slots ...
-        mx = fmaxf(mx, dpp<kRor8>(mx));
-        mx = rows_max(mx);
-        mx = fmaxf(mx, kRows == 2 ? dpp<kQuadXor2>(mx) : dpp<kQuadXor1>(mx));  // ... and pages
-        const float m_new = fmaxf(m, mx);
-        const float ref = m_new == -INFINITY ? 0.f : m_new;  // every score so far is -inf: their weights are 0, not exp(inf - inf)
-        const float alpha = fast_exp2(m - ref);              // 0 on the first step (m = -inf)
-        const float p = fast_exp2(x - ref);
-        l = l * alpha + p;
-        m = m_new;
-        if (counts) sP[wave][own_row][own_page * kPage + slot] = p;
-        __builtin_amdgcn_wave_barrier();  // (LDS operations of one wavefront execute in order)
-        const bool tail = (step + 1) * kStepKeys > len;
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            const float al = kRows == 2 ? (r ? dpp<0x55>(alpha) : dpp<0x00>(alpha)) : alpha;  // the row's factor from its lane of the quad
-            acc[r][0] *= al;
-            acc[r][1] *= al;
-            if (careful && al == 0.f) acc[r][0] = acc[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int r = 0; r < kRows; ++r) acc[r][0] = acc[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (wave < n_steps) {
+            fetch(kf, K, wave);
+            fetch(vf, V, wave);
         }
+        for (int step = wave; step < n_steps; step += n_waves) {
+            float s[kStepPages][kRows];
 #pragma unroll
-        for (int g = 0; g < kStepPages; ++g) {
-            if (tail) {  // slots past the sequence end may hold anything (NaN included)
-                const int left = len - (step * kStepPages + g) * kPage - 4 * quarter;
+            for (int g = 0; g < kStepPages; ++g)
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) vf[g][i][j] = j < left ? vf[g][i][j] : 0.f;
-            }
-#pragma unroll
-            for (int r = 0; r < kRows; ++r) {
-                const f32x4 pr = *reinterpret_cast<const f32x4 *>(&sP[wave][r][g * kPage + 4 * quarter]);
-                if (careful) {
+                for (int r = 0; r < kRows; ++r) {
+                    float dot = 0.f;
 #pragma unroll
                     for (int i = 0; i < 8; ++i)
 #pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (pr[j] != 0.f) acc[r][i >> 2][i & 3] = __builtin_fmaf(pr[j], vf[g][i][j], acc[r][i >> 2][i & 3]);
-                    continue;
+                        for (int j = 0; j < 4; ++j) dot = __builtin_fmaf(qf[r][i][j], kf[g][i][j], dot);
+                    s[g][r] = quad_sum(dot);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(kf, K, step + n_waves);  // the K registers are free (behind the last step: its page again, in bounds)
+            __builtin_amdgcn_sched_barrier(0);
+            float x = kRows == 2 ? (own_row ? (own_page ? s[1][kRows - 1] : s[0][kRows - 1]) : (own_page ? s[1][0] : s[0][0])) : (own_page ? s[1][0] : s[0][0]);
+            x = (step * kStepPages + own_page) * kPage + slot < len ? x * c : -INFINITY;
+            float mx = fmaxf(x, dpp<kRor4>(x));  // over the lanes of the own row: slots ...
+            mx = fmaxf(mx, dpp<kRor8>(mx));
+            mx = rows_max(mx);
+            mx = fmaxf(mx, kRows == 2 ? dpp<kQuadXor2>(mx) : dpp<kQuadXor1>(mx));  // ... and pages
+            const float m_new = fmaxf(m, mx);
+            const float alpha = fast_exp2(m - m_new);
+            const float p = fast_exp2(x - m_new);
+            l = l * alpha + p;
+            m = m_new;
+            if (counts) sP[wave][own_row][own_page * kPage + slot] = p;
+            __builtin_amdgcn_wave_barrier();  // (LDS operations of one wavefront execute in order)
+            const bool tail = (step + 1) * kStepKeys > len;
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const float al = kRows == 2 ? (r ? dpp<0x55>(alpha) : dpp<0x00>(alpha)) : alpha;  // the row's factor from its lane of the quad
+                acc[r][0] *= al;
+                acc[r][1] *= al;
+                if (kCareful && al == 0.f) acc[r][0] = acc[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int g = 0; g < kStepPages; ++g) {
+                if (tail) {  // slots past the sequence end may hold anything (NaN included)
+                    const int left = len - (step * kStepPages + g) * kPage - 4 * quarter;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) vf[g][i][j] = j < left ? vf[g][i][j] : 0.f;
                 }
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    float o = acc[r][i >> 2][i & 3];
+                for (int r = 0; r < kRows; ++r) {
+                    const f32x4 pr = *reinterpret_cast<const f32x4 *>(&sP[wave][r][g * kPage + 4 * quarter]);
+                    if constexpr (kCareful) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) o = __builtin_fmaf(pr[j], vf[g][i][j], o);
-                    acc[r][i >> 2][i & 3] = o;
+                        for (int i = 0; i < 8; ++i)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)
+                                if (pr[j] != 0.f) acc[r][i >> 2][i & 3] = __builtin_fmaf(pr[j], vf[g][i][j], acc[r][i >> 2][i & 3]);
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) {
+                            float o = acc[r][i >> 2][i & 3];
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) o = __builtin_fmaf(pr[j], vf[g][i][j], o);
+                            acc[r][i >> 2][i & 3] = o;
+                        }
+                    }
                 }
             }
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(vf, V, step + n_waves);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_wave_barrier();
         }
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(vf, V, step + n_waves);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_wave_barrier();
-    }
-    if (!careful) {
-        bool finite = true;
+    };
+    walk(std::false_type{});
+    float zero = 0.f;  // NaN if any sum is not finite
 #pragma unroll
-        for (int r = 0; r < kRows; ++r)
+    for (int r = 0; r < kRows; ++r)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) finite = finite && fabsf(acc[r][i >> 2][i & 3]) < INFINITY;
-        if (__builtin_amdgcn_ballot_w64(!finite)) {
-            careful = true;
-            goto walk;
-        }
-    }
+        for (int i = 0; i < 8; ++i) zero = __builtin_fmaf(acc[r][i >> 2][i & 3], 0.f, zero);
+    if (__builtin_amdgcn_ballot_w64(zero != 0.f)) walk(std::true_type{});
     // the own row's sum over its lanes, the dims over the quads; then the wavefronts
     float lt = l + dpp<kRor4>(l);
     lt += dpp<kRor8>(lt);
@@ -189,12 +190,11 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
         float M = -INFINITY;
         for (int w = 0; w < n_waves; ++w) M = fmaxf(M, sM[w][r]);
         float L = 0.f, out = 0.f;
-        if (M != -INFINITY) {
-            for (int w = 0; w < n_waves; ++w) {
-                const float f = fast_exp2(sM[w][r] - M);  // 0 for a wavefront without a step
-                L = __builtin_fmaf(sL[w][r], f, L);
-                if (f != 0.f) out = __builtin_fmaf(sO[w][r][d], f, out);
-            }
+        for (int w = 0; w < n_waves; ++w) {
+            const float f = fast_exp2(sM[w][r] - M);
+            L = __builtin_fmaf(sL[w][r], f, L);
+            const float with = __builtin_fmaf(sO[w][r][d], f, out);
+            out = f != 0.f ? with : out;
         }
         const size_t row = (size_t)tq * a.num_q_heads + kvh * G + h0 + r;
         // a row without keys gives out = 0, lse = -inf; one whose scores hold a NaN or +inf, or only -inf, gives NaN
