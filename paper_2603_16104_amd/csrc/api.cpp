@@ -648,8 +648,8 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     const int max_req_per_item = std::max(1, or_default(opt.max_rows, 64) / G);
     // Chunk lengths.  Nodes read by at most 16 rows ("leaf type") stay whole unless the forest has
     // fewer (node, head) units than workgroups fit on the chip at once; then they are cut, but not
-    // below 256 tokens.  Nodes shared by more rows run one row tile per wavefront over all tokens
-    // of the item, so their chunks are kept near the typical leaf-type item to finish together.
+    // below 256 tokens.  Nodes shared by more rows get chunks near the typical leaf-type item, so that
+    // both kinds finish together; for 32-row tiles that length is where the search below begins.
     // Nodes shared by many rows go to the 256-row tile kernel (not when the caller asked for the fp8 matrix instruction).
     const int tile_min_rows = or_default(opt.tile_min_rows, 128);
     // The second kernel, its stream and the two events pay only when that share of the step is large (measured:
@@ -665,7 +665,7 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     // heads, 17 GFLOP) it lost too (39.0 -> 46.2 us).
     // bf16 pools only if the caller asks (tile_min_gflop): the tile keeps one reference per row, so that the heaviest
     // probabilities lie anywhere in their binade when they are rounded to bf16, and the error against 64 bits grows from
-    // 0.00217 to 0.00231 (64 x 21 over 2048 + 512 tokens, 123.0 -> 97.4 us).  With fp8 pools the V scale comes in before that
+    // 0.00217 to 0.00231 (64 x 21 over 2048 + 512 tokens, 122 -> 97 us).  With fp8 pools the V scale comes in before that
     // rounding, whatever the reference, and the error is the same (0.00236).
     std::vector<char> row_node(n_nodes, 0);  // nodes whose tokens some rows see in part
     bool wide_row_node = false;
@@ -1895,8 +1895,8 @@ extern "C" size_t attn_decode_workspace_bytes(hkv_pool *pool, const hkv_node *no
 // end, cut where a worker's share is full.  Taken where the estimate says so (in key blocks of 64 tokens, 1.4 us each on a
 // full chip, a little less on one that is not): a tile or segment costs 4 blocks beside its own, the partials 135 KB each
 // on their way through memory and the second kernel 3 more.  Against a workgroup per tile, 32 / 8 heads, one request:
-// 64 / 256 / 1024 new tokens over 8192 cached ones 154 / 159 / 174 -> 33 / 51 / 147 us, 700 over 4096 95.5 -> 64.3,
-// 128 over 1024 29.9 -> 22.4; six requests of 256 to 512 over 2048 113.9 -> 104.3.  Where the estimate gains less than 13 %
+// 64 / 256 / 1024 new tokens over 8192 cached ones 154 / 159 / 183 -> 33 / 49 / 145 us, 700 over 4096 98.4 -> 62.7,
+// 128 over 1024 29.9 -> 22.7; six requests of 256 to 512 over 2048 114.5 -> 99.8.  Where the estimate gains less than 13 %
 // it was a loss as often as not (three of 1024 over 8192: estimate 0.89, measured 1.01).
 static void split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<PrefillTile> &head_tiles, int n_cu) {
     const int Hkv = pl.pool->d.num_kv_heads;

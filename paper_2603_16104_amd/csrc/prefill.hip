@@ -20,7 +20,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_tile_kernel(TileArgs a) {
 // Prefill tiles split along their keys: a persistent workgroup per compute unit runs an equal share of all key blocks.
 // Bound by the matrix cores like the tile itself; a batch of fewer tiles than compute units (or a little more than a
 // whole number of rounds) leaves the rest of the chip idle otherwise.  700 new tokens over 4096 cached ones, 88 tiles:
-// 95.5 us a workgroup per tile (0.53 PFLOP/s), 64.3 us split, both kernels (0.79).
+// 98.4 us a workgroup per tile (0.52 PFLOP/s), 62.7 us split, both kernels (0.81).
 __global__ __launch_bounds__(kThreads, 2) void prefill_split_kernel(TileArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[kLdsBytes];
     body<false, false, true>(a, lds, (int)blockIdx.x, 1);

@@ -179,8 +179,8 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
     const int G = a.num_q_heads / Hkv;
     const int rows = it.n_req * G;
     // Up to 16 rows: the four wavefronts split the tokens and read K/V straight into registers.
-    // More rows: shared_body.h; without it (the fp8 matrix instruction; bf16 plans bound by streaming their private
-    // nodes) each wavefront owns a 16-row tile, all tokens, and K/V are staged once in LDS.
+    // More rows: shared_body.h; without it (the fp8 matrix instruction; bf16 plans whose step the planner estimates shorter
+    // with 16-row tiles) each wavefront owns a 16-row tile, all tokens, and K/V are staged once in LDS.
     if constexpr (SHARED && DT != 2) {
         if (!packed && rows > 16) {  // wavefront-uniform, the same for the whole workgroup
             shared::body<DT == 1>(a, it, smem, wave, lane);

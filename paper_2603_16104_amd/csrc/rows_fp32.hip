@@ -20,7 +20,7 @@ namespace {
 // behind the first product, V behind the second), then by K/V from L2.  Every load is one KiB a wavefront: lane = (slot,
 // quarter of a 16-dimension chunk) for K, (dimension, quarter of the slots) for V, so a dot product is 32 multiply-adds in a
 // lane and two adds over its quad.  A wavefront per (token, head) with a lane per key read 64-byte pieces, walked all keys
-// alone and took 118 us for 16 requests x 32 heads over 1024 + 256 tokens on half of the chip; this takes 20.5 us (512 new
+// alone and took 118 us for 16 requests x 32 heads over 1024 + 256 tokens on half of the chip; this takes 18.3 us (512 new
 // tokens over 2048: 3.02 -> 0.77 ms), with a third of the rounding error, the dot products being shorter chains.
 constexpr int kRowWaves = 8;  // at most; fewer for short sequences (the launch decides)
 constexpr int kStepPages = 2;
