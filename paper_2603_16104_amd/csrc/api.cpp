@@ -783,8 +783,8 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
         // a partial per row (6 us together) beside 0.8 us per 64 tokens alone and 1.1 to 2.9 us on a full chip (from L2 / from
         // HBM); two run on a compute unit, dispatched in front of the others, which fill what they leave free.  So a chunk
         // that puts a few items into a second round, or leaves the others no room beside the first, costs a whole further
-        // item: 4096 tokens x 512 rows + 8 x 1024 x 64 + 128 private leaves, bf16, takes 47 us cut into 768 tokens (512 such
-        // items), 31 us at 1024 (320), 36 us at 1376 (256).  From the length above up to the longest there is, the one with
+        // item: 4096 tokens x 512 rows + 8 x 1024 x 64 + 128 private leaves, bf16, takes 45 us cut into 768 tokens (512 such
+        // items), 34 us at 1024 (320), 39 us at 1376 (256).  From the length above up to the longest there is, the one with
         // the shortest estimated step is taken.
         if (wide && !pl.fp8_matrix && opt.shared_chunk == 0 && opt.leaf_chunk == 0) {
             const bool fp8 = fp8_pool;

@@ -22,10 +22,10 @@
 //
 // Latency, not issue rate, is what the first form of this loop ran into (3900 cycles per block with a fifth of them
 // busy): an LDS read takes about 200 cycles, so a phase reads its operands in bulk, runs S(j+1) = K(j+1) Q^T beside
-// P(j) = exp2(S(j)), then O += V(j) P(j): one barrier per 64-token block.  Measured: 64 rows, 0.8 us per block alone,
-// 1.1 us for two workgroups of a compute unit from L2 (60 B/ns), 2.9 us bf16 / 1.5 us fp8 from HBM (5.8 / 5.4 TB/s).
-// Kernel over 100 requests x 5 heads below ten 8192-token contexts, fp8: 61 -> 47 us; 512 rows below 4096 tokens and 64
-// below each of 8 x 1024, bf16: 34 -> 30 us.
+// P(j) = exp2(S(j)), then O += V(j) P(j): one barrier per 64-token block.  Measured: 64 rows, 0.8 (fp8) to 0.9 us per block
+// alone, 1.1 us for two workgroups of a compute unit from L2 (60 B/ns), 2.9 us bf16 / 1.5 us fp8 from HBM (5.8 / 5.4 TB/s).
+// Kernel over 100 requests x 5 heads below ten 8192-token contexts, fp8: 61 -> 47 us; step of 512 rows below 4096 tokens and 64
+// below each of 8 x 1024, bf16: 39.7 -> 36.0 us.
 // K and V travel through one LDS ring of half-blocks in the order K(0), V(0), K(1), V(1), ...
 #pragma once
 #include "hkv_device.h"
