@@ -410,6 +410,11 @@ int32_t hkv_decode_plan_is_fused(const hkv_decode_plan *plan);
 int32_t hkv_decode_plan_has_stream(const hkv_decode_plan *plan);
 /* 1 if the plan holds items of 17 to 64 query rows and runs them as 32-row tiles x token halves, else 0. */
 int32_t hkv_decode_plan_has_wide_tiles(const hkv_decode_plan *plan);
+/* Small steps run whole root-to-leaf paths in one launch, without items and partials, where the library estimates that to be
+ * faster and the caller has neither set a planner parameter nor asked for a form of the items: the number of paths (a
+ * leaf and up to 16 * num_kv_heads / num_q_heads of its rows each; a workgroup per KV head runs one), else 0.  What is said
+ * of the plan's items, partials and workspace stands either way. */
+int32_t hkv_decode_plan_num_paths(const hkv_decode_plan *plan);
 /* Workgroups of the per-node kernel: one per item, except that in forests with more items than the
  * chip holds at once the short items of at most 16 query rows (listed last) share a workgroup four
  * at a time, one item per wavefront. */

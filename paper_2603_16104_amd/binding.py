@@ -32,7 +32,7 @@ EXPORTS = [
     "hkv_decode_plan_max_parts", "hkv_decode_plan_part_counts", "lse_merge_dense", "attn_decode_plan_run",
     "attn_decode_plan_run_static", "hkv_static_workspace_bytes",
     "hkv_decode_plan_set_profiling", "hkv_decode_plan_elapsed_ms", "hkv_decode_plan_elapsed_kernels_ms",
-    "hkv_decode_plan_num_tile_items", "hkv_decode_plan_tile_workgroups", "hkv_decode_plan_is_fused", "hkv_decode_plan_has_stream", "hkv_decode_plan_has_wide_tiles",
+    "hkv_decode_plan_num_tile_items", "hkv_decode_plan_tile_workgroups", "hkv_decode_plan_is_fused", "hkv_decode_plan_has_stream", "hkv_decode_plan_has_wide_tiles", "hkv_decode_plan_num_paths",
     "attn_decode_prefix_tree", "attn_decode_workspace_bytes", "hkv_prefill_plan_create", "hkv_prefill_plan_destroy",
     "hkv_prefill_plan_num_tiles", "hkv_prefill_plan_tiles", "hkv_prefill_plan_num_segments", "hkv_prefill_plan_segments", "attn_prefill_plan_run", "attn_prefill_plan_run_ws", "hkv_prefill_plan_workspace_bytes", "attn_prefill_with_prefix",
     "attn_prefill_workspace_bytes",
@@ -397,6 +397,11 @@ def hkv_decode_plan_is_fused(plan) -> bool:
 def hkv_decode_plan_has_stream(plan) -> bool:
     """Whether the plan holds a stream of its own, which its runs fork to."""
     return bool(_check(lib().hkv_decode_plan_has_stream(plan)))
+
+
+def hkv_decode_plan_num_paths(plan) -> int:
+    """Root-to-leaf paths the plan runs whole, in one launch (0: it runs its items)."""
+    return _check(lib().hkv_decode_plan_num_paths(plan))
 
 
 def hkv_decode_plan_has_wide_tiles(plan) -> bool:

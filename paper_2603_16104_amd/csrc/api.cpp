@@ -90,6 +90,11 @@ struct hkv_decode_plan {
     // that runs `items` (or in front of it on the caller's stream when concurrent is false).
     std::vector<DecodeItem> tile_items;
     int32_t tile_workgroups = 0;
+    // Small steps: whole paths instead of items, one launch (path_waves wavefronts per workgroup; 0: items)
+    std::vector<int32_t> paths;
+    int32_t path_stride = 0, n_paths = 0, path_waves = 0;
+    double paths_us = 0, items_us = 0;  // estimates of a step; paths_us = 0: paths are out of the question, items_us is not asked for
+    int32_t *d_paths = nullptr;
     bool row_visibility = false;  // several query tokens per request: rows see their last node in part
     bool concurrent = true;
     bool fused = false;  // both kinds of items go out as one launch (no item of `items` has more than 16 rows)
@@ -869,12 +874,13 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
         }
         return lay;
     };
-    // A plan's step in one form or the other, bf16 pools, us: three times that run beside each other (as a 3-norm), and the
+    // A plan's step in one form or the other, us: three times that run beside each other (as a 3-norm), and the
     // partials.  Latency: the workgroups, longest first, on the chip's slots; alone one takes 1.6 + 0.82 per 64 tokens as
     // 32-row tiles, 1.0 + 0.53 per 32 as 16-row tiles, 2.5 + 0.86 per 128 for few rows, and on a full chip 1.4 to 1.5 times that.
     // Issue, per compute unit: per 64 tokens of an item and per workgroup.  Memory: shared nodes at 5.5 TB/s, the others at 7.1
     // beside 16-row tiles (three workgroups per compute unit) and 6.5 beside 32-row tiles.  (Fitted to 1376 decode and
-    // verification plans, most of them random, timed in both forms; 8 % rms.)
+    // verification plans over bf16 pools, most of them random, timed in both forms; 8 % rms.  Small plans over fp8 pools, as
+    // plan_paths asks for them: 8 % more than measured in the mean, 12 % rms.)
     auto step_us = [&](const Layout &lay) {
         struct Items {
             int32_t tokens;  // of one
@@ -929,7 +935,7 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
         }
         span *= 1.0 + (lay.wide ? 0.40 : 0.54) * std::min(1.0, n_wgs / lay.slots);
         issue = (issue + (lay.wide ? 2.65 : 1.42) * n_wgs) / chip.n_cu;
-        const double stream = (unique / 5.5e6 + few_tokens / (lay.wide ? 6.5e6 : 7.07e6)) * 4 * HKV_HEAD_DIM * Hkv;
+        const double stream = (unique / 5.5e6 + few_tokens / (lay.wide ? 6.5e6 : 7.07e6)) * (fp8_pool ? 2 : 4) * HKV_HEAD_DIM * Hkv;
         return 7.5 + std::cbrt(span * span * span + issue * issue * issue + stream * stream * stream) + 0.16e-6 * 264 * 2 * (double)pl.n_req * pl.num_q_heads * parts;
     };
     // bf16 pools: shared::body where that estimate is 2 % shorter with it.  It takes two thirds as long for an item alone, but two
@@ -944,6 +950,7 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     if (either)
         if (const Layout wide = lay_out(true); step_us(wide) < 0.98 * step_us(lay)) lay = wide;
     pl.has_shared = lay.wide;
+    if (pl.paths_us > 0) pl.items_us = step_us(lay);
     const int shared_chunk = lay.shared_chunk, piece_tokens = lay.piece_tokens;
     const bool cut_leaves = lay.cut_leaves, cut_to_fill = lay.cut_to_fill;
     // The tile kernel's share of the chip: its persistent workgroups hold one compute unit each for as long as
@@ -1131,6 +1138,98 @@ static void plan_items(hkv_decode_plan &pl) {
     if (hkv_decode_plan_workspace_bytes(&pl) > kStaticWorkspaceBytes) plan_items(pl, true);
 }
 
+// Small steps.  The items' kernel and the merge are two launches, each a chain of dependent round trips (plan, blocks, K/V;
+// partials), 9 to 16 us however little there is to read.  Where the paths are short enough to be walked whole, a workgroup per
+// leaf (up to 16 of its rows) and KV head reads the path, shared nodes again for every leaf, and writes the result: one launch,
+// no partials.  What that takes, us: the launch and its chain, the steps of a wavefront, and the blocks a compute unit has to
+// take in, about 80 (bf16) resp. 60 (fp8) bytes per ns, more where the nodes are not in the L2 of every XCD that reads them.
+// (Coefficients and the margin from 1556 random plans of 16 to 3500 tokens per path and up to 3000 workgroups, timed in both
+// forms: 11 % rms; the mean of step over step with items is 0.729, the better form of each plan would give 0.721, 20 plans lose more
+// than 3 %, the worst 27 %.  Four requests over 256 + 32 + 17 tokens, bf16, 8 / 2 heads: 11.2 -> 6.6 us; 32 requests over 480 + 160
+// tokens, 32 / 8 heads: 17.3 -> 7.7; 64: 16.6 -> 13.3; 128: 22.5 as items, 23.7 this way.)
+// Eight wavefronts while every workgroup has a compute unit to itself, four where several share one (64 requests over 240 +
+// 80 tokens, fp8: 12.3 us with eight, 9.0 with four).
+// A caller that sets anything of the planner's, or asks for a form of the items, gets items; growing plans have theirs
+// changed on the device and keep them.  rows: the plan's rows by leaf (v's are rows[first[v]] .. rows[first[v + 1] - 1]).
+struct RowsByLeaf {
+    std::vector<int32_t> first, rows, blocks_to;  // blocks_to: blocks of the path that ends at a node
+};
+static void estimate_paths(hkv_decode_plan &pl, RowsByLeaf &by) {
+    const hkv_decode_plan_params &o = pl.opt;
+    if (pl.n_req == 0 || pl.fp8_matrix || pl.tile_form != 0 || pl.reserve_tokens > 0) return;
+    if (o.leaf_chunk || o.shared_chunk || o.max_rows || o.pack || o.pack_tokens || o.stages || o.interleave || o.tile_min_rows ||
+        o.tile_min_gflop || o.tile_workgroups || o.tile_chunk || o.large_batch_updates || o.fused)
+        return;
+    if (pl.pool->d.num_pages > (kPathIdMask + 1) / pl.pool->blocks_per_page) return;  // block ids share a word with a count
+    const int n_cu = chip_shape().n_cu, Hkv = pl.pool->d.num_kv_heads, per_path = std::max(1, 16 / pl.group);
+    const int64_t most_units = 12 * n_cu;
+    if ((int64_t)pl.n_req * Hkv > most_units * per_path) return;
+    const int n_nodes = (int)pl.nodes.size();
+    by.first.assign(n_nodes + 1, 0);
+    by.rows.resize(pl.n_req);
+    by.blocks_to.resize(n_nodes);
+    for (int r = 0; r < pl.n_req; ++r) ++by.first[pl.req_leaf[r] + 1];
+    int64_t longest = 0, paths = 0;
+    double block_sum = 0, unique = 0;  // blocks of all paths; K/V bytes of the forest, times the XCDs that read them
+    for (int v = 0; v < n_nodes; ++v) {
+        by.blocks_to[v] = pl.nodes[v].n_pages + (pl.nodes[v].parent >= 0 ? by.blocks_to[pl.nodes[v].parent] : 0);
+        if (pl.node_req_indptr[v + 1] > pl.node_req_indptr[v]) unique += pl.nodes[v].n_tokens;
+        const int n = by.first[v + 1];
+        by.first[v + 1] += by.first[v];
+        if (n == 0) continue;
+        longest = std::max<int64_t>(longest, by.blocks_to[v]);
+        paths += (n + per_path - 1) / per_path;
+        block_sum += (double)by.blocks_to[v] * ((n + per_path - 1) / per_path);
+    }
+    const int64_t units = paths * Hkv;
+    if (units > most_units || longest > 256) return;
+    std::vector<int32_t> at(by.first.begin(), by.first.end() - 1);
+    for (int r = 0; r < pl.n_req; ++r) by.rows[at[pl.req_leaf[r]]++] = r;
+    const bool fp8 = pl.pool->d.dtype == HKV_FP8_E4M3;
+    int xcds = 8;  // a KV head's workgroups lie Hkv apart
+    for (int h = Hkv; h % 2 == 0 && xcds > 1; h /= 2) xcds /= 2;
+    unique *= 2.0 * HKV_HEAD_DIM * Hkv * (fp8 ? 1 : 2) * xcds;
+    const int waves = units <= n_cu ? 8 : 4;
+    const double per_cu = (double)units / n_cu, most = longest * 16e-3, mean = block_sum / paths * 16e-3;  // in 1000 tokens
+    const double steps = std::ceil(longest * 16.0 / ((fp8 ? 64 : 32) * waves)), beside = std::max(0.0, per_cu * mean - most);
+    pl.paths_us = fp8 ? 5.3 + 3.8 * most + 5.2 * beside + 0.47 * per_cu + 0.026e-6 * unique + 0.42 * steps
+                      : 4.5 + 2.9 * most + 7.5 * beside + 0.23 * per_cu + 0.030e-6 * unique + 0.68 * steps;
+    pl.n_paths = (int32_t)paths;
+    pl.path_waves = waves;
+    pl.path_stride = (int32_t)((kPathBlocks + std::max<int64_t>(longest, 1) + 15) / 16 * 16);
+}
+
+// Behind plan_items: paths or items, and the paths' records.
+static void plan_paths(hkv_decode_plan &pl, const RowsByLeaf &by) {
+    if (pl.paths_us == 0 || !pl.tile_items.empty() || pl.paths_us > 0.85 * pl.items_us) {
+        pl.n_paths = pl.path_waves = 0;
+        return;
+    }
+    const int per_path = std::max(1, 16 / pl.group);
+    pl.paths.assign((size_t)pl.path_stride * pl.n_paths, 0);
+    int32_t *rec = pl.paths.data();
+    for (int v = 0; v < (int)pl.nodes.size(); ++v)
+        for (int r0 = by.first[v]; r0 < by.first[v + 1]; r0 += per_path, rec += pl.path_stride) {
+            const int n = std::min(per_path, by.first[v + 1] - r0);
+            rec[0] = by.blocks_to[v];
+            rec[1] = n;
+            rec[2] = (by.blocks_to[v] - pl.nodes[v].n_pages) * HKV_PAGE_SIZE;
+            for (int i = 0; i < 16; ++i) {
+                const int32_t row = by.rows[r0 + std::min(i, n - 1)];
+                rec[kPathRows + i] = row;
+                rec[kPathQRows + i] = pl.q_rows.empty() ? row : pl.q_rows[row];
+            }
+            int32_t *end = rec + kPathBlocks + by.blocks_to[v];
+            for (int u = v; u >= 0; u = pl.nodes[u].parent) {
+                const hkv_node &nd = pl.nodes[u];
+                for (int b = nd.n_pages - 1; b >= 0; --b) {
+                    const int tokens = std::min(HKV_PAGE_SIZE, nd.n_tokens - b * HKV_PAGE_SIZE);
+                    *--end = (int32_t)((uint32_t)pl.node_pages[nd.page_begin + b] | (uint32_t)(HKV_PAGE_SIZE - tokens) << kPathIdBits);
+                }
+            }
+        }
+}
+
 // Whether runs queue the two kinds of items side by side, on the caller's stream and on the plan's own.
 static bool forks(const hkv_decode_plan &pl) { return !pl.tile_items.empty() && !pl.items.empty() && pl.concurrent && !pl.fused; }
 
@@ -1141,7 +1240,8 @@ static int upload_decode_plan(hkv_decode_plan &pl) {
     size_t off_cnt = align_up(off_nri + sizeof(int32_t) * pl.node_req_idx.size(), 256);
     size_t off_tiles = align_up(off_cnt + sizeof(int32_t) * pl.part_count.size(), 256);
     size_t off_qrows = align_up(off_tiles + sizeof(DecodeItem) * pl.tile_items.size(), 256);
-    size_t total = align_up(off_qrows + sizeof(int32_t) * pl.q_rows.size(), 256) + 256;
+    size_t off_paths = align_up(off_qrows + sizeof(int32_t) * pl.q_rows.size(), 256);
+    size_t total = align_up(off_paths + sizeof(int32_t) * pl.paths.size(), 256) + 256;
     HKV_HIP(hipMalloc(&pl.dev, total));
     char *base = static_cast<char *>(pl.dev);
     pl.d_items = reinterpret_cast<DecodeItem *>(base + off_items);
@@ -1149,6 +1249,7 @@ static int upload_decode_plan(hkv_decode_plan &pl) {
     pl.d_node_req_idx = reinterpret_cast<int32_t *>(base + off_nri);
     pl.d_part_count = reinterpret_cast<int32_t *>(base + off_cnt);
     pl.d_tile_items = reinterpret_cast<DecodeItem *>(base + off_tiles);
+    pl.d_paths = reinterpret_cast<int32_t *>(base + off_paths);
     pl.d_q_rows = pl.q_rows.empty() ? nullptr : reinterpret_cast<int32_t *>(base + off_qrows);
     // one host image, one copy
     std::vector<char> image(total, 0);
@@ -1161,6 +1262,7 @@ static int upload_decode_plan(hkv_decode_plan &pl) {
     put(off_cnt, pl.part_count.data(), sizeof(int32_t) * pl.part_count.size());
     put(off_tiles, pl.tile_items.data(), sizeof(DecodeItem) * pl.tile_items.size());
     put(off_qrows, pl.q_rows.data(), sizeof(int32_t) * pl.q_rows.size());
+    put(off_paths, pl.paths.data(), sizeof(int32_t) * pl.paths.size());
     HKV_HIP(hipMemcpy(pl.dev, image.data(), total, hipMemcpyHostToDevice));
     if (pl.reserve_tokens > 0 && pl.n_req <= kMaxInlineAppend && !pl.grow_items.empty() && !pl.opt.large_batch_updates) {
         HKV_HIP(hipMalloc((void **)&pl.d_grow_items, sizeof(int32_t) * pl.grow_items.size()));
@@ -1326,7 +1428,10 @@ static int create_decode_plan(hkv_pool *pool, const hkv_node *nodes, int32_t n_n
         *out = pl;
         return HKV_OK;
     }
+    RowsByLeaf by_leaf;
+    estimate_paths(*pl, by_leaf);
     plan_items(*pl);
+    plan_paths(*pl, by_leaf);
     if (reserve_tokens > 0) {  // the items that grow with each request: the leaf's last chunk, one per KV head
         pl->grow_items.assign((size_t)n_req * Hkv, -1);
         for (int r = 0; r < n_req; ++r) {
@@ -1662,6 +1767,9 @@ extern "C" int32_t hkv_decode_plan_has_stream(const hkv_decode_plan *plan) {
 extern "C" int32_t hkv_decode_plan_has_wide_tiles(const hkv_decode_plan *plan) {
     return plan ? (plan->has_shared && !plan->fp8_matrix ? 1 : 0) : fail(HKV_EINVAL, "null plan");
 }
+extern "C" int32_t hkv_decode_plan_num_paths(const hkv_decode_plan *plan) {
+    return plan ? plan->n_paths : fail(HKV_EINVAL, "null plan");
+}
 extern "C" int32_t hkv_decode_plan_tile_workgroups(const hkv_decode_plan *plan) {
     return plan ? plan->tile_workgroups : fail(HKV_EINVAL, "null plan");
 }
@@ -1723,6 +1831,22 @@ static int run_decode_plan(hkv_decode_plan *plan, const void *q, float scale, vo
                          down_parts, (int32_t)plan->items.size(), plan->num_q_heads, plan->max_parts, scale,
                          plan->d_row_leaf, plan->d_row_limit, plan->d_row_mask, plan->n_single, plan->n_stages,
                          plan->fp8_matrix ? 1 : 0, plan->d_q_rows, plan->has_shared ? 1 : 0};
+    if (plan->path_waves) {
+        DecodePathLaunch p{};
+        static_cast<DecodeLaunch &>(p) = a;
+        p.paths = plan->d_paths;
+        p.path_stride = plan->path_stride;
+        p.n_paths = plan->n_paths;
+        p.out = out;
+        p.lse_out = lse_out;
+        HKV_HIP(launch_decode_paths(p, plan->path_waves, s, prof ? plan->ev[0] : nullptr, prof ? plan->ev[1] : nullptr));
+        if (prof) {
+            HKV_HIP(hipEventRecord(plan->ev[2], s));
+            HKV_HIP(hipEventRecord(plan->ev[3], s));
+            plan->profiled_run = true;
+        }
+        return HKV_OK;
+    }
     if (plan->fused) {
         HKV_HIP(launch_decode_fused(a, t, s, prof ? plan->ev[0] : nullptr, prof ? plan->ev[1] : nullptr));
     } else if (tiles) {

@@ -25,6 +25,18 @@ __global__ __launch_bounds__(rows::kThreads, SHARED || DT != 0 ? 2 : 3) void dec
     rows::body<DT, false, SHARED>(a, smem, (int)blockIdx.x, (int)threadIdx.x);
 }
 
+// Small steps: a workgroup per (path record, KV head), nothing behind it.  Bound by its chain of round trips (record; blocks'
+// K, V and the queries; 5.3 us with the launch) and, from about 500 tokens on, by what one compute unit takes in from L2:
+// 1920 + 640 tokens, one request of 8 x 4 heads, bf16, 17 us = 110 bytes per ns.  So the plan keeps it to short paths.  A record
+// holds everything the chain needs at a fixed place, so that its head, its blocks and the rows travel in one round
+// trip.  (A second set of operand registers, two steps in flight: 640 tokens 7.7 -> 8.7 us.)  16 requests x 8 heads over 480 +
+// 160 tokens, bf16: 16.2 us as items and merge, 7.4 us.
+template <int DT, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 3 : 2) void decode_path_kernel(DecodePathLaunch a) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];  // rows::combine_bytes(WAVES)
+    rows::body<DT, false, false, WAVES>(a, smem, (int)blockIdx.x, (int)threadIdx.x);
+}
+
 // Workgroups [0, n_tile_wgs) are the persistent workgroups of the tile items (all 512 threads); each
 // workgroup behind them runs two blocks of the other items, one per half.  Dispatch follows the workgroup
 // index, so the tile workgroups, which need a whole compute unit each, are placed first.
@@ -76,6 +88,10 @@ static hipError_t setup_device(DeviceSetup &st) {
             return e;
     const void *fused[2] = {reinterpret_cast<const void *>(decode_fused_kernel<false>),
                             reinterpret_cast<const void *>(decode_fused_kernel<true>)};
+    const void *paths[2] = {reinterpret_cast<const void *>(decode_path_kernel<0, 8>), reinterpret_cast<const void *>(decode_path_kernel<1, 8>)};
+    for (const void *fn : paths)
+        if (hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, rows::combine_bytes(8)); e != hipSuccess)
+            return e;
     for (const void *fn : fused)
         if (hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kFusedLds); e != hipSuccess)
             return e;
@@ -109,6 +125,19 @@ hipError_t launch_decode(const DecodeLaunch &a, hipStream_t s, hipEvent_t ev_beg
         a.has_shared ? go(decode_node_kernel<0, true>) : go(decode_node_kernel<0, false>);
     else
         a.has_shared ? go(decode_node_kernel<1, true>) : go(decode_node_kernel<1, false>);
+    return hipGetLastError();
+}
+
+hipError_t launch_decode_paths(const DecodePathLaunch &a, int waves, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end) {
+    if (a.n_paths <= 0) return hipSuccess;
+    if ((waves != 4 && waves != 8) || (a.pool.dtype != 0 && a.pool.dtype != 1) || a.fp8_matrix) return hipErrorInvalidValue;
+    if (hipError_t e = prepare_decode_device(nullptr); e != hipSuccess) return e;
+    const dim3 grid((unsigned)a.n_paths * (unsigned)a.pool.num_kv_heads), block(64 * waves);
+    auto go = [&](auto kernel) { hipExtLaunchKernelGGL(kernel, grid, block, (unsigned)rows::combine_bytes(waves), s, ev_begin, ev_end, 0, a); };
+    if (a.pool.dtype == 0)
+        waves == 4 ? go(decode_path_kernel<0, 4>) : go(decode_path_kernel<0, 8>);
+    else
+        waves == 4 ? go(decode_path_kernel<1, 4>) : go(decode_path_kernel<1, 8>);
     return hipGetLastError();
 }
 

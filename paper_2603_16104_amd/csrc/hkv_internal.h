@@ -98,6 +98,19 @@ struct DecodeLaunch {
     const int32_t *q_rows;
     int32_t has_shared;          // items shared by more than 16 query rows are run by shared::body
 };
+// Whole paths instead of items (of the base, what describes items is not read): a record of path_stride ints per leaf and up
+// to 16 / G of its rows, run by a workgroup per KV head, which writes out / lse_out (may be null) itself.
+struct DecodePathLaunch : DecodeLaunch {
+    const int32_t *paths;        // device
+    int32_t path_stride;
+    int32_t n_paths;
+    void *out;
+    float *lse_out;
+};
+// A path's record: {blocks, rows, position of the leaf's first token, 0}, the rows of the plan (16 slots), their rows of q /
+// out, then the path's blocks as id | (16 - tokens in the block) << kPathIdBits.
+constexpr int kPathRows = 4, kPathQRows = 20, kPathBlocks = 36;
+constexpr int kPathIdBits = 27, kPathIdMask = (1 << kPathIdBits) - 1;
 
 struct PrefillLaunch {
     PoolView pool;
@@ -246,6 +259,8 @@ hipError_t launch_pool_dequant(const PoolDequantLaunch &a, hipStream_t s);
 constexpr size_t kStaticWorkspaceBytes = (size_t)32 << 20;
 hipError_t prepare_decode_device(void **static_ws);
 hipError_t launch_decode(const DecodeLaunch &a, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
+// waves: 4 or 8 wavefronts per workgroup
+hipError_t launch_decode_paths(const DecodePathLaunch &a, int waves, hipStream_t s, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
 hipError_t launch_rows_fp32(const RowsLaunch &a, hipStream_t s);
 hipError_t launch_pool_write_fp32(const PoolWriteLaunch &a, hipStream_t s);
 hipError_t launch_prefill(const PrefillLaunch &a, hipStream_t s);

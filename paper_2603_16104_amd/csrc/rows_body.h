@@ -111,6 +111,7 @@ template <int DT>
 struct StepPages {
     static constexpr int N = Traits<DT>::kTokBlock / kPage;
     int id[N];
+    int valid[N];  // whole paths: tokens the page holds (0 behind the last page)
     float ksc[N], vsc[N];
 };
 
@@ -123,6 +124,22 @@ __device__ __forceinline__ void load_step_pages(StepPages<DT> &sp, const DecodeL
         if constexpr (DT != 0) {
             sp.ksc[i] = a.pool.k_scale[(size_t)sp.id[i] * a.pool.num_kv_heads + it.kv_head];
             sp.vsc[i] = a.pool.v_scale[(size_t)sp.id[i] * a.pool.num_kv_heads + it.kv_head];
+        }
+    }
+}
+
+// The same of a whole path, whose blocks carry how many of their tokens count.
+template <int DT>
+__device__ __forceinline__ void load_path_pages(StepPages<DT> &sp, const DecodeLaunch &a, const int32_t *ids, int kv_head, int blk, int last_page) {
+#pragma unroll
+    for (int i = 0; i < StepPages<DT>::N; ++i) {
+        const int pg = blk * StepPages<DT>::N + i;
+        const int e = ids[min(pg, last_page)];
+        sp.id[i] = e & kPathIdMask;
+        sp.valid[i] = pg <= last_page ? kPage - (int)((uint32_t)e >> kPathIdBits) : 0;
+        if constexpr (DT != 0) {
+            sp.ksc[i] = a.pool.k_scale[(size_t)sp.id[i] * a.pool.num_kv_heads + kv_head];
+            sp.vsc[i] = a.pool.v_scale[(size_t)sp.id[i] * a.pool.num_kv_heads + kv_head];
         }
     }
 }
@@ -146,16 +163,21 @@ __device__ __forceinline__ T pick(const T (&v)[4], int sel) {
 // FUSED: the 256 threads are one half of a 512-thread workgroup whose other half runs another block (or
 // none: vblock beyond the grid); every half executes exactly one workgroup barrier, so the launch must hold
 // no item shared by more than 16 query rows (those synchronise once per step).
-constexpr int kCombineBytes = (int)sizeof(float) * (kWaves * 16 * kORow + 2 * kWaves * 16 + 16);
+// PATH (0: off): the workgroup has that many wavefronts and walks the whole root-to-leaf path of up to 16 query rows
+// of one leaf: nothing is shared with other leaves, no partials, the results go out from here (decode_path_kernel).  vblock
+// is path * KV heads + head.
+constexpr int combine_bytes(int waves) { return (int)sizeof(float) * (waves * 16 * kORow + 2 * waves * 16 + 16); }
+constexpr int kCombineBytes = combine_bytes(kWaves);
 
-template <int DT, bool FUSED, bool SHARED>
-__device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblock, int tid) {
+template <int DT, bool FUSED, bool SHARED, int PATH = 0>
+__device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodePathLaunch, DecodeLaunch> &a, char *smem, int vblock, int tid) {
     // LDS: a ring of a.n_stages K/V stages for items shared by many query rows; items with at most 16
     // rows use the same bytes for the cross-wavefront combine instead.
     float(*sO)[16][kORow] = reinterpret_cast<float(*)[16][kORow]>(smem);
-    float(*sM)[16] = reinterpret_cast<float(*)[16]>(smem + sizeof(float) * kWaves * 16 * kORow);
-    float(*sL)[16] = sM + kWaves;
-    int *sPart = reinterpret_cast<int *>(sL + kWaves);  // partial index of each of the 16 rows
+    constexpr int W = PATH ? PATH : kWaves;
+    float(*sM)[16] = reinterpret_cast<float(*)[16]>(smem + sizeof(float) * W * 16 * kORow);
+    float(*sL)[16] = sM + W;
+    int *sPart = reinterpret_cast<int *>(sL + W);  // partial index (whole paths: output row) of each of the 16 rows
     static_assert(kCombineBytes <= kMinStages * kStageBytes, "LDS overlay");
 
     constexpr int TB = Traits<DT>::kTokBlock;
@@ -167,15 +189,22 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
     // Blocks [0, n_single) run one item each.  The blocks behind them run four short items
     // of at most 16 rows each, one per wavefront (no LDS, no barrier: the wavefronts are independent),
     // so that a forest of many short nodes does not pay a workgroup's start-up per 64 tokens.
-    const bool packed = vblock >= a.n_single;
+    const bool packed = !PATH && vblock >= a.n_single;
     const int item_idx = packed ? a.n_single + kWaves * (vblock - a.n_single) + wave : vblock;
-    if (item_idx >= a.n_items) {  // wavefront-uniform (FUSED: also the half without a block)
+    if (!PATH && item_idx >= a.n_items) {  // wavefront-uniform (FUSED: also the half without a block)
         if constexpr (FUSED) __syncthreads();
         return;
     }
-    const DecodeItem it = a.items[item_idx];
     const int m = lane & 15, g = lane >> 4;
     const int Hkv = a.pool.num_kv_heads;
+    const int32_t *path = nullptr;  // PATH: {blocks, rows' requests, leaf's first token, -, 16 rows of the plan, 16 rows of q, blocks ...}
+    DecodeItem it;
+    if constexpr (PATH != 0) {
+        path = a.paths + (size_t)(vblock / Hkv) * a.path_stride;
+        it = DecodeItem{0, path[0] * kPage, vblock % Hkv, 0, path[1], 0, 0, 0};
+    } else {
+        it = a.items[item_idx];
+    }
     const int G = a.num_q_heads / Hkv;
     const int rows = it.n_req * G;
     // Up to 16 rows: the four wavefronts split the tokens and read K/V straight into registers.
@@ -187,10 +216,10 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
             return;
         }
     }
-    constexpr bool kOwnTiles = !FUSED && (DT == 2 || (DT == 0 && !SHARED));
+    constexpr bool kOwnTiles = !FUSED && !PATH && (DT == 2 || (DT == 0 && !SHARED));
     const bool shared = kOwnTiles && !packed && rows > 16;
-    const int n_rt = shared ? kWaves : 1;
-    const int n_ts = packed ? 1 : kWaves / n_rt;
+    const int n_rt = shared ? W : 1;
+    const int n_ts = packed ? 1 : W / n_rt;
     const int rt = packed ? 0 : wave % n_rt, ts = packed ? 0 : wave / n_rt;
     const float c = a.scale * kLog2e;
 
@@ -198,14 +227,19 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
     // unconditional (row clamped) so that they can stay in flight next to the first K/V requests.
     const int row = rt * 16 + m;
     const int rowc = min(row, rows - 1);
+    int path_q_row = 0;
     auto load_req = [&]() {
+        if constexpr (PATH != 0) {
+            path_q_row = path[kPathQRows + rowc / G];
+            return (int)path[kPathRows + rowc / G];
+        }
         int req = a.node_req_idx[it.req_off];  // wavefront-uniform: scalar load
         if (it.n_req > 1) req = a.node_req_idx[it.req_off + rowc / G];
         return req;
     };
     auto load_q = [&](bf16x8 (&qf)[4], int req) {
         const int head = it.kv_head * G + rowc % G;
-        const int q_row = a.q_rows ? a.q_rows[req] : req;
+        const int q_row = PATH ? path_q_row : a.q_rows ? a.q_rows[req] : req;
         const char *qp = static_cast<const char *>(a.q) + ((size_t)q_row * a.num_q_heads + head) * (kHeadDim * 2);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -252,7 +286,12 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
     int lim = it.n_tokens;
     unsigned long long vis = 0;  // visibility of the tokens from lim on, one bit each
     auto load_limit = [&](int req) {
-        if (a.row_leaf && a.row_leaf[req] == it.node) {
+        if constexpr (PATH != 0) {  // (positions count whole blocks: the leaf begins at one)
+            if (a.row_limit) {
+                lim = path[2] + a.row_limit[req];
+                vis = a.row_mask[req];
+            }
+        } else if (a.row_leaf && a.row_leaf[req] == it.node) {
             lim = a.row_limit[req] - it.tok_begin;
             vis = a.row_mask[req];
         }
@@ -306,6 +345,7 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
     // One step over TB tokens.  LAST: the item's last step, the only one that may reach past the item's
     // end (every other instance carries no end-of-item masking at all).  MORE: another step follows, so its K and V are requested as soon as
     // the registers are free; the last step (and only it) may reach past the item's end.
+    // PATH: any step may hold blocks that are not full, the last ones of the path's nodes.
     auto step = [&](auto more_tag, auto last_tag, int b, const StepPages<DT> &cur, const StepPages<DT> &nxt) {
         constexpr bool MORE = decltype(more_tag)::value;
         constexpr bool LAST = decltype(last_tag)::value;
@@ -364,8 +404,14 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
 
         // ---- online softmax; lane-local score j belongs to token tok0 + j of the item
         const int tok0 = b * TB + g * NS;
-        const bool tail = LAST && b * TB + TB > it.n_tokens;  // step reaches past the item's end
-        const int first_bad = it.n_tokens - tok0;               // lane-local index of the first invalid token
+        bool tail = LAST && b * TB + TB > it.n_tokens;  // step reaches past the item's end
+        int first_bad = it.n_tokens - tok0;               // lane-local index of the first invalid token
+        if constexpr (PATH != 0) {
+            tail = false;
+#pragma unroll
+            for (int i = 0; i < StepPages<DT>::N; ++i) tail = tail || cur.valid[i] < kPage;
+            first_bad = pick(cur.valid, v_sel) - (DT == 0 ? 8 * (g & 1) : 0);
+        }
         if (tail) {
 #pragma unroll
             for (int j = 0; j < NS; ++j)
@@ -614,21 +660,27 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
 
     int b = ts;
     int req = 0;
+    auto load_pages = [&](StepPages<DT> &sp, int blk) {
+        if constexpr (PATH != 0)
+            load_path_pages<DT>(sp, a, path + kPathBlocks, it.kv_head, blk, last_page);
+        else
+            load_step_pages<DT>(sp, a, it, blk, last_page);
+    };
     if (b < n_blk) {
         StepPages<DT> cur, nxt;
-        load_step_pages<DT>(cur, a, it, b, last_page);
+        load_pages(cur, b);
         req = load_req();  // requested before K/V so that waiting for it does not wait for them
         issue_k(cur);
         issue_v(cur);
         load_q(qf, req);
         load_limit(req);
-        load_step_pages<DT>(nxt, a, it, b + n_ts, last_page);  // clamped: always in bounds
+        load_pages(nxt, b + n_ts);  // clamped: always in bounds
         split_q();
         while (b + n_ts < n_blk) {
             step(std::true_type{}, std::false_type{}, b, cur, nxt);
             b += n_ts;
             cur = nxt;
-            load_step_pages<DT>(nxt, a, it, b + n_ts, last_page);
+            load_pages(nxt, b + n_ts);
         }
         step(std::false_type{}, std::true_type{}, b, cur, nxt);
     }
@@ -651,20 +703,24 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
         sM[wave][m] = m_run;
         sL[wave][m] = l_row;
         // wavefront 0 always has a step (the item holds at least one token), so its req is loaded
-        if (wave == 0 && row < rows) sPart[m] = (req * a.num_q_heads + it.kv_head * G + row % G) * a.max_parts + it.part_slot;
+        if constexpr (PATH != 0) {  // (a path without tokens has not loaded it)
+            if (wave == 0 && row < rows) sPart[m] = path[kPathQRows + row / G] * a.num_q_heads + it.kv_head * G + row % G;
+        } else if (wave == 0 && row < rows)
+            sPart[m] = (req * a.num_q_heads + it.kv_head * G + row % G) * a.max_parts + it.part_slot;
     }
     __syncthreads();
     // a row's 64 pairs of neighbouring dims are one wavefront's 64 lanes: wavefront w takes rows w, w + 4, ...
-    for (int row = wave; row < rows; row += kWaves) {
+    for (int row = wave; row < rows; row += W) {
         const int d = lane * 2;
         const int r_t = row >> 4, r_c = row & 15;
         float M = -INFINITY;
         for (int t = 0; t < n_ts; ++t) M = fmaxf(M, sM[t * n_rt + r_t][r_c]);
         float L = 0.f, acc0 = 0.f, acc1 = 0.f;
-        if (M != -INFINITY) {
+        if (M != -INFINITY || PATH) {
             for (int t = 0; t < n_ts; ++t) {
                 const int w = t * n_rt + r_t;
                 const float mw = sM[w][r_c];
+                if (PATH && mw == -INFINITY) L += sL[w][r_c];  // (0, or NaN where its scores hold one)
                 if (mw == -INFINITY) continue;  // that wavefront's tokens were all invisible to the row
                 const float wgt = fast_exp2((mw - M) * c);
                 L += sL[w][r_c] * wgt;
@@ -677,6 +733,14 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, char *smem, int vblo
         const float inv = L > 0.f ? 1.0f / L : 0.f;
         acc0 *= inv;
         acc1 *= inv;
+        if constexpr (PATH != 0) {  // a row whose scores hold a NaN or +inf gives NaN
+            const float bad = L >= 0.f ? 0.f : __builtin_nanf("");
+            acc0 += bad;
+            acc1 += bad;
+            *reinterpret_cast<uint32_t *>(static_cast<uint16_t *>(a.out) + part * kHeadDim + d) = pack_bf16(acc0, acc1);
+            if (a.lse_out && lane == 0) a.lse_out[part] = L != 0.f ? (M * c + fast_log2(L)) * kLn2 : -INFINITY;
+            continue;
+        }
         float amax = fmaxf(fabsf(acc0), fabsf(acc1));
 #pragma unroll
         for (int sh = 1; sh < 64; sh <<= 1) amax = fmaxf(amax, __shfl_xor(amax, sh));

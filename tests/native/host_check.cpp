@@ -23,6 +23,7 @@ hipError_t launch_plan_grow_inline(const PlanGrowInline &, hipStream_t) { return
 hipError_t launch_decode_step_append(const PoolAppendInline &, const PlanGrowInline &, hipStream_t) { return hipSuccess; }
 hipError_t launch_pool_dequant(const PoolDequantLaunch &, hipStream_t) { return hipSuccess; }
 hipError_t launch_decode(const DecodeLaunch &, hipStream_t, hipEvent_t, hipEvent_t) { return hipSuccess; }
+hipError_t launch_decode_paths(const DecodePathLaunch &, int, hipStream_t, hipEvent_t, hipEvent_t) { return hipSuccess; }
 hipError_t prepare_decode_device(void **ws) {
     if (ws) *ws = nullptr;
     return hipSuccess;

@@ -720,6 +720,28 @@ def test_few_long_nodes_are_cut_in_both_forms(flags):
     assert items[:, 1].max() <= 1104
 
 
+@pytest.mark.parametrize("dtype, tokens, n_req, heads, params, paths", [
+    (hkv.BF16, (240, 80), 16, (32, 8), {}, True), (hkv.FP8_E4M3, (240, 80), 64, (32, 8), {}, True),
+    (hkv.BF16, (2000, 600), 64, (32, 8), {}, False), (hkv.FP8_E4M3, (240, 80), 512, (32, 8), {}, False),  # shared nodes read too often
+    (hkv.BF16, (2000, 600), 1, (8, 2), {}, False),                                                        # more than a few workgroups stream in time
+    (hkv.BF16, (240, 80), 16, (32, 8), {"interleave": 8}, False), (hkv.BF16, (240, 80), 16, (32, 8), {"reserve_tokens": 4}, False),
+    (hkv.BF16, (240, 80), 16, (32, 8), {"flags": hkv.PLAN_NARROW_TILES}, False), (hkv.FP8_E4M3, (240, 80), 16, (32, 8), {"flags": hkv.PLAN_FP8_MATRIX}, False),
+    (hkv.BF16, (240, 80), 4, (8, 2), {"tokens_per_req": 8}, True),
+])
+def test_plans_that_run_whole_paths(dtype, tokens, n_req, heads, params, paths):
+    parent, ntok = [-1] + [0] * n_req, [tokens[0]] + [tokens[1]] * n_req
+    n_used = sum((t + 15) // 16 for t in ntok)
+    f = wl.make_forest(parent, ntok, list(range(1, n_req + 1)), np.arange(n_used, dtype=np.int32))
+    pool = fake_pool(n_used, heads[1], dtype)
+    params = dict(params)
+    plan = hkv.hkv_decode_plan_create_ex(pool, f.nodes, f.node_pages, f.req_leaf, heads[0], hkv.PLAN_HOST_ONLY | params.pop("flags", 0), **params)
+    T, per_path = params.get("tokens_per_req", 1), 16 // (heads[0] // heads[1])
+    assert hkv.hkv_decode_plan_num_paths(plan) == (n_req * -(-T // per_path) if paths else 0)
+    assert len(hkv.hkv_decode_plan_items(plan)) > 0 and hkv.hkv_decode_plan_workspace_bytes(plan) > 0     # of either form
+    hkv.hkv_decode_plan_destroy(plan)
+    hkv.kv_pool_destroy(pool)
+
+
 def test_merge_argument_validation():
     with pytest.raises(hkv.HkvError) as e:
         hkv.lse_merge(0x1000, 0x2000, 0x3000, 0x4000, 4, 0x5000, 7, stream=0)
