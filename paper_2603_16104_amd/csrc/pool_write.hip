@@ -10,6 +10,7 @@
 // copies (copy-on-write), the fp8 -> bf16 pre-pass of prefill over fp8 pools, the copy kernel that
 // replaces small host-to-device DMA copies, and the in-place update of a growing decode plan.
 #include <algorithm>
+#include <type_traits>
 
 #include "hkv_device.h"
 
@@ -52,13 +53,12 @@ __device__ __forceinline__ uint32_t quant4_by(float a, float b, float c, float d
 // One workgroup's work.  single: one token per block (source row pi goes to slot one_slot of block
 // `page`) instead of a run of tokens over consecutive blocks.
 template <int DT>
-__device__ __forceinline__ void pool_write_block(const PoolWriteLaunch &a, const int page, const bool single,
+__device__ __forceinline__ void pool_write_block(const PoolWriteLaunch &a, const int pi, const int page, const int h, const bool single,
                                                  const int one_slot) {
     __shared__ uint16_t sV[kPage][kHeadDim + 8];
     __shared__ float sRed[2][4];
     __shared__ float sScale[2], sOld[2], sInv[2];
 
-    const int pi = blockIdx.x, h = blockIdx.y;
     const int tid = threadIdx.x;
     const int slot = tid >> 4, d0 = (tid & 15) * 8;
     const int tok = single ? pi : pi * kPage + slot - a.first_slot;  // source row of this thread's slot
@@ -193,24 +193,108 @@ __device__ __forceinline__ void pool_write_block(const PoolWriteLaunch &a, const
     }
 }
 
+// K (v = false) or V of one block of an fp8 pool that the call writes whole, by one wavefront, without LDS or barriers: lane
+// (row q of 16, column c) holds tokens 4 q .. 4 q + 3 of dims 8 c .. 8 c + 7, so that V's four codes of a dim make a word
+// of one lane and its dimension-major order is a transposition of words between the four rows, in the vector ALU.  Bound by the
+// chain load, maximum, quotients, store of one wavefront (up to about 4000 tokens x 8 heads a launch has all of them on the chip at
+// once): 4000 tokens 6.2 -> 5.2 us, 8192 tokens 11.1 -> 9.1 us against the general form, which passes V through LDS and the
+// maxima over two barriers.  (bf16 pools have neither maxima nor codes: the same form took 5.9 instead of 5.4 us there.)
+__device__ __forceinline__ void transpose_rows(uint32_t (&x)[4]) {  // word d of row q <-> word q of row d
+    const auto a = __builtin_amdgcn_permlane32_swap(x[0], x[2], false, false), b = __builtin_amdgcn_permlane32_swap(x[1], x[3], false, false);
+    const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false), d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+    x[0] = c[0];
+    x[1] = c[1];
+    x[2] = d[0];
+    x[3] = d[1];
+}
+__device__ __forceinline__ void write_whole_fp8_block(const PoolWriteLaunch &a, const int pi, const int page, const int h, const bool v) {
+    const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+    const size_t blk = ((size_t)page * a.num_kv_heads + h) * kBlockElems;
+    const char *src = static_cast<const char *>(v ? a.v_src : a.k_src) +
+                      (((size_t)(pi * kPage + 4 * q - a.first_slot) * a.num_kv_heads + h) * kHeadDim + 8 * c) * 2;
+    u32x4 w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = ld16(src + (size_t)i * a.num_kv_heads * kHeadDim * 2);
+    float x[4][8];
+    float am = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            x[i][2 * j] = __uint_as_float(w[i][j] << 16);
+            x[i][2 * j + 1] = __uint_as_float(w[i][j] & 0xFFFF0000u);
+            am = fmaxf(am, fabsf(x[i][2 * j]));
+            am = fmaxf(am, fabsf(x[i][2 * j + 1]));
+        }
+    am = wave_max(am);
+    const float sc = am > 0.f ? am / 448.0f : 1.0f;
+    const float inv = sc >= 0x1p-60f && sc <= 0x1p60f ? 1.0f / sc : 0.f;  // 0: divide
+    if (lane == 0) (v ? a.v_scale : a.k_scale)[(size_t)page * a.num_kv_heads + h] = sc;
+    auto encode = [&](float x0, float x1, float x2, float x3) {
+        return inv != 0.f ? quant4_by(x0, x1, x2, x3, sc, inv) : quant4(x0, x1, x2, x3, sc);  // the same for the whole wavefront
+    };
+    if (!v) {
+        uint8_t *dst = static_cast<uint8_t *>(a.k_pages) + blk + (c >> 3) * (kPage * 64) + 4 * q * 64 + (c & 7) * 8;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<u32x2 *>(dst + 64 * i) = u32x2{encode(x[i][0], x[i][1], x[i][2], x[i][3]), encode(x[i][4], x[i][5], x[i][6], x[i][7])};
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        uint32_t t[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) t[j] = encode(x[0][4 * e + j], x[1][4 * e + j], x[2][4 * e + j], x[3][4 * e + j]);
+        transpose_rows(t);
+        *reinterpret_cast<u32x4 *>(static_cast<uint8_t *>(a.v_pages) + blk + (8 * c + 4 * e + q) * kPage) = u32x4{t[0], t[1], t[2], t[3]};
+    }
+}
+
+// A run of tokens.  bf16 pools: workgroup (block, head).  fp8 pools: workgroup (block, pair of heads), wavefront w takes K (w even)
+// or V (w odd) of head w / 2 of the pair; a block that the call writes in part, its first or its last one, goes the general way,
+// the pair's second head by the workgroup in row n_pages + (whether it is the second such block) of the grid.
+__device__ __forceinline__ bool writes_whole(const PoolWriteLaunch &a, const int pi) {
+    return pi * kPage >= a.first_slot && a.first_slot + a.n_tokens >= (pi + 1) * kPage;
+}
+template <int DT>
+__device__ __forceinline__ void pool_write_run(const PoolWriteLaunch &a, const int32_t *ids) {
+    if constexpr (DT == 0) {
+        pool_write_block<0>(a, blockIdx.x, ids[blockIdx.x], blockIdx.y, false, 0);
+        return;
+    }
+    const int x = blockIdx.x;
+    const bool extra = x >= a.n_pages;
+    const int pi = !extra ? x : (x == a.n_pages && !writes_whole(a, 0)) ? 0 : a.n_pages - 1;
+    const int page = ids[pi], h0 = 2 * blockIdx.y;
+    if (!extra && writes_whole(a, pi)) {
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), h = h0 + (wave >> 1);
+        if (h < a.num_kv_heads) write_whole_fp8_block(a, pi, page, h, wave & 1);
+    } else if (h0 + extra < a.num_kv_heads) {
+        pool_write_block<1>(a, pi, page, h0 + extra, false, 0);
+    }
+}
+
 template <int DT>
 __global__ __launch_bounds__(256) void pool_write_kernel(PoolWriteLaunch a) {
-    const int pi = blockIdx.x;
-    pool_write_block<DT>(a, a.page_ids[pi], a.slots != nullptr, a.slots ? a.slots[pi] : 0);
+    if (a.slots)
+        pool_write_block<DT>(a, blockIdx.x, a.page_ids[blockIdx.x], blockIdx.y, true, a.slots[blockIdx.x]);
+    else
+        pool_write_run<DT>(a, a.page_ids);
 }
 
 // A write of up to kMaxInlineWrite blocks (15 360 tokens): the block ids travel in the kernel arguments.  Through the
 // staging ring a call was an upload kernel, this kernel and an event: 13 us per call back to back for 2 200 tokens x 8
 // heads into an fp8 pool, 6.7 us this way (the launch itself is most of either).  The line is the 4 KiB of kernel
 // arguments; larger calls go through the ring, where the two extra launches no longer matter.
+template <int N>
 struct PoolWriteInline {
     PoolWriteLaunch base;
-    int32_t block[kMaxInlineWrite];
+    int32_t block[N];
 };
-static_assert(sizeof(PoolWriteInline) <= 4096, "kernel argument segment");
-template <int DT>
-__global__ __launch_bounds__(256) void pool_write_inline_kernel(PoolWriteInline a) {
-    pool_write_block<DT>(a.base, a.block[blockIdx.x], false, 0);
+static_assert(sizeof(PoolWriteInline<kMaxInlineWrite>) <= 4096, "kernel argument segment");
+template <int DT, int N>
+__global__ __launch_bounds__(256) void pool_write_inline_kernel(PoolWriteInline<N> a) {
+    pool_write_run<DT>(a.base, a.block);
 }
 
 // The decode step's append for up to kMaxInlineAppend sequences: block ids and slots travel in the kernel
@@ -218,7 +302,7 @@ __global__ __launch_bounds__(256) void pool_write_inline_kernel(PoolWriteInline 
 template <int DT>
 __global__ __launch_bounds__(256) void pool_append_inline_kernel(PoolAppendInline a) {
     const int pi = blockIdx.x;
-    pool_write_block<DT>(a.base, a.block[pi], true, a.slot[pi]);
+    pool_write_block<DT>(a.base, pi, a.block[pi], blockIdx.y, true, a.slot[pi]);
 }
 
 // One workgroup per (pair, K or V): copies the page's blocks of all KV heads, 16 bytes per thread and
@@ -288,7 +372,7 @@ __global__ __launch_bounds__(256) void plan_grow_inline_kernel(PlanGrowInline a)
 template <int DT>
 __global__ __launch_bounds__(256) void decode_step_append_kernel(PoolAppendInline w, PlanGrowInline g) {
     const int r = blockIdx.x, h = blockIdx.y;
-    pool_write_block<DT>(w.base, w.block[r], true, w.slot[r]);
+    pool_write_block<DT>(w.base, r, w.block[r], h, true, w.slot[r]);
     if (threadIdx.x == 0) g.items[g.grow_items[r * w.base.num_kv_heads + h]].n_tokens += 1;
     if (threadIdx.x == 1 && h == 0 && g.new_block[r] >= 0) g.pages[g.block_pos[r]] = g.new_block[r];
 }
@@ -345,18 +429,27 @@ hipError_t launch_pool_append_inline(const PoolAppendInline &a, hipStream_t s) {
 
 hipError_t launch_pool_write(const PoolWriteLaunch &a, hipStream_t s) {
     if (a.n_pages <= 0) return hipSuccess;
-    dim3 grid(a.n_pages, a.num_kv_heads), block(256);
+    const bool pairs = a.dtype == 1 && !a.slots;
+    const int in_part = a.n_pages == 1 ? (a.first_slot > 0 || a.n_tokens < kPage) : (a.first_slot > 0) + ((a.first_slot + a.n_tokens) % kPage != 0);
+    const dim3 grid(a.n_pages + (pairs ? in_part : 0), pairs ? (a.num_kv_heads + 1) / 2 : a.num_kv_heads), block(256);
     if (a.host_ids) {
+        auto go = [&](auto room) {
+            constexpr int N = decltype(room)::value;
+            PoolWriteInline<N> w;
+            w.base = a;
+            w.base.host_ids = nullptr;
+            std::copy(a.host_ids, a.host_ids + a.n_pages, w.block);
+            std::fill(w.block + a.n_pages, w.block + N, 0);
+            if (a.dtype == 0)
+                hipLaunchKernelGGL((pool_write_inline_kernel<0, N>), grid, block, 0, s, w);
+            else
+                hipLaunchKernelGGL((pool_write_inline_kernel<1, N>), grid, block, 0, s, w);
+            return hipGetLastError();
+        };
         if (a.n_pages > kMaxInlineWrite) return hipErrorInvalidValue;
-        PoolWriteInline w{};
-        w.base = a;
-        w.base.host_ids = nullptr;
-        std::copy(a.host_ids, a.host_ids + a.n_pages, w.block);
-        if (a.dtype == 0)
-            hipLaunchKernelGGL(pool_write_inline_kernel<0>, grid, block, 0, s, w);
-        else
-            hipLaunchKernelGGL(pool_write_inline_kernel<1>, grid, block, 0, s, w);
-        return hipGetLastError();
+        if (a.n_pages <= 64) return go(std::integral_constant<int, 64>{});
+        if (a.n_pages <= 256) return go(std::integral_constant<int, 256>{});
+        return go(std::integral_constant<int, kMaxInlineWrite>{});
     }
     if (a.dtype == 0)
         hipLaunchKernelGGL(pool_write_kernel<0>, grid, block, 0, s, a);
