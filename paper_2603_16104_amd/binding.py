@@ -69,6 +69,14 @@ def lib():
         for name in ("hkv_decode_plan_workspace_bytes", "attn_decode_workspace_bytes", "attn_prefill_workspace_bytes",
                      "hkv_prefill_plan_workspace_bytes", "hkv_static_workspace_bytes"):
             getattr(L, name).restype = C.c_size_t
+        # the calls of an engine's step: with argument types, plain numbers go to C without an object each
+        p, i, f, n = C.c_void_p, C.c_int32, C.c_float, C.c_size_t
+        L.kv_pool_write.argtypes = [p, p, i, i, p, p, p]
+        L.kv_pool_append.argtypes = [p, p, p, i, p, p, p]
+        L.hkv_decode_plan_append_tokens.argtypes = [p, p, p, p, p]
+        L.attn_decode_plan_run.argtypes = [p, p, f, p, p, p, n, p]
+        L.attn_decode_plan_run_static.argtypes = [p, p, f, p, p, p]
+        L.attn_prefill_plan_run_ws.argtypes = [p, p, f, p, p, p, n, p]
         _lib = L
     return _lib
 
@@ -107,6 +115,28 @@ def _stream(stream) -> C.c_void_p:
     if isinstance(stream, int):
         return C.c_void_p(stream)
     return C.c_void_p(stream.cuda_stream)
+
+
+# The same as plain numbers, for the calls that have argument types.
+def _addr(t):
+    return t if t is None or isinstance(t, int) else t.data_ptr()
+
+
+def _stream_addr(stream):
+    if stream is None:
+        import torch
+        return torch.cuda.current_stream().cuda_stream
+    return stream if isinstance(stream, int) else stream.cuda_stream
+
+
+_Bytes0 = C.c_char * 0
+
+
+def _host_addr(a: Optional[np.ndarray]):
+    """Something ctypes passes as the array's address (an empty view of its buffer where that can be had: the fastest way)."""
+    if a is None:
+        return None
+    return _Bytes0.from_buffer(a) if a.flags.writeable and a.size else a.ctypes.data
 
 
 def _nodes(nodes) -> np.ndarray:
@@ -166,12 +196,13 @@ def kv_pool_refcount(pool, page_id: int) -> int:
 
 def kv_pool_write(pool, page_ids, first_slot: int, n_tokens: int, k_src, v_src, stream=None) -> None:
     ids = _host_i32(page_ids)
-    page = kv_pool_page_size(pool)
-    need = (first_slot + n_tokens + page - 1) // page if n_tokens > 0 else 0
-    if len(ids) < need:
-        raise HkvError(EINVAL, f"kv_pool_write: {need} page ids needed, {len(ids)} given")
-    _check(lib().kv_pool_write(pool, _hp(ids), C.c_int32(first_slot), C.c_int32(n_tokens), _dev(k_src), _dev(v_src),
-                               _stream(stream) if n_tokens > 0 else C.c_void_p(None)))
+    if n_tokens > 0 and len(ids) * PAGE_SIZE < first_slot + n_tokens:  # (never too few for larger pages otherwise)
+        page = kv_pool_page_size(pool)
+        need = (first_slot + n_tokens + page - 1) // page
+        if len(ids) < need:
+            raise HkvError(EINVAL, f"kv_pool_write: {need} page ids needed, {len(ids)} given")
+    _check(lib().kv_pool_write(pool, _host_addr(ids), first_slot, n_tokens, _addr(k_src), _addr(v_src),
+                               _stream_addr(stream) if n_tokens > 0 else None))
 
 
 def kv_pool_append(pool, page_ids, slots, k_src, v_src, stream=None) -> None:
@@ -179,8 +210,8 @@ def kv_pool_append(pool, page_ids, slots, k_src, v_src, stream=None) -> None:
     ids, sl = _host_i32(page_ids), _host_i32(slots)
     if len(ids) != len(sl):
         raise HkvError(EINVAL, "kv_pool_append: page_ids and slots differ in length")
-    _check(lib().kv_pool_append(pool, _hp(ids), _hp(sl), C.c_int32(len(ids)), _dev(k_src), _dev(v_src),
-                                _stream(stream) if len(ids) > 0 else C.c_void_p(None)))
+    _check(lib().kv_pool_append(pool, _host_addr(ids), _host_addr(sl), len(ids), _addr(k_src), _addr(v_src),
+                                _stream_addr(stream) if len(ids) > 0 else None))
 
 
 # ----------------------------------------------------------------------------------------- forest
@@ -246,7 +277,7 @@ def hkv_decode_plan_append(plan, new_page_ids=None, stream=None) -> None:
 
 def hkv_decode_plan_append_tokens(plan, new_page_ids, k_src, v_src, stream=None) -> None:
     ids = None if new_page_ids is None else _host_i32(new_page_ids)
-    _check(lib().hkv_decode_plan_append_tokens(plan, _hp(ids), _dev(k_src), _dev(v_src), _stream(stream)))
+    _check(lib().hkv_decode_plan_append_tokens(plan, _host_addr(ids), _addr(k_src), _addr(v_src), _stream_addr(stream)))
 
 
 def hkv_decode_plan_create(pool, nodes, node_pages, req_leaf, num_q_heads: int, flags: int = 0) -> C.c_void_p:
@@ -356,8 +387,8 @@ def hkv_decode_plan_part_counts(plan, n_req: int) -> np.ndarray:
 
 
 def attn_decode_plan_run(plan, q, scale: float, out, lse_out, workspace, workspace_bytes: int, stream=None) -> None:
-    _check(lib().attn_decode_plan_run(plan, _dev(q), C.c_float(scale), _dev(out), _dev(lse_out), _dev(workspace),
-                                      C.c_size_t(workspace_bytes), _stream(stream)))
+    _check(lib().attn_decode_plan_run(plan, _addr(q), scale, _addr(out), _addr(lse_out), _addr(workspace), workspace_bytes,
+                                      _stream_addr(stream)))
 
 
 def hkv_static_workspace_bytes() -> int:
@@ -365,7 +396,7 @@ def hkv_static_workspace_bytes() -> int:
 
 
 def attn_decode_plan_run_static(plan, q, scale: float, out, lse_out, stream=None) -> None:
-    _check(lib().attn_decode_plan_run_static(plan, _dev(q), C.c_float(scale), _dev(out), _dev(lse_out), _stream(stream)))
+    _check(lib().attn_decode_plan_run_static(plan, _addr(q), scale, _addr(out), _addr(lse_out), _stream_addr(stream)))
 
 
 def hkv_decode_plan_set_profiling(plan, mode) -> None:
@@ -484,8 +515,8 @@ def attn_prefill_plan_run(plan, q, scale: float, out, lse_out=None, stream=None,
                           workspace_bytes: int = 0) -> None:
     """workspace: device scratch of hkv_prefill_plan_workspace_bytes(plan) bytes, one per stream (needed for an fp8 pool's pages;
     without room for the partial results of split tiles they stay whole)."""
-    _check(lib().attn_prefill_plan_run_ws(plan, _dev(q), C.c_float(scale), _dev(out), _dev(lse_out), _dev(workspace),
-                                          C.c_size_t(workspace_bytes), _stream(stream)))
+    _check(lib().attn_prefill_plan_run_ws(plan, _addr(q), scale, _addr(out), _addr(lse_out), _addr(workspace), workspace_bytes,
+                                          _stream_addr(stream)))
 
 
 def hkv_prefill_plan_workspace_bytes(plan) -> int:
