@@ -182,27 +182,19 @@ hipError_t launch_lse_merge_dense(const void *o_parts, const float *lse_parts, c
     };
     auto pick = [&](auto pb16) {
         constexpr bool PB = decltype(pb16)::value;
-        if (many && max_parts <= 2) {
-            if (out_dtype == 0)
-                go(lse_merge_dense_kernel<0, 2, PB, 4>);
+        auto of = [&](auto unroll) {
+            constexpr int U = decltype(unroll)::value;
+            if (many && U <= 8)
+                out_dtype == 0 ? go(lse_merge_dense_kernel<0, U, PB, 4>) : go(lse_merge_dense_kernel<2, U, PB, 4>);
             else
-                go(lse_merge_dense_kernel<2, 2, PB, 4>);
-        } else if (many) {
-            if (out_dtype == 0)
-                go(lse_merge_dense_kernel<0, 8, PB, 4>);
-            else
-                go(lse_merge_dense_kernel<2, 8, PB, 4>);
-        } else if (max_parts <= 8) {
-            if (out_dtype == 0)
-                go(lse_merge_dense_kernel<0, 8, PB, 1>);
-            else
-                go(lse_merge_dense_kernel<2, 8, PB, 1>);
-        } else {
-            if (out_dtype == 0)
-                go(lse_merge_dense_kernel<0, 16, PB, 1>);
-            else
-                go(lse_merge_dense_kernel<2, 16, PB, 1>);
-        }
+                out_dtype == 0 ? go(lse_merge_dense_kernel<0, U, PB, 1>) : go(lse_merge_dense_kernel<2, U, PB, 1>);
+        };
+        if (max_parts <= 2) return of(std::integral_constant<int, 2>{});
+        if (max_parts == 3) return of(std::integral_constant<int, 3>{});
+        if (max_parts == 4) return of(std::integral_constant<int, 4>{});
+        if (max_parts <= 6) return of(std::integral_constant<int, 6>{});
+        if (max_parts <= 8) return of(std::integral_constant<int, 8>{});
+        of(std::integral_constant<int, 16>{});
     };
     if (down_parts)
         pick(std::true_type{});
