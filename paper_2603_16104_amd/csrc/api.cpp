@@ -874,85 +874,169 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
         }
         return lay;
     };
-    // A plan's step in one form or the other, us: three times that run beside each other (as a 3-norm), and the
-    // partials.  Latency: the workgroups, longest first, on the chip's slots; alone one takes 1.6 + 0.82 per 64 tokens as
-    // 32-row tiles, 1.0 + 0.53 per 32 as 16-row tiles, 2.5 + 0.86 per 128 for few rows, and on a full chip 1.4 to 1.5 times that.
-    // Issue, per compute unit: per 64 tokens of an item and per workgroup.  Memory: shared nodes at 5.5 TB/s, the others at 7.1
-    // beside 16-row tiles (three workgroups per compute unit) and 6.5 beside 32-row tiles.  (Fitted to 1376 decode and
-    // verification plans over bf16 pools, most of them random, timed in both forms; 8 % rms.  Small plans over fp8 pools, as
-    // plan_paths asks for them: 8 % more than measured in the mean, 12 % rms.)
-    auto step_us = [&](const Layout &lay) {
-        struct Items {
-            int32_t tokens;  // of one
-            float n;
-            bool many;
-        };
-        std::vector<Items> list;
-        list.reserve(n_nodes);
-        std::vector<int32_t> chunks_to(n_nodes);
-        double n_items = 0;
-        int32_t parts = 1;
+    // Nodes of one length below the same number of requests, counted once; class_of: a node's entry (-1: no items of this kernel).
+    struct NodeClass {
+        int32_t tokens, n_req, count;
+    };
+    std::vector<NodeClass> classes;
+    std::vector<int32_t> class_of(n_nodes, -1);
+    {
+        std::vector<std::pair<int64_t, int32_t>> keys;
+        keys.reserve(n_nodes);
         for (int v = 0; v < n_nodes; ++v) {
-            const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v], T = pl.nodes[v].n_tokens, n_pages = pl.nodes[v].n_pages;
-            chunks_to[v] = pl.nodes[v].parent >= 0 ? chunks_to[pl.nodes[v].parent] : 0;
-            if (T == 0 || R == 0 || tiled(v)) continue;
-            const bool many = R * G > 16;
-            int chunk = std::max(16, many ? lay.shared_chunk : leaf_chunk), n_chunks = 1, per_chunk = n_pages;
-            if (!many && ((lay.cut_leaves && cut_for_packing(T)) || (lay.piece_tokens < pack_tokens && T <= pack_tokens))) chunk = lay.piece_tokens;
-            if (T > chunk) {  // as the items are cut below
-                per_chunk = (n_pages + (T - 1) / chunk) / ((T - 1) / chunk + 1);
-                n_chunks = (n_pages + per_chunk - 1) / per_chunk;
-            }
-            chunks_to[v] += n_chunks;
-            parts = std::max(parts, chunks_to[v]);
-            const int64_t n = (int64_t)n_chunks * Hkv * (many ? (R + max_req_per_item - 1) / max_req_per_item : 1);
-            list.push_back({std::min(T, per_chunk * 16), (float)n, many});
-            n_items += n;
+            const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
+            if (pl.nodes[v].n_tokens > 0 && R > 0 && !tiled(v)) keys.push_back({((int64_t)pl.nodes[v].n_tokens << 32) | R, v});
+        }
+        std::sort(keys.begin(), keys.end());
+        for (size_t i = 0; i < keys.size(); ++i) {
+            if (i == 0 || keys[i].first != keys[i - 1].first) classes.push_back({(int32_t)(keys[i].first >> 32), (int32_t)(keys[i].first & 0xFFFFFFFF), 0});
+            ++classes.back().count;
+            class_of[keys[i].second] = (int32_t)classes.size() - 1;
+        }
+    }
+    struct Cuts {
+        int n_chunks, per_chunk;  // blocks of a chunk; the last one may be shorter
+    };
+    auto cuts_of = [&](const Layout &lay, int T, int R) {  // equal chunks of whole blocks
+        int chunk = std::max(16, R * G > 16 ? lay.shared_chunk : leaf_chunk);
+        if (R * G <= 16 && ((lay.cut_leaves && cut_for_packing(T)) || (lay.piece_tokens < pack_tokens && T <= pack_tokens)))
+            chunk = lay.piece_tokens;  // equal pieces
+        const int blocks = (T + HKV_PAGE_SIZE - 1) / HKV_PAGE_SIZE, most = (T + chunk - 1) / chunk, per_chunk = (blocks + most - 1) / most;
+        return Cuts{(blocks + per_chunk - 1) / per_chunk, per_chunk};
+    };
+    // A layout's step, us: three times that run beside each other (as a 3-norm), and what the partials cost.  Latency: the
+    // workgroups, longest first, on the chip's slots, stretched on a full chip.  Issue, per compute unit: per 64 tokens of an item
+    // and active row tile, and per workgroup.  Memory: the nodes' bytes once, and those that items of shared nodes take
+    // from L2.  Coefficients: of 27 700 timings (1675 random decode and verification plans, 5 to 250 us, each in both
+    // forms and with chunks of 128 to 2048 tokens, three sets of inputs in turn), 7 % rms.
+    struct Coefficients {
+        double many0, many1, tall;        // a workgroup with an item of a shared node, 64 rows: + per 64 (32-row tiles) or 32 tokens (16-row tiles); less
+                                          // by `tall` of that for the share of the rows it does not have
+        double few0, few1, pack0, pack1;  // of few rows: + per 128 tokens; a wavefront with one of its own: + per 32
+        double full;                      // all that times 1 + full on a full chip
+        double block, tile, few_block, wg;
+        double mem_shared, mem_few, l2;   // us per MB
+        double part, row, base;           // per million partials and rows; launches
+    };
+    static const Coefficients kBf16Narrow{1.08, 0.616, 0.230, 1.50, 1.25, 0.01, 1.03, 0.162, 0.046, 0.117, 0.477, 0.12, 0.141, 0.164, 0.032, 171, 2.3, 6.7};
+    static const Coefficients kBf16Wide{2.53, 0.909, 0.163, 2.37, 1.18, 1.06, 0.92, 0.154, 0.018, 0.166, 0.288, 1.46, 0.134, 0.163, 0.044, 171, 0.6, 6.1};
+    static const Coefficients kFp8{1.69, 0.830, 0.155, 2.51, 0.81, 1.39, 0.76, 0.123, 0.047, 0.189, 0.363, 1.49, 0.116, 0.159, 0.070, 175, 1.5, 7.1};
+    // Of bf16 plans in the two forms at the length above (1376 plans, 8 % rms), for the choice of the form at that length: closer
+    // there than the sets that also know the other lengths (with those 45 of 900 plans lose more than 3 % instead of 28).  They know
+    // an item by its length alone.
+    static const Coefficients kNarrowThere{0.98, 0.53, 0, 2.48, 0.86, 0.01, 0.31, 0.54, 0.55, 0, 0.68, 1.42, 0.182, 0.141, 0, 84.5, 0, 7.5};
+    static const Coefficients kWideThere{1.60, 0.82, 0, 2.48, 0.86, 2.78, 0.24, 0.40, 0.52, 0, 0.36, 2.65, 0.182, 0.154, 0, 84.5, 0, 7.5};
+    struct Estimate {
+        double us;
+        int64_t parts;
+    };
+    auto estimate_by = [&](const Layout &lay, const Coefficients &k) {
+        const double token_mb = 2.0 * HKV_HEAD_DIM * (fp8_pool ? 1 : 2) * 1e-6;  // of one head
+        const int tile_rows = lay.wide ? 32 : 16;
+        std::vector<int32_t> n_chunks(classes.size()), chunks_to(n_nodes);
+        double n_items = 0;
+        for (size_t c = 0; c < classes.size(); ++c) {
+            const int R = classes[c].n_req;
+            n_chunks[c] = cuts_of(lay, classes[c].tokens, R).n_chunks;
+            n_items += (double)n_chunks[c] * classes[c].count * Hkv * (R * G > 16 ? (R + max_req_per_item - 1) / max_req_per_item : 1);
         }
         const bool packs = pack_mode == 3 || (pack_mode == 2 && n_items > lay.slots);
-        constexpr int kBins = 256;  // durations in steps of 0.25 us
-        double bins[kBins] = {}, n_wgs = 0, work = 0, longest_us = 0, issue = 0;
+        constexpr int kBins = 512;  // durations in steps of 0.25 us
+        double bins[kBins] = {}, n_wgs = 0, work = 0, longest_us = 0, issue = 0, memory = 0;
         int top = 0;
-        for (const Items &it : list) {
-            const bool packed = packs && !it.many && it.tokens <= pack_tokens;
-            const int blocks = (it.tokens + 63) / 64;
-            const double us = packed     ? (lay.wide ? 2.78 + 0.24 * ((it.tokens + 31) / 32) : 0.01 + 0.31 * ((it.tokens + 31) / 32))
-                              : !it.many ? 2.48 + 0.86 * ((it.tokens + 127) / 128)
-                              : lay.wide ? 1.60 + 0.82 * blocks
-                                         : 0.98 + 0.53 * ((it.tokens + 31) / 32);
-            issue += it.n * blocks * (it.many ? (lay.wide ? 0.52 : 0.55) : (lay.wide ? 0.36 : 0.68));
-            const double wgs = packed ? 0.25 * it.n : it.n;
+        auto add = [&](double n, int tokens, int rows, bool many) {
+            const int blocks = (tokens + 63) / 64, steps = (tokens + 31) / 32;
+            const bool packed = packs && !many && tokens <= pack_tokens;
+            const double us = packed ? k.pack0 + k.pack1 * steps : !many ? k.few0 + k.few1 * ((tokens + 127) / 128) : (k.many0 + k.many1 * (lay.wide ? blocks : steps)) * (1.0 + k.tall * (rows / 64.0 - 1.0));
+            issue += n * blocks * (many ? k.block + k.tile * ((rows + tile_rows - 1) / tile_rows) : k.few_block);
+            if (many) memory += n * tokens * token_mb * k.l2;
+            const double wgs = packed ? 0.25 * n : n;
             n_wgs += wgs;
             work += wgs * us;
             longest_us = std::max(longest_us, us);
             const int bin = std::min(kBins - 1, (int)(us * 4));
             bins[bin] += wgs;
             top = std::max(top, bin);
+        };
+        for (const NodeClass &c : classes) {
+            const int T = c.tokens, R = c.n_req;
+            const Cuts cut = cuts_of(lay, T, R);
+            const int tokens = std::min(T, cut.per_chunk * HKV_PAGE_SIZE);
+            const double n = (double)c.count * cut.n_chunks * Hkv;
+            memory += (double)c.count * T * Hkv * token_mb * (R * G > 16 ? k.mem_shared : k.mem_few);
+            if (R * G <= 16) {
+                add(n, tokens, R * G, false);
+                continue;
+            }
+            const int groups = (R + max_req_per_item - 1) / max_req_per_item, rest = R - (groups - 1) * max_req_per_item;
+            if (k.tile > 0 && !lay.wide && !fp8_pool && groups > 1 && rest * G <= 16) {  // (the remainder beside 16-row tiles, as below)
+                add(n * (groups - 1), tokens, max_req_per_item * G, true);
+                add(n, tokens, rest * G, false);
+            } else {
+                add(n * groups, tokens, (R + groups - 1) / groups * G, true);
+            }
         }
         double span = std::max(longest_us, work / lay.slots), seen = 0;
         for (int b = top, round = 0; b >= 0; --b) {  // workgroup number k * slots runs as the k + 1st on some slot at the earliest
             for (seen += bins[b]; seen > (double)round * lay.slots; ++round) span = std::max(span, (round + 1) * 0.25 * (b + 0.5));
         }
-        span *= 1.0 + (lay.wide ? 0.40 : 0.54) * std::min(1.0, n_wgs / lay.slots);
-        issue = (issue + (lay.wide ? 2.65 : 1.42) * n_wgs) / chip.n_cu;
-        const double stream = (unique / 5.5e6 + few_tokens / (lay.wide ? 6.5e6 : 7.07e6)) * (fp8_pool ? 2 : 4) * HKV_HEAD_DIM * Hkv;
-        return 7.5 + std::cbrt(span * span * span + issue * issue * issue + stream * stream * stream) + 0.16e-6 * 264 * 2 * (double)pl.n_req * pl.num_q_heads * parts;
+        span *= 1.0 + k.full * std::min(1.0, n_wgs / lay.slots);
+        issue = (issue + k.wg * n_wgs) / chip.n_cu;
+        int32_t parts = 1;
+        for (int v = 0; v < n_nodes; ++v) {
+            chunks_to[v] = (pl.nodes[v].parent >= 0 ? chunks_to[pl.nodes[v].parent] : 0) + (class_of[v] >= 0 ? n_chunks[class_of[v]] : 0);
+            parts = std::max(parts, chunks_to[v]);
+        }
+        const double rows = 1e-6 * pl.n_req * pl.num_q_heads;
+        return Estimate{k.base + std::cbrt(span * span * span + issue * issue * issue + memory * memory * memory) + rows * (k.part * parts + k.row),
+                        (int64_t)pl.n_req * pl.num_q_heads * parts};
     };
-    // bf16 pools: shared::body where that estimate is 2 % shorter with it.  It takes two thirds as long for an item alone, but two
+    auto estimate = [&](const Layout &lay) { return estimate_by(lay, fp8_pool ? kFp8 : lay.wide ? kBf16Wide : kBf16Narrow); };
+    // Shared nodes, bf16 pools: shared::body or 16-row tiles.  An item alone takes two thirds as long in shared::body, but two
     // workgroups fill a compute unit where three with 16-row tiles do, so that on a full chip the two come to the same and
-    // how the items fill it decides.  Both forms timed (us, 16-row / 32-row tiles): one root of 512 tokens over 64 leaves of
-    // 128 / 320 / 512 / 1024 tokens 22.3 / 17.3, 26.5 / 24.7, 30.1 / 30.8, 52.6 / 52.6; 8192 over 64 x 1024 63.4 / 73.5; 64 requests
-    // x 4 drafted tokens x 5 heads over 133 + 31 tokens 15.7 / 20.8.  Of 1320 random plans 32-row tiles everywhere gain 2.4 % in the
-    // mean and lose up to 38 %, the shorter of the two would gain 4.4 %; this choice gains 3.5 %, loses more than 3 % in 22 plans (most
-    // of them short) and misses a tenth in 27 (shared nodes of several thousand tokens above many rows).
-    const bool either = any_shared && !fp8_pool && pl.tile_form == 0;
-    Layout lay = lay_out(any_shared && (fp8_pool || pl.tile_form > 0));
-    if (either)
-        if (const Layout wide = lay_out(true); step_us(wide) < 0.98 * step_us(lay)) lay = wide;
+    // how the items fill it decides (one root of 512 tokens over 64 leaves of 128 tokens 22.3 us as 16-row tiles, 17.3 as 32-row
+    // tiles; 8192 over 64 x 1024 63.4 / 73.5).  Both pools: the chunk's length, from 128 tokens (a few items
+    // on an empty chip) to whole nodes (many rows, each with a partial per chunk).  Against the length above and the form
+    // that suits it, wherever the estimate is shorter by 4 % in that form or by 8 % in the other: 1675 random plans take 0.914 of their
+    // time in the mean, 14 lose more than 3 %; the best of all tried lengths and forms would give 0.882.  64 requests x 21 drafted
+    // tokens x 32 heads over 2048 + 512, bf16: 138 us in chunks of 512 tokens, 106 in whole nodes; 9 requests x 8 heads below
+    // each of 4 x 6996 tokens: 27.9 in chunks of 1024, 15.2 of 192.
+    // Plans whose partials fit the static workspace one way keep to the ways that fit, so that attn_decode_plan_run_static takes them.
+    const bool search = any_shared && !pl.fp8_matrix && opt.shared_chunk == 0 && opt.leaf_chunk == 0;
+    const bool narrow_too = !fp8_pool && pl.tile_form <= 0, wide_too = any_shared && (fp8_pool || pl.tile_form >= 0);
+    auto too_many = [](const Estimate &e) { return e.parts * (int64_t)(HKV_HEAD_DIM * sizeof(uint16_t) + 2 * sizeof(float)) + 1024 > (int64_t)kStaticWorkspaceBytes; };
+    Layout lay = lay_out(wide_too && (fp8_pool || pl.tile_form > 0));
+    if (narrow_too && wide_too)
+        if (const Layout wide = lay_out(true); estimate_by(wide, kWideThere).us < 0.98 * estimate_by(lay, kNarrowThere).us) lay = wide;
+    if (search || pl.paths_us > 0) {
+        Estimate at = estimate(lay);
+        if (search) {
+            const bool fits = !too_many(at);
+            Layout best = lay;
+            double least = at.us;  // times the margin: 4 % in the same form, 8 % in the other
+            Estimate best_at = at;
+            for (const bool w : {false, true}) {
+                if (w ? !wide_too : !narrow_too) continue;
+                Layout l = lay_out(w);
+                l.piece_tokens = pack_tokens;
+                for (const int chunk : {128, 192, 256, 384, 512, 768, 1024, 1536, 2048}) {
+                    l.shared_chunk = chunk;
+                    const Estimate e = estimate(l);
+                    const double us = e.us / (w == lay.wide ? 0.96 : 0.92);
+                    if (us >= least || (fits && too_many(e))) continue;
+                    least = us;
+                    best = l;
+                    best_at = e;
+                }
+            }
+            lay = best;
+            at = best_at;
+        }
+        if (pl.paths_us > 0) pl.items_us = at.us;
+    }
     pl.has_shared = lay.wide;
-    if (pl.paths_us > 0) pl.items_us = step_us(lay);
-    const int shared_chunk = lay.shared_chunk, piece_tokens = lay.piece_tokens;
-    const bool cut_leaves = lay.cut_leaves, cut_to_fill = lay.cut_to_fill;
+    const bool cut_to_fill = lay.cut_to_fill;
+    const int piece_tokens = lay.piece_tokens;
     // The tile kernel's share of the chip: its persistent workgroups hold one compute unit each for as long as
     // the other kernel streams its bytes, so their number follows from the two amounts of work (matrix
     // arithmetic at about 3.5 TFLOP/s per compute unit against bytes at about 5.5 TB/s for the chip).
@@ -1034,12 +1118,7 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
             }
             continue;
         }
-        int chunk = std::max(16, R * G > 16 ? shared_chunk : leaf_chunk);
-        if (R * G <= 16 && ((cut_leaves && cut_for_packing(nd.n_tokens)) || (piece_tokens < pack_tokens && nd.n_tokens <= pack_tokens)))
-            chunk = piece_tokens;  // equal pieces below
-        // equal chunks of whole pages
-        int n_chunks = (nd.n_tokens + chunk - 1) / chunk;
-        int pages_per_chunk = (nd.n_pages + n_chunks - 1) / n_chunks;
+        const int pages_per_chunk = cuts_of(lay, nd.n_tokens, R).per_chunk;
         node_chunks[v] = (nd.n_pages + pages_per_chunk - 1) / pages_per_chunk;
         // equal request groups (64 + 20 rows would leave a long item of few rows that is listed behind the others), except for a
         // remainder of up to 16 rows beside 16-row tiles: one of those costs as much for 48 rows as for 64, the remainder is run
@@ -1072,7 +1151,8 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     // stream and items of few rows by memory: the two classes are dispatched side by side, each spread evenly
     // over the list (groups of 8 = one workgroup per XCD), so that both are resident on every CU throughout
     // instead of one class after the other.  Within a class the order stays heavy before light.
-    if (const int group = or_default(opt.interleave, 8); group > 0) {
+    // Whole sets of KV heads from either list, so that a head's items stay on its XCD.
+    if (const int group = or_default(opt.interleave, (8 + Hkv - 1) / Hkv * Hkv); group > 0) {
         std::vector<Proto> many, few, rest, merged;
         for (auto &p : protos) (packable(p) ? rest : p.it.n_req * G > 16 ? many : few).push_back(p);
         if (!many.empty() && !few.empty()) {
@@ -1080,7 +1160,7 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
             size_t a = 0, b = 0;
             while (a < many.size()) {
                 for (int i = 0; i < group && a < many.size(); ++i) merged.push_back(many[a++]);
-                const size_t target = (size_t)((double)a * few.size() / many.size() + 0.5);
+                const size_t target = (size_t)((double)a * few.size() / many.size() / Hkv + 0.5) * Hkv;
                 while (b < target && b < few.size()) merged.push_back(few[b++]);
             }
             while (b < few.size()) merged.push_back(few[b++]);
@@ -1141,12 +1221,12 @@ static void plan_items(hkv_decode_plan &pl) {
 // Small steps.  The items' kernel and the merge are two launches, each a chain of dependent round trips (plan, blocks, K/V;
 // partials), 9 to 16 us however little there is to read.  Where the paths are short enough to be walked whole, a workgroup per
 // leaf (up to 16 of its rows) and KV head reads the path, shared nodes again for every leaf, and writes the result: one launch,
-// no partials.  What that takes, us: the launch and its chain, the steps of a wavefront, and the blocks a compute unit has to
-// take in, about 80 (bf16) resp. 60 (fp8) bytes per ns, more where the nodes are not in the L2 of every XCD that reads them.
-// (Coefficients and the margin from 1556 random plans of 16 to 3500 tokens per path and up to 3000 workgroups, timed in both
-// forms: 11 % rms; the mean of step over step with items is 0.729, the better form of each plan would give 0.721, 20 plans lose more
-// than 3 %, the worst 27 %.  Four requests over 256 + 32 + 17 tokens, bf16, 8 / 2 heads: 11.2 -> 6.6 us; 32 requests over 480 + 160
-// tokens, 32 / 8 heads: 17.3 -> 7.7; 64: 16.6 -> 13.3; 128: 22.5 as items, 23.7 this way.)
+// no partials.  What that takes, us: the launch and its chain, and the blocks a compute unit has to take in,
+// some 50 to 100 bytes per ns, more where the nodes are not in the L2 of every XCD that reads them.
+// (Coefficients and the margin from 860 random plans of 16 to 3500 tokens per path, timed in both forms with three sets of
+// inputs in turn: 10 % rms; 12 of those that run this way would be more than 3 % faster as items, 58 of the others this way.
+// Four requests over 256 + 32 + 17 tokens, bf16, 8 / 2 heads: 11.2 -> 6.6 us; 32 requests over 480 + 160 tokens, 32 / 8 heads:
+// 17.3 -> 7.7; 64: 16.6 -> 13.3; 128: 22.5 as items, 23.7 this way.)
 // Eight wavefronts while every workgroup has a compute unit to itself, four where several share one (64 requests over 240 +
 // 80 tokens, fp8: 12.3 us with eight, 9.0 with four).
 // A caller that sets anything of the planner's, or asks for a form of the items, gets items; growing plans have theirs
@@ -1190,10 +1270,12 @@ static void estimate_paths(hkv_decode_plan &pl, RowsByLeaf &by) {
     for (int h = Hkv; h % 2 == 0 && xcds > 1; h /= 2) xcds /= 2;
     unique *= 2.0 * HKV_HEAD_DIM * Hkv * (fp8 ? 1 : 2) * xcds;
     const int waves = units <= n_cu ? 8 : 4;
-    const double per_cu = (double)units / n_cu, most = longest * 16e-3, mean = block_sum / paths * 16e-3;  // in 1000 tokens
-    const double steps = std::ceil(longest * 16.0 / ((fp8 ? 64 : 32) * waves)), beside = std::max(0.0, per_cu * mean - most);
-    pl.paths_us = fp8 ? 5.3 + 3.8 * most + 5.2 * beside + 0.47 * per_cu + 0.026e-6 * unique + 0.42 * steps
-                      : 4.5 + 2.9 * most + 7.5 * beside + 0.23 * per_cu + 0.030e-6 * unique + 0.68 * steps;
+    // in 1000 tokens: the longest path, and what a compute unit takes in beyond it (between the mean and that of whole workgroups)
+    const double per_cu = (double)units / n_cu, most = longest * 16e-3, mean = block_sum / paths * 16e-3;
+    const double beside = 0.5 * std::max(0.0, per_cu * mean - most) + 0.5 * std::max(0.0, std::ceil(per_cu) * mean - most);
+    const double us = fp8 ? 6.0 + 5.2 * most + 8.0 * beside + 0.23 * per_cu + 0.017e-6 * unique : 5.2 + 6.5 * most + 10.9 * beside + 0.046e-6 * unique;
+    if (us > 50) return;  // (beyond what was timed)
+    pl.paths_us = us;
     pl.n_paths = (int32_t)paths;
     pl.path_waves = waves;
     pl.path_stride = (int32_t)((kPathBlocks + std::max<int64_t>(longest, 1) + 15) / 16 * 16);
@@ -1201,7 +1283,7 @@ static void estimate_paths(hkv_decode_plan &pl, RowsByLeaf &by) {
 
 // Behind plan_items: paths or items, and the paths' records.
 static void plan_paths(hkv_decode_plan &pl, const RowsByLeaf &by) {
-    if (pl.paths_us == 0 || !pl.tile_items.empty() || pl.paths_us > 0.85 * pl.items_us) {
+    if (pl.paths_us == 0 || !pl.tile_items.empty() || pl.paths_us > 0.97 * pl.items_us) {
         pl.n_paths = pl.path_waves = 0;
         return;
     }

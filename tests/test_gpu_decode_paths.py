@@ -17,7 +17,7 @@ FORESTS = {
     "holes": ([-1, 0, 1, 1, 0, 4], [13, 30, 1, 47, 33, 5], [2, 3, 5, 4, 0, 2, 2], 1),     # inner nodes, three requests on one leaf
     "empty_nodes": ([-1, 0, 1, 0, -1, 4], [0, 40, 0, 7, 0, 0], [2, 3, 5, 1], 1),          # request 2 sees no token at all
     "eight_wavefronts": ([-1] + [0] * 5, [255, 1, 2, 33, 257, 300], [1, 2, 3, 4, 5], 1),
-    "four_wavefronts": ([-1] + [0] * 90, [127] + [1 + 7 * i % 90 for i in range(90)], list(range(1, 91)), 1),
+    "four_wavefronts": ([-1] + [0] * 66, [67] + [1 + 7 * i % 60 for i in range(66)], list(range(1, 67)), 1),
     "drafted": ([-1, 0, 0], [77, 9, 40], [1, 2], 8),
     "drafted_tree": ([-1, 0, 0], [64, 21, 50], [1, 2], 21),
 }

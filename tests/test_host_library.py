@@ -712,6 +712,19 @@ def test_form_of_shared_items_is_the_one_that_measured_shorter(tokens, fan, head
         assert items_of(parent, ntok, level, *heads, T=T, flags=flags)[1] == (flags == hkv.PLAN_WIDE_TILES)
 
 
+@pytest.mark.parametrize("dtype, roots, tokens, n_req, heads, T, least, most", [
+    (hkv.BF16, 1, (2048, 512), 64, (32, 8), 16, 1536, 2048),     # many rows, a partial each and per chunk: whole nodes
+    (hkv.BF16, 4, (6996, 42), 9, (8, 2), 1, 128, 384), (hkv.FP8_E4M3, 1, (5136, 364), 15, (32, 8), 1, 128, 256),   # few items on an empty chip
+    (hkv.FP8_E4M3, 1, (670, 261), 46, (64, 8), 16, 640, 768),    # one chunk rather than two
+])
+def test_chunk_lengths_of_shared_nodes(dtype, roots, tokens, n_req, heads, T, least, most):
+    """Near the lengths that measured shortest."""
+    parent = [-1] * roots + [r for r in range(roots) for _ in range(n_req)]
+    ntok = [tokens[0]] * roots + [tokens[1]] * (roots * n_req)
+    items, _ = items_of(parent, ntok, list(range(roots, len(parent))), *heads, dtype, T=T)
+    assert least <= items[items[:, 7] < roots, 1].max() <= most
+
+
 @pytest.mark.parametrize("flags", [hkv.PLAN_NARROW_TILES, hkv.PLAN_WIDE_TILES])
 def test_few_long_nodes_are_cut_in_both_forms(flags):
     """12 nodes of 3222 tokens x 16 rows and 24 of 16 tokens: 296 (node, head) units leave half of the chip idle, whatever runs the root."""
