@@ -196,6 +196,12 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     const int tok = r_tile / G;                  // token (request) index within the tile (>= n_slots: no such row)
     const int head = kv_head * G + r_tile % G;   // query head
     const int slot_c = min(tok, n_slots - 1);
+    // A wavefront without rows (short tiles) moves its share of K and V and leaves the matrix cores to the others: the first
+    // four wavefronts sit on one SIMD each, so up to 128 rows run a block in the time of one wavefront instead of two.  32 x 24 to
+    // 32 new tokens over 512, 32 / 8 heads: 25.9 -> 21.2 us; 16 x 72 to 96 over 1024: 41.3 -> 34.5; 32 x 750 to 1000 over 4096,
+    // whose last tiles are short: 1792 -> 1765.
+    // (Decode items have 128 rows at least, and registers to lose.)
+    const bool active = DECODE || 32 * wave < n_slots * G;
     uint32_t io_row;                             // row of out (prefill) / of the partials' owner (decode items)
     uint32_t q_row;                              // row of q
     if constexpr (DECODE) {
@@ -413,10 +419,10 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
         }
     }
     f32x16 sa, sb;  // scores of even and odd steps
-    scores(sa, k_tile(0));
-    if (31 > wave_min_pos) mask_scores(sa, 0);
-    float mc;  // reference = maximum of the row's first 32 scores (token 0 is visible), times scale * log2 e
-    {
+    float mc = 0.f;  // reference = maximum of the row's first 32 scores (token 0 is visible), times scale * log2 e
+    if (active) {
+        scores(sa, k_tile(0));
+        if (31 > wave_min_pos) mask_scores(sa, 0);
         const StepScale s0 = step_scale(0);
         float mx = sa[0] * s0.ck[0];
 #pragma unroll
@@ -478,10 +484,12 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     u32x4 wa[2], wb[2];  // probabilities (packed bf16) of even and odd steps
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf) wb[hf] = u32x4{0u, 0u, 0u, 0u};  // "P(-1)" = 0: phase 0 adds nothing to O^T
+    if (active) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        kf[i] = lds_k(k_tile(1), i);
-        vf[i] = lds_v(v_tile(0), i);  // stands in for V(-1): finite data, multiplied by zeros
+        for (int i = 0; i < 4; ++i) {
+            kf[i] = lds_k(k_tile(1), i);
+            vf[i] = lds_v(v_tile(0), i);  // stands in for V(-1): finite data, multiplied by zeros
+        }
     }
     // Iteration j = phases 2j and 2j+1: reads K of blocks j, j+1 and V of blocks j-1, j.  The
     // wait at its end allows only its own requests to be outstanding, so K(j+2) and V(j+1) are
@@ -511,8 +519,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
             if (((j + 2) & 15) == 0) vwin = window(j + 2);
         }
         const int t = 2 * j;
-        if (j > 0 && j * KB + 31 > wave_min_pos) mask_scores(sa, t);
-        phase(sa, sb, wb, wa, t, kt(1), kt(2), (S != 0 || j > 0) ? vt(-1) : vt(0), vt(0), [&]() {
+        auto front0 = [&]() {
             if constexpr (FP8) {  // widen {K(j+2), V(j+1)}: visible to everyone after this iteration's barrier
                 store_k_fp8(kq_now, (S + 2) % kStages);
                 store_v_fp8(vq_now, j + 1, (S + 1) % kStages);
@@ -520,9 +527,8 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
                 issue_k_part(j + 3, 0, (S + 3) % kStages);
                 issue_v_part(j + 2, 0, (S + 2) % kStages);
             }
-        });
-        if (j * KB + 63 > wave_min_pos) mask_scores(sb, t + 1);
-        phase(sb, sa, wa, wb, t + 1, kt(2), kt(3), vt(0), vt(1), [&]() {
+        };
+        auto front1 = [&]() {
             if constexpr (FP8) {  // the request that takes the free place has two iterations to land
                 kq_now = fetch_fp8(kbase, j + 4);
                 vq_now = fetch_fp8(vbase, j + 3);
@@ -530,7 +536,16 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
                 issue_k_part(j + 3, kParts - 1, (S + 3) % kStages);
                 issue_v_part(j + 2, kParts - 1, (S + 2) % kStages);
             }
-        });
+        };
+        if (active) {
+            if (j > 0 && j * KB + 31 > wave_min_pos) mask_scores(sa, t);
+            phase(sa, sb, wb, wa, t, kt(1), kt(2), (S != 0 || j > 0) ? vt(-1) : vt(0), vt(0), front0);
+            if (j * KB + 63 > wave_min_pos) mask_scores(sb, t + 1);
+            phase(sb, sa, wa, wb, t + 1, kt(2), kt(3), vt(0), vt(1), front1);
+        } else {
+            front0();
+            front1();
+        }
         // (after the last block the K operands come from stale stages: in bounds, never used)
         if constexpr (FP8) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -555,7 +570,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
         iteration(std::integral_constant<int, 3>{}, j + 3, kq[1], vq[1]);
     }
     // drain: O^T += V^T P^T of the last step (vf holds its operands 0-3, wb its probabilities)
-    {
+    if (active) {
         const char *vl = v_tile(2 * n_blk - 1);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -649,6 +664,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     if (SPLIT && part >= 0) {  // the partial, in register order: every store is a whole KiB per wavefront
         float *pd = a.part_data + (size_t)part * kSplitPartFloats;
         f32x4 *po = reinterpret_cast<f32x4 *>(pd) + wave * (16 * 64) + lane;
+        if (!active) continue;  // (nothing reads rows that do not exist)
 #pragma unroll
         for (int k = 0; k < 16; ++k)
             po[64 * k] = f32x4{o[k >> 2][4 * (k & 3)], o[k >> 2][4 * (k & 3) + 1], o[k >> 2][4 * (k & 3) + 2], o[k >> 2][4 * (k & 3) + 3]};
