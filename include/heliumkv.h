@@ -500,13 +500,16 @@ int hkv_prefill_plan_create_rows(hkv_pool *pool, const int32_t *q_row_begin, con
                                  int32_t num_q_heads, uint32_t flags, hkv_prefill_plan **out);
 int hkv_prefill_plan_destroy(hkv_prefill_plan *plan);
 /* Number of (request, query tile, kv head) tiles of the plan: a workgroup each, or, where a run splits them along their
- * keys, hkv_prefill_plan_num_segments pieces of work for one workgroup per compute unit (0: the plan splits nothing). */
+ * keys, hkv_prefill_plan_num_segments pieces of work for one workgroup per compute unit (0: the plan splits nothing).
+ * Small batches run their tiles in pieces of a half or a quarter of the rows instead, a workgroup each:
+ * hkv_prefill_plan_num_pieces of them (0: whole tiles). */
 int32_t hkv_prefill_plan_num_tiles(const hkv_prefill_plan *plan);
+int32_t hkv_prefill_plan_num_pieces(const hkv_prefill_plan *plan);
 int32_t hkv_prefill_plan_num_segments(const hkv_prefill_plan *plan);
 /* The prefill kernel keeps one softmax reference per row (the maximum of its first 32 scores); a tile in which a
  * later score exceeds it by more than the exponent range allows repeats with a running maximum, at about
- * twice the cost.  count (host): how many tiles did so over all runs of this plan so far (the call waits for
- * the device).  bf16 and fp8 pools; always 0 for fp32 pools. */
+ * twice the cost.  count (host): how many tiles (pieces, where there are some) did so over all runs of this
+ * plan so far (the call waits for the device).  bf16 and fp8 pools; always 0 for fp32 pools. */
 int hkv_prefill_plan_fallback_tiles(hkv_prefill_plan *plan, int64_t *count);
 /* Tile layout for tests, 8 int32 each: (req, q_begin, n_q, kv_head, q_row0, prefix_len, kv_len, bt_off). */
 int hkv_prefill_plan_tiles(const hkv_prefill_plan *plan, int32_t *tiles_out);

@@ -34,7 +34,7 @@ EXPORTS = [
     "hkv_decode_plan_set_profiling", "hkv_decode_plan_elapsed_ms", "hkv_decode_plan_elapsed_kernels_ms",
     "hkv_decode_plan_num_tile_items", "hkv_decode_plan_tile_workgroups", "hkv_decode_plan_is_fused", "hkv_decode_plan_has_stream", "hkv_decode_plan_has_wide_tiles", "hkv_decode_plan_num_paths",
     "attn_decode_prefix_tree", "attn_decode_workspace_bytes", "hkv_prefill_plan_create", "hkv_prefill_plan_destroy",
-    "hkv_prefill_plan_num_tiles", "hkv_prefill_plan_tiles", "hkv_prefill_plan_num_segments", "hkv_prefill_plan_segments", "attn_prefill_plan_run", "attn_prefill_plan_run_ws", "hkv_prefill_plan_workspace_bytes", "attn_prefill_with_prefix",
+    "hkv_prefill_plan_num_tiles", "hkv_prefill_plan_num_pieces", "hkv_prefill_plan_tiles", "hkv_prefill_plan_num_segments", "hkv_prefill_plan_segments", "attn_prefill_plan_run", "attn_prefill_plan_run_ws", "hkv_prefill_plan_workspace_bytes", "attn_prefill_with_prefix",
     "attn_prefill_workspace_bytes",
     "kv_cache_create", "kv_cache_destroy", "kv_cache_acquire", "kv_cache_release", "kv_cache_unpin", "kv_cache_stats",
     "trt_build", "trt_destroy", "trt_num_nodes", "trt_num_syms", "trt_num_calls", "trt_nodes", "trt_prefill_usage",
@@ -517,6 +517,11 @@ def attn_prefill_plan_run(plan, q, scale: float, out, lse_out=None, stream=None,
     without room for the partial results of split tiles they stay whole)."""
     _check(lib().attn_prefill_plan_run_ws(plan, _addr(q), scale, _addr(out), _addr(lse_out), _addr(workspace), workspace_bytes,
                                           _stream_addr(stream)))
+
+
+def hkv_prefill_plan_num_pieces(plan) -> int:
+    """Pieces of a half or a quarter of a tile's rows that the plan runs instead of its tiles (0: whole tiles)."""
+    return _check(lib().hkv_prefill_plan_num_pieces(plan))
 
 
 def hkv_prefill_plan_workspace_bytes(plan) -> int:

@@ -147,6 +147,7 @@ struct hkv_prefill_plan {
     int32_t max_pages = 0;       // row length of the device table (16-token blocks)
     std::vector<int32_t> cu_q, block_table, kv_len;   // key of the one-shot cache
     std::vector<PrefillTile> tiles;
+    std::vector<PrefillTile> pieces;  // small batches: the tiles in pieces of fewer rows, a workgroup each (empty: the tiles)
     void *dev = nullptr;
     PrefillTile *d_tiles = nullptr;
     int32_t *d_block_table = nullptr;
@@ -2104,17 +2105,18 @@ extern "C" size_t attn_decode_workspace_bytes(hkv_pool *pool, const hkv_node *no
 // 64 / 256 / 1024 new tokens over 8192 cached ones 154 / 159 / 183 -> 33 / 49 / 145 us, 700 over 4096 98.4 -> 62.7,
 // 128 over 1024 29.9 -> 22.7; six requests of 256 to 512 over 2048 114.5 -> 99.8.  Where the estimate gains less than 13 %
 // it was a loss as often as not (three of 1024 over 8192: estimate 0.89, measured 1.01).
-static void split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<PrefillTile> &head_tiles, int n_cu) {
+//
+// block_cost: what a key block costs such tiles, as a share of what it costs one of more than 128 rows.  Returns the estimate for the
+// way taken (0: not estimated, a workgroup per tile).
+static double split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<PrefillTile> &head_tiles, int n_cu, double block_cost) {
     const int Hkv = pl.pool->d.num_kv_heads;
     const int n = (int)head_tiles.size(), workers = n_cu / Hkv;
-    if (n == 0 || workers < 2 || n > 4 * workers) return;
-    constexpr double kOver = 4.0;
+    if (n == 0 || workers < 2 || n > 4 * workers) return 0;
+    const double kOver = 4.0 / block_cost;  // (all below in blocks of these tiles)
     std::vector<int> blocks(n);
-    int64_t total = 0;
     for (int i = 0; i < n; ++i) {
         const PrefillTile &t = head_tiles[i];
         blocks[i] = (t.prefix_len + t.q_begin + t.n_q + 63) / 64;
-        total += blocks[i];
     }
     // whole: dispatched in order, each to the workgroup that is free first
     std::vector<double> load(workers, 0.0);
@@ -2129,7 +2131,7 @@ static void split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<PrefillT
         own[w].push_back(i);
         load[w] += blocks[i] + kOver;
     }
-    if (n_whole == n) return;  // whole rounds: nothing to gain
+    if (n_whole == n) return whole_cost * block_cost;  // whole rounds: nothing to gain
     int64_t rest = 0;
     for (int i = n_whole; i < n; ++i) rest += blocks[i];
     // the level up to which the rest fills the workers (a worker whose whole tiles reach it gets none), each paying one more segment
@@ -2163,8 +2165,8 @@ static void split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<PrefillT
         if (last) break;
         ++w;
     }
-    const double split_cost = worst + 3.0 + n_cuts * (double)Hkv * kSplitPartFloats * 4 / 5e6 / 1.4;
-    if (split_cost > 0.87 * whole_cost || (int64_t)n_cuts * Hkv > 1024) return;
+    const double split_cost = worst + (3.0 + n_cuts * (double)Hkv * kSplitPartFloats * 4 / 5e6 / 1.4) / block_cost;
+    if (split_cost > 0.87 * whole_cost || (int64_t)n_cuts * Hkv > 1024) return whole_cost * block_cost;
 
     std::vector<int> pieces(n, 0);
     for (auto &c : cuts)
@@ -2204,6 +2206,7 @@ static void split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<PrefillT
             }
             pl.seg_begin.push_back((int32_t)pl.segments.size());
         }
+    return split_cost * block_cost;
 }
 
 static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_t *q_row_begin, const int32_t *block_table,
@@ -2252,30 +2255,69 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
         for (int64_t b = 0; b < nb; ++b)
             blocks[(size_t)r * max_blocks + b] = block_table[(size_t)r * max_pages + b / S] * S + (int32_t)(b % S);
     }
-    const int TQ = prefill_tile_tokens(G);
-    struct Proto { int32_t req, q_begin, n_q; int64_t extent; };
-    std::vector<Proto> protos;
-    for (int r = 0; r < n_req; ++r) {
-        int s = cu_q[r + 1] - cu_q[r];
-        int prefix = kv_len[r] - s;
-        for (int q0 = 0; q0 < s; q0 += TQ) {
-            int nq = std::min(TQ, s - q0);
-            protos.push_back({r, q0, nq, (int64_t)prefix + q0 + nq});
+    // Tiles of TQ new tokens, of one KV head; longest key range first.
+    auto head_tiles_of = [&](const int TQ) {
+        struct Proto { int32_t req, q_begin, n_q; int64_t extent; };
+        std::vector<Proto> protos;
+        for (int r = 0; r < n_req; ++r) {
+            int s = cu_q[r + 1] - cu_q[r];
+            int prefix = kv_len[r] - s;
+            for (int q0 = 0; q0 < s; q0 += TQ) {
+                int nq = std::min(TQ, s - q0);
+                protos.push_back({r, q0, nq, (int64_t)prefix + q0 + nq});
+            }
         }
-    }
-    // longest key range first; the KV heads of one query tile sit next to each other so that
-    // workgroup index mod num_kv_heads is the KV head (one head per XCD when there are 8)
-    std::stable_sort(protos.begin(), protos.end(), [](const Proto &a, const Proto &b) { return a.extent > b.extent; });
-    for (const Proto &p : protos)
-        for (int h = 0; h < Hkv; ++h) {
-            int s = cu_q[p.req + 1] - cu_q[p.req];
-            pl->tiles.push_back(PrefillTile{p.req, p.q_begin, p.n_q, h, (q_row_begin ? q_row_begin[p.req] : cu_q[p.req]) + p.q_begin, kv_len[p.req] - s,
-                                            kv_len[p.req], p.req * max_blocks});
+        std::stable_sort(protos.begin(), protos.end(), [](const Proto &a, const Proto &b) { return a.extent > b.extent; });
+        std::vector<PrefillTile> tiles;
+        tiles.reserve(protos.size());
+        for (const Proto &p : protos) {
+            const int s = cu_q[p.req + 1] - cu_q[p.req];
+            tiles.push_back(PrefillTile{p.req, p.q_begin, p.n_q, 0, (q_row_begin ? q_row_begin[p.req] : cu_q[p.req]) + p.q_begin, kv_len[p.req] - s,
+                                        kv_len[p.req], p.req * max_blocks});
         }
+        return tiles;
+    };
+    // the KV heads of one query tile sit next to each other so that workgroup index mod num_kv_heads is the KV head (one head
+    // per XCD when there are 8)
+    auto of_all_heads = [&](const std::vector<PrefillTile> &head_tiles, std::vector<PrefillTile> &out) {
+        for (const PrefillTile &t : head_tiles)
+            for (int h = 0; h < Hkv; ++h) {
+                out.push_back(t);
+                out.back().kv_head = h;
+            }
+    };
+    const std::vector<PrefillTile> head_tiles = head_tiles_of(prefill_tile_tokens(G));
+    of_all_heads(head_tiles, pl->tiles);
     if (pool->d.dtype != HKV_FP32) {
-        std::vector<PrefillTile> head_tiles;
-        for (size_t i = 0; i < pl->tiles.size(); i += Hkv) head_tiles.push_back(pl->tiles[i]);
-        split_prefill_tiles(*pl, head_tiles, chip_shape().n_cu);
+        // Tiles in pieces of fewer rows where the tiles leave compute units without one: a wavefront without rows costs a piece
+        // nothing, and a key block takes one of up to 128 rows 0.72 and one of up to 64 rows 0.64 of the time (1.3, 0.93 and 0.84 us).
+        // As long as every piece gets a compute unit, and where the estimate is 5 % shorter than the tiles', whole or split.  32 /
+        // 8 heads, 256, 128 and 64 rows: 4 x 96 to 128 new tokens over 512 22.5, 17.9, 16.7 us; 2 x 192 to 256 over 1024 29.0
+        // (split), 25.2, 24.4; but 8 x 192 to 256 over 1024, 256 tiles, 43.4, 52.3, 85.3.
+        const int n_cu = chip_shape().n_cu;
+        const auto block_cost = [](int rows) { return rows > 128 ? 1.0 : rows > 64 ? 0.72 : 0.64; };
+        int most_rows = 0;
+        for (const PrefillTile &t : head_tiles) most_rows = std::max(most_rows, t.n_q * G);
+        double best = split_prefill_tiles(*pl, head_tiles, n_cu, block_cost(most_rows));
+        std::vector<PrefillTile> taken;
+        for (const int rows : {128, 64}) {
+            if (rows >= most_rows || best == 0 || rows < G) continue;
+            std::vector<PrefillTile> pieces = head_tiles_of(rows / G);
+            if ((int64_t)pieces.size() * Hkv > n_cu) break;
+            const PrefillTile &longest = pieces.front();
+            const double cost = 4.0 + block_cost(rows) * ((longest.prefix_len + longest.q_begin + longest.n_q + 63) / 64);
+            if (cost > 0.95 * best) continue;
+            best = cost;
+            taken.swap(pieces);
+        }
+        if (!taken.empty()) {
+            pl->segments.clear();
+            pl->seg_begin.clear();
+            pl->seg_tile.clear();
+            pl->split.clear();
+            pl->n_parts = 0;
+            of_all_heads(taken, pl->pieces);
+        }
     }
     // fp8 pools: number the pages this batch reads (first use first) and point the device table at them
     std::vector<int32_t> remapped;
@@ -2297,8 +2339,9 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
         }
     }
     const std::vector<int32_t> &dev_table = pool->d.dtype == HKV_FP8_E4M3 ? remapped : blocks;
-    if (!(flags & HKV_PLAN_HOST_ONLY) && !pl->tiles.empty()) {
-        size_t off_bt = align_up(sizeof(PrefillTile) * pl->tiles.size(), 256);
+    const std::vector<PrefillTile> &run_tiles = pl->pieces.empty() ? pl->tiles : pl->pieces;
+    if (!(flags & HKV_PLAN_HOST_ONLY) && !run_tiles.empty()) {
+        size_t off_bt = align_up(sizeof(PrefillTile) * run_tiles.size(), 256);
         size_t off_src = off_bt + align_up(sizeof(int32_t) * dev_table.size(), 256);
         size_t off_fb = off_src + align_up(sizeof(int32_t) * pl->src_pages.size(), 256);
         const size_t off_seg = off_fb + 256, off_sb = off_seg + align_up(sizeof(PrefillSegment) * pl->segments.size(), 256);
@@ -2315,7 +2358,7 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
             // 30-38 this way, and a plan made for a single run has to gain that back
             std::vector<char> image(total, 0);
             auto put = [&](size_t off, const auto &v) { if (!v.empty()) memcpy(image.data() + off, v.data(), sizeof(v[0]) * v.size()); };
-            put(0, pl->tiles);
+            put(0, run_tiles);
             put(off_bt, dev_table);
             put(off_src, pl->src_pages);
             if (!pl->segments.empty()) {
@@ -2392,6 +2435,9 @@ extern "C" int32_t hkv_prefill_plan_num_tiles(const hkv_prefill_plan *plan) {
     return plan ? (int32_t)plan->tiles.size() : fail(HKV_EINVAL, "null plan");
 }
 
+extern "C" int32_t hkv_prefill_plan_num_pieces(const hkv_prefill_plan *plan) {
+    return plan ? (int32_t)plan->pieces.size() : fail(HKV_EINVAL, "null plan");
+}
 extern "C" int hkv_prefill_plan_tiles(const hkv_prefill_plan *plan, int32_t *tiles_out) {
     if (!plan || !tiles_out) return fail(HKV_EINVAL, "hkv_prefill_plan_tiles: null argument");
     static_assert(sizeof(PrefillTile) == 32, "tile layout is part of the introspection contract");
@@ -2468,7 +2514,7 @@ extern "C" int attn_prefill_plan_run_ws(hkv_prefill_plan *plan, const void *q, f
         view = PoolView{k_dst, v_dst, nullptr, nullptr, view.num_kv_heads, HKV_BF16};
     }
     PrefillLaunch a{view, q, plan->d_tiles, plan->d_block_table, out, lse_out,
-                    (int32_t)plan->tiles.size(), plan->num_q_heads, scale, plan->d_fallback,
+                    (int32_t)(plan->pieces.empty() ? plan->tiles : plan->pieces).size(), plan->num_q_heads, scale, plan->d_fallback,
                     plan->d_segments, plan->d_seg_begin, plan->d_split, nullptr, nullptr, 0, 0};
     // Split tiles need room for their partials; a caller that brings none, or only an fp8 pool's pages, gets whole tiles.
     // The room is the caller's, so that runs on different streams (of the one-shot form's cached plan too) share nothing.
