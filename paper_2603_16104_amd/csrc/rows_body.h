@@ -222,6 +222,8 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
     const int n_ts = packed ? 1 : W / n_rt;
     const int rt = packed ? 0 : wave % n_rt, ts = packed ? 0 : wave / n_rt;
     const float c = a.scale * kLog2e;
+    constexpr bool kScaled = PATH && DT == 1;
+    const float c_run = kScaled ? 1.f : c;  // what takes the running maximum to units of log2
 
     // Q^T operands of this wavefront's 16 rows; rows past the item's end are zero.  The loads are
     // unconditional (row clamped) so that they can stay in flight next to the first K/V requests.
@@ -425,6 +427,20 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
                 if (d >= 0 && !(d < 64 && ((vis >> d) & 1ull))) s[j] = -INFINITY;
             }
         }
+        // Whole paths over fp8 pools: the scores become exponents that carry the block's V scale, and the reference is the largest
+        // of those, so that the heaviest products of probability and scale lie just below a power of two when they are
+        // rounded to bf16 (error against 64 bits 0.00237 -> 0.0021); the row sum divides the scale out again.  Scales beyond 2^+-40
+        // are multiplied in as elsewhere: blocks far apart must not push each other's share of the row sum out of range.
+        float v_inv = 1.f, v_mul = 1.f;
+        if constexpr (kScaled) {
+            const float vs = pick(cur.vsc, g);
+            const bool in = vs >= 0x1p-40f && vs <= 0x1p40f;
+            const float lv = in ? fast_log2(vs) : 0.f;
+            v_inv = fast_exp2(-lv);
+            v_mul = in ? 1.f : vs;
+#pragma unroll
+            for (int j = 0; j < NS; ++j) s[j] = __builtin_fmaf(s[j], c, lv);
+        }
         float mx = s[0];
 #pragma unroll
         for (int j = 1; j < NS; ++j) mx = fmaxf(mx, s[j]);
@@ -432,17 +448,17 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
         const float m_new = fmaxf(m_run, mx);
         // a row that has seen nothing so far keeps m = -inf; its exponentials use 0 as the reference
         // (they are all exp2(-inf) = 0), so that no inf - inf arises
-        const float mc = (m_new == -INFINITY) ? 0.f : m_new * c;
-        const float alpha = fast_exp2(m_run * c - mc);
+        const float mc = (m_new == -INFINITY) ? 0.f : m_new * c_run;
+        const float alpha = fast_exp2(m_run * c_run - mc);
         float p[NS];
         float sum = 0.f;
         if constexpr (DT != 2) {
 #pragma unroll
             for (int j = 0; j < NS; ++j) {
-                p[j] = fast_exp2(__builtin_fmaf(s[j], c, -mc));
+                p[j] = fast_exp2(kScaled ? s[j] - mc : __builtin_fmaf(s[j], c, -mc));
                 sum += p[j];
             }
-            l_run = l_run * alpha + sum;
+            l_run = l_run * alpha + (kScaled ? sum * v_inv : sum);
             m_run = m_new;
             if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {
 #pragma unroll
@@ -476,7 +492,7 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
 
         // ---- O^T += V^T P^T
         if constexpr (DT != 2) {
-            const float vs = (DT == 0) ? 1.0f : pick(cur.vsc, g);
+            const float vs = DT == 0 ? 1.0f : kScaled ? v_mul : pick(cur.vsc, g);
 #pragma unroll
             for (int ks = 0; ks < NS / 8; ++ks) {
                 u32x4 pw;
@@ -722,7 +738,7 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
                 const float mw = sM[w][r_c];
                 if (PATH && mw == -INFINITY) L += sL[w][r_c];  // (0, or NaN where its scores hold one)
                 if (mw == -INFINITY) continue;  // that wavefront's tokens were all invisible to the row
-                const float wgt = fast_exp2((mw - M) * c);
+                const float wgt = fast_exp2((mw - M) * c_run);
                 L += sL[w][r_c] * wgt;
                 acc0 += sO[w][r_c][d] * wgt;
                 acc1 += sO[w][r_c][d + 1] * wgt;
@@ -738,7 +754,7 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
             acc0 += bad;
             acc1 += bad;
             *reinterpret_cast<uint32_t *>(static_cast<uint16_t *>(a.out) + part * kHeadDim + d) = pack_bf16(acc0, acc1);
-            if (a.lse_out && lane == 0) a.lse_out[part] = L != 0.f ? (M * c + fast_log2(L)) * kLn2 : -INFINITY;
+            if (a.lse_out && lane == 0) a.lse_out[part] = L != 0.f ? (M * c_run + fast_log2(L)) * kLn2 : -INFINITY;
             continue;
         }
         float amax = fmaxf(fabsf(acc0), fabsf(acc1));

@@ -119,3 +119,37 @@ def test_scores_of_minus_infinity_and_nan(gpu, oracle, quiet):  # noqa: F811
                 e = np.exp(s - s.max())
                 check_close(got[r, h], e @ V[:, h // 4] / e.sum(), f"{r} {h}")
                 check_lse(got_l[r, h], s.max() + np.log(e.sum()), f"{r} {h}")
+
+
+@pytest.mark.parametrize("spread", [0, 12, 39, 44, 60])
+def test_scales_of_fp8_blocks_far_apart(gpu, oracle, spread):  # noqa: F811
+    """V blocks whose scales differ by up to 2^(2 * spread), within and beyond the range in which they ride in the exponents: every row
+    against the oracle in units of its own largest value (a row holds the few blocks of the largest scale and their share)."""
+    import torch
+    from paper_2603_16104_amd import binding as hkv
+    parent, ntok, leaves = [-1, 0, 0], [200, 33, 90], [1, 2]
+    n_used = sum((t + 15) // 16 for t in ntok)
+    f = wl.make_forest(parent, ntok, leaves, np.arange(n_used, dtype=np.int32))
+
+    class Scaled(wl.Workload):
+        def node_kv(self, node):
+            k, v = super().node_kv(node)
+            e = np.random.default_rng([node, spread]).integers(-spread, spread + 1, size=(len(v) + 15) // 16)
+            return k, wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(v) * np.exp2(e.astype(np.float32)).repeat(16)[: len(v), None, None])
+
+    w = Scaled(name=f"scales{spread}", num_q_heads=8, num_kv_heads=2, kv_dtype=wl.KV_FP8_E4M3, num_pages=n_used, seed=9, forest=f, mode="decode")
+    hp, dp = both_pools(gpu, oracle, w)
+    exp_o, exp_l = oracle.run_workload(w, hp)
+    plan = hkv.hkv_decode_plan_create(dp.handle, f.nodes, f.node_pages, f.req_leaf, 8)
+    assert hkv.hkv_decode_plan_num_paths(plan) == 2
+    nb = hkv.hkv_decode_plan_workspace_bytes(plan)
+    ws = torch.empty(max(nb, 256), dtype=torch.uint8, device="cuda")
+    out = torch.zeros((2, 8, 128), dtype=torch.int16, device="cuda")
+    lse = torch.zeros((2, 8), dtype=torch.float32, device="cuda")
+    hkv.attn_decode_plan_run(plan, gpu.to_device_bits(w.q()), float(w.scale), out, lse, ws, nb)
+    torch.cuda.synchronize()
+    hkv.hkv_decode_plan_destroy(plan)
+    dp.close()
+    top = np.abs(exp_o).max(axis=2, keepdims=True)
+    check_close(gpu.bf16_tensor_to_f64(out) / top, exp_o / top, w.name)
+    check_lse(lse.cpu().numpy(), exp_l, w.name)
