@@ -352,7 +352,8 @@ typedef struct {
                                  for fp32 pools).  NULL: row i */
     /* ---- planner settings */
     int32_t leaf_chunk;       /* tokens per item of nodes read by at most 16 query rows; multiple of 16 */
-    int32_t shared_chunk;     /* tokens per item of nodes shared by more rows; multiple of 16, at most 2048 */
+    int32_t shared_chunk;     /* tokens per item of nodes shared by more rows; multiple of 16, at most 2048 (default: by
+                                 the estimated step, 128 to 2048) */
     int32_t max_rows;         /* query rows per item of such nodes: 16..64 */
     int32_t pack;             /* four short items per workgroup, one per wavefront: 1 never, 2 when the forest has
                                  more items than the chip holds at once (the default), 3 always */

@@ -733,7 +733,7 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     int leaf_chunk = std::max(256, (mean_leaf / leaf_split + 15) / 16 * 16);
     if (leaf_split == 1) leaf_chunk = 1 << 30;  // whole nodes
     int base_chunk = std::min(kMaxSharedItemTokens, std::max(512, std::min(mean_leaf, leaf_chunk) / 16 * 16));
-    // Long shared paths: every chunk costs each row below it one partial (written once, read once) and
+    // The default length; `estimate` below knows when another one is better.  Long shared paths: every chunk costs each row below it one partial (written once, read once) and
     // every item a start-up, while a long item is the last to finish; measured on forests with 2k to 9k
     // shared tokens the best chunk is about a sixth of the path, between 512 and 1024 tokens.  Beyond
     // 16k shared tokens the chunks grow further so that a row collects about 16 partials at most.
