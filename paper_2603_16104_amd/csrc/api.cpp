@@ -630,6 +630,11 @@ extern "C" int lse_merge_dense(const float *o_parts, const float *lse_parts, con
     return HKV_OK;
 }
 
+// Room for so many partials: o as fp16, lse, and the factor each one is to be multiplied by.
+static size_t partials_bytes(int64_t n) {
+    return align_up((size_t)n * HKV_HEAD_DIM * sizeof(uint16_t), 256) + 2 * align_up((size_t)n * sizeof(float), 256);
+}
+
 // ---------------------------------------------------------------------------------------------
 // decode planning
 //
@@ -643,8 +648,7 @@ extern "C" int lse_merge_dense(const float *o_parts, const float *lse_parts, con
 // (r, h) keeps its partials at (r*Hq + h)*max_parts + k.  The merge then needs no index lists,
 // only the number of partials per request.
 //
-// cut_more: nodes of few rows may be cut only to fill workgroup slots.  Returns whether some were.
-static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
+static void plan_items(hkv_decode_plan &pl) {
     const int G = pl.group;
     const int Hkv = pl.pool->d.num_kv_heads;
     const int n_nodes = (int)pl.nodes.size();
@@ -700,6 +704,67 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
                R * G >= std::max(tile_min_rows, kMinTileItemRows);
     };
     const bool fp8_pool = pl.pool->d.dtype == HKV_FP8_E4M3;
+    // The tile kernel's share of the chip: its persistent workgroups hold one compute unit each for as long as
+    // the other kernel streams its bytes, so their number follows from the two amounts of work (matrix
+    // arithmetic at about 3.5 TFLOP/s per compute unit against bytes at about 5.5 TB/s for the chip).
+    const int req_per_tile = std::max(1, 256 / G);
+    const bool tiles_first = pl.row_visibility;
+    if (tiles_first) pl.concurrent = false;
+    pl.tile_items.clear();
+    pl.tile_workgroups = 0;
+    int tile_chunk = kMaxTileItemTokens;
+    double step_seconds = 0;  // what streaming all the bytes of the step takes
+    {
+        double tile_flop = 0, other_bytes = 0, tile_bytes = 0;
+        int64_t tile_units = 0, tile_tokens_max = 0;
+        const double bytes_per_token = 2.0 * HKV_HEAD_DIM * (fp8_pool ? 1 : 2);
+        for (int v = 0; v < n_nodes; ++v) {
+            const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
+            if (pl.nodes[v].n_tokens == 0 || R == 0) continue;
+            if (tiled(v)) {
+                tile_flop += 4.0 * HKV_HEAD_DIM * pl.nodes[v].n_tokens * (double)R * pl.num_q_heads;
+                tile_units += (int64_t)((R + req_per_tile - 1) / req_per_tile) * Hkv;
+                tile_tokens_max = std::max<int64_t>(tile_tokens_max, pl.nodes[v].n_tokens);
+                tile_bytes += bytes_per_token * pl.nodes[v].n_tokens * Hkv;
+            } else {
+                other_bytes += bytes_per_token * pl.nodes[v].n_tokens * Hkv;
+            }
+        }
+        step_seconds = (other_bytes + tile_bytes) / 5.6e12;
+        if (tile_units > 0) {
+            const int n_cu = chip.n_cu;
+            int wgs = n_cu;
+            if (other_bytes > 0) {
+                const double t_other = other_bytes / 5.5e12;
+                wgs = (int)(tile_flop / (3.5e12 * t_other) + 0.999);
+                wgs = std::min(n_cu - 64, std::max(8, (wgs + 7) / 8 * 8));  // whole groups of 8: one per XCD
+            }
+            if (tiles_first) wgs = n_cu;
+            wgs = std::min(n_cu, or_default(opt.tile_workgroups, wgs));
+            pl.tile_workgroups = wgs;
+            // chunks: about one item per workgroup (a workgroup that is done gives its compute unit to the other
+            // items, and every chunk costs every row below the node a partial), more where the nodes are few
+            int64_t n_chunks = std::max<int64_t>(1, std::min<int64_t>((wgs + tile_units / 2) / tile_units, tile_tokens_max / 256));
+            if (tiles_first) {  // rounds of items at 1.45 us per 64 tokens and 4 us each, and what the partials cost
+                double best_us = 1e30;
+                for (int64_t n = (tile_tokens_max + kMaxTileItemTokens - 1) / kMaxTileItemTokens; n <= 8; ++n) {
+                    const int64_t blocks = (tile_tokens_max + 64 * n - 1) / (64 * n);
+                    const double us = (double)((tile_units * n + wgs - 1) / wgs) * (4.0 + 1.45 * blocks) + (double)n * pl.n_req * pl.num_q_heads * 264 * 2 / 4e6;
+                    if (us < best_us) {
+                        best_us = us;
+                        n_chunks = n;
+                    }
+                }
+            }
+            int64_t ch = ((tile_tokens_max + n_chunks - 1) / n_chunks + 63) / 64 * 64;
+            tile_chunk = (int)std::min<int64_t>(kMaxTileItemTokens, std::max<int64_t>(256, ch));
+            tile_chunk = std::min(kMaxTileItemTokens, or_default(opt.tile_chunk, tile_chunk)) / 16 * 16;
+        }
+    }
+    auto tile_pages = [&](int v) {  // of a chunk of a node that the tile kernel runs: equal chunks of whole blocks
+        const int n_chunks = (pl.nodes[v].n_tokens + tile_chunk - 1) / tile_chunk;
+        return (pl.nodes[v].n_pages + n_chunks - 1) / n_chunks;
+    };
     bool any_shared = false;
     double through = 0, unique = 0, few_tokens = 0;  // K/V tokens: of shared nodes through workgroups / from HBM, of the others
     for (int v = 0; v < n_nodes; ++v) {
@@ -769,7 +834,8 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
         bool cut_leaves, cut_to_fill;  // few-row nodes cut for packing; only to fill slots
         int shared_chunk, piece_tokens;
     };
-    auto lay_out = [&](const bool wide) {
+    // cut_more: nodes of few rows may be cut only to fill workgroup slots.
+    auto lay_out = [&](const bool wide, const bool cut_more) {
         Layout lay{wide, wide ? 2 * chip.n_cu : kNodeGroups, false, false, base_chunk, pack_tokens};
         if (leaf_split == 1 && pack_mode != 1 && opt.leaf_chunk == 0) {
             int64_t units = shared_units;
@@ -927,19 +993,28 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     // an item by its length alone.
     static const Coefficients kNarrowThere{0.98, 0.53, 0, 2.48, 0.86, 0.01, 0.31, 0.54, 0.55, 0, 0.68, 1.42, 0.182, 0.141, 0, 84.5, 0, 7.5};
     static const Coefficients kWideThere{1.60, 0.82, 0, 2.48, 0.86, 2.78, 0.24, 0.40, 0.52, 0, 0.36, 2.65, 0.182, 0.154, 0, 84.5, 0, 7.5};
-    struct Estimate {
-        double us;
-        int64_t parts;
+    // Partials per row of a layout (every row has a slot for as many as the longest list holds): chunks on the longest path.
+    auto parts_of = [&](const Layout &lay) {
+        std::vector<int32_t> n_chunks(classes.size()), chunks_to(n_nodes);
+        for (size_t c = 0; c < classes.size(); ++c) n_chunks[c] = cuts_of(lay, classes[c].tokens, classes[c].n_req).n_chunks;
+        int32_t parts = 1;
+        for (int v = 0; v < n_nodes; ++v) {
+            chunks_to[v] = pl.nodes[v].parent >= 0 ? chunks_to[pl.nodes[v].parent] : 0;
+            if (class_of[v] >= 0)
+                chunks_to[v] += n_chunks[class_of[v]];
+            else if (pl.node_req_indptr[v + 1] > pl.node_req_indptr[v] && tiled(v))
+                chunks_to[v] += (pl.nodes[v].n_pages + tile_pages(v) - 1) / tile_pages(v);
+            parts = std::max(parts, chunks_to[v]);
+        }
+        return parts;
     };
-    auto estimate_by = [&](const Layout &lay, const Coefficients &k) {
+    auto estimate_by = [&](const Layout &lay, int parts, const Coefficients &k) {
         const double token_mb = 2.0 * HKV_HEAD_DIM * (fp8_pool ? 1 : 2) * 1e-6;  // of one head
         const int tile_rows = lay.wide ? 32 : 16;
-        std::vector<int32_t> n_chunks(classes.size()), chunks_to(n_nodes);
         double n_items = 0;
         for (size_t c = 0; c < classes.size(); ++c) {
             const int R = classes[c].n_req;
-            n_chunks[c] = cuts_of(lay, classes[c].tokens, R).n_chunks;
-            n_items += (double)n_chunks[c] * classes[c].count * Hkv * (R * G > 16 ? (R + max_req_per_item - 1) / max_req_per_item : 1);
+            n_items += (double)cuts_of(lay, classes[c].tokens, R).n_chunks * classes[c].count * Hkv * (R * G > 16 ? (R + max_req_per_item - 1) / max_req_per_item : 1);
         }
         const bool packs = pack_mode == 3 || (pack_mode == 2 && n_items > lay.slots);
         constexpr int kBins = 512;  // durations in steps of 0.25 us
@@ -983,16 +1058,10 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
         }
         span *= 1.0 + k.full * std::min(1.0, n_wgs / lay.slots);
         issue = (issue + k.wg * n_wgs) / chip.n_cu;
-        int32_t parts = 1;
-        for (int v = 0; v < n_nodes; ++v) {
-            chunks_to[v] = (pl.nodes[v].parent >= 0 ? chunks_to[pl.nodes[v].parent] : 0) + (class_of[v] >= 0 ? n_chunks[class_of[v]] : 0);
-            parts = std::max(parts, chunks_to[v]);
-        }
         const double rows = 1e-6 * pl.n_req * pl.num_q_heads;
-        return Estimate{k.base + std::cbrt(span * span * span + issue * issue * issue + memory * memory * memory) + rows * (k.part * parts + k.row),
-                        (int64_t)pl.n_req * pl.num_q_heads * parts};
+        return k.base + std::cbrt(span * span * span + issue * issue * issue + memory * memory * memory) + rows * (k.part * parts + k.row);
     };
-    auto estimate = [&](const Layout &lay) { return estimate_by(lay, fp8_pool ? kFp8 : lay.wide ? kBf16Wide : kBf16Narrow); };
+    auto estimate = [&](const Layout &lay, int parts) { return estimate_by(lay, parts, fp8_pool ? kFp8 : lay.wide ? kBf16Wide : kBf16Narrow); };
     // Shared nodes, bf16 pools: shared::body or 16-row tiles.  An item alone takes two thirds as long in shared::body, but two
     // workgroups fill a compute unit where three with 16-row tiles do, so that on a full chip the two come to the same and
     // how the items fill it decides (one root of 512 tokens over 64 leaves of 128 tokens 22.3 us as 16-row tiles, 17.3 as 32-row
@@ -1002,99 +1071,65 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     // time in the mean, 14 lose more than 3 %; the best of all tried lengths and forms would give 0.882.  64 requests x 21 drafted
     // tokens x 32 heads over 2048 + 512, bf16: 138 us in chunks of 512 tokens, 106 in whole nodes; 9 requests x 8 heads below
     // each of 4 x 6996 tokens: 27.9 in chunks of 1024, 15.2 of 192.
-    // Plans whose partials fit the static workspace one way keep to the ways that fit, so that attn_decode_plan_run_static takes them.
+    // Plans whose partials fit the static workspace at that length keep to lengths that fit.
     const bool search = any_shared && !pl.fp8_matrix && opt.shared_chunk == 0 && opt.leaf_chunk == 0;
     const bool narrow_too = !fp8_pool && pl.tile_form <= 0, wide_too = any_shared && (fp8_pool || pl.tile_form >= 0);
-    auto too_many = [](const Estimate &e) { return e.parts * (int64_t)(HKV_HEAD_DIM * sizeof(uint16_t) + 2 * sizeof(float)) + 1024 > (int64_t)kStaticWorkspaceBytes; };
-    Layout lay = lay_out(wide_too && (fp8_pool || pl.tile_form > 0));
-    if (narrow_too && wide_too)
-        if (const Layout wide = lay_out(true); estimate_by(wide, kWideThere).us < 0.98 * estimate_by(lay, kNarrowThere).us) lay = wide;
-    if (search || pl.paths_us > 0) {
-        Estimate at = estimate(lay);
-        if (search) {
-            const bool fits = !too_many(at);
-            Layout best = lay;
-            double least = at.us;  // times the margin: 4 % in the same form, 8 % in the other
-            Estimate best_at = at;
+    auto too_many = [&](int parts) { return partials_bytes((int64_t)pl.n_req * pl.num_q_heads * parts) > kStaticWorkspaceBytes; };
+    auto of_default_length = [&](bool cut_more) {
+        Layout lay = lay_out(wide_too && (fp8_pool || pl.tile_form > 0), cut_more);
+        if (narrow_too && wide_too)
+            if (const Layout wide = lay_out(true, cut_more);
+                estimate_by(wide, parts_of(wide), kWideThere) < 0.98 * estimate_by(lay, parts_of(lay), kNarrowThere))
+                lay = wide;
+        return lay;
+    };
+    Layout lay = of_default_length(true);
+    // Every partial of the longest list is one of every row of the batch.  Where a form or the cutting of nodes to fill slots alone
+    // would take them beyond the static workspace (a batch of many heads in which few paths are long: 234 requests x 128 heads,
+    // 30 MB whole, 53 MB cut; 240 requests x 64 heads below 2 x 11984 and 80 x 2356 tokens, 24 MB as 32-row tiles, 36 MB as 16-row
+    // tiles), the shortest estimate of those within it is taken, so that attn_decode_plan_run_static takes the plan.
+    bool cut_more = true;
+    if (too_many(parts_of(lay))) {
+        double least = 1e30;
+        for (const bool cut : {true, false})
             for (const bool w : {false, true}) {
                 if (w ? !wide_too : !narrow_too) continue;
-                Layout l = lay_out(w);
+                const Layout l = lay_out(w, cut);
+                const int parts = parts_of(l);
+                const double us = too_many(parts) ? 1e30 : estimate(l, parts);
+                if (us >= least) continue;
+                least = us;
+                lay = l;
+                cut_more = cut;
+            }
+    }
+    if (search || pl.paths_us > 0) {
+        const int parts = parts_of(lay);
+        double at = estimate(lay, parts);
+        if (search) {
+            const bool fits = !too_many(parts);
+            Layout best = lay;
+            double least = at;  // times the margin: 4 % in the same form, 8 % in the other
+            for (const bool w : {false, true}) {
+                if (w ? !wide_too : !narrow_too) continue;
+                Layout l = lay_out(w, cut_more);
                 l.piece_tokens = pack_tokens;
                 for (const int chunk : {128, 192, 256, 384, 512, 768, 1024, 1536, 2048}) {
                     l.shared_chunk = chunk;
-                    const Estimate e = estimate(l);
-                    const double us = e.us / (w == lay.wide ? 0.96 : 0.92);
-                    if (us >= least || (fits && too_many(e))) continue;
+                    const int l_parts = parts_of(l);
+                    if (fits && too_many(l_parts)) continue;
+                    const double e = estimate(l, l_parts), us = e / (w == lay.wide ? 0.96 : 0.92);
+                    if (us >= least) continue;
                     least = us;
                     best = l;
-                    best_at = e;
+                    at = e;
                 }
             }
             lay = best;
-            at = best_at;
         }
-        if (pl.paths_us > 0) pl.items_us = at.us;
+        if (pl.paths_us > 0) pl.items_us = at;
     }
     pl.has_shared = lay.wide;
-    const bool cut_to_fill = lay.cut_to_fill;
-    const int piece_tokens = lay.piece_tokens;
-    // The tile kernel's share of the chip: its persistent workgroups hold one compute unit each for as long as
-    // the other kernel streams its bytes, so their number follows from the two amounts of work (matrix
-    // arithmetic at about 3.5 TFLOP/s per compute unit against bytes at about 5.5 TB/s for the chip).
-    const int req_per_tile = std::max(1, 256 / G);
-    const bool tiles_first = pl.row_visibility;
-    if (tiles_first) pl.concurrent = false;
-    pl.tile_items.clear();
-    pl.tile_workgroups = 0;
-    int tile_chunk = kMaxTileItemTokens;
-    double step_seconds = 0;  // what streaming all the bytes of the step takes
-    {
-        double tile_flop = 0, other_bytes = 0, tile_bytes = 0;
-        int64_t tile_units = 0, tile_tokens_max = 0;
-        const double bytes_per_token = 2.0 * HKV_HEAD_DIM * (pl.pool->d.dtype == HKV_FP8_E4M3 ? 1 : 2);
-        for (int v = 0; v < n_nodes; ++v) {
-            const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
-            if (pl.nodes[v].n_tokens == 0 || R == 0) continue;
-            if (tiled(v)) {
-                tile_flop += 4.0 * HKV_HEAD_DIM * pl.nodes[v].n_tokens * (double)R * pl.num_q_heads;
-                tile_units += (int64_t)((R + req_per_tile - 1) / req_per_tile) * Hkv;
-                tile_tokens_max = std::max<int64_t>(tile_tokens_max, pl.nodes[v].n_tokens);
-                tile_bytes += bytes_per_token * pl.nodes[v].n_tokens * Hkv;
-            } else {
-                other_bytes += bytes_per_token * pl.nodes[v].n_tokens * Hkv;
-            }
-        }
-        step_seconds = (other_bytes + tile_bytes) / 5.6e12;
-        if (tile_units > 0) {
-            const int n_cu = chip.n_cu;
-            int wgs = n_cu;
-            if (other_bytes > 0) {
-                const double t_other = other_bytes / 5.5e12;
-                wgs = (int)(tile_flop / (3.5e12 * t_other) + 0.999);
-                wgs = std::min(n_cu - 64, std::max(8, (wgs + 7) / 8 * 8));  // whole groups of 8: one per XCD
-            }
-            if (tiles_first) wgs = n_cu;
-            wgs = std::min(n_cu, or_default(opt.tile_workgroups, wgs));
-            pl.tile_workgroups = wgs;
-            // chunks: about one item per workgroup (a workgroup that is done gives its compute unit to the other
-            // items, and every chunk costs every row below the node a partial), more where the nodes are few
-            int64_t n_chunks = std::max<int64_t>(1, std::min<int64_t>((wgs + tile_units / 2) / tile_units, tile_tokens_max / 256));
-            if (tiles_first) {  // rounds of items at 1.45 us per 64 tokens and 4 us each, and what the partials cost
-                double best_us = 1e30;
-                for (int64_t n = (tile_tokens_max + kMaxTileItemTokens - 1) / kMaxTileItemTokens; n <= 8; ++n) {
-                    const int64_t blocks = (tile_tokens_max + 64 * n - 1) / (64 * n);
-                    const double us = (double)((tile_units * n + wgs - 1) / wgs) * (4.0 + 1.45 * blocks) + (double)n * pl.n_req * pl.num_q_heads * 264 * 2 / 4e6;
-                    if (us < best_us) {
-                        best_us = us;
-                        n_chunks = n;
-                    }
-                }
-            }
-            int64_t ch = ((tile_tokens_max + n_chunks - 1) / n_chunks + 63) / 64 * 64;
-            tile_chunk = (int)std::min<int64_t>(kMaxTileItemTokens, std::max<int64_t>(256, ch));
-            tile_chunk = std::min(kMaxTileItemTokens, or_default(opt.tile_chunk, tile_chunk)) / 16 * 16;
-        }
-    }
     struct Proto { DecodeItem it; int64_t cost; };
     std::vector<Proto> protos;
     std::vector<int32_t> node_chunks(n_nodes, 0), slot_base(n_nodes, 0);
@@ -1104,8 +1139,7 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
         int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
         if (nd.n_tokens == 0 || R == 0) continue;
         if (tiled(v)) {  // equal chunks of whole pages x equal request groups x KV heads, longest chunks first below
-            const int n_chunks = (nd.n_tokens + tile_chunk - 1) / tile_chunk;
-            const int pages_per_chunk = (nd.n_pages + n_chunks - 1) / n_chunks;
+            const int pages_per_chunk = tile_pages(v);
             node_chunks[v] = (nd.n_pages + pages_per_chunk - 1) / pages_per_chunk;
             const int n_groups = (R + req_per_tile - 1) / req_per_tile;
             const int req_per_group = (R + n_groups - 1) / n_groups;
@@ -1207,16 +1241,6 @@ static bool plan_items(hkv_decode_plan &pl, bool cut_more) {
     // blocks side by side, which works as long as no item synchronises per step (more than 16 query rows).
     pl.fused = !pl.tile_items.empty() && !pl.items.empty() && opt.fused >= 0 && !pl.fp8_matrix;
     for (const DecodeItem &it : pl.items) pl.fused = pl.fused && it.n_req * G <= 16;
-    return cut_to_fill || piece_tokens < pack_tokens;
-}
-
-// A piece more on one path is a partial more for every row of the batch.  Where that alone would take the partials beyond the
-// static workspace (a batch of many heads in which few paths are long: 234 requests x 128 heads, 30 MB whole, 53 MB cut), the
-// nodes stay whole, so that attn_decode_plan_run_static takes the plan.
-static void plan_items(hkv_decode_plan &pl) {
-    if (!plan_items(pl, true) || hkv_decode_plan_workspace_bytes(&pl) <= kStaticWorkspaceBytes) return;
-    plan_items(pl, false);
-    if (hkv_decode_plan_workspace_bytes(&pl) > kStaticWorkspaceBytes) plan_items(pl, true);
 }
 
 // Small steps.  The items' kernel and the merge are two launches, each a chain of dependent round trips (plan, blocks, K/V;
@@ -1831,8 +1855,7 @@ extern "C" int hkv_decode_plan_destroy(hkv_decode_plan *plan) {
 
 extern "C" size_t hkv_decode_plan_workspace_bytes(const hkv_decode_plan *plan) {
     if (!plan || plan->pool->d.dtype == HKV_FP32) return 0;
-    return align_up((size_t)plan->n_parts * HKV_HEAD_DIM * sizeof(uint16_t), 256) +
-           2 * align_up((size_t)plan->n_parts * sizeof(float), 256);
+    return partials_bytes(plan->n_parts);
 }
 
 extern "C" int32_t hkv_decode_plan_num_items(const hkv_decode_plan *plan) {

@@ -675,6 +675,26 @@ def test_cutting_nodes_keeps_a_plan_within_the_static_workspace(dtype, n_req, sh
     hkv.kv_pool_destroy(pool)
 
 
+@pytest.mark.parametrize("heads, tokens, fan", [((64, 8), (11984, 2356, 478), (2, 40, 3)), ((40, 8), (6175, 914, 370), (1, 46, 18))])
+def test_form_and_chunks_keep_a_plan_within_the_static_workspace(heads, tokens, fan):
+    """Long roots that the tile kernel runs, shared nodes beside them, leaves of 70 to 100 % of a length: 32-row tiles at the default
+    chunk length leave 24 and 26 MB of partials, the tiles' among them; 16-row tiles, 2 % from the others' estimate, 36 and 35 MB."""
+    rng = np.random.default_rng(0)
+    parent, ntok, level = [], [], [-1]
+    for d, (t, n) in enumerate(zip(tokens, fan)):
+        parent += [p for p in level for _ in range(n)]
+        level = list(range(len(ntok), len(parent)))
+        ntok += [t] * len(level) if d < 2 else rng.integers(int(0.7 * t), t + 1, size=len(level)).tolist()
+    n_pages = sum(-(-t // 16) for t in ntok)
+    f = wl.make_forest(parent, ntok, level, np.arange(n_pages, dtype=np.int32))
+    pool = fake_pool(n_pages, heads[1])
+    plan = hkv.hkv_decode_plan_create(pool, f.nodes, f.node_pages, f.req_leaf, heads[0], hkv.PLAN_HOST_ONLY)
+    assert hkv.hkv_decode_plan_num_tile_items(plan) > 0
+    assert hkv.hkv_decode_plan_workspace_bytes(plan) <= hkv.hkv_static_workspace_bytes()
+    hkv.hkv_decode_plan_destroy(plan)
+    hkv.kv_pool_destroy(pool)
+
+
 def items_of(parent, ntok, leaves, hq, hk, dtype=hkv.BF16, T=1, flags=0):
     """Work items of a host-only plan over a forest in page order, and whether shared ones run as 32-row tiles."""
     f = wl.make_forest(parent, ntok, leaves, np.arange(sum((t + 15) // 16 for t in ntok), dtype=np.int32))
