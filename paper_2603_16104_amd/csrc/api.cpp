@@ -95,6 +95,7 @@ struct hkv_decode_plan {
     int32_t path_stride = 0, n_paths = 0, path_waves = 0;
     double paths_us = 0, items_us = 0;  // estimates of a step; paths_us = 0: paths are out of the question, items_us is not asked for
     int32_t *d_paths = nullptr;
+    int32_t restart_tokens = kMaxSharedItemTokens;  // a stretch of a shared node's item with one reference per row
     bool row_visibility = false;  // several query tokens per request: rows see their last node in part
     bool concurrent = true;
     bool fused = false;  // both kinds of items go out as one launch (no item of `items` has more than 16 rows)
@@ -815,6 +816,7 @@ static void plan_items(hkv_decode_plan &pl) {
         if (longest > 16 * by_path) by_path = std::min<int64_t>(kMaxSharedItemTokens, (longest / 16 + 255) / 256 * 256);
         base_chunk = std::max(base_chunk, (int)by_path);
     }
+    const int default_chunk = base_chunk;
     leaf_chunk = or_default(opt.leaf_chunk, leaf_chunk) / 16 * 16;
     base_chunk = std::min(kMaxSharedItemTokens, or_default(opt.shared_chunk, base_chunk)) / 16 * 16;
     // Few-row nodes a little longer than what one wavefront takes alone (pack_tokens): run whole, their
@@ -1103,6 +1105,8 @@ static void plan_items(hkv_decode_plan &pl) {
                 cut_more = cut;
             }
     }
+    // Longer items than these take their rows' references anew at this length (rows_body.h): results no further off than with it.
+    pl.restart_tokens = std::max(64, (opt.shared_chunk ? default_chunk : lay.shared_chunk) / 64 * 64);
     if (search || pl.paths_us > 0) {
         const int parts = parts_of(lay);
         double at = estimate(lay, parts);
@@ -1936,7 +1940,7 @@ static int run_decode_plan(hkv_decode_plan *plan, const void *q, float scale, vo
     const DecodeLaunch a{view_of(plan->pool), q, plan->d_items, plan->d_pages, plan->d_node_req_idx, o_parts, lse_parts,
                          down_parts, (int32_t)plan->items.size(), plan->num_q_heads, plan->max_parts, scale,
                          plan->d_row_leaf, plan->d_row_limit, plan->d_row_mask, plan->n_single, plan->n_stages,
-                         plan->fp8_matrix ? 1 : 0, plan->d_q_rows, plan->has_shared ? 1 : 0};
+                         plan->fp8_matrix ? 1 : 0, plan->d_q_rows, plan->has_shared ? 1 : 0, plan->restart_tokens};
     if (plan->path_waves) {
         DecodePathLaunch p{};
         static_cast<DecodeLaunch &>(p) = a;

@@ -97,6 +97,7 @@ struct DecodeLaunch {
     // Row r of the plan reads row q_rows[r] of q (device; null: row r).  Partials stay indexed by r.
     const int32_t *q_rows;
     int32_t has_shared;          // items shared by more than 16 query rows are run by shared::body
+    int32_t restart_tokens;      // bf16 pools: after so many tokens such an item takes its rows' references anew (a multiple of 64)
 };
 // Whole paths instead of items (of the base, what describes items is not read): a record of path_stride ints per leaf and up
 // to 16 / G of its rows, run by a workgroup per KV head, which writes out / lse_out (may be null) itself.

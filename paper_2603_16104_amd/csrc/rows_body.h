@@ -668,7 +668,28 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
                 step(std::false_type{}, last_tag, b, cur, cur);
             }
         };
-        for (int b = 0; b + 1 < n_blk; ++b) staged_step(std::false_type{}, b);
+        // bf16 pools, items longer than the default length: there the maximum begins anew, 2^4 below the row's maximum so far (what
+        // lies further down hardly counts).  The maximum is the one weight that bf16 holds exactly, and the next ones lie just
+        // below a power of two, where its rounding is finest; in a longer item those are a smaller share of the weights.  2048
+        // tokens, error against 64 bits: chunks of 512 0.00219, whole 0.00225, whole with restarts 0.00219.
+        float m_top = -INFINITY;
+        int restart_at = DT == 0 ? a.restart_tokens / TB : -1;
+        auto restart = [&](int b) {
+            if (b != restart_at) return;
+            restart_at += a.restart_tokens / TB;
+            m_top = fmaxf(m_top, m_run);
+            if (m_top == -INFINITY) return;
+            const float m_new = m_top - 4.0f / c, alpha = fast_exp2((m_run - m_new) * c);
+            m_run = m_new;
+            l_run *= alpha;
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt) o[dt] *= alpha;
+        };
+        for (int b = 0; b + 1 < n_blk; ++b) {
+            restart(b);
+            staged_step(std::false_type{}, b);
+        }
+        restart(n_blk - 1);
         staged_step(std::true_type{}, n_blk - 1);
         if (active) write_rows(req);
         return;
