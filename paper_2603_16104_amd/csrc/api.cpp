@@ -1085,54 +1085,56 @@ static void plan_items(hkv_decode_plan &pl) {
                 lay = wide;
         return lay;
     };
-    Layout lay = of_default_length(true);
-    // Every partial of the longest list is one of every row of the batch.  Where a form or the cutting of nodes to fill slots alone
-    // would take them beyond the static workspace (a batch of many heads in which few paths are long: 234 requests x 128 heads,
-    // 30 MB whole, 53 MB cut; 240 requests x 64 heads below 2 x 11984 and 80 x 2356 tokens, 24 MB as 32-row tiles, 36 MB as 16-row
-    // tiles), the shortest estimate of those within it is taken, so that attn_decode_plan_run_static takes the plan.
-    bool cut_more = true;
-    if (too_many(parts_of(lay))) {
-        double least = 1e30;
-        for (const bool cut : {true, false})
-            for (const bool w : {false, true}) {
-                if (w ? !wide_too : !narrow_too) continue;
-                const Layout l = lay_out(w, cut);
+    struct Choice {
+        Layout lay;
+        int32_t default_chunk;  // of the layout at the default length
+        int parts;
+        double us;
+    };
+    auto choose = [&](const Layout &from, bool cut_more) {
+        Choice best{from, from.shared_chunk, parts_of(from), 0};
+        if (!search && pl.paths_us == 0) return best;
+        best.us = estimate(from, best.parts);
+        if (!search) return best;
+        const bool fits = !too_many(best.parts);
+        double least = best.us;  // times the margin: 4 % in the same form, 8 % in the other
+        for (const bool w : {false, true}) {
+            if (w ? !wide_too : !narrow_too) continue;
+            Layout l = lay_out(w, cut_more);
+            l.piece_tokens = pack_tokens;
+            for (const int chunk : {128, 192, 256, 384, 512, 768, 1024, 1536, 2048}) {
+                l.shared_chunk = chunk;
                 const int parts = parts_of(l);
-                const double us = too_many(parts) ? 1e30 : estimate(l, parts);
+                if (fits && too_many(parts)) continue;
+                const double e = estimate(l, parts), us = e / (w == from.wide ? 0.96 : 0.92);
                 if (us >= least) continue;
                 least = us;
-                lay = l;
-                cut_more = cut;
+                best = Choice{l, from.shared_chunk, parts, e};
             }
-    }
-    // Longer items than these take their rows' references anew at this length (rows_body.h): results no further off than with it.
-    pl.restart_tokens = std::max(64, (opt.shared_chunk ? default_chunk : lay.shared_chunk) / 64 * 64);
-    if (search || pl.paths_us > 0) {
-        const int parts = parts_of(lay);
-        double at = estimate(lay, parts);
-        if (search) {
-            const bool fits = !too_many(parts);
-            Layout best = lay;
-            double least = at;  // times the margin: 4 % in the same form, 8 % in the other
-            for (const bool w : {false, true}) {
-                if (w ? !wide_too : !narrow_too) continue;
-                Layout l = lay_out(w, cut_more);
-                l.piece_tokens = pack_tokens;
-                for (const int chunk : {128, 192, 256, 384, 512, 768, 1024, 1536, 2048}) {
-                    l.shared_chunk = chunk;
-                    const int l_parts = parts_of(l);
-                    if (fits && too_many(l_parts)) continue;
-                    const double e = estimate(l, l_parts), us = e / (w == lay.wide ? 0.96 : 0.92);
-                    if (us >= least) continue;
-                    least = us;
-                    best = l;
-                    at = e;
-                }
-            }
-            lay = best;
         }
-        if (pl.paths_us > 0) pl.items_us = at;
+        return best;
+    };
+    // Every partial of the longest list is one of every row of the batch.  Where the cutting of nodes to fill slots, or the form, alone
+    // takes them beyond the static workspace, the nodes stay whole (a batch of many heads in which few paths are long: 234
+    // requests x 128 heads, 30 MB whole, 53 MB cut) or run in the other form (240 requests x 64 heads below 2 x 11984 and 80 x 2356
+    // tokens: 24 MB as 32-row tiles, 36 MB as 16-row tiles), so that attn_decode_plan_run_static takes the plan.
+    const Layout first = of_default_length(true);
+    Choice chosen = choose(first, true);
+    if (too_many(chosen.parts)) {
+        auto take_if_it_fits = [&](const Layout &from, bool cut_more) {
+            const Choice other = choose(from, cut_more);
+            if (too_many(other.parts)) return false;
+            chosen = other;
+            return true;
+        };
+        if (!take_if_it_fits(of_default_length(false), false) && narrow_too && wide_too)
+            for (const bool cut_more : {true, false})
+                if (take_if_it_fits(lay_out(!first.wide, cut_more), cut_more)) break;
     }
+    const Layout lay = chosen.lay;
+    pl.items_us = chosen.us;
+    // Longer items than these take their rows' references anew at this length (rows_body.h): results no further off than with it.
+    pl.restart_tokens = std::max(64, (opt.shared_chunk ? default_chunk : chosen.default_chunk) / 64 * 64);
     pl.has_shared = lay.wide;
     struct Proto { DecodeItem it; int64_t cost; };
     std::vector<Proto> protos;
