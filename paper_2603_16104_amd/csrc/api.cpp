@@ -837,7 +837,7 @@ static void plan_items(hkv_decode_plan &pl) {
         int shared_chunk, piece_tokens;
     };
     // cut_more: nodes of few rows may be cut only to fill workgroup slots.
-    auto lay_out = [&](const bool wide, const bool cut_more) {
+    auto lay_out_anew = [&](const bool wide, const bool cut_more) {
         Layout lay{wide, wide ? 2 * chip.n_cu : kNodeGroups, false, false, base_chunk, pack_tokens};
         if (leaf_split == 1 && pack_mode != 1 && opt.leaf_chunk == 0) {
             int64_t units = shared_units;
@@ -943,26 +943,13 @@ static void plan_items(hkv_decode_plan &pl) {
         }
         return lay;
     };
-    // Nodes of one length below the same number of requests, counted once; class_of: a node's entry (-1: no items of this kernel).
-    struct NodeClass {
-        int32_t tokens, n_req, count;
+    Layout laid_out[2][2];
+    bool is_laid_out[2][2] = {};
+    auto lay_out = [&](const bool wide, const bool cut_more) {
+        if (!is_laid_out[wide][cut_more]) laid_out[wide][cut_more] = lay_out_anew(wide, cut_more);
+        is_laid_out[wide][cut_more] = true;
+        return laid_out[wide][cut_more];
     };
-    std::vector<NodeClass> classes;
-    std::vector<int32_t> class_of(n_nodes, -1);
-    {
-        std::vector<std::pair<int64_t, int32_t>> keys;
-        keys.reserve(n_nodes);
-        for (int v = 0; v < n_nodes; ++v) {
-            const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
-            if (pl.nodes[v].n_tokens > 0 && R > 0 && !tiled(v)) keys.push_back({((int64_t)pl.nodes[v].n_tokens << 32) | R, v});
-        }
-        std::sort(keys.begin(), keys.end());
-        for (size_t i = 0; i < keys.size(); ++i) {
-            if (i == 0 || keys[i].first != keys[i - 1].first) classes.push_back({(int32_t)(keys[i].first >> 32), (int32_t)(keys[i].first & 0xFFFFFFFF), 0});
-            ++classes.back().count;
-            class_of[keys[i].second] = (int32_t)classes.size() - 1;
-        }
-    }
     struct Cuts {
         int n_chunks, per_chunk;  // blocks of a chunk; the last one may be shorter
     };
@@ -972,6 +959,81 @@ static void plan_items(hkv_decode_plan &pl) {
             chunk = lay.piece_tokens;  // equal pieces
         const int blocks = (T + HKV_PAGE_SIZE - 1) / HKV_PAGE_SIZE, most = (T + chunk - 1) / chunk, per_chunk = (blocks + most - 1) / most;
         return Cuts{(blocks + per_chunk - 1) / per_chunk, per_chunk};
+    };
+    // The estimates below look at up to 21 layouts.  Shared nodes of one length below the same number of requests are counted
+    // once; `above`: the next shared node on the way up (-1: none).
+    struct NodeClass {
+        int32_t tokens, n_req, count;
+    };
+    struct SharedNode {
+        int32_t cls, above;
+    };
+    std::vector<NodeClass> classes;
+    std::vector<SharedNode> shared_nodes;
+    std::vector<int32_t> shared_at(any_shared ? n_nodes : 0);  // the last shared node down to a node (-1: none)
+    if (any_shared) {
+        std::vector<std::pair<int64_t, int32_t>> keys;
+        for (int v = 0; v < n_nodes; ++v) {
+            const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
+            shared_at[v] = pl.nodes[v].parent >= 0 ? shared_at[pl.nodes[v].parent] : -1;
+            if (pl.nodes[v].n_tokens == 0 || R * G <= 16 || tiled(v)) continue;
+            keys.push_back({((int64_t)pl.nodes[v].n_tokens << 32) | R, (int32_t)shared_nodes.size()});
+            shared_nodes.push_back({0, shared_at[v]});
+            shared_at[v] = (int32_t)shared_nodes.size() - 1;
+        }
+        std::sort(keys.begin(), keys.end());
+        for (size_t i = 0; i < keys.size(); ++i) {
+            if (i == 0 || keys[i].first != keys[i - 1].first) classes.push_back({(int32_t)(keys[i].first >> 32), (int32_t)(keys[i].first & 0xFFFFFFFF), 0});
+            ++classes.back().count;
+            shared_nodes[keys[i].second].cls = (int32_t)classes.size() - 1;
+        }
+    }
+    // The other nodes, the same at every chunk length: items of few rows by 32-token steps and by whether one wavefront may
+    // take them alone; chunks on the longest path down to the last node without (entry 0) and below each shared one.
+    struct FewItems {
+        int32_t steps;
+        bool packable;
+        double n;
+    };
+    struct Others {
+        bool cut_leaves;
+        int32_t piece_tokens;
+        std::vector<FewItems> few;
+        double n_few;
+        std::vector<int32_t> chunks;
+    };
+    std::vector<Others> known;
+    auto others_of = [&](const Layout &lay) -> const Others & {
+        for (const Others &o : known)
+            if (o.cut_leaves == lay.cut_leaves && o.piece_tokens == lay.piece_tokens) return o;
+        Others o{lay.cut_leaves, lay.piece_tokens, {}, 0, std::vector<int32_t>(shared_nodes.size() + 1, 0)};
+        std::vector<int32_t> chunks_to(n_nodes), count[2];
+        for (int v = 0; v < n_nodes; ++v) {
+            const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v], T = pl.nodes[v].n_tokens;
+            chunks_to[v] = pl.nodes[v].parent >= 0 ? chunks_to[pl.nodes[v].parent] : 0;
+            if (T > 0 && R > 0) {
+                if (tiled(v)) {
+                    chunks_to[v] += (pl.nodes[v].n_pages + tile_pages(v) - 1) / tile_pages(v);
+                } else if (R * G <= 16) {
+                    const Cuts cut = cuts_of(lay, T, R);
+                    const int tokens = std::min(T, cut.per_chunk * HKV_PAGE_SIZE), steps = (tokens + 31) / 32;
+                    std::vector<int32_t> &c = count[tokens <= pack_tokens];
+                    if ((int)c.size() <= steps) c.resize(steps + 1);
+                    c[steps] += cut.n_chunks;
+                    chunks_to[v] += cut.n_chunks;
+                }
+            }
+            int32_t &most = o.chunks[any_shared ? shared_at[v] + 1 : 0];
+            most = std::max(most, chunks_to[v]);
+        }
+        for (int packable = 0; packable < 2; ++packable)
+            for (size_t steps = 0; steps < count[packable].size(); ++steps)
+                if (count[packable][steps]) {
+                    o.few.push_back({(int32_t)steps, packable != 0, (double)count[packable][steps] * Hkv});
+                    o.n_few += o.few.back().n;
+                }
+        known.push_back(std::move(o));
+        return known.back();
     };
     // A layout's step, us: three times that run beside each other (as a 3-norm), and what the partials cost.  Latency: the
     // workgroups, longest first, on the chip's slots, stretched on a full chip.  Issue, per compute unit: per 64 tokens of an item
@@ -996,39 +1058,30 @@ static void plan_items(hkv_decode_plan &pl) {
     static const Coefficients kNarrowThere{0.98, 0.53, 0, 2.48, 0.86, 0.01, 0.31, 0.54, 0.55, 0, 0.68, 1.42, 0.182, 0.141, 0, 84.5, 0, 7.5};
     static const Coefficients kWideThere{1.60, 0.82, 0, 2.48, 0.86, 2.78, 0.24, 0.40, 0.52, 0, 0.36, 2.65, 0.182, 0.154, 0, 84.5, 0, 7.5};
     // Partials per row of a layout (every row has a slot for as many as the longest list holds): chunks on the longest path.
+    std::vector<int32_t> class_chunks(classes.size()), shared_chunks_to(shared_nodes.size());
     auto parts_of = [&](const Layout &lay) {
-        std::vector<int32_t> n_chunks(classes.size()), chunks_to(n_nodes);
-        for (size_t c = 0; c < classes.size(); ++c) n_chunks[c] = cuts_of(lay, classes[c].tokens, classes[c].n_req).n_chunks;
-        int32_t parts = 1;
-        for (int v = 0; v < n_nodes; ++v) {
-            chunks_to[v] = pl.nodes[v].parent >= 0 ? chunks_to[pl.nodes[v].parent] : 0;
-            if (class_of[v] >= 0)
-                chunks_to[v] += n_chunks[class_of[v]];
-            else if (pl.node_req_indptr[v + 1] > pl.node_req_indptr[v] && tiled(v))
-                chunks_to[v] += (pl.nodes[v].n_pages + tile_pages(v) - 1) / tile_pages(v);
-            parts = std::max(parts, chunks_to[v]);
+        const Others &others = others_of(lay);
+        for (size_t c = 0; c < classes.size(); ++c) class_chunks[c] = cuts_of(lay, classes[c].tokens, classes[c].n_req).n_chunks;
+        int32_t parts = std::max(1, others.chunks[0]);
+        for (size_t i = 0; i < shared_nodes.size(); ++i) {
+            const SharedNode &n = shared_nodes[i];
+            shared_chunks_to[i] = (n.above >= 0 ? shared_chunks_to[n.above] : 0) + class_chunks[n.cls];
+            parts = std::max(parts, shared_chunks_to[i] + others.chunks[i + 1]);
         }
         return parts;
     };
     auto estimate_by = [&](const Layout &lay, int parts, const Coefficients &k) {
         const double token_mb = 2.0 * HKV_HEAD_DIM * (fp8_pool ? 1 : 2) * 1e-6;  // of one head
         const int tile_rows = lay.wide ? 32 : 16;
-        double n_items = 0;
-        for (size_t c = 0; c < classes.size(); ++c) {
-            const int R = classes[c].n_req;
-            n_items += (double)cuts_of(lay, classes[c].tokens, R).n_chunks * classes[c].count * Hkv * (R * G > 16 ? (R + max_req_per_item - 1) / max_req_per_item : 1);
-        }
+        const Others &others = others_of(lay);
+        double n_items = others.n_few;
+        for (const NodeClass &c : classes)
+            n_items += (double)cuts_of(lay, c.tokens, c.n_req).n_chunks * c.count * Hkv * ((c.n_req + max_req_per_item - 1) / max_req_per_item);
         const bool packs = pack_mode == 3 || (pack_mode == 2 && n_items > lay.slots);
         constexpr int kBins = 512;  // durations in steps of 0.25 us
-        double bins[kBins] = {}, n_wgs = 0, work = 0, longest_us = 0, issue = 0, memory = 0;
+        double bins[kBins] = {}, n_wgs = 0, work = 0, longest_us = 0, issue = 0, memory = few_tokens * Hkv * token_mb * k.mem_few;
         int top = 0;
-        auto add = [&](double n, int tokens, int rows, bool many) {
-            const int blocks = (tokens + 63) / 64, steps = (tokens + 31) / 32;
-            const bool packed = packs && !many && tokens <= pack_tokens;
-            const double us = packed ? k.pack0 + k.pack1 * steps : !many ? k.few0 + k.few1 * ((tokens + 127) / 128) : (k.many0 + k.many1 * (lay.wide ? blocks : steps)) * (1.0 + k.tall * (rows / 64.0 - 1.0));
-            issue += n * blocks * (many ? k.block + k.tile * ((rows + tile_rows - 1) / tile_rows) : k.few_block);
-            if (many) memory += n * tokens * token_mb * k.l2;
-            const double wgs = packed ? 0.25 * n : n;
+        auto add = [&](double wgs, double us) {
             n_wgs += wgs;
             work += wgs * us;
             longest_us = std::max(longest_us, us);
@@ -1036,22 +1089,29 @@ static void plan_items(hkv_decode_plan &pl) {
             bins[bin] += wgs;
             top = std::max(top, bin);
         };
+        auto add_few = [&](double n, int steps, bool packed) {
+            issue += n * ((steps + 1) / 2) * k.few_block;
+            packed ? add(0.25 * n, k.pack0 + k.pack1 * steps) : add(n, k.few0 + k.few1 * ((steps + 3) / 4));
+        };
+        auto add_many = [&](double n, int tokens, int rows) {
+            const int blocks = (tokens + 63) / 64, steps = (tokens + 31) / 32;
+            issue += n * blocks * (k.block + k.tile * ((rows + tile_rows - 1) / tile_rows));
+            memory += n * tokens * token_mb * k.l2;
+            add(n, (k.many0 + k.many1 * (lay.wide ? blocks : steps)) * (1.0 + k.tall * (rows / 64.0 - 1.0)));
+        };
+        for (const FewItems &f : others.few) add_few(f.n, f.steps, packs && f.packable);
         for (const NodeClass &c : classes) {
             const int T = c.tokens, R = c.n_req;
             const Cuts cut = cuts_of(lay, T, R);
             const int tokens = std::min(T, cut.per_chunk * HKV_PAGE_SIZE);
             const double n = (double)c.count * cut.n_chunks * Hkv;
-            memory += (double)c.count * T * Hkv * token_mb * (R * G > 16 ? k.mem_shared : k.mem_few);
-            if (R * G <= 16) {
-                add(n, tokens, R * G, false);
-                continue;
-            }
+            memory += (double)c.count * T * Hkv * token_mb * k.mem_shared;
             const int groups = (R + max_req_per_item - 1) / max_req_per_item, rest = R - (groups - 1) * max_req_per_item;
             if (k.tile > 0 && !lay.wide && !fp8_pool && groups > 1 && rest * G <= 16) {  // (the remainder beside 16-row tiles, as below)
-                add(n * (groups - 1), tokens, max_req_per_item * G, true);
-                add(n, tokens, rest * G, false);
+                add_many(n * (groups - 1), tokens, max_req_per_item * G);
+                add_few(n, (tokens + 31) / 32, packs && tokens <= pack_tokens);
             } else {
-                add(n * groups, tokens, (R + groups - 1) / groups * G, true);
+                add_many(n * groups, tokens, (R + groups - 1) / groups * G);
             }
         }
         double span = std::max(longest_us, work / lay.slots), seen = 0;
@@ -1102,7 +1162,10 @@ static void plan_items(hkv_decode_plan &pl) {
             if (w ? !wide_too : !narrow_too) continue;
             Layout l = lay_out(w, cut_more);
             l.piece_tokens = pack_tokens;
+            bool whole = false;  // every node is, at this length and at those behind it
             for (const int chunk : {128, 192, 256, 384, 512, 768, 1024, 1536, 2048}) {
+                if (whole) break;
+                whole = chunk >= classes.back().tokens;
                 l.shared_chunk = chunk;
                 const int parts = parts_of(l);
                 if (fits && too_many(parts)) continue;
