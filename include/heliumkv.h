@@ -360,7 +360,8 @@ typedef struct {
     int32_t pack_tokens;      /* longest item of that mode, tokens */
     int32_t stages;           /* 16 KiB LDS stages a workgroup owns: 3..5 (3 counts as 4 where items run as 32-row tiles) */
     int32_t interleave;       /* items shared by many rows and items of few rows are listed side by side in
-                                 groups of this size (default 8); -1: one class after the other */
+                                 groups of this size (default 8, rounded up to whole sets of KV heads), the few rows'
+                                 share always in whole sets; -1: one class after the other */
     int32_t tile_min_rows;    /* nodes shared by this many query rows or more may go to the 256-row tile kernel
                                  (default 128, at least 65) ... */
     int32_t tile_min_gflop;   /* ... if the forest holds this much such work (default 40); -1: whatever the amount.  With
@@ -412,9 +413,9 @@ int32_t hkv_decode_plan_has_stream(const hkv_decode_plan *plan);
 /* 1 if the plan holds items of 17 to 64 query rows and runs them as 32-row tiles x token halves, else 0. */
 int32_t hkv_decode_plan_has_wide_tiles(const hkv_decode_plan *plan);
 /* Small steps run whole root-to-leaf paths in one launch, without items and partials, where the library estimates that to be
- * faster and the caller has neither set a planner parameter nor asked for a form of the items: the number of paths (a
- * leaf and up to 16 * num_kv_heads / num_q_heads of its rows each; a workgroup per KV head runs one), else 0.  What is said
- * of the plan's items, partials and workspace stands either way. */
+ * faster and the caller has neither set a planner parameter (other than to its stated default) nor asked for a form of the
+ * items: the number of paths (a leaf and up to 16 * num_kv_heads / num_q_heads of its rows each; a workgroup per KV head
+ * runs one), else 0.  What is said of the plan's items, partials and workspace stands either way. */
 int32_t hkv_decode_plan_num_paths(const hkv_decode_plan *plan);
 /* Workgroups of the per-node kernel: one per item, except that in forests with more items than the
  * chip holds at once the short items of at most 16 query rows (listed last) share a workgroup four

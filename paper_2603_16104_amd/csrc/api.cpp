@@ -1565,6 +1565,11 @@ static int create_decode_plan(hkv_pool *pool, const hkv_node *nodes, int32_t n_n
     pl->opt.visible = nullptr;
     pl->row_visibility = (flags & kPlanRowVisibility) != 0;
     pl->concurrent = !(flags & HKV_PLAN_ONE_STREAM);
+    // the documented default of a setting is the library's own choice, as 0 is
+    if (pl->opt.pack == 2) pl->opt.pack = 0;
+    if (pl->opt.interleave == 8) pl->opt.interleave = 0;
+    if (pl->opt.tile_min_rows == 128) pl->opt.tile_min_rows = 0;
+    if (pl->opt.tile_min_gflop == 40 && !pl->row_visibility) pl->opt.tile_min_gflop = 0;
     if (int rc = build_node_req_csr(nodes, n_nodes, req_leaf, n_req, pl->node_req_indptr, pl->node_req_idx,
                                     "hkv_decode_plan_create")) {
         delete pl;

@@ -10,7 +10,7 @@ from test_gpu_parity import both_pools, check_close, check_lse, gpu  # noqa: F40
 
 pytestmark = pytest.mark.gpu
 
-FORMS = [{}, {"interleave": 8}]      # the library's choice; a planner setting (here its default): items
+FORMS = [{}, {"tile_workgroups": 8}]     # the library's choice; a planner setting (one that these plans have no use for): items
 FORESTS = {
     "one_token": ([-1], [1], [0], 1),
     "block_edges": ([-1, 0, 0, 0], [16, 15, 16, 17], [1, 2, 3], 1),

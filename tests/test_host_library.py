@@ -757,7 +757,9 @@ def test_few_long_nodes_are_cut_in_both_forms(flags):
     (hkv.BF16, (240, 80), 16, (32, 8), {}, True), (hkv.FP8_E4M3, (240, 80), 64, (32, 8), {}, True),
     (hkv.BF16, (2000, 600), 64, (32, 8), {}, False), (hkv.FP8_E4M3, (240, 80), 512, (32, 8), {}, False),  # shared nodes read too often
     (hkv.BF16, (2000, 600), 1, (8, 2), {}, False),                                                        # more than a few workgroups stream in time
-    (hkv.BF16, (240, 80), 16, (32, 8), {"interleave": 8}, False), (hkv.BF16, (240, 80), 16, (32, 8), {"reserve_tokens": 4}, False),
+    (hkv.BF16, (240, 80), 16, (32, 8), {"tile_workgroups": 8}, False), (hkv.BF16, (240, 80), 16, (32, 8), {"interleave": 16}, False),
+    (hkv.BF16, (240, 80), 16, (32, 8), {"interleave": 8, "pack": 2, "tile_min_rows": 128, "tile_min_gflop": 40}, True),   # the defaults
+    (hkv.BF16, (240, 80), 16, (35, 5), {"interleave": 8}, True), (hkv.BF16, (240, 80), 16, (32, 8), {"reserve_tokens": 4}, False),
     (hkv.BF16, (240, 80), 16, (32, 8), {"flags": hkv.PLAN_NARROW_TILES}, False), (hkv.FP8_E4M3, (240, 80), 16, (32, 8), {"flags": hkv.PLAN_FP8_MATRIX}, False),
     (hkv.BF16, (240, 80), 4, (8, 2), {"tokens_per_req": 8}, True),
 ])
