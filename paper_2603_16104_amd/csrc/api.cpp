@@ -766,10 +766,11 @@ static void plan_items(hkv_decode_plan &pl) {
         const int n_chunks = (pl.nodes[v].n_tokens + tile_chunk - 1) / tile_chunk;
         return (pl.nodes[v].n_pages + n_chunks - 1) / n_chunks;
     };
-    bool any_shared = false;
+    bool any_shared = false, any_tiled = false;
     double through = 0, unique = 0, few_tokens = 0;  // K/V tokens: of shared nodes through workgroups / from HBM, of the others
     for (int v = 0; v < n_nodes; ++v) {
         const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
+        any_tiled = any_tiled || (R > 0 && tiled(v));
         if (pl.nodes[v].n_tokens == 0 || R == 0 || tiled(v)) continue;
         if (R * G > 16) {
             any_shared = true;
@@ -1146,13 +1147,12 @@ static void plan_items(hkv_decode_plan &pl) {
         return lay;
     };
     struct Choice {
-        Layout lay;
-        int32_t default_chunk;  // of the layout at the default length
+        Layout lay, from;  // from: the one at the default length
         int parts;
         double us;
     };
     auto choose = [&](const Layout &from, bool cut_more) {
-        Choice best{from, from.shared_chunk, parts_of(from), 0};
+        Choice best{from, from, parts_of(from), 0};
         if (!search && pl.paths_us == 0) return best;
         best.us = estimate(from, best.parts);
         if (!search) return best;
@@ -1172,7 +1172,7 @@ static void plan_items(hkv_decode_plan &pl) {
                 const double e = estimate(l, parts), us = e / (w == from.wide ? 0.96 : 0.92);
                 if (us >= least) continue;
                 least = us;
-                best = Choice{l, from.shared_chunk, parts, e};
+                best = Choice{l, from, parts, e};
             }
         }
         return best;
@@ -1194,10 +1194,13 @@ static void plan_items(hkv_decode_plan &pl) {
             for (const bool cut_more : {true, false})
                 if (take_if_it_fits(lay_out(!first.wide, cut_more), cut_more)) break;
     }
-    const Layout lay = chosen.lay;
+    // Paths instead of items (estimate_paths): the items are described as ever, their workspace is that of the default length.
     pl.items_us = chosen.us;
+    const bool paths = pl.paths_us > 0 && !any_tiled && pl.paths_us <= 0.97 * pl.items_us;
+    if (!paths) pl.n_paths = pl.path_waves = 0;
+    const Layout lay = paths && !too_many(parts_of(chosen.from)) ? chosen.from : chosen.lay;
     // Longer items than these take their rows' references anew at this length (rows_body.h): results no further off than with it.
-    pl.restart_tokens = std::max(64, (opt.shared_chunk ? default_chunk : chosen.default_chunk) / 64 * 64);
+    pl.restart_tokens = std::max(64, (opt.shared_chunk ? default_chunk : chosen.from.shared_chunk) / 64 * 64);
     pl.has_shared = lay.wide;
     struct Proto { DecodeItem it; int64_t cost; };
     std::vector<Proto> protos;
@@ -1375,12 +1378,9 @@ static void estimate_paths(hkv_decode_plan &pl, RowsByLeaf &by) {
     pl.path_stride = (int32_t)((kPathBlocks + std::max<int64_t>(longest, 1) + 15) / 16 * 16);
 }
 
-// Behind plan_items: paths or items, and the paths' records.
+// The records of the paths that plan_items has left.
 static void plan_paths(hkv_decode_plan &pl, const RowsByLeaf &by) {
-    if (pl.paths_us == 0 || !pl.tile_items.empty() || pl.paths_us > 0.97 * pl.items_us) {
-        pl.n_paths = pl.path_waves = 0;
-        return;
-    }
+    if (pl.n_paths == 0) return;
     const int per_path = std::max(1, 16 / pl.group);
     pl.paths.assign((size_t)pl.path_stride * pl.n_paths, 0);
     int32_t *rec = pl.paths.data();

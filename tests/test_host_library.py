@@ -777,6 +777,20 @@ def test_plans_that_run_whole_paths(dtype, tokens, n_req, heads, params, paths):
     hkv.kv_pool_destroy(pool)
 
 
+def test_workspace_of_plans_that_run_whole_paths():
+    """They have no use for one, but a run asks for the items' at their default length: two partials per row, not one per 128 tokens."""
+    n_req, ntok = 64, [300] + [30 + 70 * r // 63 for r in range(64)]
+    n_used = sum((t + 15) // 16 for t in ntok)
+    f = wl.make_forest([-1] + [0] * n_req, ntok, list(range(1, n_req + 1)), np.arange(n_used, dtype=np.int32))
+    pool = fake_pool(n_used, 8)
+    plan = hkv.hkv_decode_plan_create(pool, f.nodes, f.node_pages, f.req_leaf, 32, hkv.PLAN_HOST_ONLY)
+    assert hkv.hkv_decode_plan_num_paths(plan) == n_req
+    assert hkv.hkv_decode_plan_max_parts(plan) == 2
+    assert hkv.hkv_decode_plan_workspace_bytes(plan) == n_req * 32 * 2 * (256 + 4 + 4)
+    hkv.hkv_decode_plan_destroy(plan)
+    hkv.kv_pool_destroy(pool)
+
+
 def test_merge_argument_validation():
     with pytest.raises(hkv.HkvError) as e:
         hkv.lse_merge(0x1000, 0x2000, 0x3000, 0x4000, 4, 0x5000, 7, stream=0)
