@@ -1196,7 +1196,7 @@ static void plan_items(hkv_decode_plan &pl) {
     }
     // Paths instead of items (estimate_paths): the items are described as ever, their workspace is that of the default length.
     pl.items_us = chosen.us;
-    const bool paths = pl.paths_us > 0 && !any_tiled && pl.paths_us <= 0.97 * pl.items_us;
+    const bool paths = pl.paths_us > 0 && !any_tiled && pl.paths_us <= 0.93 * pl.items_us;
     if (!paths) pl.n_paths = pl.path_waves = 0;
     const Layout lay = paths && !too_many(parts_of(chosen.from)) ? chosen.from : chosen.lay;
     // Longer items than these take their rows' references anew at this length (rows_body.h): results no further off than with it.
@@ -1320,9 +1320,12 @@ static void plan_items(hkv_decode_plan &pl) {
 // leaf (up to 16 of its rows) and KV head reads the path, shared nodes again for every leaf, and writes the result: one launch,
 // no partials.  What that takes, us: the launch and its chain, and the blocks a compute unit has to take in,
 // some 50 to 100 bytes per ns, more where the nodes are not in the L2 of every XCD that reads them.
-// (Coefficients and the margin from 860 random plans of 16 to 3500 tokens per path, timed in both forms with three sets of
-// inputs in turn: 10 % rms; 12 of those that run this way would be more than 3 % faster as items, 58 of the others this way.
-// Four requests over 256 + 32 + 17 tokens, bf16, 8 / 2 heads: 11.2 -> 6.6 us; 32 requests over 480 + 160 tokens, 32 / 8 heads:
+// (Coefficients from 860 random plans of 16 to 3500 tokens per path, timed in both forms with three sets of inputs in turn: 10 %
+// rms.  Paths where that is 7 % below the items' estimate: of 700 other plans 409 run this way, none of which is more than 2 % faster
+// as items, and 71 of the others would be more than 3 % faster this way; at 3 % 426 and two, 58.  What the estimate does not know is
+// that a few compute units get two of the longest paths: 38 leaves of 160 to 527 tokens below 496, 32 / 8 heads, bf16, 304 workgroups, 18.0
+// us as items, 21.3 this way, estimated at 0.937 of the items' time.
+// Four requests over 256 + 32 + 17 tokens, bf16, 8 / 2 heads: 10.7 -> 5.5 us; 32 requests over 480 + 160 tokens, 32 / 8 heads:
 // 17.3 -> 7.7; 64: 16.6 -> 13.3; 128: 22.5 as items, 23.7 this way.)
 // Eight wavefronts while every workgroup has a compute unit to itself, four where several share one (64 requests over 240 +
 // 80 tokens, fp8: 12.3 us with eight, 9.0 with four).

@@ -777,9 +777,22 @@ def test_plans_that_run_whole_paths(dtype, tokens, n_req, heads, params, paths):
     hkv.kv_pool_destroy(pool)
 
 
+def test_a_second_round_of_long_paths_runs_as_items():
+    """38 leaves of 158 to 527 tokens below 496, 8 KV heads: 304 workgroups, a few compute units would get two of the longest paths
+    (21.3 us; 18.0 as items)."""
+    ntok = [496] + np.random.default_rng(38).integers(158, 528, size=38).tolist()
+    n_used = sum((t + 15) // 16 for t in ntok)
+    f = wl.make_forest([-1] + [0] * 38, ntok, list(range(1, 39)), np.arange(n_used, dtype=np.int32))
+    pool = fake_pool(n_used, 8)
+    plan = hkv.hkv_decode_plan_create(pool, f.nodes, f.node_pages, f.req_leaf, 32, hkv.PLAN_HOST_ONLY)
+    assert hkv.hkv_decode_plan_num_paths(plan) == 0
+    hkv.hkv_decode_plan_destroy(plan)
+    hkv.kv_pool_destroy(pool)
+
+
 def test_workspace_of_plans_that_run_whole_paths():
     """They have no use for one, but a run asks for the items' at their default length: two partials per row, not one per 128 tokens."""
-    n_req, ntok = 64, [300] + [30 + 70 * r // 63 for r in range(64)]
+    n_req, ntok = 40, [300] + [30 + 70 * r // 39 for r in range(40)]
     n_used = sum((t + 15) // 16 for t in ntok)
     f = wl.make_forest([-1] + [0] * n_req, ntok, list(range(1, n_req + 1)), np.arange(n_used, dtype=np.int32))
     pool = fake_pool(n_used, 8)
