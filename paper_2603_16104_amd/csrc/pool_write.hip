@@ -197,7 +197,7 @@ __device__ __forceinline__ void pool_write_block(const PoolWriteLaunch &a, const
 // (row q of 16, column c) holds tokens 4 q .. 4 q + 3 of dims 8 c .. 8 c + 7, so that V's four codes of a dim make a word
 // of one lane and its dimension-major order is a transposition of words between the four rows, in the vector ALU.  Bound by the
 // chain load, maximum, quotients, store of one wavefront (up to about 4000 tokens x 8 heads a launch has all of them on the chip at
-// once): 4000 tokens 6.2 -> 5.2 us, 8192 tokens 11.1 -> 9.1 us against the general form, which passes V through LDS and the
+// once): 4096 tokens 5.9 -> 5.1 us, 8192 tokens 11.0 -> 9.1 us against the general form, which passes V through LDS and the
 // maxima over two barriers.  (bf16 pools have neither maxima nor codes: the same form took 5.9 instead of 5.4 us there.)
 __device__ __forceinline__ void transpose_rows(uint32_t (&x)[4]) {  // word d of row q <-> word q of row d
     const auto a = __builtin_amdgcn_permlane32_swap(x[0], x[2], false, false), b = __builtin_amdgcn_permlane32_swap(x[1], x[3], false, false);
@@ -250,16 +250,17 @@ __device__ __forceinline__ void write_whole_fp8_block(const PoolWriteLaunch &a, 
     }
 }
 
-// A run of tokens.  bf16 pools: workgroup (block, head).  fp8 pools: workgroup (block, pair of heads), wavefront w takes K (w even)
-// or V (w odd) of head w / 2 of the pair; a block that the call writes in part, its first or its last one, goes the general way,
+// A run of tokens: workgroup (block, head), or (PAIRS, large writes into fp8 pools) workgroup (block, pair of heads), of which
+// wavefront w takes K (w even) or V (w odd) of head w / 2 of the pair; a block that the call writes in part, its first or its last one, goes the general way,
 // the pair's second head by the workgroup in row n_pages + (whether it is the second such block) of the grid.
 __device__ __forceinline__ bool writes_whole(const PoolWriteLaunch &a, const int pi) {
     return pi * kPage >= a.first_slot && a.first_slot + a.n_tokens >= (pi + 1) * kPage;
 }
-template <int DT>
+template <int DT, bool PAIRS>
 __device__ __forceinline__ void pool_write_run(const PoolWriteLaunch &a, const int32_t *ids) {
-    if constexpr (DT == 0) {
-        pool_write_block<0>(a, blockIdx.x, ids[blockIdx.x], blockIdx.y, false, 0);
+    static_assert(DT == 1 || !PAIRS, "only fp8 blocks have the other form");
+    if constexpr (!PAIRS) {
+        pool_write_block<DT>(a, blockIdx.x, ids[blockIdx.x], blockIdx.y, false, 0);
         return;
     }
     const int x = blockIdx.x;
@@ -274,12 +275,12 @@ __device__ __forceinline__ void pool_write_run(const PoolWriteLaunch &a, const i
     }
 }
 
-template <int DT>
+template <int DT, bool PAIRS>
 __global__ __launch_bounds__(256) void pool_write_kernel(PoolWriteLaunch a) {
-    if (a.slots)
+    if (!PAIRS && a.slots)
         pool_write_block<DT>(a, blockIdx.x, a.page_ids[blockIdx.x], blockIdx.y, true, a.slots[blockIdx.x]);
     else
-        pool_write_run<DT>(a, a.page_ids);
+        pool_write_run<DT, PAIRS>(a, a.page_ids);
 }
 
 // A write of up to kMaxInlineWrite blocks (15 360 tokens): the block ids travel in the kernel arguments.  Through the
@@ -292,9 +293,9 @@ struct PoolWriteInline {
     int32_t block[N];
 };
 static_assert(sizeof(PoolWriteInline<kMaxInlineWrite>) <= 4096, "kernel argument segment");
-template <int DT, int N>
+template <int DT, bool PAIRS, int N>
 __global__ __launch_bounds__(256) void pool_write_inline_kernel(PoolWriteInline<N> a) {
-    pool_write_run<DT>(a.base, a.block);
+    pool_write_run<DT, PAIRS>(a.base, a.block);
 }
 
 // The decode step's append for up to kMaxInlineAppend sequences: block ids and slots travel in the kernel
@@ -429,7 +430,11 @@ hipError_t launch_pool_append_inline(const PoolAppendInline &a, hipStream_t s) {
 
 hipError_t launch_pool_write(const PoolWriteLaunch &a, hipStream_t s) {
     if (a.n_pages <= 0) return hipSuccess;
-    const bool pairs = a.dtype == 1 && !a.slots;
+    // A wavefront per K or V of a block takes longer alone than the four of a workgroup together; from 400 blocks x heads on that no
+    // longer counts (fp8, device time of a write, workgroup per block and head / this: 8 heads, 320 tokens 2.80 / 2.99 us, 500 3.10 /
+    // 3.33, 1000 3.51 / 3.26, 4096 5.89 / 5.08; 2 heads, 2000 tokens 2.88 / 3.06, 4096 3.20 / 3.22, 8192 3.99 / 3.72; 1 head, half
+    // of whose wavefronts would idle, 8192 3.19 / 3.36).
+    const bool pairs = a.dtype == 1 && !a.slots && a.num_kv_heads > 1 && (int64_t)a.n_pages * a.num_kv_heads >= 400;
     const int in_part = a.n_pages == 1 ? (a.first_slot > 0 || a.n_tokens < kPage) : (a.first_slot > 0) + ((a.first_slot + a.n_tokens) % kPage != 0);
     const dim3 grid(a.n_pages + (pairs ? in_part : 0), pairs ? (a.num_kv_heads + 1) / 2 : a.num_kv_heads), block(256);
     if (a.host_ids) {
@@ -441,9 +446,11 @@ hipError_t launch_pool_write(const PoolWriteLaunch &a, hipStream_t s) {
             std::copy(a.host_ids, a.host_ids + a.n_pages, w.block);
             std::fill(w.block + a.n_pages, w.block + N, 0);
             if (a.dtype == 0)
-                hipLaunchKernelGGL((pool_write_inline_kernel<0, N>), grid, block, 0, s, w);
+                hipLaunchKernelGGL((pool_write_inline_kernel<0, false, N>), grid, block, 0, s, w);
+            else if (!pairs)
+                hipLaunchKernelGGL((pool_write_inline_kernel<1, false, N>), grid, block, 0, s, w);
             else
-                hipLaunchKernelGGL((pool_write_inline_kernel<1, N>), grid, block, 0, s, w);
+                hipLaunchKernelGGL((pool_write_inline_kernel<1, true, N>), grid, block, 0, s, w);
             return hipGetLastError();
         };
         if (a.n_pages > kMaxInlineWrite) return hipErrorInvalidValue;
@@ -452,9 +459,11 @@ hipError_t launch_pool_write(const PoolWriteLaunch &a, hipStream_t s) {
         return go(std::integral_constant<int, kMaxInlineWrite>{});
     }
     if (a.dtype == 0)
-        hipLaunchKernelGGL(pool_write_kernel<0>, grid, block, 0, s, a);
+        hipLaunchKernelGGL((pool_write_kernel<0, false>), grid, block, 0, s, a);
+    else if (!pairs)
+        hipLaunchKernelGGL((pool_write_kernel<1, false>), grid, block, 0, s, a);
     else
-        hipLaunchKernelGGL(pool_write_kernel<1>, grid, block, 0, s, a);
+        hipLaunchKernelGGL((pool_write_kernel<1, true>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 

@@ -1,5 +1,6 @@
-"""kv_pool_write: blocks written whole next to blocks written in part, odd and even numbers of KV heads (a workgroup of an fp8 write takes
-two), and the numbers of blocks at which another size of kernel arguments is used: bytes and scales equal the oracle's."""
+"""kv_pool_write: blocks written whole next to blocks written in part, odd and even numbers of KV heads (a workgroup of an fp8 write of
+400 blocks x heads or more takes two), and the numbers of blocks at which another size of kernel arguments, or none, is used: bytes
+and scales equal the oracle's."""
 import numpy as np
 import pytest
 
@@ -14,7 +15,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("H", [1, 2, 3, 8])
 def test_whole_and_partial_blocks(gpu, oracle, kv_dtype, H):  # noqa: F811
     import torch
-    for first, tokens in [(0, 1), (0, 15), (0, 16), (0, 17), (0, 32), (0, 47), (5, 3), (5, 11), (5, 12), (5, 27), (5, 28), (7, 50), (15, 1), (15, 33),
+    least = -(-400 // H) * 16
+    for first, tokens in [(0, least - 16), (0, least), (0, least + 1), (0, least + 15), (5, least - 5), (5, least), (5, least + 11), (5, least + 12), (15, least + 2),
+                          (0, 960 * 16), (7, 960 * 16), (0, 1), (0, 15), (0, 16), (0, 17), (0, 32), (0, 47), (5, 3), (5, 11), (5, 12), (5, 27), (5, 28), (7, 50), (15, 1), (15, 33),
                           (0, 64 * 16), (0, 64 * 16 + 1), (3, 256 * 16 - 3), (3, 256 * 16 - 2)]:
         n_pages = (first + tokens + 15) // 16
         rng = np.random.default_rng([H, first, tokens])
