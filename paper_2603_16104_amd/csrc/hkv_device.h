@@ -131,4 +131,8 @@ __device__ __forceinline__ f32x16 zero16() {
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
+// lse of a partial from its reference (in powers of two) and row sum.  A row that saw nothing has the empty partial, -inf; one whose
+// scores hold a NaN or +inf (its sum is no number) gets +inf, with which every merge gives NaN, whatever the other partials hold.
+__device__ __forceinline__ float partial_lse(float m, float l) { return l > 0.f ? (m + fast_log2(l)) * kLn2 : l == 0.f ? -INFINITY : INFINITY; }
+
 }  // namespace hkv

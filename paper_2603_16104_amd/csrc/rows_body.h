@@ -537,7 +537,8 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
     // Partials of a wavefront that has seen all tokens of its rows: normalise and store from registers.
     auto write_rows = [&](int req) {
         const float l_row = rows_sum(l_run);
-        // a row that saw no token of this item delivers the empty partial (o = 0, lse = -inf)
+        // a row that saw no token of this item delivers the empty partial (o = 0, lse = -inf); one whose scores hold a NaN or +inf
+        // (a sum that is no number) lse = +inf, which makes the merged row NaN whatever else it holds
         float inv = l_row > 0.f ? 1.0f / l_row : 0.f;
         if constexpr (DT == 2) inv *= __uint_as_float(v_ref_bits) * 0.00390625f;  // o is in units of v_ref * 2^-8
         float amax = 0.f;
@@ -561,7 +562,7 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
                 *reinterpret_cast<u32x2 *>(op + 16 * dt) = w;
             }
             if (g == 0) a.down_parts[part] = down;
-            if (g == 0) a.lse_parts[part] = l_row > 0.f ? (m_run * c + fast_log2(l_row)) * kLn2 : -INFINITY;
+            if (g == 0) a.lse_parts[part] = partial_lse(m_run * c, l_row);
         }
     };
 
@@ -753,17 +754,15 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
         float M = -INFINITY;
         for (int t = 0; t < n_ts; ++t) M = fmaxf(M, sM[t * n_rt + r_t][r_c]);
         float L = 0.f, acc0 = 0.f, acc1 = 0.f;
-        if (M != -INFINITY || PATH) {
-            for (int t = 0; t < n_ts; ++t) {
-                const int w = t * n_rt + r_t;
-                const float mw = sM[w][r_c];
-                if (PATH && mw == -INFINITY) L += sL[w][r_c];  // (0, or NaN where its scores hold one)
-                if (mw == -INFINITY) continue;  // that wavefront's tokens were all invisible to the row
-                const float wgt = fast_exp2((mw - M) * c_run);
-                L += sL[w][r_c] * wgt;
-                acc0 += sO[w][r_c][d] * wgt;
-                acc1 += sO[w][r_c][d + 1] * wgt;
-            }
+        for (int t = 0; t < n_ts; ++t) {
+            const int w = t * n_rt + r_t;
+            const float mw = sM[w][r_c];
+            if (mw == -INFINITY) L += sL[w][r_c];  // that wavefront's tokens were all invisible to the row: 0, or NaN where its scores hold one
+            if (mw == -INFINITY) continue;
+            const float wgt = fast_exp2((mw - M) * c_run);
+            L += sL[w][r_c] * wgt;
+            acc0 += sO[w][r_c][d] * wgt;
+            acc1 += sO[w][r_c][d + 1] * wgt;
         }
         const size_t part = (size_t)sPart[row];
         // a row that saw no token of this item delivers the empty partial (o = 0, lse = -inf)
@@ -786,7 +785,7 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
         *reinterpret_cast<uint32_t *>(a.o_parts + part * kHeadDim + d) = pack_f16(acc0 * up, acc1 * up);
         if (lane == 0) {
             a.down_parts[part] = down;
-            a.lse_parts[part] = L > 0.f ? (M * c + fast_log2(L)) * kLn2 : -INFINITY;
+            a.lse_parts[part] = partial_lse(M * c, L);
         }
     }
 }

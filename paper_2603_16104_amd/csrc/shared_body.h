@@ -369,7 +369,7 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, const DecodeItem &it
             }
         if (h == 0) {
             a.down_parts[part] = down;
-            a.lse_parts[part] = L > 0.f ? (M + fast_log2(L)) * kLn2 : -INFINITY;
+            a.lse_parts[part] = partial_lse(M, L);
         }
     }
 }

@@ -702,7 +702,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
                     *reinterpret_cast<u32x2 *>(op + 32 * dm + 8 * q4) = w;
                 }
             if (h == 0) a.down_parts[part] = down;
-            if (h == 0) a.lse_parts[part] = (m_fin + fast_log2(l_tot)) * kLn2;
+            if (h == 0) a.lse_parts[part] = partial_lse(m_fin, l_tot);
         } else {
             uint16_t *op = static_cast<uint16_t *>(a.out) + (size_t)io_row * kHeadDim;
 #pragma unroll
