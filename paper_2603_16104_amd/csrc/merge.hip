@@ -236,6 +236,7 @@ hipError_t launch_lse_merge_dense(const void *o_parts, const float *lse_parts, c
                                   int32_t out_dtype, float *lse_out, hipStream_t s, hipEvent_t ev_begin,
                                   hipEvent_t ev_end, const int32_t *out_rows, const float *down_parts) {
     if (n_rows <= 0) return hipSuccess;
+    if (down_parts && out_dtype != 0) return hipErrorInvalidValue;  // fp16 partials are a decode step's, whose results are bf16
     const bool many = n_rows >= kManyRows;
     const int per_block = kDenseRowsPerBlock * (many ? 4 : 1);
     dim3 grid((n_rows + per_block - 1) / per_block), block(32 * kDenseRowsPerBlock);
@@ -252,7 +253,10 @@ hipError_t launch_lse_merge_dense(const void *o_parts, const float *lse_parts, c
         auto of = [&](auto unroll, auto pb16) {
             constexpr int U = decltype(unroll)::value;
             constexpr bool PB = decltype(pb16)::value;
-            out_dtype == 0 ? deep(lse_merge_deep_kernel<0, U, PB>) : deep(lse_merge_deep_kernel<2, U, PB>);
+            if constexpr (PB)
+                deep(lse_merge_deep_kernel<0, U, true>);
+            else
+                out_dtype == 0 ? deep(lse_merge_deep_kernel<0, U, false>) : deep(lse_merge_deep_kernel<2, U, false>);
         };
         if (max_parts <= 16)
             down_parts ? of(std::integral_constant<int, 4>{}, std::true_type{}) : of(std::integral_constant<int, 4>{}, std::false_type{});
@@ -264,10 +268,12 @@ hipError_t launch_lse_merge_dense(const void *o_parts, const float *lse_parts, c
         constexpr bool PB = decltype(pb16)::value;
         auto of = [&](auto unroll) {
             constexpr int U = decltype(unroll)::value;
-            if (many)
-                out_dtype == 0 ? go(lse_merge_dense_kernel<0, U, PB, 4>) : go(lse_merge_dense_kernel<2, U, PB, 4>);
+            if constexpr (PB)
+                many ? go(lse_merge_dense_kernel<0, U, true, 4>) : go(lse_merge_dense_kernel<0, U, true, 1>);
+            else if (many)
+                out_dtype == 0 ? go(lse_merge_dense_kernel<0, U, false, 4>) : go(lse_merge_dense_kernel<2, U, false, 4>);
             else
-                out_dtype == 0 ? go(lse_merge_dense_kernel<0, U, PB, 1>) : go(lse_merge_dense_kernel<2, U, PB, 1>);
+                out_dtype == 0 ? go(lse_merge_dense_kernel<0, U, false, 1>) : go(lse_merge_dense_kernel<2, U, false, 1>);
         };
         if (max_parts <= 2) return of(std::integral_constant<int, 2>{});
         if (max_parts == 3) return of(std::integral_constant<int, 3>{});
