@@ -324,6 +324,34 @@ def plan_settings(monkeypatch, flags=0, **settings):
     monkeypatch.setattr(hkv, "hkv_decode_plan_create_ex", create_ex)
 
 
+@pytest.fixture(params=["paths", "items"])
+def both_forms(request, monkeypatch):
+    """A test of small decode steps twice: as the library plans them, whole root-to-leaf paths in one launch, and as items with
+    their partials and the merge (kept by a planner setting that these plans have no use for)."""
+    yield from _form(request.param, monkeypatch, (request.param == "paths",))
+
+
+@pytest.fixture(params=["default", "items"])
+def either_form(request, monkeypatch):
+    """The same where the library plans some of a test's steps as items anyway."""
+    yield from _form(request.param, monkeypatch, (False, True) if request.param == "default" else (False,))
+
+
+def _form(form, monkeypatch, runs_paths):
+    from paper_2603_16104_amd import binding as hkv
+    if form == "items":
+        plan_settings(monkeypatch, tile_workgroups=8)
+    seen = []
+    for name in ("create", "create_growing", "create_multi", "create_tree", "create_ex"):
+        def create(*args, _create=getattr(hkv, "hkv_decode_plan_" + name), **kw):
+            plan = _create(*args, **kw)
+            seen.append(hkv.hkv_decode_plan_num_paths(plan) > 0)
+            return plan
+        monkeypatch.setattr(hkv, "hkv_decode_plan_" + name, create)
+    yield form
+    assert seen and set(seen) <= set(runs_paths), f"{form}: {seen}"
+
+
 def run_decode(gpu, oracle, w, one_shot=False):
     import torch
     from paper_2603_16104_amd import binding as hkv
@@ -353,6 +381,7 @@ def run_decode(gpu, oracle, w, one_shot=False):
     return res
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("seed", [51, 52, 53, 54])
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
 def test_decode_random_forests(gpu, oracle, seed, kv_dtype):
@@ -368,6 +397,7 @@ def test_decode_many_requests_per_node(gpu, oracle):
     run_decode(gpu, oracle, w)
 
 
+@pytest.mark.usefixtures("either_form")
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
 def test_decode_deep_chain(gpu, oracle, kv_dtype):
     """A chain of 26 nodes with requests hanging off at several depths: paths collect up to 27 partials
@@ -389,6 +419,7 @@ def test_decode_deep_chain(gpu, oracle, kv_dtype):
     run_decode(gpu, oracle, w)
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("seed", [61, 62, 63, 64])
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
 def test_decode_nodes_that_end_inside_a_page(gpu, oracle, seed, kv_dtype):
@@ -404,6 +435,7 @@ def test_decode_nodes_that_end_inside_a_page(gpu, oracle, seed, kv_dtype):
     run_decode(gpu, oracle, w)
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
 def test_decode_verifies_a_tree_of_drafted_tokens(gpu, oracle, kv_dtype):
     """Tree-structured verification of drafted tokens expressed as a forest: two calls over a shared system
@@ -452,6 +484,19 @@ def test_decode_verifies_a_tree_of_drafted_tokens(gpu, oracle, kv_dtype):
 def test_decode_config1_one_shot(gpu, oracle):
     _, dec = wl.config1()
     run_decode(gpu, oracle, dec, one_shot=True)
+
+
+def test_decode_one_shot_of_items(gpu, oracle):
+    """More tokens per path than the library walks whole: items and merge, from the cached plan the second time."""
+    from paper_2603_16104_amd import binding as hkv
+    w = wl.config2(seed=77, n_req=40, root_tokens=1200 // 16 * 16, private_tokens=100)
+    _, dp = both_pools(gpu, oracle, w)
+    f = w.forest
+    plan = hkv.hkv_decode_plan_create(dp.handle, f.nodes, f.node_pages, f.req_leaf, w.num_q_heads, hkv.PLAN_HOST_ONLY)
+    assert hkv.hkv_decode_plan_num_paths(plan) == 0
+    hkv.hkv_decode_plan_destroy(plan)
+    dp.close()
+    run_decode(gpu, oracle, w, one_shot=True)
 
 
 def test_decode_empty_and_degenerate(gpu, oracle):
@@ -578,6 +623,7 @@ def test_prefill_mixed_with_single_token_requests(gpu, oracle):
     run_prefill(gpu, oracle, w)
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
 @pytest.mark.parametrize("order", ["interleaved", "decode_first"])
 def test_mixed_step_tree_decode_plus_prefill(gpu, oracle, order, kv_dtype):
@@ -674,6 +720,7 @@ def test_prefill_late_dominant_key(gpu, oracle, beta):
     assert np.abs(got_o[hot:, 0] - vb[hot, 0]).max() <= 2e-2
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
 @pytest.mark.parametrize("case", ["zero_query", "huge_scores", "early_dominant_key"])
 def test_decode_closed_forms_on_the_gpu(gpu, oracle, kv_dtype, case):
@@ -836,6 +883,7 @@ def _ancestor_masks(parents):
     return masks
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
 @pytest.mark.parametrize("widths", [(3, 2, 2), (2, 2, 1), (1, 1, 1, 1, 1), (4, 4, 3)])
 def test_decode_tree_of_drafted_tokens_by_masks(gpu, oracle, kv_dtype, widths):
@@ -882,6 +930,7 @@ def _multi_forest(kv_dtype, hq, hkv_, leaf_tokens, req_leaf, root_tokens=64, see
                        seed=seed, forest=f, mode="decode")
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
 @pytest.mark.parametrize("T", [1, 3, 4])
 def test_decode_several_query_tokens(gpu, oracle, kv_dtype, T):
@@ -932,6 +981,7 @@ def test_decode_short_items_four_to_a_workgroup(gpu, oracle, kv_dtype, monkeypat
     run_decode_multi(gpu, oracle, _multi_forest(kv_dtype, 4, 1, [40, 16, 33, 7, 90], [1, 2, 3, 4, 5, 0]), 4)
 
 
+@pytest.mark.usefixtures("both_forms")
 def test_decode_and_prefill_runs_are_graph_capturable(gpu, oracle):
     """attn_decode_plan_run and attn_prefill_plan_run only queue kernels (no allocation, no copies, no
     memset nodes), so a caller may capture them in a HIP graph: several replays, with eager work and
@@ -1143,6 +1193,7 @@ def test_prefix_cache_engine_under_page_budget(gpu, oracle, seed, n_pages):
     r.close()
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("shape", ["map_reduce", "debate"])
 def test_workflow_decode_levels(gpu, oracle, shape):
     """The decode step of every dependency level of a small workflow: the workflow's templated radix tree
@@ -1158,6 +1209,7 @@ def test_workflow_decode_levels(gpu, oracle, shape):
         run_decode(gpu, oracle, w)
 
 
+@pytest.mark.usefixtures("either_form")
 # ------------------------------------------------------------------------------ pages of 32, 64, 128 tokens
 
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3, wl.KV_FP32])
@@ -1214,6 +1266,7 @@ def test_larger_pages_appends_bit_exact(gpu, oracle, P):
     dp.close()
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
 @pytest.mark.parametrize("P", [32, 64])
 def test_larger_pages_decode_nodes_that_end_inside_a_page(gpu, oracle, P, kv_dtype):
@@ -1308,11 +1361,12 @@ def test_fp8_matrix_variant_random_forests(gpu, oracle, seed, fp8_matrix):
     run_decode(gpu, oracle, w)
 
 
-def test_fp8_matrix_variant_by_plan_flag(gpu, oracle):
+def test_fp8_matrix_variant_by_plan_flag(gpu, oracle, monkeypatch):
     """The flag of hkv_decode_plan_create selects the path (no environment involved); c2-like shape with
     LDS-staged shared items, register items and a ragged tail, both paths inside the bounds."""
     import torch
     from paper_2603_16104_amd import binding as hkv
+    plan_settings(monkeypatch, tile_workgroups=8)          # (no whole paths)
     w = wl.random_forest_workload(57, kv_dtype=wl.KV_FP8_E4M3, num_q_heads=16, num_kv_heads=2, depth=3, fanout=4,
                                   max_node_pages=20, n_roots=1, zero_weight_nodes=False)
     hp, dp = both_pools(gpu, oracle, w)
@@ -1320,6 +1374,7 @@ def test_fp8_matrix_variant_by_plan_flag(gpu, oracle):
     got = {}
     for flags in (0, hkv.PLAN_FP8_MATRIX):
         r = gpu.DecodeRunner(dp, w, flags=flags)
+        assert hkv.hkv_decode_plan_num_paths(r.plan) == 0
         r.run()
         torch.cuda.synchronize()
         got[flags] = gpu.bf16_tensor_to_f64(r.out)

@@ -8,6 +8,8 @@ import pytest
 
 from paper_2603_16104_amd import workloads as wl
 
+from test_gpu_parity import both_forms  # noqa: F401
+
 pytestmark = pytest.mark.gpu
 
 
@@ -52,6 +54,7 @@ def _run_both(gpu, oracle, w, kv_dtype):
     dp.close()
 
 
+@pytest.mark.usefixtures("both_forms")
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
 def test_static_workspace_run_equals_workspace_run_twice(gpu, oracle, kv_dtype):
     big = wl.random_forest_workload(71, kv_dtype=kv_dtype, n_roots=2, depth=3, fanout=3, max_node_pages=9)
