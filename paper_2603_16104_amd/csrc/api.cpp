@@ -1129,9 +1129,10 @@ static void plan_items(hkv_decode_plan &pl) {
     // workgroups fill a compute unit where three with 16-row tiles do, so that on a full chip the two come to the same and
     // how the items fill it decides (one root of 512 tokens over 64 leaves of 128 tokens 22.3 us as 16-row tiles, 17.3 as 32-row
     // tiles; 8192 over 64 x 1024 63.4 / 73.5).  Both pools: the chunk's length, from 128 tokens (a few items
-    // on an empty chip) to whole nodes (many rows, each with a partial per chunk).  Against the length above and the form
-    // that suits it, wherever the estimate is shorter by 4 % in that form or by 8 % in the other: 1675 random plans take 0.914 of their
-    // time in the mean, 14 lose more than 3 %; the best of all tried lengths and forms would give 0.882.  64 requests x 21 drafted
+    // on an empty chip) to whole nodes (many rows, each with a partial per chunk).  Against the length above and the form that
+    // suits it, wherever the estimate is shorter by 8 % in that form or by 10 % in the other: 1687 random plans take 0.922 of their time
+    // in the mean, 7 lose more than 3 %, none 8 %; at 4 and 8 % 0.918, 18 and 4 up to 12 %; the best of all tried lengths and
+    // forms would give 0.887 (profiles/decode_plan_timings.csv).  64 requests x 21 drafted
     // tokens x 32 heads over 2048 + 512, bf16: 138 us in chunks of 512 tokens, 106 in whole nodes; 9 requests x 8 heads below
     // each of 4 x 6996 tokens: 27.9 in chunks of 1024, 15.2 of 192.
     // Plans whose partials fit the static workspace at that length keep to lengths that fit.
@@ -1157,7 +1158,7 @@ static void plan_items(hkv_decode_plan &pl) {
         best.us = estimate(from, best.parts);
         if (!search) return best;
         const bool fits = !too_many(best.parts);
-        double least = best.us;  // times the margin: 4 % in the same form, 8 % in the other
+        double least = best.us;  // times the margin: 8 % in the same form, 10 % in the other
         for (const bool w : {false, true}) {
             if (w ? !wide_too : !narrow_too) continue;
             Layout l = lay_out(w, cut_more);
@@ -1169,7 +1170,7 @@ static void plan_items(hkv_decode_plan &pl) {
                 l.shared_chunk = chunk;
                 const int parts = parts_of(l);
                 if (fits && too_many(parts)) continue;
-                const double e = estimate(l, parts), us = e / (w == from.wide ? 0.96 : 0.92);
+                const double e = estimate(l, parts), us = e / (w == from.wide ? 0.92 : 0.90);
                 if (us >= least) continue;
                 least = us;
                 best = Choice{l, from, parts, e};

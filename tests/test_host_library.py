@@ -736,6 +736,7 @@ def test_form_of_shared_items_is_the_one_that_measured_shorter(tokens, fan, head
     (hkv.BF16, 1, (2048, 512), 64, (32, 8), 16, 1536, 2048),     # many rows, a partial each and per chunk: whole nodes
     (hkv.BF16, 4, (6996, 42), 9, (8, 2), 1, 128, 384), (hkv.FP8_E4M3, 1, (5136, 364), 15, (32, 8), 1, 128, 256),   # few items on an empty chip
     (hkv.FP8_E4M3, 1, (670, 261), 46, (64, 8), 16, 640, 768),    # one chunk rather than two
+    (hkv.FP8_E4M3, 1, (1572, 140), 14, (32, 8), 4, 400, 512),    # the default (16.9 us; of 384 18.3), 7 % from the estimate of another
 ])
 def test_chunk_lengths_of_shared_nodes(dtype, roots, tokens, n_req, heads, T, least, most):
     """Near the lengths that measured shortest."""
