@@ -1322,11 +1322,12 @@ static void plan_items(hkv_decode_plan &pl) {
 // no partials.  What that takes, us: the launch and its chain, and the blocks a compute unit has to take in,
 // some 50 to 100 bytes per ns, more where the nodes are not in the L2 of every XCD that reads them.
 // (Coefficients from 860 random plans of 16 to 3500 tokens per path, timed in both forms with three sets of inputs in turn: 10 %
-// rms.  Paths where that is 7 % below the items' estimate: of 700 other plans 409 run this way, none of which is more than 2 % faster
-// as items, and 71 of the others would be more than 3 % faster this way; at 3 % 426 and two, 58.  What the estimate does not know is
-// that a few compute units get two of the longest paths: 38 leaves of 160 to 527 tokens below 496, 32 / 8 heads, bf16, 304 workgroups, 18.0
-// us as items, 21.3 this way, estimated at 0.937 of the items' time.
-// Four requests over 256 + 32 + 17 tokens, bf16, 8 / 2 heads: 10.7 -> 5.5 us; 32 requests over 480 + 160 tokens, 32 / 8 heads:
+// rms; both forms have become shorter since, paths by 11 % and items by 6 %.  Paths where that is 7 % below the items' estimate: of
+// 700 other plans (profiles/decode_path_timings.csv) 434 run this way, one of which is more than 3 % (3.5 %) faster as items, and
+// 94 of the others would be that much faster this way; at 3 % 464 and four, by up to 14 %, and 68.  What the estimate does not
+// know is that a few compute units get two of the longest paths: 38 leaves of 160 to 527 tokens below 496, 32 / 8 heads, bf16,
+// 304 workgroups, 18.0 us as items, 21.3 this way, estimated at 0.937 of the items' time.
+// Four requests over 256 + 32 + 17 tokens, bf16, 8 / 2 heads: 10.7 -> 5.3 us; 32 requests over 480 + 160 tokens, 32 / 8 heads:
 // 17.3 -> 7.7; 64: 16.6 -> 13.3; 128: 22.5 as items, 23.7 this way.)
 // Eight wavefronts while every workgroup has a compute unit to itself, four where several share one (64 requests over 240 +
 // 80 tokens, fp8: 12.3 us with eight, 9.0 with four).
