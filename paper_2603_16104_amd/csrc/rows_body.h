@@ -747,7 +747,7 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<f32x4 *>(&sO[wave][m][16 * dt + 4 * g]) = o[dt];
     if (g == 0) {
-        sM[wave][m] = m_run;
+        sM[wave][m] = l_row == l_row ? m_run : INFINITY;  // (a NaN or +inf among the scores: the row's sum is no number below, whatever the others hold)
         sL[wave][m] = l_row;
         // wavefront 0 always has a step (the item holds at least one token), so its req is loaded
         if constexpr (PATH != 0) {  // (a path without tokens has not loaded it)
@@ -757,25 +757,45 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
     }
     __syncthreads();
     // a row's 64 pairs of neighbouring dims are one wavefront's 64 lanes: wavefront w takes rows w, w + 4, ... (all W wavefronts
-    // hold a share of each: items of several row tiles, and packed ones, have returned).  Unrolled over the shares, whose reads
-    // from LDS would otherwise be a chain of W round trips at the end of every item (decode steps of 11 to 13 us 0.5 to 1.2 us shorter).
+    // hold a share of each: items of several row tiles, and packed ones, have returned).  Where only items of few rows run, the
+    // loop over the shares is unrolled, whose reads from LDS are a chain of W round trips at the end of every item otherwise:
+    // decode steps of 11 to 13 us 0.5 to 1.2 us shorter.  Beside items of many rows it gains nothing (4096 + 8 x 1024 + 128 x 256
+    // tokens, 32 / 8 heads: 34.7 us, unrolled 35.2).
     for (int row = wave; row < rows; row += W) {
         const int d = lane * 2;
-        float mw[W], M = -INFINITY;
+        float M = -INFINITY, L = 0.f, acc0 = 0.f, acc1 = 0.f;
+        if constexpr (SHARED || FUSED) {
+#pragma unroll 1
+            for (int w = 0; w < W; ++w) M = fmaxf(M, sM[w][row]);
+            if (M != -INFINITY) {
+#pragma unroll 1
+                for (int w = 0; w < W; ++w) {
+                    const float mw = sM[w][row];
+                    if (mw == -INFINITY) continue;  // that wavefront's tokens were all invisible to the row
+                    const float wgt = fast_exp2((mw - M) * c_run);
+                    L += sL[w][row] * wgt;
+                    acc0 += sO[w][row][d] * wgt;
+                    acc1 += sO[w][row][d + 1] * wgt;
+                }
+            }
+        } else {
+            float mw[W], l[W], o0[W], o1[W];
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
-            mw[w] = sM[w][row];
-            M = fmaxf(M, mw[w]);
-        }
-        float L = 0.f, acc0 = 0.f, acc1 = 0.f;
+            for (int w = 0; w < W; ++w) {
+                mw[w] = sM[w][row];
+                l[w] = sL[w][row];
+                o0[w] = sO[w][row][d];
+                o1[w] = sO[w][row][d + 1];
+                M = fmaxf(M, mw[w]);
+            }
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
-            const float l = sL[w][row], o0 = sO[w][row][d], o1 = sO[w][row][d + 1];
-            const bool none = mw[w] == -INFINITY;  // all of that wavefront's tokens are invisible to the row: l is 0, or NaN where its scores hold one
-            const float wgt = none ? 0.f : fast_exp2((mw[w] - M) * c_run);
-            L += none ? l : l * wgt;
-            acc0 += none ? 0.f : o0 * wgt;
-            acc1 += none ? 0.f : o1 * wgt;
+            for (int w = 0; w < W; ++w) {
+                const bool none = mw[w] == -INFINITY;
+                const float wgt = none ? 0.f : fast_exp2((mw[w] - M) * c_run);
+                L += l[w] * wgt;
+                acc0 += none ? 0.f : o0[w] * wgt;
+                acc1 += none ? 0.f : o1[w] * wgt;
+            }
         }
         const size_t part = (size_t)sPart[row];
         // a row that saw no token of this item delivers the empty partial (o = 0, lse = -inf)
