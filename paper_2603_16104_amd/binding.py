@@ -91,6 +91,17 @@ def _check(rc: int) -> int:
     return rc
 
 
+def _run(f, *args) -> int:
+    """_check of a call that has argument types: a number of the wrong type is a TypeError, as where the arguments are ctypes objects."""
+    try:
+        rc = f(*args)
+    except C.ArgumentError as e:
+        raise TypeError(str(e)) from None
+    if rc < 0:
+        raise HkvError(rc, last_error())
+    return rc
+
+
 def _dev(t) -> C.c_void_p:
     """Device address of a torch tensor, a raw int address, or None."""
     if t is None:
@@ -201,8 +212,8 @@ def kv_pool_write(pool, page_ids, first_slot: int, n_tokens: int, k_src, v_src, 
         need = (first_slot + n_tokens + page - 1) // page
         if len(ids) < need:
             raise HkvError(EINVAL, f"kv_pool_write: {need} page ids needed, {len(ids)} given")
-    _check(lib().kv_pool_write(pool, _host_addr(ids), first_slot, n_tokens, _addr(k_src), _addr(v_src),
-                               _stream_addr(stream) if n_tokens > 0 else None))
+    _run(lib().kv_pool_write, pool, _host_addr(ids), first_slot, n_tokens, _addr(k_src), _addr(v_src),
+         _stream_addr(stream) if n_tokens > 0 else None)
 
 
 def kv_pool_append(pool, page_ids, slots, k_src, v_src, stream=None) -> None:
@@ -210,8 +221,8 @@ def kv_pool_append(pool, page_ids, slots, k_src, v_src, stream=None) -> None:
     ids, sl = _host_i32(page_ids), _host_i32(slots)
     if len(ids) != len(sl):
         raise HkvError(EINVAL, "kv_pool_append: page_ids and slots differ in length")
-    _check(lib().kv_pool_append(pool, _host_addr(ids), _host_addr(sl), len(ids), _addr(k_src), _addr(v_src),
-                                _stream_addr(stream) if len(ids) > 0 else None))
+    _run(lib().kv_pool_append, pool, _host_addr(ids), _host_addr(sl), len(ids), _addr(k_src), _addr(v_src),
+         _stream_addr(stream) if len(ids) > 0 else None)
 
 
 # ----------------------------------------------------------------------------------------- forest
@@ -277,7 +288,7 @@ def hkv_decode_plan_append(plan, new_page_ids=None, stream=None) -> None:
 
 def hkv_decode_plan_append_tokens(plan, new_page_ids, k_src, v_src, stream=None) -> None:
     ids = None if new_page_ids is None else _host_i32(new_page_ids)
-    _check(lib().hkv_decode_plan_append_tokens(plan, _host_addr(ids), _addr(k_src), _addr(v_src), _stream_addr(stream)))
+    _run(lib().hkv_decode_plan_append_tokens, plan, _host_addr(ids), _addr(k_src), _addr(v_src), _stream_addr(stream))
 
 
 def hkv_decode_plan_create(pool, nodes, node_pages, req_leaf, num_q_heads: int, flags: int = 0) -> C.c_void_p:
@@ -387,8 +398,8 @@ def hkv_decode_plan_part_counts(plan, n_req: int) -> np.ndarray:
 
 
 def attn_decode_plan_run(plan, q, scale: float, out, lse_out, workspace, workspace_bytes: int, stream=None) -> None:
-    _check(lib().attn_decode_plan_run(plan, _addr(q), scale, _addr(out), _addr(lse_out), _addr(workspace), workspace_bytes,
-                                      _stream_addr(stream)))
+    _run(lib().attn_decode_plan_run, plan, _addr(q), scale, _addr(out), _addr(lse_out), _addr(workspace), workspace_bytes,
+         _stream_addr(stream))
 
 
 def hkv_static_workspace_bytes() -> int:
@@ -396,7 +407,7 @@ def hkv_static_workspace_bytes() -> int:
 
 
 def attn_decode_plan_run_static(plan, q, scale: float, out, lse_out, stream=None) -> None:
-    _check(lib().attn_decode_plan_run_static(plan, _addr(q), scale, _addr(out), _addr(lse_out), _stream_addr(stream)))
+    _run(lib().attn_decode_plan_run_static, plan, _addr(q), scale, _addr(out), _addr(lse_out), _stream_addr(stream))
 
 
 def hkv_decode_plan_set_profiling(plan, mode) -> None:
@@ -515,8 +526,8 @@ def attn_prefill_plan_run(plan, q, scale: float, out, lse_out=None, stream=None,
                           workspace_bytes: int = 0) -> None:
     """workspace: device scratch of hkv_prefill_plan_workspace_bytes(plan) bytes, one per stream (needed for an fp8 pool's pages;
     without room for the partial results of split tiles they stay whole)."""
-    _check(lib().attn_prefill_plan_run_ws(plan, _addr(q), scale, _addr(out), _addr(lse_out), _addr(workspace), workspace_bytes,
-                                          _stream_addr(stream)))
+    _run(lib().attn_prefill_plan_run_ws, plan, _addr(q), scale, _addr(out), _addr(lse_out), _addr(workspace), workspace_bytes,
+         _stream_addr(stream))
 
 
 def hkv_prefill_plan_num_pieces(plan) -> int:

@@ -805,6 +805,22 @@ def test_workspace_of_plans_that_run_whole_paths():
     hkv.kv_pool_destroy(pool)
 
 
+def test_numbers_of_the_wrong_type_are_type_errors():
+    pool = fake_pool()
+    plan = hkv.hkv_decode_plan_create(pool, [[-1, 0, 1, 5]], [0], [0], 4, hkv.PLAN_HOST_ONLY)
+    for call in (lambda: hkv.kv_pool_write(pool, [0], 0.0, 3, 0x1000, 0x1000, stream=0), lambda: hkv.kv_pool_write(pool, [0], 0, 3.0, 0x1000, 0x1000, stream=0),
+                 lambda: hkv.attn_decode_plan_run(plan, 0x1000, "1", 0x1000, None, 0x1000, 4096, stream=0),
+                 lambda: hkv.attn_decode_plan_run(plan, 0x1000, 1.0, 0x1000, None, 0x1000, 4096.0, stream=0),
+                 lambda: hkv.attn_decode_plan_run_static(plan, 0x1000, None, 0x1000, None, stream=0)):
+        with pytest.raises(TypeError):
+            call()
+    for scale in (np.float32(0.1), np.array(0.1), 1):      # what has a float is one; the plan itself cannot run
+        with pytest.raises(hkv.HkvError):
+            hkv.attn_decode_plan_run(plan, 0x1000, scale, 0x1000, None, 0x1000, np.int64(4096), stream=0)
+    hkv.hkv_decode_plan_destroy(plan)
+    hkv.kv_pool_destroy(pool)
+
+
 def test_merge_argument_validation():
     with pytest.raises(hkv.HkvError) as e:
         hkv.lse_merge(0x1000, 0x2000, 0x3000, 0x4000, 4, 0x5000, 7, stream=0)
