@@ -778,12 +778,13 @@ def test_plans_that_run_whole_paths(dtype, tokens, n_req, heads, params, paths):
     hkv.kv_pool_destroy(pool)
 
 
-def test_a_second_round_of_long_paths_runs_as_items():
-    """38 leaves of 158 to 527 tokens below 496, 8 KV heads: 304 workgroups, a few compute units would get two of the longest paths
-    (21.3 us; 18.0 as items)."""
-    ntok = [496] + np.random.default_rng(38).integers(158, 528, size=38).tolist()
+@pytest.mark.parametrize("roots, least, most, leaves", [(1, (496, 158), 527, 38), (4, (493, 963), 1926, 10)])
+def test_a_second_round_of_long_paths_runs_as_items(roots, least, most, leaves):
+    """304 and 320 workgroups of 8 KV heads: a few compute units would get two of the longest paths (21.3 us, 18.0 as items; 55 and 46)."""
+    n = roots * leaves
+    ntok = [least[0]] * roots + np.random.default_rng(38).integers(least[1], most + 1, size=n).tolist()
     n_used = sum((t + 15) // 16 for t in ntok)
-    f = wl.make_forest([-1] + [0] * 38, ntok, list(range(1, 39)), np.arange(n_used, dtype=np.int32))
+    f = wl.make_forest([-1] * roots + [i // leaves for i in range(n)], ntok, list(range(roots, roots + n)), np.arange(n_used, dtype=np.int32))
     pool = fake_pool(n_used, 8)
     plan = hkv.hkv_decode_plan_create(pool, f.nodes, f.node_pages, f.req_leaf, 32, hkv.PLAN_HOST_ONLY)
     assert hkv.hkv_decode_plan_num_paths(plan) == 0
