@@ -1327,8 +1327,8 @@ static void plan_items(hkv_decode_plan &pl) {
 // 94 of the others would be that much faster this way; at 3 % 464 and four, by up to 14 %, and 68.  What the estimate does not
 // know is that a few compute units get two of the longest paths: 38 leaves of 160 to 527 tokens below 496, 32 / 8 heads, bf16,
 // 304 workgroups, 18.0 us as items, 21.3 this way, estimated at 0.937 of the items' time.
-// Four requests over 256 + 32 + 17 tokens, bf16, 8 / 2 heads: 10.7 -> 5.3 us; 32 requests over 480 + 160 tokens, 32 / 8 heads:
-// 17.3 -> 7.7; 64: 16.6 -> 13.3; 128: 22.5 as items, 23.7 this way.)
+// Four requests over 256 + 32 + 17 tokens, bf16, 8 / 2 heads: 10.7 -> 5.3 us; 16 requests over 480 + 160 tokens, 32 / 8 heads:
+// 16.2 -> 7.8; 32: 18.5 -> 9.1; 64 run as items, 13.9 (this way 13.3 to 13.8); 128: 22.5 as items, 23.7 this way.)
 // Eight wavefronts while every workgroup has a compute unit to itself, four where several share one (64 requests over 240 +
 // 80 tokens, fp8: 12.3 us with eight, 9.0 with four).
 // A caller that sets anything of the planner's, or asks for a form of the items, gets items; growing plans have theirs

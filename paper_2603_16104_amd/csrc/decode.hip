@@ -30,7 +30,7 @@ __global__ __launch_bounds__(rows::kThreads, SHARED || DT != 0 ? 2 : 3) void dec
 // 1920 + 640 tokens, one request of 8 x 4 heads, bf16, 17 us = 110 bytes per ns.  So the plan keeps it to short paths.  A record
 // holds everything the chain needs at a fixed place, so that its head, its blocks and the rows travel in one round
 // trip.  (A second set of operand registers, two steps in flight: 640 tokens 7.7 -> 8.7 us.)  16 requests x 8 heads over 480 +
-// 160 tokens, bf16: 16.2 us as items and merge, 7.4 us.
+// 160 tokens, bf16: 16.2 us as items and merge, 7.8 us.
 template <int DT, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 3 : 2) void decode_path_kernel(DecodePathLaunch a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];  // rows::combine_bytes(WAVES)

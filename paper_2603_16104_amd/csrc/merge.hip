@@ -143,9 +143,9 @@ __global__ __launch_bounds__(32 * kDenseRowsPerBlock) void lse_merge_dense_kerne
 
 // Rows of many partials: a wavefront per row, whose four rows of 16 lanes (8 dims a lane) take every fourth partial each, 4 * U
 // of them in flight at once.  Bound by latency: half a wavefront per row, with 16 partials at once and the others one after
-// the other, took 3.3 us for 512 rows x 9 (this: 2.8), 5.3 for 24 (3.1), 12.3 for 48 (3.9), 13.2 for 2048 rows x 32 (4.2); from
-// some 8192 rows on both are bound by the partials' bytes.  Below 9 partials half a wavefront per row is the faster form
-// (512 x 8: 2.69 against 2.71 us, 2048 x 8: 2.85 against 3.08).
+// the other, took 3.2 us for 512 rows x 9 (this: 2.6), 5.3 for 24 (3.1), 12.2 for 48 (3.8), 13.2 for 2048 rows x 32 (4.5); from
+// some 8192 rows on both are bound by the partials' bytes (16 384 x 24: 34 / 30).  Below 9 partials half a wavefront per row is the
+// faster form (512 x 8: 2.69 against 2.71 us, 2048 x 8: 2.85 against 3.08).
 template <bool PB16>
 __device__ __forceinline__ void load_part8(const void *o_parts, size_t elem, f32x4 &lo, f32x4 &hi) {
     if constexpr (PB16) {
