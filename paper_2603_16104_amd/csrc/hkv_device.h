@@ -121,6 +121,14 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// Rows of 32x32 results on their way out: lane (n, h) of an accumulator holds dims 8 q + 4 h .. + 3 of row n in words q of some
+// packed form (two dwords each).  For two such groups, q even and q + 1: the 16 bytes of group q + h, all eight dims, so that a row goes
+// out in pieces of 16 bytes instead of 8.
+__device__ __forceinline__ u32x4 join_halves(u32x2 even, u32x2 odd) {
+    const auto a = __builtin_amdgcn_permlane32_swap(even[0], odd[0], false, false), b = __builtin_amdgcn_permlane32_swap(even[1], odd[1], false, false);
+    return u32x4{a[0], b[0], a[1], b[1]};
+}
+
 __device__ __forceinline__ f32x16 zero16() {
     f32x16 z;
 #pragma unroll

@@ -93,6 +93,11 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, const DecodeItem &it
     // keeps these items at 2048 tokens = 32 blocks or fewer).  Pages past the end are clamped: in bounds, masked below.
     const int32_t *ids = a.pages + it.page_off;
     const int id_lane = ids[min(4 * lane + wave, last_page)];
+    // In the same round trip as the ids (the requests below wait for those, and what stands behind them is loaded one trip later), as
+    // the three words of a row's visibility are: with these and the partials going out in pieces of 16 bytes instead of 8, 512 rows
+    // below 4096 tokens and 64 below each of 8 x 1024 35.13 -> 34.55 us, 100 requests x 5 heads over fp8 53.31 -> 52.76.
+    const int row = 32 * rt + n, rowc = min(row, rows - 1);
+    const int req = a.node_req_idx[it.req_off + rowc / G];
     // fp8: lane 32 j + b holds the scales of page 4 b + 2 th + j, the page whose tokens half j of the wavefront scores
     float ksc_lane = 1.f, vsc_lane = 1.f;
     if constexpr (FP8) {
@@ -134,8 +139,6 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, const DecodeItem &it
     request();
 
     // Q^T operands of this lane's row; rows past the item's end repeat its last row (their results are not stored)
-    const int row = 32 * rt + n, rowc = min(row, rows - 1);
-    const int req = a.node_req_idx[it.req_off + rowc / G];
     bf16x8 qf[8];
     {
         const int q_row = a.q_rows ? a.q_rows[req] : req;
@@ -147,11 +150,12 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, const DecodeItem &it
     // Tokens of this item that the row may see: all, unless this is the node that holds its request's newest tokens
     int lim = it.n_tokens;
     unsigned long long vis = 0;
-    if (a.row_leaf && a.row_leaf[req] == it.node) {
-        const int before = a.row_limit[req] - it.tok_begin;
-        if (before < it.n_tokens) {  // (else the whole item lies in front of them, and lim stays the item's end)
-            lim = before;
-            vis = a.row_mask[req];
+    if (a.row_leaf) {  // (all three at once)
+        const int leaf = a.row_leaf[req], limit = a.row_limit[req];
+        const unsigned long long mask = a.row_mask[req];
+        if (leaf == it.node && limit - it.tok_begin < it.n_tokens) {  // (else the whole item lies in front of them, and lim stays its end)
+            lim = limit - it.tok_begin;
+            vis = mask;
         }
     }
 
@@ -355,22 +359,25 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, const DecodeItem &it
     amax = halves_max(amax);
     float up, down;
     part_factors(amax, up, down);
-    if (row < rows) {
-        const size_t part = (size_t)(req * a.num_q_heads + it.kv_head * G + row % G) * a.max_parts + it.part_slot;
-        uint16_t *op = a.o_parts + part * kHeadDim + 4 * h;
+    // (both halves of a row's lanes take part in every exchange)
+    uint16_t *op = a.o_parts + ((size_t)(req * a.num_q_heads + it.kv_head * G + rowc % G) * a.max_parts + it.part_slot) * kHeadDim + 8 * h;
 #pragma unroll
-        for (int dm = 0; dm < 4; ++dm)
+    for (int dm = 0; dm < 4; ++dm)
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                u32x2 w;
-                w[0] = pack_f16(o[dm][4 * q4] * up, o[dm][4 * q4 + 1] * up);
-                w[1] = pack_f16(o[dm][4 * q4 + 2] * up, o[dm][4 * q4 + 3] * up);
-                *reinterpret_cast<u32x2 *>(op + 32 * dm + 8 * q4) = w;
+        for (int q4 = 0; q4 < 4; q4 += 2) {
+            u32x2 w[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int i = 4 * (q4 + k);
+                w[k] = u32x2{pack_f16(o[dm][i] * up, o[dm][i + 1] * up), pack_f16(o[dm][i + 2] * up, o[dm][i + 3] * up)};
             }
-        if (h == 0) {
-            a.down_parts[part] = down;
-            a.lse_parts[part] = partial_lse(M, L);
+            const u32x4 both = join_halves(w[0], w[1]);
+            if (row < rows) *reinterpret_cast<u32x4 *>(op + 32 * dm + 8 * q4) = both;
         }
+    if (row < rows && h == 0) {
+        const size_t part = (size_t)(req * a.num_q_heads + it.kv_head * G + row % G) * a.max_parts + it.part_slot;
+        a.down_parts[part] = down;
+        a.lse_parts[part] = partial_lse(M, L);
     }
 }
 
