@@ -278,10 +278,12 @@ enum {
      * on the caller's stream, one kernel after the other. */
     HKV_PLAN_ONE_STREAM = 4,
     /* Decode plans over bf16 pools (no effect on others): items of 17 to 64 query rows run as 16-row tiles, a wavefront each
-     * over all their tokens, or as 32-row tiles x token halves.  The library takes the form it estimates the shorter step
-     * for (hkv_decode_plan_has_wide_tiles); the flags are for tests and comparisons, NARROW wins over WIDE. */
+     * over all their tokens, or as 32-row tiles x token halves, and beside the latter items of 65 to 128 rows (TALL) as a
+     * 32-row tile per wavefront.  The library takes the form it estimates the shorter step for
+     * (hkv_decode_plan_has_wide_tiles); the flags are for tests and comparisons, NARROW wins over WIDE and that over TALL. */
     HKV_PLAN_NARROW_TILES = 8,
-    HKV_PLAN_WIDE_TILES = 16
+    HKV_PLAN_WIDE_TILES = 16,
+    HKV_PLAN_TALL_TILES = 32
 };
 
 /* nodes, node_pages, req_leaf: host.  Validates the forest (ETREE/ERANGE, page ids against the
@@ -410,7 +412,7 @@ int32_t hkv_decode_plan_num_tile_items(const hkv_decode_plan *plan);
 int32_t hkv_decode_plan_tile_workgroups(const hkv_decode_plan *plan);
 int32_t hkv_decode_plan_is_fused(const hkv_decode_plan *plan);
 int32_t hkv_decode_plan_has_stream(const hkv_decode_plan *plan);
-/* 1 if the plan holds items of 17 to 64 query rows and runs them as 32-row tiles x token halves, else 0. */
+/* 1 if the plan holds items of 17 to 128 query rows and runs them as 32-row tiles, else 0. */
 int32_t hkv_decode_plan_has_wide_tiles(const hkv_decode_plan *plan);
 /* Small steps run whole root-to-leaf paths in one launch, without items and partials, where the library estimates that to be
  * faster and the caller has neither set a planner parameter (other than to its stated default) nor asked for a form of the

@@ -19,7 +19,7 @@ LIB_PATH = os.path.join(_HERE, "libheliumkv.so")
 
 OK, EINVAL, ERANGE, ESHAPE, ETREE, ENOMEM, EHIP = 0, -1, -2, -3, -4, -5, -6
 BF16, FP8_E4M3, FP32 = 0, 1, 2
-PLAN_HOST_ONLY, PLAN_FP8_MATRIX, PLAN_ONE_STREAM, PLAN_NARROW_TILES, PLAN_WIDE_TILES = 1, 2, 4, 8, 16
+PLAN_HOST_ONLY, PLAN_FP8_MATRIX, PLAN_ONE_STREAM, PLAN_NARROW_TILES, PLAN_WIDE_TILES, PLAN_TALL_TILES = 1, 2, 4, 8, 16, 32
 PAGE_SIZE, HEAD_DIM = 16, 128
 
 EXPORTS = [
@@ -447,7 +447,7 @@ def hkv_decode_plan_num_paths(plan) -> int:
 
 
 def hkv_decode_plan_has_wide_tiles(plan) -> bool:
-    """Whether items of 17 to 64 query rows run as 32-row tiles x token halves."""
+    """Whether items of 17 to 128 query rows run as 32-row tiles."""
     return bool(_check(lib().hkv_decode_plan_has_wide_tiles(plan)))
 
 

@@ -109,7 +109,7 @@ struct hkv_decode_plan {
     int32_t n_single = 0;  // items [0, n_single) run one per workgroup, the rest four per workgroup
     int32_t n_stages = 3;  // LDS stages of 16 KiB per workgroup of the per-node kernel
     bool has_shared = false;  // items of `items` shared by more than 16 query rows are run by shared::body
-    int tile_form = 0;  // bf16 pools: -1 never, 1 always shared::body (HKV_PLAN_NARROW_TILES, HKV_PLAN_WIDE_TILES)
+    int tile_form = 0;  // bf16 pools: -1 never, 1 always shared::body, 2 with tall tiles (HKV_PLAN_NARROW_TILES, _WIDE_TILES, _TALL_TILES)
     bool fp8_matrix = false;  // fp8 pools: both products on the fp8 matrix instruction (HKV_PLAN_FP8_MATRIX)
     hkv_decode_plan_params opt{};  // the planner's settings (0 = the library's choice)
     int32_t *d_pages = nullptr, *d_node_req_idx = nullptr, *d_part_count = nullptr;
@@ -639,7 +639,7 @@ static size_t partials_bytes(int64_t n) {
 // ---------------------------------------------------------------------------------------------
 // decode planning
 //
-// A node with T tokens that R requests pass through is cut into work items of at most 64 query
+// A node with T tokens that R requests pass through is cut into work items of at most 64 (tall tiles: 128) query
 // rows (R_item * G) and a token chunk each.  Every item yields one partial result per row, so the
 // chunk length trades parallelism (more items) against partial-result traffic (516 B per row and
 // item, written once and read once).
@@ -656,7 +656,7 @@ static void plan_items(hkv_decode_plan &pl) {
     const hkv_decode_plan_params &opt = pl.opt;
     auto or_default = [](int32_t v, int dflt) { return v != 0 ? (int)v : dflt; };
     const ChipShape chip = chip_shape();
-    const int max_req_per_item = std::max(1, or_default(opt.max_rows, 64) / G);
+    const int max_req_per_item = std::max(1, or_default(opt.max_rows, pl.tile_form == 2 ? 128 : 64) / G);
     // Chunk lengths.  Nodes read by at most 16 rows ("leaf type") stay whole unless the forest has
     // fewer (node, head) units than workgroups fit on the chip at once; then they are cut, but not
     // below 256 tokens.  Nodes shared by more rows get chunks near the typical leaf-type item, so that
@@ -767,6 +767,7 @@ static void plan_items(hkv_decode_plan &pl) {
         return (pl.nodes[v].n_pages + n_chunks - 1) / n_chunks;
     };
     bool any_shared = false, any_tiled = false;
+    int most_req = 0;  // requests below a shared node
     double through = 0, unique = 0, few_tokens = 0;  // K/V tokens: of shared nodes through workgroups / from HBM, of the others
     for (int v = 0; v < n_nodes; ++v) {
         const int R = pl.node_req_indptr[v + 1] - pl.node_req_indptr[v];
@@ -774,6 +775,7 @@ static void plan_items(hkv_decode_plan &pl) {
         if (pl.nodes[v].n_tokens == 0 || R == 0 || tiled(v)) continue;
         if (R * G > 16) {
             any_shared = true;
+            most_req = std::max(most_req, R);
             through += (double)pl.nodes[v].n_tokens * ((R + max_req_per_item - 1) / max_req_per_item);
             unique += pl.nodes[v].n_tokens;
         } else {
@@ -836,10 +838,11 @@ static void plan_items(hkv_decode_plan &pl) {
         int slots;                     // workgroups the chip holds at once
         bool cut_leaves, cut_to_fill;  // few-row nodes cut for packing; only to fill slots
         int shared_chunk, piece_tokens;
+        int max_req;                   // requests of an item: up to 64 rows, with tall tiles (tall_body.h) up to 128
     };
     // cut_more: nodes of few rows may be cut only to fill workgroup slots.
     auto lay_out_anew = [&](const bool wide, const bool cut_more) {
-        Layout lay{wide, wide ? 2 * chip.n_cu : kNodeGroups, false, false, base_chunk, pack_tokens};
+        Layout lay{wide, wide ? 2 * chip.n_cu : kNodeGroups, false, false, base_chunk, pack_tokens, max_req_per_item};
         if (leaf_split == 1 && pack_mode != 1 && opt.leaf_chunk == 0) {
             int64_t units = shared_units;
             bool any = false;
@@ -1053,6 +1056,8 @@ static void plan_items(hkv_decode_plan &pl) {
     static const Coefficients kBf16Narrow{1.08, 0.616, 0.230, 1.50, 1.25, 0.01, 1.03, 0.162, 0.046, 0.117, 0.477, 0.12, 0.141, 0.164, 0.032, 171, 2.3, 6.7};
     static const Coefficients kBf16Wide{2.53, 0.909, 0.163, 2.37, 1.18, 1.06, 0.92, 0.154, 0.018, 0.166, 0.288, 1.46, 0.134, 0.163, 0.044, 171, 0.6, 6.1};
     static const Coefficients kFp8{1.69, 0.830, 0.155, 2.51, 0.81, 1.39, 0.76, 0.123, 0.047, 0.189, 0.363, 1.49, 0.116, 0.159, 0.070, 175, 1.5, 7.1};
+    // Tall tiles (items of up to 128 rows; shorter ones beside them run in shared::body): 8700 timings of 1100 plans of this kind, 5 % rms.
+    static const Coefficients kBf16Tall{4.34, 1.01, 0.126, 4.48, 1.47, 3.16, 0.937, 0.103, 0.00341, 0.236, 0.69, 2.69, 0.125, 0.142, 0.0621, 94.1, 0.802, 5.15};
     // Of bf16 plans in the two forms at the length above (1376 plans, 8 % rms), for the choice of the form at that length: closer
     // there than the sets that also know the other lengths (with those 45 of 900 plans lose more than 3 % instead of 28).  They know
     // an item by its length alone.
@@ -1077,7 +1082,7 @@ static void plan_items(hkv_decode_plan &pl) {
         const Others &others = others_of(lay);
         double n_items = others.n_few;
         for (const NodeClass &c : classes)
-            n_items += (double)cuts_of(lay, c.tokens, c.n_req).n_chunks * c.count * Hkv * ((c.n_req + max_req_per_item - 1) / max_req_per_item);
+            n_items += (double)cuts_of(lay, c.tokens, c.n_req).n_chunks * c.count * Hkv * ((c.n_req + lay.max_req - 1) / lay.max_req);
         const bool packs = pack_mode == 3 || (pack_mode == 2 && n_items > lay.slots);
         constexpr int kBins = 512;  // durations in steps of 0.25 us
         double bins[kBins] = {}, n_wgs = 0, work = 0, longest_us = 0, issue = 0, memory = few_tokens * Hkv * token_mb * k.mem_few;
@@ -1107,9 +1112,9 @@ static void plan_items(hkv_decode_plan &pl) {
             const int tokens = std::min(T, cut.per_chunk * HKV_PAGE_SIZE);
             const double n = (double)c.count * cut.n_chunks * Hkv;
             memory += (double)c.count * T * Hkv * token_mb * k.mem_shared;
-            const int groups = (R + max_req_per_item - 1) / max_req_per_item, rest = R - (groups - 1) * max_req_per_item;
+            const int groups = (R + lay.max_req - 1) / lay.max_req, rest = R - (groups - 1) * lay.max_req;
             if (k.tile > 0 && !lay.wide && !fp8_pool && groups > 1 && rest * G <= 16) {  // (the remainder beside 16-row tiles, as below)
-                add_many(n * (groups - 1), tokens, max_req_per_item * G);
+                add_many(n * (groups - 1), tokens, lay.max_req * G);
                 add_few(n, (tokens + 31) / 32, packs && tokens <= pack_tokens);
             } else {
                 add_many(n * groups, tokens, (R + groups - 1) / groups * G);
@@ -1124,7 +1129,7 @@ static void plan_items(hkv_decode_plan &pl) {
         const double rows = 1e-6 * pl.n_req * pl.num_q_heads;
         return k.base + std::cbrt(span * span * span + issue * issue * issue + memory * memory * memory) + rows * (k.part * parts + k.row);
     };
-    auto estimate = [&](const Layout &lay, int parts) { return estimate_by(lay, parts, fp8_pool ? kFp8 : lay.wide ? kBf16Wide : kBf16Narrow); };
+    auto estimate = [&](const Layout &lay, int parts) { return estimate_by(lay, parts, fp8_pool ? kFp8 : lay.max_req > std::max(1, 64 / G) ? kBf16Tall : lay.wide ? kBf16Wide : kBf16Narrow); };
     // Shared nodes, bf16 pools: shared::body or 16-row tiles.  An item alone takes two thirds as long in shared::body, but two
     // workgroups fill a compute unit where three with 16-row tiles do, so that on a full chip the two come to the same and
     // how the items fill it decides (one root of 512 tokens over 64 leaves of 128 tokens 22.3 us as 16-row tiles, 17.3 as 32-row
@@ -1138,6 +1143,11 @@ static void plan_items(hkv_decode_plan &pl) {
     // Plans whose partials fit the static workspace at that length keep to lengths that fit.
     const bool search = any_shared && !pl.fp8_matrix && opt.shared_chunk == 0 && opt.leaf_chunk == 0;
     const bool narrow_too = !fp8_pool && pl.tile_form <= 0, wide_too = any_shared && (fp8_pool || pl.tile_form >= 0);
+    // Tall tiles, where some node has more than 64 rows: 1200 other plans, each timed in all forms and lengths, with this margin 164 run that way
+    // and take 0.888 of the time, three lose more than 3 % (up to 6.7 %); at 7 % 306 and 21 (up to 10 %).  They pay from about 35 us on
+    // (best length against the best of the other forms, verification: steps of 12 to 20 us 1.05, 35 to 60 us 0.93, 100 us and more 0.88).
+    const int tall_req = std::max(1, 128 / G);
+    const bool tall_too = narrow_too && wide_too && opt.max_rows == 0 && most_req > max_req_per_item;
     auto too_many = [&](int parts) { return partials_bytes((int64_t)pl.n_req * pl.num_q_heads * parts) > kStaticWorkspaceBytes; };
     auto of_default_length = [&](bool cut_more) {
         Layout lay = lay_out(wide_too && (fp8_pool || pl.tile_form > 0), cut_more);
@@ -1159,10 +1169,12 @@ static void plan_items(hkv_decode_plan &pl) {
         if (!search) return best;
         const bool fits = !too_many(best.parts);
         double least = best.us;  // times the margin: 8 % in the same form, 10 % in the other
-        for (const bool w : {false, true}) {
-            if (w ? !wide_too : !narrow_too) continue;
+        for (const int form : {0, 1, 2}) {  // 16-row tiles, 32-row tiles, tall ones
+            const bool w = form > 0;
+            if (form == 2 ? !tall_too : w ? !wide_too : !narrow_too) continue;
             Layout l = lay_out(w, cut_more);
             l.piece_tokens = pack_tokens;
+            if (form == 2) l.max_req = tall_req;
             bool whole = false;  // every node is, at this length and at those behind it
             for (const int chunk : {128, 192, 256, 384, 512, 768, 1024, 1536, 2048}) {
                 if (whole) break;
@@ -1170,7 +1182,7 @@ static void plan_items(hkv_decode_plan &pl) {
                 l.shared_chunk = chunk;
                 const int parts = parts_of(l);
                 if (fits && too_many(parts)) continue;
-                const double e = estimate(l, parts), us = e / (w == from.wide ? 0.92 : 0.90);
+                const double e = estimate(l, parts), us = e / (w == from.wide && form < 2 ? 0.92 : 0.90);
                 if (us >= least) continue;
                 least = us;
                 best = Choice{l, from, parts, e};
@@ -1231,9 +1243,9 @@ static void plan_items(hkv_decode_plan &pl) {
         // equal request groups (64 + 20 rows would leave a long item of few rows that is listed behind the others), except for a
         // remainder of up to 16 rows beside 16-row tiles: one of those costs as much for 48 rows as for 64, the remainder is run
         // by four wavefronts that share its tokens (4 x 2848 tokens over 18 requests x 8 heads 25.2 -> 22.9 us)
-        const int n_groups = (R + max_req_per_item - 1) / max_req_per_item;
-        const bool remainder = !pl.has_shared && pl.pool->d.dtype == HKV_BF16 && (R - (n_groups - 1) * max_req_per_item) * G <= 16;
-        const int req_per_group = remainder ? max_req_per_item : (R + n_groups - 1) / n_groups;
+        const int n_groups = (R + lay.max_req - 1) / lay.max_req;
+        const bool remainder = !pl.has_shared && pl.pool->d.dtype == HKV_BF16 && (R - (n_groups - 1) * lay.max_req) * G <= 16;
+        const int req_per_group = remainder ? lay.max_req : (R + n_groups - 1) / n_groups;
         for (int r0 = 0; r0 < R; r0 += req_per_group) {
             int nr = std::min(req_per_group, R - r0);
             for (int pg = 0, ci = 0; pg < nd.n_pages; pg += pages_per_chunk, ++ci) {
@@ -1546,7 +1558,7 @@ static int create_decode_plan(hkv_pool *pool, const hkv_node *nodes, int32_t n_n
         }
     hkv_decode_plan *pl = new (std::nothrow) hkv_decode_plan;
     if (!pl) return fail(HKV_ENOMEM, "hkv_decode_plan_create: out of host memory");
-    if (pool->d.dtype == HKV_BF16) pl->tile_form = flags & HKV_PLAN_NARROW_TILES ? -1 : flags & HKV_PLAN_WIDE_TILES ? 1 : 0;
+    if (pool->d.dtype == HKV_BF16) pl->tile_form = flags & HKV_PLAN_NARROW_TILES ? -1 : flags & HKV_PLAN_WIDE_TILES ? 1 : flags & HKV_PLAN_TALL_TILES ? 2 : 0;
     pl->pool = pool;
     pl->n_req = n_req;
     pl->num_q_heads = num_q_heads;

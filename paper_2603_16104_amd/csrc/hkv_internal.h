@@ -13,7 +13,7 @@ constexpr int kHeadDim = 128;
 constexpr int kBlockElems = kPage * kHeadDim;  // elements of one (page, head) K or V block
 
 // One decode workgroup: the tokens [tok_begin, tok_begin + n_tokens) of one tree node, one KV
-// head, applied to n_req of the requests below the node (n_req * G query rows, at most 64).
+// head, applied to n_req of the requests below the node (n_req * G query rows, at most 64; in bf16 plans with tall tiles 128).
 struct DecodeItem {
     int32_t page_off;   // index of the item's first page in the plan's page list
     int32_t n_tokens;   // tokens of this item; only the node's last item may end inside a page

@@ -25,6 +25,7 @@
 
 #include "hkv_device.h"
 #include "shared_body.h"
+#include "tall_body.h"
 
 namespace hkv {
 
@@ -212,6 +213,11 @@ __device__ __forceinline__ void body(const std::conditional_t<PATH != 0, DecodeP
     // with 16-row tiles) each wavefront owns a 16-row tile, all tokens, and K/V are staged once in LDS.
     if constexpr (SHARED && DT != 2) {
         if (!packed && rows > 16) {  // wavefront-uniform, the same for the whole workgroup
+            if constexpr (DT == 0)
+                if (rows > 64) {
+                    tall::body(a, it, smem, wave, lane);
+                    return;
+                }
             shared::body<DT == 1>(a, it, smem, wave, lane);
             return;
         }
