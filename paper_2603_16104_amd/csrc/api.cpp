@@ -2220,9 +2220,9 @@ extern "C" size_t attn_decode_workspace_bytes(hkv_pool *pool, const hkv_node *no
 // 128 over 1024 29.9 -> 22.7; six requests of 256 to 512 over 2048 114.5 -> 99.8.  Where the estimate gains less than 13 %
 // it was a loss as often as not (three of 1024 over 8192: estimate 0.89, measured 1.01).
 //
-// block_cost: what a key block costs such tiles, as a share of what it costs one of more than 128 rows.  Returns the estimate for the
+// block_cost: what a key block costs segments of such tiles, as a share of what it costs one of more than 128 rows; whole_block_cost: whole tiles.  Returns the estimate for the
 // way taken (0: not estimated, a workgroup per tile).
-static double split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<PrefillTile> &head_tiles, int n_cu, double block_cost) {
+static double split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<PrefillTile> &head_tiles, int n_cu, double block_cost, double whole_block_cost) {
     const int Hkv = pl.pool->d.num_kv_heads;
     const int n = (int)head_tiles.size(), workers = n_cu / Hkv;
     if (n == 0 || workers < 2 || n > 4 * workers) return 0;
@@ -2234,7 +2234,7 @@ static double split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<Prefil
     }
     // whole: dispatched in order, each to the workgroup that is free first
     std::vector<double> load(workers, 0.0);
-    for (int i = 0; i < n; ++i) *std::min_element(load.begin(), load.end()) += blocks[i] + kOver;
+    for (int i = 0; i < n; ++i) *std::min_element(load.begin(), load.end()) += blocks[i] * (whole_block_cost / block_cost) + kOver;
     const double whole_cost = *std::max_element(load.begin(), load.end());
 
     const int n_whole = n / workers * workers;
@@ -2404,23 +2404,25 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
     of_all_heads(head_tiles, pl->tiles);
     if (pool->d.dtype != HKV_FP32) {
         // Tiles in pieces of fewer rows where the tiles leave compute units without one: a wavefront without rows costs a piece
-        // nothing, and a key block takes one of up to 128 rows 0.72 and one of up to 64 rows 0.64 of the time (1.3, 0.93 and 0.84 us).
-        // As long as every piece gets a compute unit, and where the estimate is 5 % shorter than the tiles', whole or split.  32 /
-        // 8 heads, 256, 128 and 64 rows: 4 x 96 to 128 new tokens over 512 22.5, 17.9, 16.7 us; 2 x 192 to 256 over 1024 29.0
-        // (split), 25.2, 24.4; but 8 x 192 to 256 over 1024, 256 tiles, 43.4, 52.3, 85.3.
+        // nothing, up to 64 rows run as token halves (tile_body.h) over more than kPrefillHalvesTokens keys, and a key block takes one of up to 128 rows 0.72 and one of up to 64
+        // rows 0.54 of the time (1.3, 0.93 and 0.7 us).  As long as every piece gets a compute unit, and where the estimate is 5 %
+        // shorter than the whole tiles' or 15 % than the split tiles', which come out better than theirs (14 x 12 to 23 over 2656 30.5 us
+        // split, 31.7 in pieces).  32 / 8 heads, 256, 128 and 64 rows: 4 x 96 to 128 new tokens over 512 22.5, 17.9,
+        // 14.5 us; 2 x 192 to 256 over 1024 29.0 (split), 25.2, 19.8; but 8 x 192 to 256 over 1024, 256 tiles, 43.4, 52.3, 85.3.
         const int n_cu = chip_shape().n_cu;
-        const auto block_cost = [](int rows) { return rows > 128 ? 1.0 : rows > 64 ? 0.72 : 0.64; };
+        const auto keys_of = [](const PrefillTile &t) { return t.prefix_len + t.q_begin + t.n_q; };
+        const auto block_cost = [](int rows, int keys) { return rows > 128 ? 1.0 : rows > 64 ? 0.72 : keys > kPrefillHalvesTokens ? 0.54 : 0.64; };
         int most_rows = 0;
         for (const PrefillTile &t : head_tiles) most_rows = std::max(most_rows, t.n_q * G);
-        double best = split_prefill_tiles(*pl, head_tiles, n_cu, block_cost(most_rows));
+        const int most_keys = head_tiles.empty() ? 0 : keys_of(head_tiles.front());
+        double best = split_prefill_tiles(*pl, head_tiles, n_cu, most_rows > 128 ? 1.0 : most_rows > 64 ? 0.72 : 0.64, block_cost(most_rows, most_keys));
         std::vector<PrefillTile> taken;
         for (const int rows : {128, 64}) {
             if (rows >= most_rows || best == 0 || rows < G) continue;
             std::vector<PrefillTile> pieces = head_tiles_of(rows / G);
             if ((int64_t)pieces.size() * Hkv > n_cu) break;
-            const PrefillTile &longest = pieces.front();
-            const double cost = 4.0 + block_cost(rows) * ((longest.prefix_len + longest.q_begin + longest.n_q + 63) / 64);
-            if (cost > 0.95 * best) continue;
+            const double cost = 4.0 + block_cost(rows, most_keys) * ((most_keys + 63) / 64);
+            if (cost > (taken.empty() && !pl->segments.empty() ? 0.85 : 0.95) * best) continue;
             best = cost;
             taken.swap(pieces);
         }

@@ -239,6 +239,10 @@ struct DecodeTilesLaunch {
     const int32_t *q_rows;       // device, may be null: as DecodeLaunch::q_rows
 };
 
+// A prefill tile of up to 64 rows runs as token halves (tile_body.h) where it has more keys than this: below, bringing the halves together
+// costs what they save (16 x 12 new tokens over 2048, 32 / 8 heads, 34.5 -> 26.8 us, 30 x 16 over 512 15.3 -> 13.8; 32 x 16
+// over 64 9.6 -> 9.8).
+constexpr int kPrefillHalvesTokens = 256;
 // Query tokens per prefill workgroup for a given group size G (rows per workgroup / G).
 int prefill_tile_tokens(int group);
 // Both kinds of decode items in one launch (no item of `a` may be shared by more than 16 query rows).

@@ -14,6 +14,13 @@ using namespace tile;
 template <bool DECODE, bool FP8>
 __global__ __launch_bounds__(kThreads, 2) void attn_tile_kernel(TileArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[kLdsBytes];
+    if constexpr (!DECODE) {
+        const PrefillTile t = static_cast<const PrefillTile *>(a.tiles)[blockIdx.x];
+        if (t.n_q * (a.num_q_heads / a.pool.num_kv_heads) <= 64 && t.prefix_len + t.q_begin + t.n_q > kPrefillHalvesTokens) {
+            body<false, false, false, true>(a, lds, (int)blockIdx.x, 1);
+            return;
+        }
+    }
     body<DECODE, FP8>(a, lds, (int)blockIdx.x, (int)gridDim.x);
 }
 

@@ -98,13 +98,19 @@ struct TileArgs {
 // SPLIT: segments of prefill tiles (a run of a tile's key blocks), several per workgroup; a segment that is not the whole
 // tile writes a partial result (unnormalised o, reference, row sum, all fp32) for prefill_merge_kernel.
 // FP8: the pool holds e4m3 codes with a scale per 16-token block and head (decode items only).
+// HALVES: prefill tiles of up to 64 rows.  Two wavefronts on two of the four SIMDs, two steps of 32 tokens per block each, are bound by
+// their own chain of instructions (0.84 us a block; a lone wavefront issues a vector instruction every 6 to 8 cycles); four with a step
+// each take 0.65.  K is requested four blocks ahead instead of three (a phase reads a whole block ahead), and the results of the two
+// halves, each with its own reference, come together through LDS at the end.  Up to 128 rows the same split over eight
+// wavefronts gained nothing (0.93 -> 0.92 us: the barrier per block then holds one step).
 // lds: kLdsBytes of the workgroup's LDS, 16-byte aligned.  The workgroup (kThreads threads, thread index
 // threadIdx.x) runs tiles first, first + stride, ... (prefill runs one: stride is not used).
 constexpr int kLdsBytes = 2 * kStages * kTileBytes + kIdSlots * 4 + kScaleSlots * 16 + 16;
 
-template <bool DECODE, bool FP8, bool SPLIT = false>
+template <bool DECODE, bool FP8, bool SPLIT = false, bool HALVES = false>
 __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, int stride) {
     static_assert(!SPLIT || !DECODE, "segments are cut from prefill tiles");
+    static_assert(!HALVES || (!DECODE && !SPLIT), "token halves are for whole prefill tiles");
     static_assert(DECODE || !FP8, "prefill reads fp8 pools through the dequantising pre-pass");
     char(*sK)[kTileBytes] = reinterpret_cast<char(*)[kTileBytes]>(lds);
     char(*sV)[kTileBytes] = reinterpret_cast<char(*)[kTileBytes]>(lds + kStages * kTileBytes);
@@ -191,8 +197,9 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
         bt = a.ids + tl.bt_off;
     }
 
-    // the 32-row tile of this wavefront
-    const int r_tile = 32 * wave + n;            // this lane's row within the workgroup's rows
+    // the 32-row tile of this wavefront; HALVES: and its half of every 64-token block (the first four wavefronts sit on a SIMD each)
+    const int rt = HALVES ? wave & 1 : wave, kh = HALVES ? wave >> 1 : 0;
+    const int r_tile = 32 * rt + n;              // this lane's row within the workgroup's rows
     const int tok = r_tile / G;                  // token (request) index within the tile (>= n_slots: no such row)
     const int head = kv_head * G + r_tile % G;   // query head
     const int slot_c = min(tok, n_slots - 1);
@@ -201,7 +208,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     // 32 new tokens over 512, 32 / 8 heads: 25.9 -> 21.2 us; 16 x 72 to 96 over 1024: 41.3 -> 34.5; 32 x 750 to 1000 over 4096,
     // whose last tiles are short: 1792 -> 1765.
     // (Decode items have 128 rows at least, and registers to lose.)
-    const bool active = DECODE || 32 * wave < n_slots * G;
+    const bool active = DECODE || (32 * rt < n_slots * G && kh < 2);
     uint32_t io_row;                             // row of out (prefill) / of the partials' owner (decode items)
     uint32_t q_row;                              // row of q
     if constexpr (DECODE) {
@@ -218,7 +225,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
         for (int kk = 0; kk < 8; ++kk) qf[kk] = as_bf16x8(ld16(qp + (16 * kk + 8 * h) * 2));
     }
     // wavefront-uniform: smallest absolute position among this wavefront's rows
-    const int wave_min_pos = DECODE ? pos_first : pos_first + min((32 * wave) / G, n_slots - 1);
+    const int wave_min_pos = DECODE ? pos_first : pos_first + min((32 * rt) / G, n_slots - 1);
     // Rows past the tile's end behave like its last row, so they never see the garbage slots behind the sequence.
     const int pos = DECODE ? pos_first : pos_first + slot_c;
 
@@ -409,9 +416,17 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
 #pragma unroll
         for (int u = 0; u < kParts; ++u) {
             issue_k_part(2, u, 2);
-            issue_v_part(1, u, 1);
+            if constexpr (!HALVES) issue_v_part(1, u, 1);
         }
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(kLoadsPerBlock));  // all but the last group: K(0), K(1), V(0) are here
+        if constexpr (HALVES)
+#pragma unroll
+            for (int u = 0; u < kParts; ++u) issue_v_part(1, u, 1);
+        if constexpr (HALVES) {
+#pragma unroll
+            for (int u = 0; u < kParts; ++u) issue_k_part(3, u, 3);
+        }
+        // all but the last group: K(0), K(1), V(0) are here (HALVES: K(2) too)
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(kLoadsPerBlock));
         __builtin_amdgcn_s_barrier();
         if (KB > kv_len) {  // the sequence ends inside block 0
             zero_tail(0, 0);
@@ -421,8 +436,8 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     f32x16 sa, sb;  // scores of even and odd steps
     float mc = 0.f;  // reference = maximum of the row's first 32 scores (token 0 is visible), times scale * log2 e
     if (active) {
-        scores(sa, k_tile(0));
-        if (31 > wave_min_pos) mask_scores(sa, 0);
+        scores(sa, k_tile(kh));
+        if (32 * kh + 31 > wave_min_pos) mask_scores(sa, kh);
         const StepScale s0 = step_scale(0);
         float mx = sa[0] * s0.ck[0];
 #pragma unroll
@@ -430,8 +445,10 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
         mc = fmaxf(mx, __shfl_xor(mx, 32));
         // A row that lies in front of the whole segment sees nothing of it: exp2(-inf - 0) = 0 throughout.  (A row that sees it
         // and whose first scores are all -inf ends up with a sum that is no number, and so in the running-maximum loop.)
-        if (SPLIT && pos < 0) mc = 0.f;
+        // The same for a row in front of the first step of this half: it lies in front of all later ones.
+        if ((SPLIT && pos < 0) || (HALVES && pos < 32 * kh)) mc = 0.f;
     }
+    if constexpr (HALVES) __syncthreads();  // K(0) has been read: iteration 0 requests K(4) in its place
 
     // One phase, written in issue order and fenced so that the compiler keeps it.  Operands live in
     // two rings of four registers sets: each set is reloaded right after the matrix instruction
@@ -487,8 +504,8 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     if (active) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            kf[i] = lds_k(k_tile(1), i);
-            vf[i] = lds_v(v_tile(0), i);  // stands in for V(-1): finite data, multiplied by zeros
+            kf[i] = lds_k(HALVES ? k_tile(2 + kh) : k_tile(1), i);
+            vf[i] = lds_v(v_tile(kh), i);  // stands in for V(-1): finite data, multiplied by zeros
         }
     }
     // Iteration j = phases 2j and 2j+1: reads K of blocks j, j+1 and V of blocks j-1, j.  The
@@ -505,16 +522,17 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
         // K resp. V tile of step 2j + c (c >= -1): block j + c / 2, half c % 2
         auto kt = [&](int c) { return sK[(S + kStages + (c >> 1)) % kStages] + (c & 1) * 8192; };
         auto vt = [&](int c) { return sV[(S + kStages + (c >> 1)) % kStages] + (c & 1) * 8192; };
+        constexpr int KA = HALVES ? 4 : 3;  // K is requested so many blocks ahead
         if constexpr (!FP8) {
-            if (((j + 3) & 15) == 0) {
-                if ((j + 3) * 4 - id_base >= kIdSlots && (j + 3) * 4 <= last_page) {  // id slots exhausted (rare)
+            if (((j + KA) & 15) == 0) {
+                if ((j + KA) * 4 - id_base >= kIdSlots && (j + KA) * 4 <= last_page) {  // id slots exhausted (rare)
                     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
                     __syncthreads();
-                    id_base = (j + 3) * 4;  // a multiple of 64: the windows stay aligned
+                    id_base = (j + KA) * 4;  // a multiple of 64: the windows stay aligned
                     fill_ids(id_base);
                     __syncthreads();
                 }
-                kwin = window(j + 3);
+                kwin = window(j + KA);
             }
             if (((j + 2) & 15) == 0) vwin = window(j + 2);
         }
@@ -524,7 +542,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
                 store_k_fp8(kq_now, (S + 2) % kStages);
                 store_v_fp8(vq_now, j + 1, (S + 1) % kStages);
             } else {
-                issue_k_part(j + 3, 0, (S + 3) % kStages);
+                issue_k_part(j + KA, 0, (S + KA) % kStages);
                 issue_v_part(j + 2, 0, (S + 2) % kStages);
             }
         };
@@ -533,11 +551,20 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
                 kq_now = fetch_fp8(kbase, j + 4);
                 vq_now = fetch_fp8(vbase, j + 3);
             } else {
-                issue_k_part(j + 3, kParts - 1, (S + 3) % kStages);
+                issue_k_part(j + KA, kParts - 1, (S + KA) % kStages);
                 issue_v_part(j + 2, kParts - 1, (S + 2) % kStages);
             }
         };
-        if (active) {
+        if (HALVES && active) {  // one step of the block: scores of the next one, V of the one before
+            const int half = kh * 8192;
+            f32x16 &sp = S & 1 ? sb : sa, &sn = S & 1 ? sa : sb;
+            if (j > 0 && j * KB + 32 * kh + 31 > wave_min_pos) mask_scores(sp, t + kh);
+            phase(sp, sn, S & 1 ? wa : wb, S & 1 ? wb : wa, t + kh, kt(2) + half, kt(4) + half, ((S != 0 || j > 0) ? vt(-2) : vt(0)) + half, vt(0) + half,
+                  [&]() {
+                      front0();
+                      front1();
+                  });
+        } else if (active) {
             if (j > 0 && j * KB + 31 > wave_min_pos) mask_scores(sa, t);
             phase(sa, sb, wb, wa, t, kt(1), kt(2), (S != 0 || j > 0) ? vt(-1) : vt(0), vt(0), front0);
             if (j * KB + 63 > wave_min_pos) mask_scores(sb, t + 1);
@@ -571,7 +598,12 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     }
     // drain: O^T += V^T P^T of the last step (vf holds its operands 0-3, wb its probabilities)
     if (active) {
-        const char *vl = v_tile(2 * n_blk - 1);
+        const char *vl = v_tile(2 * n_blk - 2 + (HALVES ? kh : 1));
+        if constexpr (HALVES)
+            if (n_blk & 1) {
+                wb[0] = wa[0];
+                wb[1] = wa[1];
+            }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             o[i & 3] = mfma32(vf[i & 3], as_bf16x8(wb[i >> 2]), o[i & 3]);
@@ -622,6 +654,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
             }
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt) {
+                if (HALVES && mt != kh) continue;
                 f32x16 s;
                 scores(s, sK[0] + mt * 8192);
                 if (j * KB + mt * 32 + 31 > wave_min_pos) mask_scores(s, 2 * j + mt);
@@ -631,7 +664,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
                 for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i] * sc.ck[i >> 3]);
                 mx = fmaxf(mx, __shfl_xor(mx, 32));
                 const float m_top = fmaxf(m_run, mx);
-                const float m_new = SPLIT && m_top == -INFINITY ? 0.f : m_top;  // (nothing seen so far)
+                const float m_new = (SPLIT || HALVES) && m_top == -INFINITY ? 0.f : m_top;  // (nothing seen so far)
                 const float alpha = fast_exp2(m_run - m_new);
                 float p[16];
                 float sum0 = 0.f, sum1 = 0.f;
@@ -660,7 +693,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     }
 
     // ---- normalise and store; lane (n, h) holds dims 32*dm + 8*(i/4) + 4*h + i%4 of its row
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
+    float l_tot = l_run + __shfl_xor(l_run, 32);
     if (SPLIT && part >= 0) {  // the partial, in register order: every store is a whole KiB per wavefront
         float *pd = a.part_data + (size_t)part * kSplitPartFloats;
         f32x4 *po = reinterpret_cast<f32x4 *>(pd) + wave * (16 * 64) + lane;
@@ -675,6 +708,32 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
         }
         if (tid == 0) a.part_bail[part] = bail ? 1 : 0;
         continue;
+    }
+    if constexpr (HALVES) {  // the second half's results come to the first half's wavefront through LDS, lane by lane
+        static_assert(2 * 16 * 64 * sizeof(f32x4) + 2 * 128 * sizeof(float) <= 2 * kStages * kTileBytes, "hand-over buffer inside the stages");
+        f32x4 *xo = reinterpret_cast<f32x4 *>(lds) + rt * (16 * 64) + lane;
+        float *xm = reinterpret_cast<float *>(lds + 2 * 16 * 64 * sizeof(f32x4)) + rt * 128 + lane;
+        __syncthreads();  // the stages have been read
+        const float m_own = l_tot > 0.f ? m_fin : -INFINITY;
+        if (active && kh == 1) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+                xo[64 * k] = f32x4{o[k >> 2][4 * (k & 3)], o[k >> 2][4 * (k & 3) + 1], o[k >> 2][4 * (k & 3) + 2], o[k >> 2][4 * (k & 3) + 3]};
+            xm[0] = m_own;
+            xm[64] = l_tot;
+        }
+        __syncthreads();
+        if (!active || kh == 1) return;
+        const float m1 = xm[0], M = fmaxf(m_own, m1);
+        const float w0 = fast_exp2(m_own - M), w1 = fast_exp2(m1 - M);  // (a row sees its own key at least: M is finite)
+        l_tot = l_tot * w0 + xm[64] * w1;
+        m_fin = M;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const f32x4 x = xo[64 * k];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[k >> 2][4 * (k & 3) + j] = o[k >> 2][4 * (k & 3) + j] * w0 + x[j] * w1;
+        }
     }
     float up = 1.f, down = 1.f;
     if constexpr (DECODE) {  // the partial goes out as fp16 times a power of two that puts the row's largest value near 2^14

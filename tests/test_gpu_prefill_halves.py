@@ -1,0 +1,59 @@
+"""Prefill tiles of up to 64 rows over more than 256 keys, whose four wavefronts take a 32-row tile and a token half each: the edges of row
+tiles, of halves and blocks, page-id windows that are refilled, a late dominant key (the running-maximum loop).  Against the
+oracle."""
+import numpy as np
+import pytest
+
+from paper_2603_16104_amd import workloads as wl
+
+from test_gpu_parity import LSE_ABS_FP8_PREFILL, both_pools, check_close, check_lse, gpu  # noqa: F401
+from test_gpu_shared_items import Rising
+
+pytestmark = pytest.mark.gpu
+
+
+def run(gpu, oracle, kv_dtype, hq, hk, prefix, new, pieces=None, gain=0.0, fallback=None, lse_fp8=LSE_ABS_FP8_PREFILL):  # noqa: F811
+    import torch
+    from paper_2603_16104_amd import binding as hkv
+    parent, ntok = [-1] + [0] * len(new), [prefix] + list(new)
+    n_pages = sum((t + 15) // 16 for t in ntok)
+    f = wl.make_forest(parent, ntok, list(range(1, len(new) + 1)), np.random.default_rng([prefix, *new[:8]]).permutation(n_pages + 3).astype(np.int32))
+    w = Rising(name=f"{hq}_{hk}_{prefix}_{new}", num_q_heads=hq, num_kv_heads=hk, kv_dtype=kv_dtype, num_pages=n_pages + 3, seed=prefix + len(new),
+               forest=f, mode="prefill", q_len=np.asarray(new, dtype=np.int32), gain=gain)
+    hp, dp = both_pools(gpu, oracle, w)
+    exp_o, exp_l = oracle.run_workload(w, hp)
+    r = gpu.PrefillRunner(dp, w)
+    if pieces is not None:
+        assert hkv.hkv_prefill_plan_num_pieces(r.plan) == pieces
+    for _ in range(2):
+        r.out.fill_(0x7FC0)
+        r.lse.fill_(float("nan"))
+        r.run()
+        torch.cuda.synchronize()
+        check_close(gpu.bf16_tensor_to_f64(r.out), exp_o, w.name)
+        check_lse(r.lse.cpu().numpy(), exp_l, w.name, tol=lse_fp8 if kv_dtype == wl.KV_FP8_E4M3 else 2e-3)
+    if fallback is not None:
+        assert (hkv.hkv_prefill_plan_fallback_tiles(r.plan) > 0) == fallback
+    r.close()
+    dp.close()
+
+
+@pytest.mark.parametrize("hq, hk, prefix, new", [
+    (4, 1, 256, (1, 2, 7, 8, 9, 16)), (4, 1, 272, (15, 16, 1)), (4, 1, 288, (16, 3)), (4, 1, 304, (5, 16)), (5, 1, 320, (12, 6, 1)), (16, 1, 496, (3, 4, 1)),
+    (1, 1, 512, (33, 64, 31)), (8, 2, 960, (13, 16)), (4, 1, 1008, (16,)), (4, 1, 1024, (16, 1)), (4, 1, 1200, (9,)), (4, 1, 16 * 130, (16, 11)),
+])
+@pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
+def test_token_halves(gpu, oracle, kv_dtype, hq, hk, prefix, new):  # noqa: F811
+    run(gpu, oracle, kv_dtype, hq, hk, prefix, new)
+
+
+def test_page_ids_are_refilled(gpu, oracle):  # noqa: F811
+    """More than 2048 blocks of 16 keys, in a batch of one whole round of tiles (which is not split along the keys)."""
+    run(gpu, oracle, wl.KV_BF16, 32, 32, 33008, (3, 1) * 4, 0)
+
+
+@pytest.mark.parametrize("gain, fallback", [(15.0, None), (400.0, True)])
+def test_scores_that_rise(gpu, oracle, gain, fallback):  # noqa: F811
+    """The largest scores lie in the last blocks: references far behind them, and sums beyond what one reference carries."""
+    run(gpu, oracle, wl.KV_BF16, 8, 2, 16, (300,), gain=gain, fallback=fallback)
+    run(gpu, oracle, wl.KV_BF16, 4, 1, 704, (16, 5), gain=gain)
