@@ -505,8 +505,8 @@ int hkv_prefill_plan_create_rows(hkv_pool *pool, const int32_t *q_row_begin, con
 int hkv_prefill_plan_destroy(hkv_prefill_plan *plan);
 /* Number of (request, query tile, kv head) tiles of the plan: a workgroup each, or, where a run splits them along their
  * keys, hkv_prefill_plan_num_segments pieces of work for one workgroup per compute unit (0: the plan splits nothing).
- * Small batches run their tiles in pieces of a half or a quarter of the rows instead, a workgroup each:
- * hkv_prefill_plan_num_pieces of them (0: whole tiles). */
+ * Small batches run their tiles in pieces of a half or a quarter of the rows instead, a workgroup each, and batches of more tiles
+ * than compute units may run what exceeds whole rounds as half tiles: hkv_prefill_plan_num_pieces of them (0: the tiles as they are). */
 int32_t hkv_prefill_plan_num_tiles(const hkv_prefill_plan *plan);
 int32_t hkv_prefill_plan_num_pieces(const hkv_prefill_plan *plan);
 int32_t hkv_prefill_plan_num_segments(const hkv_prefill_plan *plan);
