@@ -218,19 +218,25 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     } else {
         q_row = io_row = (uint32_t)(tl.q_row0 + slot_c) * Hq + head;
     }
+    // The first page ids are requested in front of the queries: loads complete in order, and K and V wait for the ids alone.
+    const int last_page = (kv_len - 1) >> 4;
+    int first_ids[kIdSlots / kThreads];
+#pragma unroll
+    for (int i = 0; i < kIdSlots / kThreads; ++i) first_ids[i] = bt[min(tid + i * kThreads, last_page)];
+    __builtin_amdgcn_sched_barrier(0);
     bf16x8 qf[8];
     {
         const char *qp = static_cast<const char *>(a.q) + (size_t)q_row * (kHeadDim * 2);
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) qf[kk] = as_bf16x8(ld16(qp + (16 * kk + 8 * h) * 2));
     }
+    __builtin_amdgcn_sched_barrier(0);
     // wavefront-uniform: smallest absolute position among this wavefront's rows
     const int wave_min_pos = DECODE ? pos_first : pos_first + min((32 * rt) / G, n_slots - 1);
     // Rows past the tile's end behave like its last row, so they never see the garbage slots behind the sequence.
     const int pos = DECODE ? pos_first : pos_first + slot_c;
 
     const int n_blk = (kv_end + KB - 1) / KB;
-    const int last_page = (kv_len - 1) >> 4;
     const char *kbase = static_cast<const char *>(a.pool.k_pages) + (size_t)kv_head * BB;
     const char *vbase = static_cast<const char *>(a.pool.v_pages) + (size_t)kv_head * BB;
 
@@ -379,7 +385,8 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
 #pragma unroll
     for (int dm = 0; dm < 4; ++dm) o[dm] = zero16();
     if (tid == 0) sBail = 0;
-    fill_ids(0);
+#pragma unroll
+    for (int i = 0; i < kIdSlots / kThreads; ++i) sIds[tid + i * kThreads] = first_ids[i];
     if constexpr (FP8) {
         for (int p = tid; p < min(4 * n_blk, kScaleSlots); p += kThreads) {  // every page of every 64-token block
             const size_t id = (size_t)bt[min(p, last_page)];
@@ -413,18 +420,25 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
             issue_k_part(1, u, 1);
             issue_v_part(0, u, 0);
         }
+        // The queries have to be waited for before the loop (the compiler would otherwise wait inside it, for everything in flight), and
+        // that wait ends with the blocks that have to be here anyway: what it must not hold up is requested behind it.
+        auto queries_are_here = [&]() {
 #pragma unroll
-        for (int u = 0; u < kParts; ++u) {
-            issue_k_part(2, u, 2);
-            if constexpr (!HALVES) issue_v_part(1, u, 1);
-        }
+            for (int kk = 0; kk < 8; ++kk) {
+                u32x4 w = __builtin_bit_cast(u32x4, qf[kk]);
+                asm volatile("" : "+v"(w));
+                qf[kk] = as_bf16x8(w);
+            }
+        };
+        if constexpr (!HALVES) queries_are_here();
+#pragma unroll
+        for (int u = 0; u < kParts; ++u) issue_k_part(2, u, 2);
+        if constexpr (HALVES) queries_are_here();
+#pragma unroll
+        for (int u = 0; u < kParts; ++u) issue_v_part(1, u, 1);
         if constexpr (HALVES)
 #pragma unroll
-            for (int u = 0; u < kParts; ++u) issue_v_part(1, u, 1);
-        if constexpr (HALVES) {
-#pragma unroll
             for (int u = 0; u < kParts; ++u) issue_k_part(3, u, 3);
-        }
         // all but the last group: K(0), K(1), V(0) are here (HALVES: K(2) too)
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(kLoadsPerBlock));
         __builtin_amdgcn_s_barrier();
@@ -746,34 +760,31 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
         part_factors(amax, up, down);
         up *= 1.0f / l_tot;
     }
-    if (tok < n_slots) {
-        const float inv = 1.0f / l_tot;
-        if constexpr (DECODE) {  // the row's partial for this chunk of the node
-            const size_t part = (size_t)io_row * a.max_parts + it.part_slot;
-            uint16_t *op = a.o_parts + part * kHeadDim + 4 * h;
+    {
+        const float factor = DECODE ? up : 1.0f / l_tot;
+        const size_t part = DECODE ? (size_t)io_row * a.max_parts + it.part_slot : io_row;  // DECODE: the row's partial for this chunk of the node
+        uint16_t *op = (DECODE ? a.o_parts : static_cast<uint16_t *>(a.out)) + part * kHeadDim + 8 * h;
 #pragma unroll
-            for (int dm = 0; dm < 4; ++dm)
+        for (int dm = 0; dm < 4; ++dm)
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    u32x2 w;
-                    w[0] = pack_f16(o[dm][4 * q4] * up, o[dm][4 * q4 + 1] * up);
-                    w[1] = pack_f16(o[dm][4 * q4 + 2] * up, o[dm][4 * q4 + 3] * up);
-                    *reinterpret_cast<u32x2 *>(op + 32 * dm + 8 * q4) = w;
+            for (int q4 = 0; q4 < 4; q4 += 2) {
+                u32x2 w[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int i = 4 * (q4 + k);
+                    const float x0 = o[dm][i] * factor, x1 = o[dm][i + 1] * factor, x2 = o[dm][i + 2] * factor, x3 = o[dm][i + 3] * factor;
+                    w[k] = DECODE ? u32x2{pack_f16(x0, x1), pack_f16(x2, x3)} : u32x2{pack_bf16(x0, x1), pack_bf16(x2, x3)};
                 }
-            if (h == 0) a.down_parts[part] = down;
-            if (h == 0) a.lse_parts[part] = partial_lse(m_fin, l_tot);
-        } else {
-            uint16_t *op = static_cast<uint16_t *>(a.out) + (size_t)io_row * kHeadDim;
-#pragma unroll
-            for (int dm = 0; dm < 4; ++dm)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    u32x2 w;
-                    w[0] = pack_bf16(o[dm][4 * q4] * inv, o[dm][4 * q4 + 1] * inv);
-                    w[1] = pack_bf16(o[dm][4 * q4 + 2] * inv, o[dm][4 * q4 + 3] * inv);
-                    *reinterpret_cast<u32x2 *>(op + 32 * dm + 8 * q4 + 4 * h) = w;
-                }
-            if (a.lse_out && h == 0) a.lse_out[io_row] = (m_fin + fast_log2(l_tot)) * kLn2;
+                const u32x4 both = join_halves(w[0], w[1]);
+                if (tok < n_slots) *reinterpret_cast<u32x4 *>(op + 32 * dm + 8 * q4) = both;
+            }
+        if (tok < n_slots && h == 0) {
+            if constexpr (DECODE) {
+                a.down_parts[part] = down;
+                a.lse_parts[part] = partial_lse(m_fin, l_tot);
+            } else if (a.lse_out) {
+                a.lse_out[io_row] = (m_fin + fast_log2(l_tot)) * kLn2;
+            }
         }
     }
     if constexpr (!DECODE && !SPLIT) break;
