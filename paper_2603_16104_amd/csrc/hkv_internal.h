@@ -213,6 +213,7 @@ struct RowsLaunch {
     int32_t max_pages;
     float scale;
 };
+constexpr int kRowWorkgroups = 256;  // what fills the chip: rows are given fewer of their heads a workgroup until there are so many
 
 // Largest token count of a decode item that is shared by more than 16 query rows.
 constexpr int kMaxSharedItemTokens = 2048;

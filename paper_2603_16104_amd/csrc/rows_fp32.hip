@@ -16,15 +16,14 @@ namespace hkv {
 namespace {
 
 // One workgroup per (query token, KV head, up to kRows of its query heads): its wavefronts take turns at steps of two
-// pages and combine in LDS.  Bound by the latency of a chain of steps per wavefront (K of the next step is requested
-// behind the first product, V behind the second), then by K/V from L2.  Every load is one KiB a wavefront: lane = (slot,
-// quarter of a 16-dimension chunk) for K, (dimension, quarter of the slots) for V, so a dot product is 32 multiply-adds in a
-// lane and two adds over its quad.  A wavefront per (token, head) with a lane per key read 64-byte pieces, walked all keys
-// alone and took 118 us for 16 requests x 32 heads over 1024 + 256 tokens on half of the chip; this takes 18.3 us (512 new
-// tokens over 2048: 3.02 -> 0.77 ms), with a third of the rounding error, the dot products being shorter chains.
+// pages (kRows = 4: of one) and combine in LDS.  Bound by the latency of a chain of steps per wavefront (K of the next step is
+// requested behind the first product, V behind the second), then by K/V from L2: a compute unit takes in about 110 bytes per ns, so
+// what counts is how many heads share a read.  Every load is one KiB a wavefront: lane = (slot, quarter of a 16-dimension chunk) for
+// K, (dimension, quarter of the slots) for V, so a dot product is 32 multiply-adds in a lane and two adds over its quad.  A wavefront
+// per (token, head) with a lane per key read 64-byte pieces, walked all keys alone and took 118 us for 16 requests x 32 heads over
+// 1024 + 256 tokens on half of the chip, with three times the rounding error, the dot products being longer chains; two heads a
+// workgroup take 18.2 us there (512 new tokens over 2048: 3.02 -> 0.77 ms).  Four heads and twice the rows: see heads_per_workgroup.
 constexpr int kRowWaves = 8;  // at most; fewer for short sequences (the launch decides)
-constexpr int kStepPages = 2;
-constexpr int kStepKeys = kStepPages * kPage;
 
 __device__ __forceinline__ float quad_sum(float v) {
     v += dpp<kQuadXor1>(v);
@@ -33,14 +32,15 @@ __device__ __forceinline__ float quad_sum(float v) {
 
 template <int kRows>
 __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch a) {
-    static_assert(kRows == 1 || kRows == 2, "a lane of a quad stands for one row and page of a step");
+    static_assert(kRows == 1 || kRows == 2 || kRows == 4, "a lane of a quad stands for one row and page of a step");
+    constexpr int kStepPages = kRows == 4 ? 1 : 2, kStepKeys = kStepPages * kPage;
     __shared__ float sP[kRowWaves][kRows][kStepKeys];
     __shared__ float sO[kRowWaves][kRows][kHeadDim];
     __shared__ float sM[kRowWaves][kRows], sL[kRowWaves][kRows];
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int Hkv = a.pool.num_kv_heads, G = a.num_q_heads / Hkv, groups = (G + kRows - 1) / kRows;
+    const int Hkv = a.pool.num_kv_heads, G = a.num_q_heads / Hkv, groups = (G + kRows - 1) / kRows, per_group = (G + groups - 1) / groups;
     const int kvh = (int)(blockIdx.x % Hkv);  // a head stays on its XCD where there are eight
-    const int rest = (int)(blockIdx.x / Hkv), h0 = rest % groups * kRows, tq = rest / groups;
+    const int rest = (int)(blockIdx.x / Hkv), h0 = rest % groups * per_group, tq = rest / groups;
     const int len = a.row_len[tq];  // keys this query token sees
     const int32_t *bt = a.block_table + (size_t)a.row_req[tq] * a.max_pages;
     const float *K = static_cast<const float *>(a.pool.k_pages) + (size_t)kvh * kBlockElems + 4 * lane;
@@ -48,8 +48,8 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
     const size_t page_stride = (size_t)Hkv * kBlockElems;
     const int slot = lane >> 2, quarter = lane & 3, n_waves = (int)blockDim.x >> 6;
     // in a quad every lane owns one (page of the step, row): its exponentials and row sums
-    const int own_page = kRows == 2 ? quarter >> 1 : quarter & 1, own_row = kRows == 2 ? quarter & 1 : 0;
-    const bool counts = kRows == 2 || quarter < 2;  // (one row: the upper two lanes repeat the lower two)
+    const int own_page = kRows == 4 ? 0 : kRows == 2 ? quarter >> 1 : quarter & 1, own_row = kRows == 4 ? quarter : kRows == 2 ? quarter & 1 : 0;
+    const bool counts = kRows > 1 || quarter < 2;  // (one row: the upper two lanes repeat the lower two)
     const float c = a.scale * kLog2e;
 
     f32x4 qf[kRows][8];
@@ -59,7 +59,8 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
 #pragma unroll
         for (int i = 0; i < 8; ++i) qf[r][i] = *reinterpret_cast<const f32x4 *>(qp + 16 * i);
     }
-    const int n_steps = (len + kStepKeys - 1) / kStepKeys, last_page = max(len - 1, 0) >> 4;
+    const int n_steps = (len + kStepKeys - 1) / kStepKeys;
+    const int last_page = max(len - 1, 0) >> 4;
     f32x4 kf[kStepPages][8], vf[kStepPages][8];
     auto fetch = [&](f32x4 (&f)[kStepPages][8], const float *base, int step) {
 #pragma unroll
@@ -104,12 +105,17 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
             __builtin_amdgcn_sched_barrier(0);
             fetch(kf, K, step + n_waves);  // the K registers are free (behind the last step: its page again, in bounds)
             __builtin_amdgcn_sched_barrier(0);
-            float x = kRows == 2 ? (own_row ? (own_page ? s[1][kRows - 1] : s[0][kRows - 1]) : (own_page ? s[1][0] : s[0][0])) : (own_page ? s[1][0] : s[0][0]);
+            float x = s[0][0];  // of the own row and page
+#pragma unroll
+            for (int g = 0; g < kStepPages; ++g)
+#pragma unroll
+                for (int r = 0; r < kRows; ++r)
+                    if (g + r > 0) x = own_page == g && own_row == r ? s[g][r] : x;
             x = (step * kStepPages + own_page) * kPage + slot < len ? x * c : -INFINITY;
             float mx = fmaxf(x, dpp<kRor4>(x));  // over the lanes of the own row: slots ...
             mx = fmaxf(mx, dpp<kRor8>(mx));
             mx = rows_max(mx);
-            mx = fmaxf(mx, kRows == 2 ? dpp<kQuadXor2>(mx) : dpp<kQuadXor1>(mx));  // ... and pages
+            if (kStepPages == 2) mx = fmaxf(mx, kRows == 2 ? dpp<kQuadXor2>(mx) : dpp<kQuadXor1>(mx));  // ... and pages
             const float m_new = fmaxf(m, mx);
             const float alpha = fast_exp2(m - m_new);
             const float p = fast_exp2(x - m_new);
@@ -120,7 +126,8 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
             const bool tail = (step + 1) * kStepKeys > len;
 #pragma unroll
             for (int r = 0; r < kRows; ++r) {
-                const float al = kRows == 2 ? (r ? dpp<0x55>(alpha) : dpp<0x00>(alpha)) : alpha;  // the row's factor from its lane of the quad
+                // the row's factor from its lane of the quad
+                const float al = kRows == 1 ? alpha : r == 0 ? dpp<0x00>(alpha) : r == 1 ? dpp<0x55>(alpha) : r == 2 ? dpp<0xAA>(alpha) : dpp<0xFF>(alpha);
                 acc[r][0] *= al;
                 acc[r][1] *= al;
                 if (kCareful && al == 0.f) acc[r][0] = acc[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -171,8 +178,8 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
     float lt = l + dpp<kRor4>(l);
     lt += dpp<kRor8>(lt);
     lt = rows_sum(lt);
-    lt += kRows == 2 ? dpp<kQuadXor2>(lt) : dpp<kQuadXor1>(lt);
-    if (lane < kRows) {  // lanes 0 and 1 own rows 0 and 1
+    if (kStepPages == 2) lt += kRows == 2 ? dpp<kQuadXor2>(lt) : dpp<kQuadXor1>(lt);
+    if (lane < kRows) {  // lane r owns row r
         sM[wave][lane] = m;
         sL[wave][lane] = lt;
     }
@@ -186,7 +193,7 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
     __syncthreads();
     for (int t = threadIdx.x; t < kRows * kHeadDim; t += blockDim.x) {
         const int r = t / kHeadDim, d = t % kHeadDim;
-        if (h0 + r >= G) return;
+        if (r >= per_group || h0 + r >= G) return;
         float M = -INFINITY;
         for (int w = 0; w < n_waves; ++w) M = fmaxf(M, sM[w][r]);
         float L = 0.f, out = 0.f;
@@ -217,13 +224,25 @@ __global__ __launch_bounds__(256) void pool_write_fp32_kernel(PoolWriteLaunch a)
 
 }  // namespace
 
+namespace {
+// Query heads of a KV head that a workgroup takes: they share its K/V reads, which are what long rows are bound by (a compute unit takes in
+// about 110 bytes per ns).  Four where that still gives every compute unit a workgroup, and where a wavefront has more than a step
+// or two: 32 requests x 32 / 8 heads over 1024 + 256 tokens 36.0 -> 25.0 us, 16 x 64 / 8 32.8 -> 21.4, 2 x 64 new tokens over 512 69.8 -> 42.8;
+// but 48 x 32 / 8 over 16 + 30 tokens 7.7 -> 8.6, and 33 x 40 / 8 over 96 + 17 10.4 -> 11.1.
+int heads_per_workgroup(const RowsLaunch &a, int Hkv, int G) {
+    if (G <= 2) return G;
+    const bool short_rows = a.max_pages <= 4 || (a.max_pages <= 8 && G % 4 != 0);
+    return !short_rows && (int64_t)a.n_q_tokens * Hkv * ((G + 3) / 4) >= kRowWorkgroups ? 4 : 2;
+}
+}  // namespace
+
 hipError_t launch_rows_fp32(const RowsLaunch &a, hipStream_t s) {
     const int Hkv = a.pool.num_kv_heads, G = a.num_q_heads / Hkv;
-    // a step is 32 keys: sequences that never reach four steps a wavefront would pay for wavefronts without one (128 query
+    // a step is 32 keys (four heads: 16): sequences that never reach four steps a wavefront would pay for wavefronts without one (128 query
     // tokens of 17 to 32 keys, 32 heads: 24.2 us with eight, 12.5 us with two)
     const int waves = a.max_pages > 16 ? kRowWaves : a.max_pages > 8 ? 4 : 2;
-    // two query heads of a KV head per workgroup: they share its K/V reads
-    const size_t per_token = (size_t)Hkv * (G == 1 ? 1 : (G + 1) / 2);
+    const int rows = heads_per_workgroup(a, Hkv, G);
+    const size_t per_token = (size_t)Hkv * ((G + rows - 1) / rows);
     const size_t most = std::max<size_t>(1, ((size_t)1 << 31) / (per_token * 64 * waves));  // query tokens of a launch: below 2^32 threads
     for (size_t t0 = 0; t0 < (size_t)std::max(a.n_q_tokens, 0); t0 += most) {
         RowsLaunch b = a;
@@ -234,10 +253,8 @@ hipError_t launch_rows_fp32(const RowsLaunch &a, hipStream_t s) {
         b.row_req += t0;
         b.row_len += t0;
         const dim3 grid((unsigned)(b.n_q_tokens * per_token)), block(64 * waves);
-        if (G == 1)
-            hipLaunchKernelGGL(rows_fp32_kernel<1>, grid, block, 0, s, b);
-        else
-            hipLaunchKernelGGL(rows_fp32_kernel<2>, grid, block, 0, s, b);
+        auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, b); };
+        rows == 1 ? go(rows_fp32_kernel<1>) : rows == 2 ? go(rows_fp32_kernel<2>) : go(rows_fp32_kernel<4>);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
     return hipSuccess;
