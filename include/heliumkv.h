@@ -80,8 +80,9 @@ enum {
 /* Pool element types.  bf16 and fp8 pools are the throughput paths (matrix cores, bf16 q and out).
  * An fp32 pool selects the full-precision path: k_src / v_src of kv_pool_write, q, and out of the
  * attention calls are then fp32 as well, all arithmetic is fp32 on the vector ALUs, one workgroup
- * per (query token, up to four query heads) without sharing between requests, no workspace is needed, and
- * results agree with exact attention to about 1e-6 (the bound asked of fp32 inputs is 1e-4).
+ * per (query token, up to four query heads) without sharing between requests, no workspace is needed (a decode plan of few rows
+ * cuts their keys into shares where it is given one), and results agree with exact attention to about 1e-6 (the bound asked
+ * of fp32 inputs is 1e-4).
  * fp32 block format: K in 64-byte chunks of 16 floats ((d/16)*256 + slot*16 + d%16), V
  * dimension-major (d*16 + slot). */
 enum { HKV_BF16 = 0, HKV_FP8_E4M3 = 1, HKV_FP32 = 2 };
@@ -391,7 +392,8 @@ int hkv_decode_plan_append_tokens(hkv_decode_plan *plan, const int32_t *new_page
 int hkv_decode_plan_destroy(hkv_decode_plan *plan);
 /* Bytes of device workspace attn_decode_plan_run needs (per partial: o as 128 fp16 values times a power of two,
  * that power's reciprocal and lse as floats),
- * 0 on a null plan. */
+ * 0 on a null plan.  fp32 pools: the bytes with which a run spreads few rows over the chip (528 per query row and share of its keys,
+ * 540 KB at most; 0 where the rows are many or short): a run without them, also one given less, keeps its rows whole. */
 size_t hkv_decode_plan_workspace_bytes(const hkv_decode_plan *plan);
 /* Introspection for tests and tools (host copies).  Work item layout, 8 int32 each:
  * (page_off, n_tokens, kv_head, req_off, n_req, part_slot, tok_begin, node).  page_off indexes
@@ -431,7 +433,7 @@ int hkv_decode_plan_part_counts(const hkv_decode_plan *plan, int32_t *part_count
 
 /* Runs one decode step.  q: device [n_req][num_q_heads][128] bf16.  out: device, same shape,
  * bf16.  lse_out: device [n_req][num_q_heads] float or NULL.  workspace: device, at least
- * hkv_decode_plan_workspace_bytes(plan) bytes, 256-byte aligned; its contents are scratch.
+ * hkv_decode_plan_workspace_bytes(plan) bytes, 256-byte aligned; its contents are scratch (fp32 pools: may be NULL or smaller).
  * A request whose path holds no token gets out = 0, lse = -inf.  A row whose scores hold a NaN or +inf gets NaN in out and lse.
  * EINVAL (null/unaligned), ENOMEM (workspace too small), EHIP. */
 int attn_decode_plan_run(hkv_decode_plan *plan, const void *q, float scale, void *out, float *lse_out,

@@ -127,6 +127,7 @@ struct hkv_decode_plan {
     std::vector<int32_t> row_len;
     int32_t max_pages = 0;
     int32_t *d_bt = nullptr, *d_rows_req = nullptr, *d_rows_len = nullptr;
+    int32_t row_parts = 1;  // shares that a row's keys are cut into where the caller's workspace has room for their results
     // growing plans (hkv_decode_plan_create_growing): every request's leaf has block slots in node_pages
     // for reserve_tokens more tokens; grow_items holds, per request, the num_kv_heads items of the leaf's
     // last chunk.  Items and block list are re-sent after every append through a ring of pinned buffers.
@@ -1494,6 +1495,14 @@ static int build_fp32_rows(hkv_decode_plan &pl, bool upload) {
         }
         pl.max_pages = std::max<int32_t>(pl.max_pages, (int32_t)paths[r].size());
     }
+    // Few rows leave compute units idle, and a row's workgroup takes in no more than one can: its keys are cut, down to 128 a share,
+    // until every compute unit has a share (of up to four heads).  The second kernel takes 3 us, so shorter rows stay whole: over 518
+    // keys 9.6 -> 10.6 us for one request (32 / 8 heads), 11.2 -> 12.9 for 16; over 1020 keys 14.3 -> 10.6 for 2.
+    // Two shares pay later: 24 requests x 4 / 4 heads over 1026 keys 14.1 -> 14.5, 16 x 32 / 8 over 1280 18.2 -> 16.7.
+    const int G = pl.group, heads = G <= 2 ? G : 4;
+    const int64_t units = std::max<int64_t>(1, (int64_t)n * pl.pool->d.num_kv_heads * ((G + heads - 1) / heads));
+    pl.row_parts = (int32_t)std::max<int64_t>(1, std::min<int64_t>({kMaxRowParts, kRowWorkgroups / units, pl.max_pages / 8}));
+    if (pl.max_pages < (pl.row_parts == 2 ? kMinHalvedPages : kMinCutPages)) pl.row_parts = 1;
     if (!upload || n == 0) return HKV_OK;
     std::vector<int32_t> bt((size_t)n * pl.max_pages, 0), req(n);
     for (int r = 0; r < n; ++r) {
@@ -1946,7 +1955,9 @@ extern "C" int hkv_decode_plan_destroy(hkv_decode_plan *plan) {
 }
 
 extern "C" size_t hkv_decode_plan_workspace_bytes(const hkv_decode_plan *plan) {
-    if (!plan || plan->pool->d.dtype == HKV_FP32) return 0;
+    if (!plan) return 0;
+    if (plan->pool->d.dtype == HKV_FP32)
+        return plan->row_parts > 1 ? sizeof(float) * kRowPartFloats * (size_t)plan->n_req * plan->num_q_heads * plan->row_parts : 0;
     return partials_bytes(plan->n_parts);
 }
 
@@ -1996,12 +2007,13 @@ extern "C" int hkv_decode_plan_part_counts(const hkv_decode_plan *plan, int32_t 
 }
 
 // The common part of the two run calls; arguments are checked by the callers.  workspace holds at least
-// hkv_decode_plan_workspace_bytes(plan) bytes (unused for fp32 pools).
+// hkv_decode_plan_workspace_bytes(plan) bytes (fp32 pools: or is null, and the rows stay whole).
 static int run_decode_plan(hkv_decode_plan *plan, const void *q, float scale, void *out, float *lse_out,
                            void *workspace, void *stream) {
     if (plan->pool->d.dtype == HKV_FP32) {
         RowsLaunch a{view_of(plan->pool), static_cast<const float *>(q), plan->d_bt, plan->d_rows_req, plan->d_rows_len,
-                     static_cast<float *>(out), lse_out, plan->n_req, plan->num_q_heads, plan->max_pages, scale};
+                     static_cast<float *>(out), lse_out, plan->n_req, plan->num_q_heads, plan->max_pages, scale,
+                     workspace ? plan->row_parts : 1, static_cast<float *>(workspace)};
         HKV_HIP(launch_rows_fp32(a, static_cast<hipStream_t>(stream)));
         return HKV_OK;
     }
@@ -2080,6 +2092,10 @@ extern "C" int attn_decode_plan_run(hkv_decode_plan *plan, const void *q, float 
     if (plan->n_req == 0) return HKV_OK;
     if (int rc = check_decode_run(plan, q, out, "attn_decode_plan_run")) return rc;
     const size_t need = hkv_decode_plan_workspace_bytes(plan);
+    if (plan->pool->d.dtype == HKV_FP32) {  // a workspace is welcome, not needed
+        const bool room = workspace && !(reinterpret_cast<uintptr_t>(workspace) & 15) && workspace_bytes >= need;
+        return run_decode_plan(plan, q, scale, out, lse_out, room ? workspace : nullptr, stream);
+    }
     if (need && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255)))
         return fail(HKV_EINVAL, "attn_decode_plan_run: workspace must be non-null and 256-byte aligned");
     if (workspace_bytes < need)
@@ -2094,6 +2110,7 @@ extern "C" int attn_decode_plan_run_static(hkv_decode_plan *plan, const void *q,
     if (!plan) return fail(HKV_EINVAL, "attn_decode_plan_run_static: null plan");
     if (plan->n_req == 0) return HKV_OK;
     if (int rc = check_decode_run(plan, q, out, "attn_decode_plan_run_static")) return rc;
+    if (plan->pool->d.dtype == HKV_FP32) return run_decode_plan(plan, q, scale, out, lse_out, nullptr, stream);  // (no partials: whole rows)
     const size_t need = hkv_decode_plan_workspace_bytes(plan);
     if (need > kStaticWorkspaceBytes)
         return fail(HKV_ENOMEM, "attn_decode_plan_run_static: the plan needs %zu bytes of workspace, the static "

@@ -212,8 +212,15 @@ struct RowsLaunch {
     int32_t num_q_heads;
     int32_t max_pages;
     float scale;
+    // Few rows: their keys cut into n_parts shares, a workgroup each, whose results part_data (device, kRowPartFloats per row of out and
+    // share) holds for a second kernel; n_parts <= 1: whole rows.
+    int32_t n_parts;
+    float *part_data;
 };
-constexpr int kRowWorkgroups = 256;  // what fills the chip: rows are given fewer of their heads a workgroup until there are so many
+constexpr int kMaxRowParts = 32;
+constexpr int kMinCutPages = 64, kMinHalvedPages = 80;  // rows whose longest has fewer stay whole (the latter: where there would be two shares)
+constexpr int kRowPartFloats = kHeadDim + 4;  // o, reference, row sum; 16-byte pieces
+constexpr int kRowWorkgroups = 256;           // what fills the chip: rows are cut, or given fewer of their heads a workgroup, until there are so many
 
 // Largest token count of a decode item that is shared by more than 16 query rows.
 constexpr int kMaxSharedItemTokens = 2048;

@@ -23,6 +23,9 @@ namespace {
 // per (token, head) with a lane per key read 64-byte pieces, walked all keys alone and took 118 us for 16 requests x 32 heads over
 // 1024 + 256 tokens on half of the chip, with three times the rounding error, the dot products being longer chains; two heads a
 // workgroup take 18.2 us there (512 new tokens over 2048: 3.02 -> 0.77 ms).  Four heads and twice the rows: see heads_per_workgroup.
+// SPLIT: a workgroup takes one of n_parts shares of its rows' steps and leaves its sums to rows_fp32_merge_kernel, so that few rows
+// use the whole chip: those 16 requests 18.2 -> 16.8 us (two shares of four heads), 4 of them 17.4 -> 11.7, one over 4196 tokens 44.1 -> 16.1,
+// 32 of 8 / 2 heads over 2348 25.9 -> 19.4.
 constexpr int kRowWaves = 8;  // at most; fewer for short sequences (the launch decides)
 
 __device__ __forceinline__ float quad_sum(float v) {
@@ -30,7 +33,7 @@ __device__ __forceinline__ float quad_sum(float v) {
     return v + dpp<kQuadXor2>(v);
 }
 
-template <int kRows>
+template <int kRows, bool SPLIT>
 __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch a) {
     static_assert(kRows == 1 || kRows == 2 || kRows == 4, "a lane of a quad stands for one row and page of a step");
     constexpr int kStepPages = kRows == 4 ? 1 : 2, kStepKeys = kStepPages * kPage;
@@ -38,9 +41,12 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
     __shared__ float sO[kRowWaves][kRows][kHeadDim];
     __shared__ float sM[kRowWaves][kRows], sL[kRowWaves][kRows];
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int Hkv = a.pool.num_kv_heads, G = a.num_q_heads / Hkv, groups = (G + kRows - 1) / kRows, per_group = (G + groups - 1) / groups;
+    const int Hkv = a.pool.num_kv_heads, G = a.num_q_heads / Hkv;
+    const int groups = kRows == 1 ? 1 : (G + kRows - 1) / kRows;  // (one row: for G = 1)
+    const int per_group = kRows == 4 ? (G + groups - 1) / groups : kRows;
     const int kvh = (int)(blockIdx.x % Hkv);  // a head stays on its XCD where there are eight
-    const int rest = (int)(blockIdx.x / Hkv), h0 = rest % groups * per_group, tq = rest / groups;
+    const int n_parts = SPLIT ? a.n_parts : 1, part = SPLIT ? (int)(blockIdx.x / Hkv) % n_parts : 0;
+    const int rest = (int)(blockIdx.x / Hkv) / n_parts, h0 = kRows == 1 ? 0 : rest % groups * per_group, tq = kRows == 1 ? rest : rest / groups;
     const int len = a.row_len[tq];  // keys this query token sees
     const int32_t *bt = a.block_table + (size_t)a.row_req[tq] * a.max_pages;
     const float *K = static_cast<const float *>(a.pool.k_pages) + (size_t)kvh * kBlockElems + 4 * lane;
@@ -59,7 +65,9 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
 #pragma unroll
         for (int i = 0; i < 8; ++i) qf[r][i] = *reinterpret_cast<const f32x4 *>(qp + 16 * i);
     }
-    const int n_steps = (len + kStepKeys - 1) / kStepKeys;
+    // (SPLIT: this workgroup's share of the steps, in whole ones)
+    const int all_steps = (len + kStepKeys - 1) / kStepKeys;
+    const int first_step = SPLIT ? (int)((int64_t)all_steps * part / n_parts) : 0, n_steps = SPLIT ? (int)((int64_t)all_steps * (part + 1) / n_parts) : all_steps;
     const int last_page = max(len - 1, 0) >> 4;
     f32x4 kf[kStepPages][8], vf[kStepPages][8];
     auto fetch = [&](f32x4 (&f)[kStepPages][8], const float *base, int step) {
@@ -85,11 +93,11 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
         l = 0.f;
 #pragma unroll
         for (int r = 0; r < kRows; ++r) acc[r][0] = acc[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (wave < n_steps) {
-            fetch(kf, K, wave);
-            fetch(vf, V, wave);
+        if (first_step + wave < n_steps) {
+            fetch(kf, K, first_step + wave);
+            fetch(vf, V, first_step + wave);
         }
-        for (int step = wave; step < n_steps; step += n_waves) {
+        for (int step = first_step + wave; step < n_steps; step += n_waves) {
             float s[kStepPages][kRows];
 #pragma unroll
             for (int g = 0; g < kStepPages; ++g)
@@ -204,10 +212,49 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void rows_fp32_kernel(RowsLaunch
             out = f != 0.f ? with : out;
         }
         const size_t row = (size_t)tq * a.num_q_heads + kvh * G + h0 + r;
+        if constexpr (SPLIT) {  // for rows_fp32_merge_kernel
+            float *pd = a.part_data + (row * n_parts + part) * kRowPartFloats;
+            pd[d] = out;
+            if (d == 0) {
+                pd[kHeadDim] = M;
+                pd[kHeadDim + 1] = L;
+            }
+            continue;
+        }
         // a row without keys gives out = 0, lse = -inf; one whose scores hold a NaN or +inf, or only -inf, gives NaN
         a.out[row * kHeadDim + d] = L > 0.f ? out / L : len > 0 ? __builtin_nanf("") : 0.f;
         if (a.lse_out && d == 0) a.lse_out[row] = L > 0.f ? (M + fast_log2(L)) * kLn2 : -INFINITY;
     }
+}
+
+// Combines the parts of a row that SPLIT leaves: a wavefront per row.  The same sums, in the same manner, as those over the
+// wavefronts of a workgroup.
+__global__ __launch_bounds__(256) void rows_fp32_merge_kernel(RowsLaunch a) {
+    const int row = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63, n = a.n_parts;
+    if (row >= a.n_q_tokens * a.num_q_heads) return;
+    const int len = a.row_len[row / a.num_q_heads];
+    const float *pd = a.part_data + (size_t)row * n * kRowPartFloats;
+    const float m = lane < n ? pd[lane * kRowPartFloats + kHeadDim] : -INFINITY, l = lane < n ? pd[lane * kRowPartFloats + kHeadDim + 1] : 0.f;  // (n <= kMaxRowParts)
+    float M = m;
+#pragma unroll
+    for (int sh = 1; sh < 64; sh <<= 1) M = fmaxf(M, __shfl_xor(M, sh));
+    const float f = fast_exp2(m - M);
+    float L = 0.f, o0 = 0.f, o1 = 0.f;
+    for (int k0 = 0; k0 < n; k0 += 8) {  // (shares beyond the last have weight 0)
+        float2 o[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = *reinterpret_cast<const float2 *>(pd + min(k0 + j, n - 1) * kRowPartFloats + 2 * lane);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float fk = __shfl(f, k0 + j);
+            L = __builtin_fmaf(__shfl(l, k0 + j), fk, L);
+            o0 = fk != 0.f ? __builtin_fmaf(o[j].x, fk, o0) : o0;
+            o1 = fk != 0.f ? __builtin_fmaf(o[j].y, fk, o1) : o1;
+        }
+    }
+    const float none = len > 0 ? __builtin_nanf("") : 0.f;
+    *reinterpret_cast<float2 *>(a.out + (size_t)row * kHeadDim + 2 * lane) = L > 0.f ? make_float2(o0 / L, o1 / L) : make_float2(none, none);
+    if (a.lse_out && lane == 0) a.lse_out[row] = L > 0.f ? (M + fast_log2(L)) * kLn2 : -INFINITY;
 }
 
 // fp32 source tokens -> fp32 block format, one thread per element
@@ -232,17 +279,19 @@ namespace {
 int heads_per_workgroup(const RowsLaunch &a, int Hkv, int G) {
     if (G <= 2) return G;
     const bool short_rows = a.max_pages <= 4 || (a.max_pages <= 8 && G % 4 != 0);
-    return !short_rows && (int64_t)a.n_q_tokens * Hkv * ((G + 3) / 4) >= kRowWorkgroups ? 4 : 2;
+    return a.n_parts > 1 || (!short_rows && (int64_t)a.n_q_tokens * Hkv * ((G + 3) / 4) >= kRowWorkgroups) ? 4 : 2;
 }
 }  // namespace
 
 hipError_t launch_rows_fp32(const RowsLaunch &a, hipStream_t s) {
     const int Hkv = a.pool.num_kv_heads, G = a.num_q_heads / Hkv;
+    const bool split = a.n_parts > 1;
+    if (split && (!a.part_data || a.n_parts > kMaxRowParts)) return hipErrorInvalidValue;
     // a step is 32 keys (four heads: 16): sequences that never reach four steps a wavefront would pay for wavefronts without one (128 query
-    // tokens of 17 to 32 keys, 32 heads: 24.2 us with eight, 12.5 us with two)
-    const int waves = a.max_pages > 16 ? kRowWaves : a.max_pages > 8 ? 4 : 2;
+    // tokens of 17 to 32 keys, 32 heads: 24.2 us with eight, 12.5 us with two; a share has 128 keys and more)
+    const int waves = split || a.max_pages > 16 ? kRowWaves : a.max_pages > 8 ? 4 : 2;
     const int rows = heads_per_workgroup(a, Hkv, G);
-    const size_t per_token = (size_t)Hkv * ((G + rows - 1) / rows);
+    const size_t per_token = (size_t)Hkv * ((G + rows - 1) / rows) * std::max(1, a.n_parts);
     const size_t most = std::max<size_t>(1, ((size_t)1 << 31) / (per_token * 64 * waves));  // query tokens of a launch: below 2^32 threads
     for (size_t t0 = 0; t0 < (size_t)std::max(a.n_q_tokens, 0); t0 += most) {
         RowsLaunch b = a;
@@ -254,8 +303,15 @@ hipError_t launch_rows_fp32(const RowsLaunch &a, hipStream_t s) {
         b.row_len += t0;
         const dim3 grid((unsigned)(b.n_q_tokens * per_token)), block(64 * waves);
         auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, b); };
-        rows == 1 ? go(rows_fp32_kernel<1>) : rows == 2 ? go(rows_fp32_kernel<2>) : go(rows_fp32_kernel<4>);
+        if (split)
+            rows == 1 ? go(rows_fp32_kernel<1, true>) : rows == 2 ? go(rows_fp32_kernel<2, true>) : go(rows_fp32_kernel<4, true>);
+        else
+            rows == 1 ? go(rows_fp32_kernel<1, false>) : rows == 2 ? go(rows_fp32_kernel<2, false>) : go(rows_fp32_kernel<4, false>);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    if (split && a.n_q_tokens > 0) {
+        hipLaunchKernelGGL(rows_fp32_merge_kernel, dim3((unsigned)((a.n_q_tokens * a.num_q_heads + 3) / 4)), dim3(256), 0, s, a);
+        return hipGetLastError();
     }
     return hipSuccess;
 }
