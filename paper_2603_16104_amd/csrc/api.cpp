@@ -2428,9 +2428,10 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
         // Tiles in pieces of fewer rows where the tiles leave compute units without one: a wavefront without rows costs a piece
         // nothing, up to 64 rows run as token halves (tile_body.h) over more than kPrefillHalvesTokens keys, and a key block takes one of up to 128 rows 0.72 and one of up to 64
         // rows 0.54 of the time (1.3, 0.93 and 0.7 us).  As long as every piece gets a compute unit, and where the estimate is 5 %
-        // shorter than the whole tiles' or 15 % than the split tiles', which come out better than theirs (14 x 12 to 23 over 2656 30.5 us
-        // split, 31.7 in pieces).  32 / 8 heads, 256, 128 and 64 rows: 4 x 96 to 128 new tokens over 512 22.5, 17.9,
-        // 14.5 us; 2 x 192 to 256 over 1024 29.0 (split), 25.2, 19.8; but 8 x 192 to 256 over 1024, 256 tiles, 43.4, 52.3, 85.3.
+        // shorter than the whole tiles' or 15 % than the split tiles', which come out better than theirs (14 x 12 to 23 over 2656 30.0 us
+        // split, 30.3 in pieces).  32 / 8 heads, 256, 128 and 64 rows: 4 x 96 to 128 new tokens over 512 19.4, 15.6,
+        // 12.9 us; 2 x 192 to 256 over 1024 27.5 (split), 24.0, 18.5; but 8 x 192 to 256 over 1024, 256 tiles, by an earlier form of the
+        // tile, 43.4, 52.3, 85.3.
         const int n_cu = chip_shape().n_cu;
         const auto keys_of = [](const PrefillTile &t) { return t.prefix_len + t.q_begin + t.n_q; };
         const auto block_cost = [](int rows, int keys) { return rows > 128 ? 1.0 : rows > 64 ? 0.72 : keys > kPrefillHalvesTokens ? 0.54 : 0.64; };
@@ -2452,8 +2453,9 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
         // estimate is 5 % shorter.  A key block costs a half tile 0.6 of a whole one's time on a full chip (1.6 us, the power limit holds
         // the clock at 1.75 GHz), but the few whole tiles of a last round run at 2.4 GHz, 1.15 us a block, so that only the larger
         // gains are there: of 1046 random batches of one to eight rounds 79 run this way and take 0.956 of the time, none of them more than
-        // 1.003 (at 3 % 130, 0.959 and six that lose over 2 %).  24 x 128 new tokens over 256, 32 / 8 heads, 43.7 -> 32.5 us; 9 x 256 over
-        // 1024 67.9 -> 63.0; six of 256 to 512 over 2048, fp8, 40 / 8 heads, 120.8 -> 116.6.
+        // 1.003 (at 3 % 130, 0.959 and six that lose over 2 %).  24 x 128 new tokens over 256, 32 / 8 heads, 31.9 -> 30.2 us (27.6 on another
+        // card; with page ids behind the queries 43.7 -> 32.5); 9 x 256 over 1024 61.8 -> 58.0; six of 256 to 512 over 2048, fp8, 40 / 8 heads, 116.4
+        // -> 112.5.
         const int workers = n_cu / Hkv, most = prefill_tile_tokens(G), half = 128 / G;
         if (taken.empty() && workers > 0 && half > 0 && most_rows > 128 && (int)head_tiles.size() > workers) {
             // by workgroups in order, each on the compute unit that is free first, in key blocks of whole tiles

@@ -248,8 +248,8 @@ struct DecodeTilesLaunch {
 };
 
 // A prefill tile of up to 64 rows runs as token halves (tile_body.h) where it has more keys than this: below, bringing the halves together
-// costs what they save (16 x 12 new tokens over 2048, 32 / 8 heads, 34.5 -> 26.8 us, 30 x 16 over 512 15.3 -> 13.8; 32 x 16
-// over 64 9.6 -> 9.8).
+// costs what they save (16 x 12 new tokens over 2048, 32 / 8 heads, 33.4 -> 25.4 us, 30 x 16 over 512 14.3 -> 12.5, over 256 10.9 ->
+// 10.3; over 128 9.3 either way, 32 x 16 over 64 8.6 -> 8.8).
 constexpr int kPrefillHalvesTokens = 256;
 // Query tokens per prefill workgroup for a given group size G (rows per workgroup / G).
 int prefill_tile_tokens(int group);
