@@ -55,7 +55,7 @@ __global__ __launch_bounds__(64 * kRowsPerBlock) void lse_merge_kernel(const flo
 // per row (32 lanes x 4 dims); the partials and their lse values are requested together, so a row costs one memory round
 // trip (kUnroll: the number of slots, 2, 3, 4, 6 or 8).
 constexpr int kDenseRowsPerBlock = 8;
-constexpr int kManyRows = 16384;  // from here on a half wavefront merges four rows
+constexpr int kManyRows = 16384;  // from here on a half wavefront merges four rows (fp16 partials: lse_merge_wide_kernel)
 
 // four consecutive values of a partial, as floats
 template <bool PB16>
@@ -141,11 +141,6 @@ __global__ __launch_bounds__(32 * kDenseRowsPerBlock) void lse_merge_dense_kerne
     }
 }
 
-// Rows of many partials: a wavefront per row, whose four rows of 16 lanes (8 dims a lane) take every fourth partial each, 4 * U
-// of them in flight at once.  Bound by latency: half a wavefront per row, with 16 partials at once and the others one after
-// the other, took 3.2 us for 512 rows x 9 (this: 2.6), 5.3 for 24 (3.1), 12.2 for 48 (3.8), 13.2 for 2048 rows x 32 (4.5); from
-// some 8192 rows on both are bound by the partials' bytes (16 384 x 24: 34 / 30).  Below 9 partials half a wavefront per row is the
-// faster form (512 x 8: 2.69 against 2.71 us, 2048 x 8: 2.85 against 3.08).
 template <bool PB16>
 __device__ __forceinline__ void load_part8(const void *o_parts, size_t elem, f32x4 &lo, f32x4 &hi) {
     if constexpr (PB16) {
@@ -159,6 +154,61 @@ __device__ __forceinline__ void load_part8(const void *o_parts, size_t elem, f32
         hi = reinterpret_cast<const f32x4 *>(static_cast<const float *>(o_parts) + elem)[1];
     }
 }
+
+// Decode steps of kManyRows rows and more: a quarter of a wavefront per row, 16 bytes a lane, so that one load takes a KiB.  Bound by the
+// partials' bytes (from L2 and the last-level cache, 5 to 6 TB/s).  Half a wavefront with 8 bytes a lane, four rows of it in flight, took 8.2 us for 43008
+// rows x 2 (this: 6.9), 7.2 for 32768 x 2 (5.7), 6.6 for 16384 x 3 (4.7); with two rows in flight this takes 0.1 to 0.4 more, and below
+// 16384 rows the two forms are within 0.2 of each other either way.
+template <int kUnroll>
+__global__ __launch_bounds__(256) void lse_merge_wide_kernel(const uint16_t *__restrict__ o_parts, const float *__restrict__ lse_parts,
+                                                             const int32_t *__restrict__ part_count, int32_t rows_per_count, int32_t max_parts,
+                                                             int32_t n_rows, void *__restrict__ out, float *__restrict__ lse_out,
+                                                             const int32_t *__restrict__ out_rows, const float *__restrict__ down_parts) {
+    const int row = (int)blockIdx.x * 16 + (int)(threadIdx.x >> 4), l = threadIdx.x & 15;
+    if (row >= n_rows) return;
+    const int cnt = min(part_count[row / rows_per_count], max_parts);
+    const size_t base = (size_t)row * max_parts;
+    // (all slots requested before the count is known, as in merge_dense_row)
+    float ls[kUnroll], ds[kUnroll];
+    f32x4 lo[kUnroll], hi[kUnroll];
+#pragma unroll
+    for (int k = 0; k < kUnroll; ++k) {
+        const int kc = min(k, max_parts - 1);
+        ls[k] = lse_parts[base + kc];
+        ds[k] = down_parts[base + kc];
+        load_part8<true>(o_parts, (base + kc) * kHeadDim + 8 * l, lo[k], hi[k]);
+    }
+    float M = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < kUnroll; ++k) {
+        if (k >= cnt) ls[k] = -INFINITY;
+        M = fmaxf(M, ls[k]);
+    }
+    f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
+    float z = 0.f;
+    if (M != -INFINITY) {
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k)
+            if (ls[k] != -INFINITY) {  // an empty partial may hold anything in o
+                const float w = fast_exp2((ls[k] - M) * kLog2e), wd = w * ds[k];
+                z += w;
+                a0 += lo[k] * wd;
+                a1 += hi[k] * wd;
+            }
+        const float inv = 1.0f / z;
+        a0 *= inv;
+        a1 *= inv;
+    }
+    const size_t dst = out_rows ? (size_t)out_rows[row / rows_per_count] * rows_per_count + row % rows_per_count : (size_t)row;
+    reinterpret_cast<u32x4 *>(out)[dst * (kHeadDim / 8) + l] = u32x4{pack_bf16(a0[0], a0[1]), pack_bf16(a0[2], a0[3]), pack_bf16(a1[0], a1[1]), pack_bf16(a1[2], a1[3])};
+    if (lse_out && l == 0) lse_out[dst] = (M == -INFINITY) ? -INFINITY : M + fast_log2(z) * kLn2;
+}
+
+// Rows of many partials: a wavefront per row, whose four rows of 16 lanes (8 dims a lane) take every fourth partial each, 4 * U
+// of them in flight at once.  Bound by latency: half a wavefront per row, with 16 partials at once and the others one after
+// the other, took 3.2 us for 512 rows x 9 (this: 2.6), 5.3 for 24 (3.1), 12.2 for 48 (3.8), 13.2 for 2048 rows x 32 (4.5); from
+// some 8192 rows on both are bound by the partials' bytes (16 384 x 24: 34 / 30).  Below 9 partials half a wavefront per row is the
+// faster form (512 x 8: 2.69 against 2.71 us, 2048 x 8: 2.85 against 3.08).
 template <int OUT_DT, int U, bool PB16>
 __global__ __launch_bounds__(64 * kRowsPerBlock) void lse_merge_deep_kernel(
     const void *__restrict__ o_parts, const float *__restrict__ lse_parts, const int32_t *__restrict__ part_count,
@@ -264,12 +314,24 @@ hipError_t launch_lse_merge_dense(const void *o_parts, const float *lse_parts, c
             down_parts ? of(std::integral_constant<int, 8>{}, std::true_type{}) : of(std::integral_constant<int, 8>{}, std::false_type{});
         return hipGetLastError();
     }
+    if (down_parts && many) {
+        auto wide = [&](auto unroll) {
+            hipExtLaunchKernelGGL(lse_merge_wide_kernel<decltype(unroll)::value>, dim3((n_rows + 15) / 16), dim3(256), 0, s, ev_begin, ev_end, 0,
+                                  static_cast<const uint16_t *>(o_parts), lse_parts, part_count, rows_per_count, max_parts, n_rows, out, lse_out, out_rows, down_parts);
+        };
+        if (max_parts <= 2) wide(std::integral_constant<int, 2>{});
+        else if (max_parts == 3) wide(std::integral_constant<int, 3>{});
+        else if (max_parts == 4) wide(std::integral_constant<int, 4>{});
+        else if (max_parts <= 6) wide(std::integral_constant<int, 6>{});
+        else wide(std::integral_constant<int, 8>{});
+        return hipGetLastError();
+    }
     auto pick = [&](auto pb16) {
         constexpr bool PB = decltype(pb16)::value;
         auto of = [&](auto unroll) {
             constexpr int U = decltype(unroll)::value;
             if constexpr (PB)
-                many ? go(lse_merge_dense_kernel<0, U, true, 4>) : go(lse_merge_dense_kernel<0, U, true, 1>);
+                go(lse_merge_dense_kernel<0, U, true, 1>);
             else if (many)
                 out_dtype == 0 ? go(lse_merge_dense_kernel<0, U, false, 4>) : go(lse_merge_dense_kernel<2, U, false, 4>);
             else
