@@ -2427,14 +2427,16 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
     if (pool->d.dtype != HKV_FP32) {
         // Tiles in pieces of fewer rows where the tiles leave compute units without one: a wavefront without rows costs a piece
         // nothing, up to 64 rows run as token halves (tile_body.h) over more than kPrefillHalvesTokens keys, and a key block takes one of up to 128 rows 0.72 and one of up to 64
-        // rows 0.54 of the time (1.3, 0.93 and 0.7 us).  As long as every piece gets a compute unit, and where the estimate is 5 %
+        // rows 0.54 of the time (1.3, 0.93 and 0.7 us; over fewer keys, as whole tiles, 0.64 by their blocks, but the start and the end, which the
+        // estimate takes to be the same for all, are shorter with fewer rows: 0.59, at which 17 of 70 random batches over 256 keys
+        // at most run in smaller pieces than at 0.64 and take 0.96 of the time, none more than 1.009: 2 x 154 new tokens over 16, 32 / 8 heads, 9.6 -> 9.0 us).  As long as every piece gets a compute unit, and where the estimate is 5 %
         // shorter than the whole tiles' or 15 % than the split tiles', which come out better than theirs (14 x 12 to 23 over 2656 30.0 us
         // split, 30.3 in pieces).  32 / 8 heads, 256, 128 and 64 rows: 4 x 96 to 128 new tokens over 512 19.4, 15.6,
         // 12.9 us; 2 x 192 to 256 over 1024 27.5 (split), 24.0, 18.5; but 8 x 192 to 256 over 1024, 256 tiles, by an earlier form of the
         // tile, 43.4, 52.3, 85.3.
         const int n_cu = chip_shape().n_cu;
         const auto keys_of = [](const PrefillTile &t) { return t.prefix_len + t.q_begin + t.n_q; };
-        const auto block_cost = [](int rows, int keys) { return rows > 128 ? 1.0 : rows > 64 ? 0.72 : keys > kPrefillHalvesTokens ? 0.54 : 0.64; };
+        const auto block_cost = [](int rows, int keys) { return rows > 128 ? 1.0 : rows > 64 ? 0.72 : keys > kPrefillHalvesTokens ? 0.54 : 0.59; };
         int most_rows = 0;
         for (const PrefillTile &t : head_tiles) most_rows = std::max(most_rows, t.n_q * G);
         const int most_keys = head_tiles.empty() ? 0 : keys_of(head_tiles.front());
