@@ -2461,18 +2461,28 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
         const int workers = n_cu / Hkv, most = prefill_tile_tokens(G), half = 128 / G;
         if (taken.empty() && workers > 0 && half > 0 && most_rows > 128 && (int)head_tiles.size() > workers) {
             // by workgroups in order, each on the compute unit that is free first, in key blocks of whole tiles
+            auto cost_of = [&](const PrefillTile &t, bool full_round) {
+                return 4.0 + (t.n_q * G > 128 ? (full_round ? 1.0 : 0.85) : t.n_q * G > 64 ? 0.62 : 0.42) * ((keys_of(t) + 63) / 64);
+            };
             auto rounds_of = [&](const std::vector<PrefillTile> &tiles) {
                 std::vector<double> load(workers, 0.0);  // a heap, least first
                 const size_t last = tiles.size() - tiles.size() % workers;
                 for (size_t i = 0; i < tiles.size(); ++i) {
-                    const PrefillTile &t = tiles[i];
                     std::pop_heap(load.begin(), load.end(), std::greater<>());
-                    load.back() += 4.0 + (t.n_q * G > 128 ? (i < last ? 1.0 : 0.85) : t.n_q * G > 64 ? 0.62 : 0.42) * ((keys_of(t) + 63) / 64);
+                    load.back() += cost_of(tiles[i], i < last);
                     std::push_heap(load.begin(), load.end(), std::greater<>());
                 }
                 return *std::max_element(load.begin(), load.end());
             };
-            const double whole = rounds_of(head_tiles);
+            // Half tiles come to no less than the whole ones they replace, so the best there can be is the whole tiles' cost in equal
+            // shares, and in order these take no longer than that and the longest of them: batches of many rounds are not looked at further.
+            double even = 0, longest = 0;
+            for (size_t i = 0; i < head_tiles.size(); ++i) {
+                const double cost = cost_of(head_tiles[i], i < head_tiles.size() - head_tiles.size() % workers);
+                even += cost / workers;
+                longest = std::max(longest, cost);
+            }
+            const double whole = even < 0.95 * (even + longest) ? rounds_of(head_tiles) : even;
             double least = 0.95 * (best > 0 ? std::min(best, whole) : whole);
             // a request's whole tiles, and what half tiles for the rest then come to
             std::vector<int32_t> wholes(n_req);
@@ -2484,8 +2494,9 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
                 n_whole += wholes[r];
             }
             // Whole tiles become two half tiles (three where a request's tokens need that: as few of these as possible), those of
-            // the shortest key ranges first, until whole rounds of whole tiles are left.
-            for (int64_t rounds = n_whole / workers; rounds >= std::max<int64_t>(0, n_whole / workers - 1); --rounds) {
+            // the shortest key ranges first, until whole rounds of whole tiles are left: as many as there are, or one fewer.
+            const int64_t most_rounds = n_whole / workers, least_rounds = even < least ? std::max<int64_t>(0, most_rounds - 1) : most_rounds + 1;
+            for (int64_t rounds = most_rounds; rounds >= least_rounds; --rounds) {
                 using Entry = std::pair<std::pair<int32_t, int32_t>, int32_t>;  // {half tiles more, keys}, request
                 std::vector<Entry> heap;
                 auto entry = [&](int r) { return Entry{{halves_beside(r, wholes[r] - 1) - halves_beside(r, wholes[r]), kv_len[r]}, r}; };

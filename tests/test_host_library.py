@@ -3,6 +3,7 @@ logic (pool bookkeeping, forest flattening, token usage, work planning, argument
 right.  Integer outputs are compared bit-exactly with the oracle.  No kernel is launched."""
 import os
 import re
+import time
 
 import numpy as np
 import pytest
@@ -652,6 +653,25 @@ def test_split_prefill_covers_every_key_block_once(hq, hk, prefix, new, whole):
         else:
             assert np.array_equal(own[:, 9], own[0, 9] + np.arange(len(own)))
     hkv.hkv_prefill_plan_destroy(plan)
+    hkv.kv_pool_destroy(pool)
+
+
+def test_prefill_planning_time_is_linear_in_the_tiles():
+    """Sixteen times the prompts of 8190 tokens take sixteen times as long to plan, and up to four times that where the smaller plan fits the
+    host's caches (the shortest of several): the search for half tiles looks at a fixed number of layouts, one per round of tiles took 246."""
+    pool, table = fake_pool(512, 8), np.arange(512, dtype=np.int32)
+
+    def shortest(n, runs):
+        best = np.inf
+        for _ in range(runs):
+            t0 = time.perf_counter()
+            plan = hkv.hkv_prefill_plan_create(pool, 8190 * np.arange(n + 1), np.tile(table, (n, 1)), [8190] * n, 32, hkv.PLAN_HOST_ONLY)
+            best = min(best, time.perf_counter() - t0)
+            hkv.hkv_prefill_plan_destroy(plan)
+        return best
+
+    shortest(16, 2)
+    assert shortest(256, 3) < 128 * shortest(16, 20)
     hkv.kv_pool_destroy(pool)
 
 
