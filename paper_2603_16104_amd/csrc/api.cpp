@@ -2430,8 +2430,11 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
         // rows 0.54 of the time (1.3, 0.93 and 0.7 us; over fewer keys, as whole tiles, 0.64 by their blocks, but the start and the end, which the
         // estimate takes to be the same for all, are shorter with fewer rows: 0.59, at which 17 of 70 random batches over 256 keys
         // at most run in smaller pieces than at 0.64 and take 0.96 of the time, none more than 1.009: 2 x 154 new tokens over 16, 32 / 8 heads, 9.6 -> 9.0 us).  As long as every piece gets a compute unit, and where the estimate is 5 %
-        // shorter than the whole tiles' or 15 % than the split tiles', which come out better than theirs (14 x 12 to 23 over 2656 30.0 us
-        // split, 30.3 in pieces).  32 / 8 heads, 256, 128 and 64 rows: 4 x 96 to 128 new tokens over 512 19.4, 15.6,
+        // shorter than the whole tiles', or than the split tiles' (64 rows: 6 %).  Of 220 random batches on both sides of the latter lines, pieces of 128 rows
+        // take 0.65 to 0.90 of the split tiles' time up to the line, and the first take longer at 3 % (1.025); pieces of 64 rows take 0.84 in the mean
+        // up to the line, the worst 1.019, and 0.92 from 6 to 0 %, the worst 1.055: 3 x 102 new tokens over 1600, 32 / 8 heads, 27.4 -> 21.9 us,
+        // 6 x 92 over 1792 35.8 -> 32.8.
+        // 32 / 8 heads, 256, 128 and 64 rows: 4 x 96 to 128 new tokens over 512 19.4, 15.6,
         // 12.9 us; 2 x 192 to 256 over 1024 27.5 (split), 24.0, 18.5; but 8 x 192 to 256 over 1024, 256 tiles, by an earlier form of the
         // tile, 43.4, 52.3, 85.3.
         const int n_cu = chip_shape().n_cu;
@@ -2447,7 +2450,7 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
             std::vector<PrefillTile> pieces = head_tiles_of(rows / G);
             if ((int64_t)pieces.size() * Hkv > n_cu) break;
             const double cost = 4.0 + block_cost(rows, most_keys) * ((most_keys + 63) / 64);
-            if (cost > (taken.empty() && !pl->segments.empty() ? 0.85 : 0.95) * best) continue;
+            if (cost > (rows == 64 && taken.empty() && !pl->segments.empty() ? 0.94 : 0.95) * best) continue;
             best = cost;
             taken.swap(pieces);
         }

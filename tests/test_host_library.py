@@ -656,6 +656,20 @@ def test_split_prefill_covers_every_key_block_once(hq, hk, prefix, new, whole):
     hkv.kv_pool_destroy(pool)
 
 
+@pytest.mark.parametrize("hq, hk, prefix, new, pieces", [(32, 8, 1792, (92,) * 6, 144), (32, 8, 1600, (102,) * 3, 168), (40, 8, 1360, (60,) * 3, 120),
+                                                         (64, 8, 1520, (43,) * 3, 144), (32, 8, 4096, (700,), 0)])
+def test_small_prefill_batches_run_in_pieces_where_that_measured_shorter(hq, hk, prefix, new, pieces):
+    """Than split along the keys; the last one is longer in pieces."""
+    n_pages = -(-(prefix + max(new)) // 16)
+    pool = fake_pool(n_pages, hk)
+    plan = hkv.hkv_prefill_plan_create(pool, np.concatenate([[0], np.cumsum(new)]), np.tile(np.arange(n_pages, dtype=np.int32), (len(new), 1)),
+                                       [prefix + n for n in new], hq, hkv.PLAN_HOST_ONLY)
+    assert hkv.hkv_prefill_plan_num_pieces(plan) == pieces
+    assert (len(hkv.hkv_prefill_plan_segments(plan)) > 0) == (pieces == 0)
+    hkv.hkv_prefill_plan_destroy(plan)
+    hkv.kv_pool_destroy(pool)
+
+
 def test_prefill_planning_time_is_linear_in_the_tiles():
     """Sixteen times the prompts of 8190 tokens take sixteen times as long to plan, and up to four times that where the smaller plan fits the
     host's caches (the shortest of several): the search for half tiles looks at a fixed number of layouts, one per round of tiles took 246."""
