@@ -1498,7 +1498,9 @@ static int build_fp32_rows(hkv_decode_plan &pl, bool upload) {
     // Few rows leave compute units idle, and a row's workgroup takes in no more than one can: its keys are cut, down to 128 a share,
     // until every compute unit has a share (of up to four heads).  The second kernel takes 3 us, so shorter rows stay whole: over 518
     // keys 9.6 -> 10.6 us for one request (32 / 8 heads), 11.2 -> 12.9 for 16; over 1020 keys 14.3 -> 10.6 for 2.
-    // Two shares pay later: 24 requests x 4 / 4 heads over 1026 keys 14.1 -> 14.5, 16 x 32 / 8 over 1280 18.2 -> 16.7.
+    // Two shares save half of the walk at most and pay later.  Their time over the whole rows', at head ratios of 1, 2, 4 and 8: over 1020
+    // keys 0.97 to 1.01, 0.93 to 0.95, 0.95 to 1.01 and 1.02, over 1148 keys 0.92 to 0.97, 0.90, 0.93 to 0.98 and 0.99 (ratio 5: 1.00 to
+    // 1.01), over 1276 keys 0.90 to 0.94, 0.88, 0.91 to 0.93 and 0.94 (16 x 32 / 8 over 1260 17.0 -> 15.9, over 1532 19.6 -> 17.3).
     const int G = pl.group, heads = G <= 2 ? G : 4;
     const int64_t units = std::max<int64_t>(1, (int64_t)n * pl.pool->d.num_kv_heads * ((G + heads - 1) / heads));
     pl.row_parts = (int32_t)std::max<int64_t>(1, std::min<int64_t>({kMaxRowParts, kRowWorkgroups / units, pl.max_pages / 8}));

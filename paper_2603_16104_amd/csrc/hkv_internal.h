@@ -218,7 +218,7 @@ struct RowsLaunch {
     float *part_data;
 };
 constexpr int kMaxRowParts = 32;
-constexpr int kMinCutPages = 64, kMinHalvedPages = 80;  // rows whose longest has fewer stay whole (the latter: where there would be two shares)
+constexpr int kMinCutPages = 64, kMinHalvedPages = 72;  // rows whose longest has fewer stay whole (the latter: where there would be two shares)
 constexpr int kRowPartFloats = kHeadDim + 4;  // o, reference, row sum; 16-byte pieces
 constexpr int kRowWorkgroups = 256;           // what fills the chip: rows are cut, or given fewer of their heads a workgroup, until there are so many
 

@@ -32,6 +32,11 @@ def test_shares(gpu, oracle, hq, hk, lens):  # noqa: F811
     dp.close()
 
 
+@pytest.mark.parametrize("hq, hk, lens", [(32, 8, (1137,) * 16), (8, 8, (1152, 1151, 17, 0) * 4), (24, 8, (1300,) * 11 + (570,)), (32, 8, (1009,) * 10)])
+def test_two_and_three_shares(gpu, oracle, hq, hk, lens):  # noqa: F811
+    test_shares(gpu, oracle, hq, hk, lens)
+
+
 def test_workspaces(gpu, oracle):  # noqa: F811
     """None, too small, misaligned and the static form: whole rows; enough: shares.  All the same numbers but for the order of 32-bit sums."""
     import torch

@@ -840,6 +840,19 @@ def test_workspace_of_plans_that_run_whole_paths():
     hkv.kv_pool_destroy(pool)
 
 
+@pytest.mark.parametrize("hq, hk, n_req, tokens, shares", [
+    (32, 8, 16, 1136, 0), (32, 8, 16, 1137, 2), (32, 8, 16, 1264, 2), (32, 8, 17, 4000, 0), (64, 8, 8, 1264, 2), (4, 4, 32, 1152, 2), (4, 4, 32, 1100, 0),
+    (32, 8, 10, 1008, 0), (32, 8, 10, 1009, 3), (32, 8, 1, 600, 0), (32, 8, 1, 1100, 8), (32, 8, 1, 8000, 32)])
+def test_shares_of_few_fp32_rows(hq, hk, n_req, tokens, shares):
+    """Rows of an fp32 pool are cut from 64 pages on, into two shares from 72: the workspace holds 132 floats per row and share."""
+    pool = fake_pool(-(-tokens // 16), hk, hkv.FP32)
+    f = wl.make_forest([-1], [tokens], [0] * n_req, np.arange(-(-tokens // 16), dtype=np.int32))
+    plan = hkv.hkv_decode_plan_create(pool, f.nodes, f.node_pages, f.req_leaf, hq, hkv.PLAN_HOST_ONLY)
+    assert hkv.hkv_decode_plan_workspace_bytes(plan) == 528 * n_req * hq * shares
+    hkv.hkv_decode_plan_destroy(plan)
+    hkv.kv_pool_destroy(pool)
+
+
 def test_numbers_of_the_wrong_type_are_type_errors():
     pool = fake_pool()
     plan = hkv.hkv_decode_plan_create(pool, [[-1, 0, 1, 5]], [0], [0], 4, hkv.PLAN_HOST_ONLY)
