@@ -301,6 +301,7 @@ hipError_t launch_rows_fp32(const RowsLaunch &a, hipStream_t s) {
         if (b.lse_out) b.lse_out += t0 * a.num_q_heads;
         b.row_req += t0;
         b.row_len += t0;
+        if (split) b.part_data += t0 * a.num_q_heads * a.n_parts * kRowPartFloats;
         const dim3 grid((unsigned)(b.n_q_tokens * per_token)), block(64 * waves);
         auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, b); };
         if (split)
