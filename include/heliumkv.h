@@ -433,8 +433,10 @@ int hkv_decode_plan_part_counts(const hkv_decode_plan *plan, int32_t *part_count
 
 /* Runs one decode step.  q: device [n_req][num_q_heads][128] bf16.  out: device, same shape,
  * bf16.  lse_out: device [n_req][num_q_heads] float or NULL.  workspace: device, at least
- * hkv_decode_plan_workspace_bytes(plan) bytes, 256-byte aligned; its contents are scratch (fp32 pools: may be NULL or smaller).
- * A request whose path holds no token gets out = 0, lse = -inf.  A row whose scores hold a NaN or +inf gets NaN in out and lse.
+ * hkv_decode_plan_workspace_bytes(plan) bytes, 256-byte aligned (fp32 pools: may be NULL or smaller); its contents are scratch:
+ * runs on different streams take one each, fp32 pools' too.
+ * A request whose path holds no token gets out = 0, lse = -inf.  A row whose scores hold a NaN or +inf gets NaN in out and lse; over an
+ * fp32 pool, whether its keys are cut into shares or not, such a row gets NaN in out and -inf in lse, like one whose scores are all -inf.
  * EINVAL (null/unaligned), ENOMEM (workspace too small), EHIP. */
 int attn_decode_plan_run(hkv_decode_plan *plan, const void *q, float scale, void *out, float *lse_out,
                          void *workspace, size_t workspace_bytes, void *stream);

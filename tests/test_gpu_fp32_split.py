@@ -69,7 +69,7 @@ def test_workspaces(gpu, oracle):  # noqa: F811
 
 
 @pytest.mark.parametrize("hq, hk", [(4, 1), (8, 2), (5, 1)])
-@pytest.mark.parametrize("what", ["v_inf_of_no_weight", "nan_score", "all_minus_inf_in_a_share", "all_minus_inf"])
+@pytest.mark.parametrize("what", ["v_inf_of_no_weight", "nan_score", "inf_score", "all_minus_inf_in_a_share", "all_minus_inf"])
 def test_values_that_must_not_spread(gpu, hq, hk, what):  # noqa: F811
     import torch
     n = 1500
@@ -80,8 +80,8 @@ def test_values_that_must_not_spread(gpu, hq, hk, what):  # noqa: F811
         K[700, :, 0] = -1000.0
         V[700] = np.inf
         keep = keep[keep != 700]
-    elif what == "nan_score":
-        K[700, 0, 0] = np.nan
+    elif what in ("nan_score", "inf_score"):
+        K[700, 0, 0] = np.nan if what == "nan_score" else np.inf
     else:
         quiet = slice(128, 400) if what == "all_minus_inf_in_a_share" else slice(None)
         K[quiet, :, 0] = -np.inf
@@ -101,8 +101,8 @@ def test_values_that_must_not_spread(gpu, hq, hk, what):  # noqa: F811
     hkv.hkv_decode_plan_destroy(plan)
     dp.close()
     G = hq // hk
-    bad = slice(0, 0) if what in ("v_inf_of_no_weight", "all_minus_inf_in_a_share") else slice(0, G) if what == "nan_score" else slice(0, hq)
-    assert np.isnan(got[bad]).all()
+    bad = slice(0, 0) if what in ("v_inf_of_no_weight", "all_minus_inf_in_a_share") else slice(0, G) if what in ("nan_score", "inf_score") else slice(0, hq)
+    assert np.isnan(got[bad]).all() and np.isneginf(got_l[bad]).all()     # as whole rows do
     rest = np.ones(hq, dtype=bool)
     rest[bad] = False
     if rest.any():
