@@ -288,7 +288,7 @@ hipError_t launch_rows_fp32(const RowsLaunch &a, hipStream_t s) {
     const bool split = a.n_parts > 1;
     if (split && (!a.part_data || a.n_parts > kMaxRowParts)) return hipErrorInvalidValue;
     // a step is 32 keys (four heads: 16): sequences that never reach four steps a wavefront would pay for wavefronts without one (128 query
-    // tokens of 17 to 32 keys, 32 heads: 24.2 us with eight, 12.5 us with two; a share has 128 keys and more)
+    // tokens of 17 to 32 keys, 32 heads: 24.2 us with eight, 12.5 us with two; a share has about 128 keys and more of the longest row, and what there is of the others)
     const int waves = split || a.max_pages > 16 ? kRowWaves : a.max_pages > 8 ? 4 : 2;
     const int rows = heads_per_workgroup(a, Hkv, G);
     const size_t per_token = (size_t)Hkv * ((G + rows - 1) / rows) * std::max(1, a.n_parts);

@@ -396,7 +396,8 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     }
     __syncthreads();
     // Request schedule: K runs one block ahead of V (phase t multiplies K(t+1) but V(t-1)).  The
-    // prologue requests K(0); {K(1), V(0)}; {K(2), V(1)}; iteration j requests {K(j+3), V(j+2)}.
+    // prologue requests K(0); {K(1), V(0)}; {K(2), V(1)}; iteration j requests {K(j+3), V(j+2)}.  HALVES, where a phase steps over a whole
+    // block: K(0); {K(1), V(0)}; K(2); {V(1), K(3)}; iteration j requests {K(j+4), V(j+2)}.
     // fp8: K(0), K(1), V(0) are widened into LDS here; {K(2), V(1)} and {K(3), V(2)} wait in the register
     // queue; iteration j widens {K(j+2), V(j+1)} and requests {K(j+4), V(j+3)} in their place.
     u32x4 kq[2], vq[2];
@@ -451,7 +452,8 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     float mc = 0.f;  // reference = maximum of the row's first 32 scores (token 0 is visible), times scale * log2 e
     if (active) {
         scores(sa, k_tile(kh));
-        if (32 * kh + 31 > wave_min_pos) mask_scores(sa, kh);
+        static_assert(kPrefillHalvesTokens >= 126, "token halves: of at most 64 rows over more keys the first sees both halves' first step whole");
+        if (!HALVES && 31 > wave_min_pos) mask_scores(sa, 0);
         const StepScale s0 = step_scale(0);
         float mx = sa[0] * s0.ck[0];
 #pragma unroll
@@ -459,8 +461,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
         mc = fmaxf(mx, __shfl_xor(mx, 32));
         // A row that lies in front of the whole segment sees nothing of it: exp2(-inf - 0) = 0 throughout.  (A row that sees it
         // and whose first scores are all -inf ends up with a sum that is no number, and so in the running-maximum loop.)
-        // The same for a row in front of the first step of this half: it lies in front of all later ones.
-        if ((SPLIT && pos < 0) || (HALVES && pos < 32 * kh)) mc = 0.f;
+        if (SPLIT && pos < 0) mc = 0.f;
     }
     if constexpr (HALVES) __syncthreads();  // K(0) has been read: iteration 0 requests K(4) in its place
 
@@ -527,6 +528,8 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
     // complete before iteration j+1 and a request has two iterations to land; K stage (j-1) % 4 and
     // V stage (j-2) % 4 are free from the barrier at the end of iteration j-1 on, which is where
     // iteration j's requests go.  One barrier per iteration.
+    // HALVES: iteration j reads K of blocks j+1, j+2 and V of blocks j-1, j, and finds K(j+2) and V(j) complete in the same manner.  Its K request
+    // goes to stage j % 4: K(j) was read to its end in iteration j-1 (K(0) in front of the barrier above).
     // fp8: kq_now / vq_now hold {K(j+2), V(j+1)} on entry and {K(j+4), V(j+3)} on exit; the other pair of
     // the register queue holds {K(j+3), V(j+2)} throughout (the two pairs swap roles every iteration).
     // The loop body exists four times, once per value of j % kStages, so that every LDS stage it touches is a
@@ -739,7 +742,7 @@ __device__ __forceinline__ void body(const TileArgs &a, char *lds, int first, in
         __syncthreads();
         if (!active || kh == 1) return;
         const float m1 = xm[0], M = fmaxf(m_own, m1);
-        const float w0 = fast_exp2(m_own - M), w1 = fast_exp2(m1 - M);  // (a row sees its own key at least: M is finite)
+        const float w0 = fast_exp2(m_own - M), w1 = fast_exp2(m1 - M);  // (a row sees its own key at least; M is not finite where its sum is no number, and the row comes out NaN)
         l_tot = l_tot * w0 + xm[64] * w1;
         m_fin = M;
 #pragma unroll
