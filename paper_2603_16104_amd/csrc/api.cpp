@@ -2236,12 +2236,12 @@ extern "C" size_t attn_decode_workspace_bytes(hkv_pool *pool, const hkv_node *no
 // end, cut where a worker's share is full.  Taken where the estimate says so (in key blocks of 64 tokens, 1.4 us each on a
 // full chip, a little less on one that is not): a tile or segment costs 4 blocks beside its own, the partials 135 KB each
 // on their way through memory and the second kernel 3 more.  Against a workgroup per tile, 32 / 8 heads, one request:
-// 64 / 256 / 1024 new tokens over 8192 cached ones 154 / 159 / 183 -> 33 / 49 / 145 us, 700 over 4096 98.4 -> 62.7,
-// 128 over 1024 29.9 -> 22.7; six requests of 256 to 512 over 2048 114.5 -> 99.8.  Where the estimate gains less than 13 %
-// it was a loss as often as not (three of 1024 over 8192: estimate 0.89, measured 1.01).
+// 64 / 256 / 1024 new tokens over 8192 cached ones 154 / 159 / 178 -> 32 / 47 / 141 us, 700 over 4096 94.2 -> 60.4,
+// 128 over 1024 28.1 -> 21.9; six requests of 256 to 512 over 2048 106.0 -> 92.9.  Where the estimate gains less than 13 %
+// it was a loss as often as not (three of 1024 over 8192: estimate 0.89, measured 0.98 to 1.01).
 //
-// block_cost: what a key block costs segments of such tiles, as a share of what it costs one of more than 128 rows; whole_block_cost: whole tiles.  Returns the estimate for the
-// way taken (0: not estimated, a workgroup per tile).
+// block_cost: what a key block costs segments of such tiles, as a share of what it costs one of more than 128 rows; whole_block_cost:
+// the same of whole tiles.  Returns the estimate for the way taken (0: not estimated, a workgroup per tile).
 static double split_prefill_tiles(hkv_prefill_plan &pl, const std::vector<PrefillTile> &head_tiles, int n_cu, double block_cost, double whole_block_cost) {
     const int Hkv = pl.pool->d.num_kv_heads;
     const int n = (int)head_tiles.size(), workers = n_cu / Hkv;
@@ -2427,18 +2427,19 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
     const std::vector<PrefillTile> head_tiles = head_tiles_of(prefill_tile_tokens(G));
     of_all_heads(head_tiles, pl->tiles);
     if (pool->d.dtype != HKV_FP32) {
-        // Tiles in pieces of fewer rows where the tiles leave compute units without one: a wavefront without rows costs a piece
-        // nothing, up to 64 rows run as token halves (tile_body.h) over more than kPrefillHalvesTokens keys, and a key block takes one of up to 128 rows 0.72 and one of up to 64
-        // rows 0.54 of the time (1.3, 0.93 and 0.7 us; over fewer keys, as whole tiles, 0.64 by their blocks, but the start and the end, which the
-        // estimate takes to be the same for all, are shorter with fewer rows: 0.59, at which 17 of 70 random batches over 256 keys
-        // at most run in smaller pieces than at 0.64 and take 0.96 of the time, none more than 1.009: 2 x 154 new tokens over 16, 32 / 8 heads, 9.6 -> 9.0 us).  As long as every piece gets a compute unit, and where the estimate is 5 %
-        // shorter than the whole tiles', or than the split tiles' (64 rows: 6 %).  Of 220 random batches on both sides of the latter lines, pieces of 128 rows
-        // take 0.65 to 0.90 of the split tiles' time up to the line, and the first take longer at 3 % (1.025); pieces of 64 rows take 0.84 in the mean
-        // up to the line, the worst 1.019, and 0.92 from 6 to 0 %, the worst 1.055: 3 x 102 new tokens over 1600, 32 / 8 heads, 27.4 -> 21.9 us,
-        // 6 x 92 over 1792 35.8 -> 32.8.
-        // 32 / 8 heads, 256, 128 and 64 rows: 4 x 96 to 128 new tokens over 512 19.4, 15.6,
-        // 12.9 us; 2 x 192 to 256 over 1024 27.5 (split), 24.0, 18.5; but 8 x 192 to 256 over 1024, 256 tiles, by an earlier form of the
-        // tile, 43.4, 52.3, 85.3.
+        // Tiles in pieces of fewer rows where the tiles leave compute units without one, as long as every piece gets a compute unit.  A
+        // wavefront without rows costs a piece nothing, and up to 64 rows run as token halves (tile_body.h) over more than
+        // kPrefillHalvesTokens keys: a key block takes 1.3, 0.93 and 0.7 us for 256, 128 and 64 rows, 1, 0.72 and 0.54 of a whole tile's.  Over
+        // fewer keys, as whole tiles, 64 rows take 0.64 by their blocks; the estimate counts the same start and end for all tiles, but
+        // those of fewer rows are shorter, and 0.59 stands for both (17 of 70 random batches over up to 256 keys run in smaller pieces than
+        // at 0.64 and take 0.96 of the time, none more than 1.009).
+        // Taken where the estimate is 5 % shorter than the whole tiles', or than the split tiles' (64 rows: 6 %).  Of 220 random batches on
+        // both sides of the latter lines, pieces of 128 rows take 0.65 to 0.90 of the split tiles' time up to the line, and the first
+        // take longer at 3 % (1.025); pieces of 64 rows take 0.84 in the mean up to the line, the worst 1.019, and 0.92 from 6 to
+        // 0 %, the worst 1.055.
+        // 32 / 8 heads, whole, split, pieces of 128 and of 64 rows, us: 4 x 96 to 128 new tokens over 512 19.3, -, 15.6, 12.9; 2 x 192 to 256
+        // over 1024 30.5, 27.4, 23.5, 18.3; 3 x 102 over 1600 37.9, 27.7, 29.7, 22.1; 6 x 92 over 1792 41.4, 35.3, 32.3, 45.2 (288 pieces);
+        // 2 x 154 over 16 11.6, -, 9.5, 9.0; but 8 x 192 to 256 over 1024, 256 tiles, 38.0, -, 46.3, 65.4.
         const int n_cu = chip_shape().n_cu;
         const auto keys_of = [](const PrefillTile &t) { return t.prefix_len + t.q_begin + t.n_q; };
         const auto block_cost = [](int rows, int keys) { return rows > 128 ? 1.0 : rows > 64 ? 0.72 : keys > kPrefillHalvesTokens ? 0.54 : 0.59; };
@@ -2460,9 +2461,8 @@ static int create_prefill_plan(hkv_pool *pool, const int32_t *cu_q, const int32_
         // estimate is 5 % shorter.  A key block costs a half tile 0.6 of a whole one's time on a full chip (1.6 us, the power limit holds
         // the clock at 1.75 GHz), but the few whole tiles of a last round run at 2.4 GHz, 1.15 us a block, so that only the larger
         // gains are there: of 1046 random batches of one to eight rounds 79 run this way and take 0.956 of the time, none of them more than
-        // 1.003 (at 3 % 130, 0.959 and six that lose over 2 %).  24 x 128 new tokens over 256, 32 / 8 heads, 31.9 -> 30.2 us (27.6 on another
-        // card; with page ids behind the queries 43.7 -> 32.5); 9 x 256 over 1024 61.8 -> 58.0; six of 256 to 512 over 2048, fp8, 40 / 8 heads, 116.4
-        // -> 112.5.
+        // 1.003 (at 3 % 130, 0.959 and six that lose over 2 %).  32 / 8 heads: 24 x 128 new tokens over 256 31.5 -> 29.9 us; 9 x 256 over 1024
+        // 62.3 -> 58.5; one tile more than a whole round gains least, 11 x 200 over 1024 60.1 -> 60.0.
         const int workers = n_cu / Hkv, most = prefill_tile_tokens(G), half = 128 / G;
         if (taken.empty() && workers > 0 && half > 0 && most_rows > 128 && (int)head_tiles.size() > workers) {
             // by workgroups in order, each on the compute unit that is free first, in key blocks of whole tiles

@@ -27,7 +27,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_tile_kernel(TileArgs a) {
 // Prefill tiles split along their keys: a persistent workgroup per compute unit runs an equal share of all key blocks.
 // Bound by the matrix cores like the tile itself; a batch of fewer tiles than compute units (or a little more than a
 // whole number of rounds) leaves the rest of the chip idle otherwise.  700 new tokens over 4096 cached ones, 88 tiles:
-// 98.4 us a workgroup per tile (0.52 PFLOP/s), 62.7 us split, both kernels (0.81).
+// 94.2 us a workgroup per tile (0.54 PFLOP/s), 60.4 us split, both kernels (0.84).
 __global__ __launch_bounds__(kThreads, 2) void prefill_split_kernel(TileArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[kLdsBytes];
     body<false, false, true>(a, lds, (int)blockIdx.x, 1);
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_split_kernel(TileArgs a) 
 // the accumulators' register order, so that every load is a whole KiB; log-sum-exp weights from the references and row sums.
 // Bound by the partials' bytes once enough wavefronts have loads in flight: 88 tiles in 256 shares (45 MB)
 // 12.4 -> 8.9 us (5 TB/s) against a wavefront per 32 whole rows; 64 new tokens over 8192 cached ones, 8 tiles of one
-// 32-row part each in 256 shares, 53 -> 33 us with the tiles.
+// 32-row part each in 256 shares, 53 -> 33 us with the tiles (32 by now).
 __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillLaunch p) {
     const PrefillSplitTile st = p.split[blockIdx.x];
     const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;

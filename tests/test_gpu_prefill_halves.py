@@ -12,7 +12,7 @@ from test_gpu_shared_items import Rising
 pytestmark = pytest.mark.gpu
 
 
-def run(gpu, oracle, kv_dtype, hq, hk, prefix, new, pieces=None, gain=0.0, fallback=None, lse_fp8=LSE_ABS_FP8_PREFILL):  # noqa: F811
+def run(gpu, oracle, kv_dtype, hq, hk, prefix, new, pieces=0, gain=0.0, fallback=None, lse_fp8=LSE_ABS_FP8_PREFILL):  # noqa: F811
     import torch
     from paper_2603_16104_amd import binding as hkv
     parent, ntok = [-1] + [0] * len(new), [prefix] + list(new)
@@ -23,8 +23,7 @@ def run(gpu, oracle, kv_dtype, hq, hk, prefix, new, pieces=None, gain=0.0, fallb
     hp, dp = both_pools(gpu, oracle, w)
     exp_o, exp_l = oracle.run_workload(w, hp)
     r = gpu.PrefillRunner(dp, w)
-    if pieces is not None:
-        assert hkv.hkv_prefill_plan_num_pieces(r.plan) == pieces
+    assert hkv.hkv_prefill_plan_num_pieces(r.plan) == pieces and len(hkv.hkv_prefill_plan_segments(r.plan)) == 0
     for _ in range(2):
         r.out.fill_(0x7FC0)
         r.lse.fill_(float("nan"))
@@ -40,7 +39,7 @@ def run(gpu, oracle, kv_dtype, hq, hk, prefix, new, pieces=None, gain=0.0, fallb
 
 @pytest.mark.parametrize("hq, hk, prefix, new", [
     (4, 1, 256, (1, 2, 7, 8, 9, 16)), (4, 1, 272, (15, 16, 1)), (4, 1, 288, (16, 3)), (4, 1, 304, (5, 16)), (5, 1, 320, (12, 6, 1)), (16, 1, 496, (3, 4, 1)),
-    (1, 1, 512, (33, 64, 31)), (8, 2, 960, (13, 16)), (4, 1, 1008, (16,)), (4, 1, 1024, (16, 1)), (4, 1, 1200, (9,)), (4, 1, 16 * 130, (16, 11)),
+    (1, 1, 512, (33, 64, 31)), (8, 2, 960, (13, 16)), (4, 1, 1008, (16,)), (4, 1, 1024, (16, 1)), (4, 1, 1200, (9,)), (32, 8, 16 * 130, (16, 11, 8) * 6),
 ])
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
 def test_token_halves(gpu, oracle, kv_dtype, hq, hk, prefix, new):  # noqa: F811
@@ -49,21 +48,113 @@ def test_token_halves(gpu, oracle, kv_dtype, hq, hk, prefix, new):  # noqa: F811
 
 def test_page_ids_are_refilled(gpu, oracle):  # noqa: F811
     """More than 2048 blocks of 16 keys, in a batch of one whole round of tiles (which is not split along the keys)."""
-    run(gpu, oracle, wl.KV_BF16, 32, 32, 33008, (3, 1) * 4, 0)
+    run(gpu, oracle, wl.KV_BF16, 32, 32, 33008, (3, 1) * 4)
 
 
 @pytest.mark.parametrize("gain, fallback", [(15.0, None), (400.0, True)])
 def test_scores_that_rise(gpu, oracle, gain, fallback):  # noqa: F811
     """The largest scores lie in the last blocks: references far behind them, and sums beyond what one reference carries."""
-    run(gpu, oracle, wl.KV_BF16, 8, 2, 16, (300,), gain=gain, fallback=fallback)
-    run(gpu, oracle, wl.KV_BF16, 4, 1, 704, (16, 5), gain=gain)
+    run(gpu, oracle, wl.KV_BF16, 8, 2, 16, (300,), 38, gain=gain, fallback=fallback)
+    run(gpu, oracle, wl.KV_BF16, 4, 1, 704, (16, 5), gain=gain, fallback=fallback)
 
 
+# whole and half tiles of one request, half tiles of 42, 25 and 18 tokens (three for a tile of 85, 51 or 36 where its tokens need that), and
+# batches that keep whole tiles
 @pytest.mark.parametrize("hq, hk, prefix, new, pieces", [
-    (16, 16, 16, (256,) * 18, 320), (16, 16, 32, (256, 255, 129, 257, 200, 128) * 4, None), (32, 32, 48, (250,) * 9, 320), (32, 4, 0, (32,) * 66, None)])
+    (16, 16, 16, (256,) * 18, 320), (32, 32, 48, (250,) * 9, 320), (48, 16, 16, (141, 90, 87, 49, 55, 158, 97, 217, 146, 130, 78), 336),
+    (96, 32, 16, (59, 109, 216, 239, 172), 448), (80, 16, 112, (49, 98, 117, 46, 87, 37, 144, 30, 120), 512),
+    (160, 32, 112, (105, 30, 36, 52, 80, 82), 384), (112, 16, 112, (52, 55, 26, 98, 39, 34, 25, 56, 93, 57), 320),
+    (16, 16, 32, (256, 255, 129, 257, 200, 128) * 4, 0), (32, 4, 0, (32,) * 66, 0)])
 @pytest.mark.parametrize("kv_dtype", [wl.KV_BF16, wl.KV_FP8_E4M3])
 def test_whole_rounds_and_half_tiles(gpu, oracle, kv_dtype, hq, hk, prefix, new, pieces):  # noqa: F811
     # fp8 pools: K is rounded to bf16 on the way: 128 products of normal values with relative errors of 2^-9 / sqrt(3) in the mean move the one
     # score of a row with one key by 1.42e-3 rms (20 000 such rows in 64 bits); 5.5 of these are passed once in 3e7 rows, and there are up
     # to 7e4 here (of rows with 16 keys one had moved by 5.03e-3, past the 5e-3 of smaller cases, of rows with one key one by 6.9e-3).
     run(gpu, oracle, kv_dtype, hq, hk, prefix, new, pieces, lse_fp8=5.5 * 1.42e-3)
+
+
+LN2 = float(np.log(2.0))                                 # as the scale: scores count in powers of two
+
+
+def one_tile(gpu, K, V, q, new):  # noqa: F811
+    """out, lse and repeated tiles of `new` tokens (8 heads over 2) behind the rest of K / V [tokens][2][128], one tile of 64 rows a KV head."""
+    import torch
+    from paper_2603_16104_amd import binding as hkv
+    n = K.shape[0]
+    dp = gpu.DevicePool((n + 15) // 16, 2, wl.KV_BF16)
+    pages = np.arange((n + 15) // 16, dtype=np.int32)
+    dp.write(pages, 0, *(gpu.to_device_bits(wl.f32_to_bf16_bits(x)) for x in (K, V)))
+    plan = hkv.hkv_prefill_plan_create(dp.handle, np.asarray([0, new]), pages[None], np.asarray([n]), 8)
+    assert len(hkv.hkv_prefill_plan_tiles(plan)) == 2 and hkv.hkv_prefill_plan_num_pieces(plan) == 0 and len(hkv.hkv_prefill_plan_segments(plan)) == 0
+    out = torch.full((new, 8, 128), 0x7F80, dtype=torch.int16, device="cuda")
+    lse = torch.full((new, 8), 7.0, dtype=torch.float32, device="cuda")
+    hkv.attn_prefill_plan_run(plan, gpu.to_device_bits(wl.f32_to_bf16_bits(q)), LN2, out, lse)
+    torch.cuda.synchronize()
+    repeated = hkv.hkv_prefill_plan_fallback_tiles(plan)
+    hkv.hkv_prefill_plan_destroy(plan)
+    dp.close()
+    return gpu.bf16_tensor_to_f64(out), lse.cpu().numpy(), repeated
+
+
+def one_tile_inputs(n, new):
+    rng = np.random.default_rng(n)
+    K, V, q = (wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(x * rng.standard_normal(shape).astype(np.float32)))
+               for x, shape in ((1.0, (n, 2, 128)), (1.0, (n, 2, 128)), (0.1, (new, 8, 128))))
+    K[:, :, :2], q[:, :, :2] = 0.0, 1.0
+    return K, V, q
+
+
+def exact_tile(K, V, q, keep):
+    """The same in float64 over the tokens of `keep` [tokens][2] that a row sees."""
+    n, new = K.shape[0], q.shape[0]
+    o, ls = np.zeros(q.shape), np.zeros(q.shape[:2])
+    for i in range(new):
+        for h in range(8):
+            seen = np.flatnonzero(keep[:n - new + i + 1, h // 4])
+            s = K[seen, h // 4].astype(np.float64) @ q[i, h].astype(np.float64) * LN2
+            ls[i, h] = s.max() + np.log(np.exp(s - s.max()).sum())
+            o[i, h] = np.exp(s - ls[i, h]) @ V[seen, h // 4]
+    return o, ls
+
+
+@pytest.mark.parametrize("token", [0, 31, 32, 63, 330, 360, 703, 704, 713, 719])     # either half of a block, the causal part
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_a_key_without_a_score_gives_nan_to_the_rows_that_see_it(gpu, bad, token):  # noqa: F811
+    new, n = 16, 720
+    K, V, q = one_tile_inputs(n, new)
+    K[token, 0, 5] = 0.0
+    q[:, :, 5] = 0.25
+    exp_o, exp_l = exact_tile(K, V, q, np.ones((n, 2), dtype=bool))
+    clean_o, clean_l, repeated = one_tile(gpu, K, V, q, new)
+    assert repeated == 0
+    check_close(clean_o, exp_o, "finite keys")
+    K[token, 0, 5] = bad
+    got_o, got_l, repeated = one_tile(gpu, K, V, q, new)
+    hit = np.zeros((new, 8), dtype=bool)
+    hit[max(0, token - (n - new)):, :4] = True
+    assert repeated == 1 and np.isnan(got_o[hit]).all() and np.isnan(got_l[hit]).all()
+    assert np.array_equal(got_o[:, 4:], clean_o[:, 4:]) and np.array_equal(got_l[:, 4:], clean_l[:, 4:])
+    check_close(got_o[~hit], exp_o[~hit], f"{bad} at {token}")
+    check_lse(got_l[~hit], exp_l[~hit], f"{bad} at {token}")
+
+
+@pytest.mark.parametrize("level", [0.0, -300.0])         # of the other keys, in powers of two: below what a reference of 0 would leave of them
+@pytest.mark.parametrize("quiet", ["first step", "second half's first step", "first half", "second half", "all"])
+def test_keys_that_score_minus_infinity(gpu, quiet, level):  # noqa: F811
+    new, n = 16, 720
+    K, V, q = one_tile_inputs(n, new)
+    K[:, :, 1] = level
+    at = np.arange(n)
+    out = {"first step": at < 32, "second half's first step": (at >= 32) & (at < 64), "first half": at % 64 < 32, "second half": at % 64 >= 32,
+           "all": at >= 0}[quiet]
+    K[out, 0, 0] = -np.inf                               # of KV head 0 only
+    keep = np.ones((n, 2), dtype=bool)
+    keep[out, 0] = quiet == "all"
+    exp_o, exp_l = exact_tile(np.where(np.isinf(K), 0.0, K), V, q, keep)
+    got_o, got_l, repeated = one_tile(gpu, K, V, q, new)
+    rest = slice(4, 8) if quiet == "all" else slice(0, 8)
+    assert repeated == 1
+    if quiet == "all":
+        assert np.isnan(got_o[:, :4]).all() and np.isnan(got_l[:, :4]).all()
+    check_close(got_o[:, rest], exp_o[:, rest], quiet)
+    check_lse(got_l[:, rest], exp_l[:, rest], quiet, tol=2e-3 + 1e-6 * np.abs(exp_l).max())
