@@ -11,8 +11,7 @@
 #include <random>
 #include <vector>
 
-#include "../../include/heliumkv.h"
-#include "../../paper_2603_16104_amd/csrc/hkv_internal.h"
+#include "../../paper_2603_16104_amd/csrc/api.cpp"  // (itself: what plans hold is looked at)
 
 namespace hkv {
 hipError_t launch_pool_write(const PoolWriteLaunch &, hipStream_t) { return hipSuccess; }
@@ -402,6 +401,57 @@ static void growing_plans(std::mt19937 &rng) {
     }
 }
 
+// What a prefill plan runs (tiles, or pieces of them) holds every (new token, KV head) once, heads side by side, and a run of whole
+// tiles in front of smaller ones: small batches in pieces, and batches of one to a few rounds with half tiles.
+static void prefill_pieces(std::mt19937 &rng) {
+    int in_pieces = 0, in_halves = 0;
+    for (int trial = 0; trial < 3000; ++trial) {
+        const int heads = 1 << rng() % 6, G = 1 + (int)(rng() % 16), n_req = 1 + (int)(rng() % 40), most = 1 + (int)(rng() % (rng() % 4 ? 300 : 1200));
+        std::vector<int32_t> cu{0}, kv_len;
+        const int prefix = rng() % 3 ? 16 * (int)(rng() % 200) : 0;
+        for (int r = 0; r < n_req; ++r) {
+            const int s = rng() % 8 ? 1 + (int)(rng() % most) : rng() % 2 ? 0 : most;
+            cu.push_back(cu.back() + s);
+            kv_len.push_back(prefix + s);
+        }
+        const int max_pages = (prefix + most + 15) / 16;
+        std::vector<int32_t> table((size_t)n_req * max_pages);
+        for (size_t i = 0; i < table.size(); ++i) table[i] = (int32_t)(i % max_pages);
+        hkv_pool *pool = make_pool(max_pages, heads, HKV_BF16);
+        hkv_prefill_plan *pl = nullptr;
+        CHECK(hkv_prefill_plan_create(pool, cu.data(), table.data(), max_pages, kv_len.data(), n_req, heads * G, HKV_PLAN_HOST_ONLY, &pl) == HKV_OK);
+        if (!pl) continue;
+        const std::vector<hkv::PrefillTile> &run = pl->pieces.empty() ? pl->tiles : pl->pieces;
+        CHECK(run.size() % heads == 0 && (pl->pieces.empty() || pl->segments.empty()));
+        std::vector<int> covered((size_t)cu.back() * heads, 0);
+        bool small = false, order = true, fields = true;
+        int wholes = 0;
+        for (size_t i = 0; i < run.size(); ++i) {
+            const hkv::PrefillTile &t = run[i];
+            const int s = cu[t.req + 1] - cu[t.req];
+            fields = fields && t.kv_head == (int)(i % heads) && t.n_q > 0 && t.n_q * G <= 256 && t.q_begin >= 0 && t.q_begin + t.n_q <= s &&
+                     t.q_row0 == cu[t.req] + t.q_begin && t.prefix_len == kv_len[t.req] - s && t.kv_len == kv_len[t.req] && t.bt_off == t.req * max_pages;
+            if (!fields) break;
+            if (!pl->pieces.empty()) {
+                order = order && !(small && t.n_q * G > 128);
+                small = small || t.n_q * G <= 128;
+                wholes += t.n_q * G > 128;
+            }
+            for (int q = 0; q < t.n_q; ++q) ++covered[(size_t)(t.q_row0 + q) * heads + t.kv_head];
+        }
+        CHECK(fields);
+        CHECK(order);
+        CHECK(wholes % (256 / heads * heads) == 0);  // whole rounds on 256 compute units
+        CHECK(std::all_of(covered.begin(), covered.end(), [](int c) { return c == 1; }));
+        in_pieces += !pl->pieces.empty() && wholes == 0;
+        in_halves += wholes > 0;
+        CHECK(hkv_prefill_plan_destroy(pl) == HKV_OK);
+        CHECK(kv_pool_destroy(pool) == HKV_OK);
+    }
+    CHECK(in_pieces > 100 && in_halves > 20);
+    std::printf("prefill: %d plans in pieces, %d with whole and half tiles\n", in_pieces, in_halves);
+}
+
 int main() {
     std::mt19937 rng(20260316u);
     pool_traces(rng);
@@ -409,6 +459,7 @@ int main() {
     scheduling_layer(rng);
     prefix_cache(rng);
     growing_plans(rng);
+    prefill_pieces(rng);
     std::printf("host_check: %d failed checks\n", failures);
     return failures ? 1 : 0;
 }

@@ -17,8 +17,8 @@ def test_host_layer_under_asan_and_ubsan(tmp_path):
         pytest.skip("needs g++ and the HIP runtime library")
     exe = str(tmp_path / "host_check")
     cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
-           "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", os.path.join(ROOT, "tests", "native", "host_check.cpp"),
-           os.path.join(CSRC, "api.cpp"), os.path.join(CSRC, "trt.cpp"), os.path.join(CSRC, "cache.cpp"),
+           "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", os.path.join(ROOT, "tests", "native", "host_check.cpp"),  # (includes api.cpp)
+           os.path.join(CSRC, "trt.cpp"), os.path.join(CSRC, "cache.cpp"),
            "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib", "-o", exe]
     subprocess.check_call(cmd)
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0")
