@@ -3,7 +3,7 @@ leaves, optionally a second shared level; any node may end inside a page), a hea
 hkv_decode_plan_params / flags, builds the plan through hkv_decode_plan_create_ex and compares the step, element by
 element, with the fp64 oracle.  The draws reach the one-launch path, the two-kernel path (tile kernel beside the
 kernel that streams the other nodes, on one or two streams), plans without tile items, ragged chunks of every
-kind and the fp8 matrix instruction."""
+kind, the forms of bf16 items of 17 to 128 rows and the fp8 matrix instruction."""
 import numpy as np
 import pytest
 
@@ -53,13 +53,14 @@ def draw_case(seed):
     from paper_2603_16104_amd import binding as hkv
     if pick(0.2): flags |= hkv.PLAN_ONE_STREAM
     if kv_dtype == wl.KV_FP8_E4M3 and pick(0.1): flags |= hkv.PLAN_FP8_MATRIX
+    if kv_dtype == wl.KV_BF16 and pick(0.8): flags |= int(rng.choice([hkv.PLAN_NARROW_TILES, hkv.PLAN_WIDE_TILES, hkv.PLAN_TALL_TILES, hkv.PLAN_TALL_TILES]))
     return w, st, flags
 
 
 def test_random_forests_and_planner_settings(gpu, oracle):
     import torch
     from paper_2603_16104_amd import binding as hkv
-    seen = {"one_launch": 0, "two_kernels": 0, "no_tiles": 0}
+    seen = {"one_launch": 0, "two_kernels": 0, "no_tiles": 0, "tall": 0}
     for seed in range(9000, 9040):
         w, st, flags = draw_case(seed)
         f, hq = w.forest, w.num_q_heads
@@ -74,10 +75,12 @@ def test_random_forests_and_planner_settings(gpu, oracle):
         torch.cuda.synchronize()
         tiles, fused = hkv.hkv_decode_plan_num_tile_items(plan), hkv.hkv_decode_plan_is_fused(plan)
         seen["one_launch" if fused else "two_kernels" if tiles else "no_tiles"] += 1
+        items = hkv.hkv_decode_plan_items(plan)
+        seen["tall"] += bool((items[: len(items) - tiles, 4] * (hq // w.num_kv_heads) > 64).any())
         hkv.hkv_decode_plan_destroy(plan)
         dp.close()
         what = f"{w.name} {hq}/{w.num_kv_heads} dtype {w.kv_dtype} flags {flags} {st}"
         check_close(gpu.bf16_tensor_to_f64(out), exp_o, what)
         check_lse(lse.cpu().numpy(), exp_l, what)
     print(seen)
-    assert min(seen.values()) >= 3, seen      # the draws do reach all three launch shapes
+    assert min(seen.values()) >= 3, seen      # the draws do reach all three launch shapes and the tall items

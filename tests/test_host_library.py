@@ -731,13 +731,18 @@ def test_form_and_chunks_keep_a_plan_within_the_static_workspace(heads, tokens, 
 
 def items_of(parent, ntok, leaves, hq, hk, dtype=hkv.BF16, T=1, flags=0):
     """Work items of a host-only plan over a forest in page order, and whether shared ones run as 32-row tiles."""
+    return all_items_of(parent, ntok, leaves, hq, hk, dtype, T, flags)[:2]
+
+
+def all_items_of(parent, ntok, leaves, hq, hk, dtype, T, flags, visible=None):
+    """The same, and how many of the items (the last ones) run on the 256-row tile kernel."""
     f = wl.make_forest(parent, ntok, leaves, np.arange(sum((t + 15) // 16 for t in ntok), dtype=np.int32))
     pool = fake_pool(len(f.node_pages), hk, dtype)
-    plan = hkv.hkv_decode_plan_create_ex(pool, f.nodes, f.node_pages, f.req_leaf, hq, hkv.PLAN_HOST_ONLY | flags, tokens_per_req=T)
-    items, wide = hkv.hkv_decode_plan_items(plan), hkv.hkv_decode_plan_has_wide_tiles(plan)
+    plan = hkv.hkv_decode_plan_create_ex(pool, f.nodes, f.node_pages, f.req_leaf, hq, hkv.PLAN_HOST_ONLY | flags, tokens_per_req=T, visible=visible)
+    items, wide, n_tile = hkv.hkv_decode_plan_items(plan), hkv.hkv_decode_plan_has_wide_tiles(plan), hkv.hkv_decode_plan_num_tile_items(plan)
     hkv.hkv_decode_plan_destroy(plan)
     hkv.kv_pool_destroy(pool)
-    return items, wide
+    return items, wide, n_tile
 
 
 @pytest.mark.parametrize("G, n_req, narrow, wide", [(8, 18, {8, 2}, {6}), (4, 36, {16, 4}, {12}), (4, 21, {11, 10}, {11, 10}), (1, 65, {64, 1}, {33, 32})])
@@ -764,6 +769,38 @@ def test_form_of_shared_items_is_the_one_that_measured_shorter(tokens, fan, head
     assert items_of(parent, ntok, level, *heads, T=T)[1] == wide
     for flags in (hkv.PLAN_NARROW_TILES, hkv.PLAN_WIDE_TILES):
         assert items_of(parent, ntok, level, *heads, T=T, flags=flags)[1] == (flags == hkv.PLAN_WIDE_TILES)
+
+
+@pytest.mark.parametrize("tokens, n_req, heads, T, dtype, tall", [
+    ((2048, 512), 64, (32, 8), 21, hkv.BF16, True), ((2048, 512), 64, (32, 8), 16, hkv.BF16, True), ((2626, 613), 49, (64, 8), 8, hkv.BF16, True),
+    ((2048, 512), 64, (32, 8), 21, hkv.FP8_E4M3, False), ((512, 64), 64, (32, 8), 4, hkv.BF16, False), ((309, 44), 8, (32, 8), 8, hkv.BF16, False),
+    ((2048, 512), 64, (32, 8), 1, hkv.BF16, False)])
+def test_tall_items_are_for_long_verification_steps(tokens, n_req, heads, T, dtype, tall):
+    """Items of more than 64 rows: bf16 pools, steps of some 35 us and more."""
+    G = heads[0] // heads[1]
+    visible = None if T <= 16 else np.tile((np.uint64(2) << np.arange(T, dtype=np.uint64)) - np.uint64(1), n_req)
+    items, wide, n_tile = all_items_of([-1] + [0] * n_req, [tokens[0]] + [tokens[1]] * n_req, list(range(1, n_req + 1)), *heads, dtype, T, 0, visible)
+    rows = items[: len(items) - n_tile, 4] * G
+    assert (rows.max() > 64) == tall and rows.max() <= 128 and (wide or not tall)
+
+
+def test_rows_of_items_of_random_plans():
+    """Up to 64 rows, 128 in bf16 plans with 32-row tiles that no setting or flag rules out; every (request, head, token) of a node in one item."""
+    rng, tall = np.random.default_rng(11), 0
+    for _ in range(150):
+        hq, hk = [(32, 8), (64, 8), (8, 2), (5, 1), (4, 4), (16, 1), (33, 3)][rng.integers(7)]
+        n_req, T = int(rng.integers(1, 70)), int(rng.choice([1, 4, 8, 16]))
+        root, leaf = int(rng.integers(1, 5000)), T + int(rng.integers(0, 900))
+        dtype = [hkv.BF16, hkv.BF16, hkv.FP8_E4M3][rng.integers(3)]
+        flags = int(rng.choice([0, 0, 0, hkv.PLAN_NARROW_TILES, hkv.PLAN_WIDE_TILES, hkv.PLAN_TALL_TILES]))
+        items, wide, n_tile = all_items_of([-1] + [0] * n_req, [root] + [leaf] * n_req, list(range(1, n_req + 1)), hq, hk, dtype, T, flags)
+        rows = items[: len(items) - n_tile, 4] * (hq // hk)
+        tall += rows.max() > 64
+        assert rows.max() <= (128 if dtype == hkv.BF16 and wide and flags in (0, hkv.PLAN_TALL_TILES) else 64)
+        for v in (0, 1):
+            own = items[items[:, 7] == v]
+            assert (own[:, 1] * own[:, 4]).sum() == hk * (root * n_req * T if v == 0 else leaf * T)
+    assert tall > 10
 
 
 @pytest.mark.parametrize("dtype, roots, tokens, n_req, heads, T, least, most", [
