@@ -221,6 +221,28 @@ constexpr int kMaxRowParts = 32;
 constexpr int kMinCutPages = 64, kMinHalvedPages = 72;  // rows whose longest has fewer stay whole (the latter: where there would be two shares)
 constexpr int kRowPartFloats = kHeadDim + 4;  // o, reference, row sum; 16-byte pieces
 constexpr int kRowWorkgroups = 256;           // what fills the chip: rows are cut, or given fewer of their heads a workgroup, until there are so many
+// Query heads of a KV head that a workgroup of theirs takes: they share its K/V reads, which are what long rows are bound by (a compute unit
+// takes in about 110 bytes per ns).  Four, where every compute unit then still has a workgroup, for half as many workgroups that cost 1.25 times
+// as much each: what counts is how many rounds of them a compute unit gets.  1277 shapes, head ratios 3 to 16, keys shared or private, time
+// over that with two heads:
+// - rows of more than 16 pages: 0.51 to 0.96 with fewer rounds (32 requests x 32 / 8 heads over 1024 + 256 tokens 36.0 -> 25.0 us, 16 x 64 / 8
+//   32.8 -> 21.4), 1.04 to 1.17 with as many (17 to 21 requests x 40 / 8, two rounds either way);
+// - 9 to 16 pages: 0.56 to 0.97 with up to 0.7 of the rounds (1.05 at worst, private keys of 33 requests x 32 / 8), 0.94 to 1.19 above;
+// - 5 to 8 pages: 0.61 to 1.02 with up to 0.6 of five rounds and more, of fewer 0.96 to 1.22 (33 x 32 / 8 over 48 + 30 7.9 -> 8.7).  Where the
+//   workgroups of a row's KV head lie on different XCDs (neighbours in the grid are num_kv_heads apart) two heads read private keys from
+//   memory twice: 0.61 to 0.85, shared ones up to 1.13;
+// - ratios that four does not divide, 5 to 8 pages: 33 x 40 / 8 over 96 + 17 10.4 -> 11.1; up to 4 pages 48 x 32 / 8 over 16 + 30 7.7 -> 8.6.
+inline int row_heads_per_workgroup(int64_t n_rows, int num_kv_heads, int group, int max_pages, bool in_shares) {
+    if (group <= 2) return group;
+    if (in_shares) return 4;
+    const int64_t n4 = n_rows * num_kv_heads * ((group + 3) / 4), n2 = n_rows * num_kv_heads * ((group + 1) / 2);
+    const int64_t four = (n4 + kRowWorkgroups - 1) / kRowWorkgroups, two = (n2 + kRowWorkgroups - 1) / kRowWorkgroups;
+    if (n4 < kRowWorkgroups || max_pages <= 4) return 2;
+    if (max_pages > 16) return four < two ? 4 : 2;
+    if (max_pages > 8) return 10 * four <= 7 * two ? 4 : 2;
+    if (group % 4 != 0) return 2;
+    return num_kv_heads % 8 != 0 ? (10 * four <= 7 * two ? 4 : 2) : two >= 5 && 10 * four <= 6 * two ? 4 : 2;
+}
 
 // Largest token count of a decode item that is shared by more than 16 query rows.
 constexpr int kMaxSharedItemTokens = 2048;

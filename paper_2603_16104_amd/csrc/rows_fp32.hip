@@ -22,7 +22,7 @@ namespace {
 // K, (dimension, quarter of the slots) for V, so a dot product is 32 multiply-adds in a lane and two adds over its quad.  A wavefront
 // per (token, head) with a lane per key read 64-byte pieces, walked all keys alone and took 118 us for 16 requests x 32 heads over
 // 1024 + 256 tokens on half of the chip, with three times the rounding error, the dot products being longer chains; two heads a
-// workgroup take 18.2 us there (512 new tokens over 2048: 3.02 -> 0.77 ms).  Four heads and twice the rows: see heads_per_workgroup.
+// workgroup take 18.2 us there (512 new tokens over 2048: 3.02 -> 0.77 ms).  Four heads and twice the rows: see row_heads_per_workgroup.
 // SPLIT: a workgroup takes one of n_parts shares of its rows' steps and leaves its sums to rows_fp32_merge_kernel, so that few rows
 // use the whole chip: those 16 requests 18.2 -> 16.8 us (two shares of four heads), 4 of them 17.4 -> 11.7, one over 4196 tokens 44.1 -> 16.1,
 // 32 of 8 / 2 heads over 2348 25.9 -> 19.4.
@@ -271,18 +271,6 @@ __global__ __launch_bounds__(256) void pool_write_fp32_kernel(PoolWriteLaunch a)
 
 }  // namespace
 
-namespace {
-// Query heads of a KV head that a workgroup takes: they share its K/V reads, which are what long rows are bound by (a compute unit takes in
-// about 110 bytes per ns).  Four where that still gives every compute unit a workgroup, and where a wavefront has more than a step
-// or two: 32 requests x 32 / 8 heads over 1024 + 256 tokens 36.0 -> 25.0 us, 16 x 64 / 8 32.8 -> 21.4, 2 x 64 new tokens over 512 69.8 -> 42.8;
-// but 48 x 32 / 8 over 16 + 30 tokens 7.7 -> 8.6, and 33 x 40 / 8 over 96 + 17 10.4 -> 11.1.
-int heads_per_workgroup(const RowsLaunch &a, int Hkv, int G) {
-    if (G <= 2) return G;
-    const bool short_rows = a.max_pages <= 4 || (a.max_pages <= 8 && G % 4 != 0);
-    return a.n_parts > 1 || (!short_rows && (int64_t)a.n_q_tokens * Hkv * ((G + 3) / 4) >= kRowWorkgroups) ? 4 : 2;
-}
-}  // namespace
-
 hipError_t launch_rows_fp32(const RowsLaunch &a, hipStream_t s) {
     const int Hkv = a.pool.num_kv_heads, G = a.num_q_heads / Hkv;
     const bool split = a.n_parts > 1;
@@ -290,7 +278,7 @@ hipError_t launch_rows_fp32(const RowsLaunch &a, hipStream_t s) {
     // a step is 32 keys (four heads: 16): sequences that never reach four steps a wavefront would pay for wavefronts without one (128 query
     // tokens of 17 to 32 keys, 32 heads: 24.2 us with eight, 12.5 us with two; a share has about 128 keys and more of the longest row, and what there is of the others)
     const int waves = split || a.max_pages > 16 ? kRowWaves : a.max_pages > 8 ? 4 : 2;
-    const int rows = heads_per_workgroup(a, Hkv, G);
+    const int rows = row_heads_per_workgroup(a.n_q_tokens, Hkv, G, a.max_pages, split);
     const size_t per_token = (size_t)Hkv * ((G + rows - 1) / rows) * std::max(1, a.n_parts);
     const size_t most = std::max<size_t>(1, ((size_t)1 << 31) / (per_token * 64 * waves));  // query tokens of a launch: below 2^32 threads
     for (size_t t0 = 0; t0 < (size_t)std::max(a.n_q_tokens, 0); t0 += most) {

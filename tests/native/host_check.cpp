@@ -401,6 +401,22 @@ static void growing_plans(std::mt19937 &rng) {
     }
 }
 
+// Rows over an fp32 pool: four heads a workgroup where that measured shorter, two on the other side of each line.
+static void row_heads() {
+    using hkv::row_heads_per_workgroup;
+    const struct { int rows, kv_heads, group, pages, heads; } points[] = {
+        {17, 8, 5, 20, 2}, {21, 8, 5, 40, 2}, {24, 8, 5, 20, 4}, {32, 8, 4, 17, 4}, {33, 8, 4, 40, 4}, {17, 8, 8, 72, 4}, {31, 8, 4, 40, 2},  // long rows
+        {17, 8, 5, 9, 2}, {24, 8, 5, 9, 4}, {32, 8, 4, 16, 4}, {33, 8, 4, 12, 4}, {16, 8, 8, 16, 4}, {64, 8, 5, 9, 4}, {35, 8, 5, 12, 2},      // 9 to 16 pages
+        {33, 8, 4, 5, 2}, {64, 8, 4, 8, 2}, {70, 8, 4, 8, 4}, {192, 2, 4, 8, 4}, {90, 8, 5, 8, 2}, {100, 8, 4, 4, 2},                          // short rows
+        {500, 8, 1, 40, 1}, {500, 8, 2, 40, 2}};
+    for (const auto &p : points) {
+        const int heads = row_heads_per_workgroup(p.rows, p.kv_heads, p.group, p.pages, false);
+        if (heads != p.heads) std::fprintf(stderr, "%d rows x %d KV heads, ratio %d, %d pages: %d\n", p.rows, p.kv_heads, p.group, p.pages, heads);
+        CHECK(heads == p.heads);
+        CHECK(row_heads_per_workgroup(p.rows, p.kv_heads, p.group, p.pages, true) == (p.group <= 2 ? p.group : 4));
+    }
+}
+
 // What a prefill plan runs (tiles, or pieces of them) holds every (new token, KV head) once, heads side by side, and a run of whole
 // tiles in front of smaller ones: small batches in pieces, and batches of one to a few rounds with half tiles.
 static void prefill_pieces(std::mt19937 &rng) {
@@ -460,6 +476,7 @@ int main() {
     prefix_cache(rng);
     growing_plans(rng);
     prefill_pieces(rng);
+    row_heads();
     std::printf("host_check: %d failed checks\n", failures);
     return failures ? 1 : 0;
 }

@@ -21,7 +21,7 @@ def batch(gpu, oracle, hq, hk, lens):  # noqa: F811
 
 
 @pytest.mark.parametrize("hq, hk", [(2, 1), (3, 1), (4, 1), (5, 1), (8, 2), (16, 1), (7, 1)])
-@pytest.mark.parametrize("lens", [(140,) * 300, (129, 0, 1, 143, 144, 145, 700, 16) * 35])
+@pytest.mark.parametrize("lens", [(140,) * 300, (129, 0, 1, 143, 144, 145, 700, 16) * 35, (140, 129) * 300, (100, 1, 128, 65) * 160])
 def test_four_heads(gpu, oracle, hq, hk, lens):  # noqa: F811
     import torch
     w, dp, exp_o, exp_l = batch(gpu, oracle, hq, hk, lens)
