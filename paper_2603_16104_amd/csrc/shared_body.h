@@ -95,7 +95,7 @@ __device__ __forceinline__ void body(const DecodeLaunch &a, const DecodeItem &it
     const int id_lane = ids[min(4 * lane + wave, last_page)];
     // In the same round trip as the ids (the requests below wait for those, and what stands behind them is loaded one trip later), as
     // the three words of a row's visibility are: with these and the partials going out in pieces of 16 bytes instead of 8, 512 rows
-    // below 4096 tokens and 64 below each of 8 x 1024 35.13 -> 34.55 us, 100 requests x 5 heads over fp8 53.31 -> 52.76.
+    // below 4096 tokens and 64 below each of 8 x 1024 35.13 -> 34.55 us (100 requests x 5 heads over fp8 53.31 -> 52.76, no more than runs differ).
     const int row = 32 * rt + n, rowc = min(row, rows - 1);
     const int req = a.node_req_idx[it.req_off + rowc / G];
     // fp8: lane 32 j + b holds the scales of page 4 b + 2 th + j, the page whose tokens half j of the wavefront scores
