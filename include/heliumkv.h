@@ -393,7 +393,7 @@ int hkv_decode_plan_destroy(hkv_decode_plan *plan);
 /* Bytes of device workspace attn_decode_plan_run needs (per partial: o as 128 fp16 values times a power of two,
  * that power's reciprocal and lse as floats),
  * 0 on a null plan.  fp32 pools: the bytes with which a run spreads few rows over the chip (528 per query row and share of its keys,
- * 540 KB at most; 0 where the rows are many or short): a run without them, also one given less, keeps its rows whole. */
+ * 540 KB at most; 0 where the rows are many or short, or keep too much K/V of their own): a run without them, also one given less, keeps its rows whole. */
 size_t hkv_decode_plan_workspace_bytes(const hkv_decode_plan *plan);
 /* Introspection for tests and tools (host copies).  Work item layout, 8 int32 each:
  * (page_off, n_tokens, kv_head, req_off, n_req, part_slot, tok_begin, node).  page_off indexes

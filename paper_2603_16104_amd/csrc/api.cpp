@@ -1483,6 +1483,8 @@ static int upload_decode_plan(hkv_decode_plan &pl) {
 static int build_fp32_rows(hkv_decode_plan &pl, bool upload) {
     const int n = pl.n_req;
     std::vector<std::vector<int32_t>> paths(n);
+    std::vector<char> seen(pl.nodes.size(), 0);
+    int64_t n_pages = 0;  // of the nodes on some row's path
     pl.row_len.assign(n, 0);
     pl.max_pages = 1;
     for (int r = 0; r < n; ++r) {
@@ -1490,21 +1492,15 @@ static int build_fp32_rows(hkv_decode_plan &pl, bool upload) {
         for (int v = pl.req_leaf[r]; v >= 0; v = pl.nodes[v].parent) chain.push_back(v);
         for (auto it = chain.rbegin(); it != chain.rend(); ++it) {
             const hkv_node &nd = pl.nodes[*it];
+            if (!seen[*it]) n_pages += nd.n_pages;
+            seen[*it] = 1;
             paths[r].insert(paths[r].end(), pl.node_pages.begin() + nd.page_begin, pl.node_pages.begin() + nd.page_begin + nd.n_pages);
             pl.row_len[r] += nd.n_tokens;
         }
         pl.max_pages = std::max<int32_t>(pl.max_pages, (int32_t)paths[r].size());
     }
-    // Few rows leave compute units idle, and a row's workgroup takes in no more than one can: its keys are cut, down to 128 a share,
-    // until every compute unit has a share (of up to four heads).  The second kernel takes 3 us, so shorter rows stay whole: over 518
-    // keys 9.6 -> 10.6 us for one request (32 / 8 heads), 11.2 -> 12.9 for 16; over 1020 keys 14.3 -> 10.6 for 2.
-    // Two shares save half of the walk at most and pay later.  Their time over the whole rows', at head ratios of 1, 2, 4 and 8: over 1020
-    // keys 0.97 to 1.01, 0.93 to 0.95, 0.95 to 1.01 and 1.02, over 1148 keys 0.92 to 0.97, 0.90, 0.93 to 0.98 and 0.99 (ratio 5: 1.00 to
-    // 1.01), over 1276 keys 0.90 to 0.94, 0.88, 0.91 to 0.93 and 0.94 (16 x 32 / 8 over 1260 17.0 -> 15.9, over 1532 19.6 -> 17.3).
-    const int G = pl.group, heads = G <= 2 ? G : 4;
-    const int64_t units = std::max<int64_t>(1, (int64_t)n * pl.pool->d.num_kv_heads * ((G + heads - 1) / heads));
-    pl.row_parts = (int32_t)std::max<int64_t>(1, std::min<int64_t>({kMaxRowParts, kRowWorkgroups / units, pl.max_pages / 8}));
-    if (pl.max_pages < (pl.row_parts == 2 ? kMinHalvedPages : kMinCutPages)) pl.row_parts = 1;
+    const double page_mb = 1e-6 * 2 * kBlockElems * sizeof(float) * pl.pool->d.num_kv_heads;
+    pl.row_parts = row_shares(n, pl.pool->d.num_kv_heads, pl.group, pl.max_pages, page_mb * n_pages);
     if (!upload || n == 0) return HKV_OK;
     std::vector<int32_t> bt((size_t)n * pl.max_pages, 0), req(n);
     for (int r = 0; r < n; ++r) {

@@ -218,9 +218,30 @@ struct RowsLaunch {
     float *part_data;
 };
 constexpr int kMaxRowParts = 32;
-constexpr int kMinCutPages = 64, kMinHalvedPages = 72;  // rows whose longest has fewer stay whole (the latter: where there would be two shares)
 constexpr int kRowPartFloats = kHeadDim + 4;  // o, reference, row sum; 16-byte pieces
 constexpr int kRowWorkgroups = 256;           // what fills the chip: rows are cut, or given fewer of their heads a workgroup, until there are so many
+// Shares that the keys of a decode plan's rows are cut into (1: rows stay whole), where the caller gives room for their results.  Few rows
+// leave compute units idle, and a row's workgroup takes in no more than one can: shares of up to four heads, down to 128 keys each, until
+// every compute unit has one.  They save their part of the walk, 0.13 us a page, less 4.5 us for the second kernel and a second start, so
+// shorter rows stay whole: over 518 keys 9.6 -> 10.6 us for one request (32 / 8 heads), 11.2 -> 12.9 for 16; over 1020 keys 14.3 -> 10.6 for 2.
+// But keys that are read all at once come slower than a walk reads them: 0.1 us more for each MB beyond 40 (ratio 1: 0.13 beyond 15) of the
+// plan's K/V.  Not so where it comes from memory anyway (128 MB and more, three shares and more), where the walk is long (100 pages; ratio 1, three
+// shares and more, 160), and where a row's keys are read from memory twice without shares, by workgroups of two heads on different XCDs.  1214
+// plans of 64 to 400 pages, ratios 1 to 16, keys shared in all proportions, time over the whole rows', K/V from the last-level cache
+// and from memory: where shares are taken 0.21 to 1.14 and 0.33 to 0.98 (0.78 and 0.71 in the mean), else 0.84 to 1.53 (16 requests x 4 / 4
+// heads over 1021 keys of their own 15.5 -> 23.8 us) and 0.68 to 1.13 (1.10 and 0.90).
+inline int row_shares(int64_t n_rows, int num_kv_heads, int group, int max_pages, double plan_mb) {
+    const int heads = group <= 2 ? group : 4;
+    const int64_t units = n_rows * num_kv_heads * ((group + heads - 1) / heads);
+    int64_t shares = units > 0 ? kRowWorkgroups / units : 1;
+    if (shares > max_pages / 8) shares = max_pages / 8;
+    if (shares > kMaxRowParts) shares = kMaxRowParts;
+    if (shares < 2 || max_pages < (shares == 2 ? 72 : 64)) return 1;
+    if (group > 2 && num_kv_heads % 8 != 0) return (int)shares;
+    const double saved = 0.13 * max_pages * (1.0 - 1.0 / (double)shares) - 4.5;
+    const bool far = plan_mb >= 128.0 && shares > 2, long_rows = group == 1 ? max_pages >= 160 && shares > 2 : max_pages >= 100;
+    return far || long_rows || plan_mb <= (group == 1 ? 15.0 + saved / 0.13 : 40.0 + saved / 0.1) ? (int)shares : 1;
+}
 // Query heads of a KV head that a workgroup of theirs takes: they share its K/V reads, which are what long rows are bound by (a compute unit
 // takes in about 110 bytes per ns).  Four, where every compute unit then still has a workgroup, for half as many workgroups that cost 1.25 times
 // as much each: what counts is how many rounds of them a compute unit gets.  1277 shapes, head ratios 3 to 16, keys shared or private, time

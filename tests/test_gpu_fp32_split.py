@@ -8,7 +8,7 @@ from paper_2603_16104_amd import binding as hkv, workloads as wl
 
 from test_gpu_fp32_rows import exact_row, row_inputs
 from test_gpu_fp32_rows_heads import batch
-from test_gpu_parity import check_close_fp32, check_lse, gpu  # noqa: F401
+from test_gpu_parity import both_pools, check_close_fp32, check_lse, gpu  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -32,9 +32,27 @@ def test_shares(gpu, oracle, hq, hk, lens):  # noqa: F811
     dp.close()
 
 
-@pytest.mark.parametrize("hq, hk, lens", [(32, 8, (1137,) * 16), (8, 8, (1152, 1151, 17, 0) * 4), (24, 8, (1300,) * 11 + (570,)), (32, 8, (1009,) * 10)])
-def test_two_and_three_shares(gpu, oracle, hq, hk, lens):  # noqa: F811
-    test_shares(gpu, oracle, hq, hk, lens)
+@pytest.mark.parametrize("hq, hk, root, lens, shares", [(32, 8, 1120, (17, 32, 1, 31) * 4, 2), (8, 8, 1136, (16, 1, 64, 15) * 4, 2),
+                                                        (24, 8, 1200, (100, 1, 7, 0) * 3, 2), (32, 8, 1008, (1, 16) * 5, 3), (6, 2, 0, (1152, 1151, 17, 0) * 12, 2)])
+def test_two_and_three_shares(gpu, oracle, hq, hk, root, lens, shares):  # noqa: F811
+    import torch
+    parent, ntok = [-1] + [0 if root else -1] * len(lens), [root] + list(lens)
+    n_used = sum((t + 15) // 16 for t in ntok)
+    f = wl.make_forest(parent, ntok, list(range(1, len(lens) + 1)), np.random.default_rng(root).permutation(n_used + 3).astype(np.int32))
+    w = wl.Workload(name=f"fp32_{hq}_{hk}_{root}", num_q_heads=hq, num_kv_heads=hk, kv_dtype=wl.KV_FP32, num_pages=n_used + 3, seed=7,
+                    forest=f, mode="decode", src_dtype="fp32")
+    hp, dp = both_pools(gpu, oracle, w)
+    exp_o, exp_l = oracle.run_workload(w, hp)
+    r = gpu.DecodeRunner(dp, w)
+    assert hkv.hkv_decode_plan_workspace_bytes(r.plan) == 528 * len(lens) * hq * shares
+    r.out.fill_(float("nan"))
+    r.lse.fill_(float("nan"))
+    r.run()
+    torch.cuda.synchronize()
+    check_close_fp32(gpu.bf16_tensor_to_f64(r.out), exp_o, w.name)
+    check_lse(r.lse.cpu().numpy(), exp_l, w.name, tol=1e-4)
+    r.close()
+    dp.close()
 
 
 def test_workspaces(gpu, oracle):  # noqa: F811

@@ -877,13 +877,24 @@ def test_workspace_of_plans_that_run_whole_paths():
     hkv.kv_pool_destroy(pool)
 
 
-@pytest.mark.parametrize("hq, hk, n_req, tokens, shares", [
-    (32, 8, 16, 1136, 0), (32, 8, 16, 1137, 2), (32, 8, 16, 1264, 2), (32, 8, 17, 4000, 0), (64, 8, 8, 1264, 2), (4, 4, 32, 1152, 2), (4, 4, 32, 1100, 0),
-    (32, 8, 10, 1008, 0), (32, 8, 10, 1009, 3), (32, 8, 1, 600, 0), (32, 8, 1, 1100, 8), (32, 8, 1, 8000, 32)])
-def test_shares_of_few_fp32_rows(hq, hk, n_req, tokens, shares):
-    """Rows of an fp32 pool are cut from 64 pages on, into two shares from 72: the workspace holds 132 floats per row and share."""
-    pool = fake_pool(-(-tokens // 16), hk, hkv.FP32)
-    f = wl.make_forest([-1], [tokens], [0] * n_req, np.arange(-(-tokens // 16), dtype=np.int32))
+@pytest.mark.parametrize("hq, hk, n_req, tokens, own, shares", [
+    (32, 8, 16, 1136, 0, 0), (32, 8, 16, 1152, 0, 2), (32, 8, 16, 1264, 0, 2), (32, 8, 17, 4000, 0, 0), (64, 8, 8, 1264, 0, 2), (4, 4, 32, 1152, 0, 2),
+    (4, 4, 32, 1136, 0, 0), (32, 8, 10, 1008, 0, 0), (32, 8, 10, 1024, 0, 3), (32, 8, 1, 600, 0, 0), (32, 8, 1, 1104, 0, 8), (32, 8, 1, 8000, 0, 32),
+    (32, 8, 16, 1024, 240, 2), (32, 8, 16, 640, 640, 0), (32, 8, 16, 0, 1280, 0), (32, 8, 5, 0, 1280, 6), (32, 8, 10, 0, 1280, 0), (32, 8, 10, 0, 2560, 3),
+    (4, 4, 16, 992, 32, 4), (4, 4, 16, 512, 512, 0), (4, 4, 16, 0, 1024, 0), (4, 4, 4, 0, 1024, 8), (4, 4, 32, 576, 576, 0), (8, 2, 64, 0, 1152, 2),
+    (4, 4, 16, 0, 2560, 4), (32, 8, 16, 0, 1600, 2), (4, 4, 27, 0, 2560, 0), (16, 8, 10, 0, 1024, 0)])
+def test_shares_of_few_fp32_rows(hq, hk, n_req, tokens, own, shares):
+    """Rows of an fp32 pool over `tokens` shared and `own` tokens each: cut from 64 pages on, into two shares from 72, and where their K/V is not so
+    much that shares only read it all at once.  The workspace holds 132 floats per row and share."""
+    parent, ntok = ([-1], [tokens]) if tokens else ([], [])
+    leaves = [0] * n_req
+    if own:
+        leaves = [len(parent) + r for r in range(n_req)]
+        ntok = ntok + [own] * n_req
+        parent = parent + [0 if tokens else -1] * n_req
+    n_pages = sum(-(-t // 16) for t in ntok)
+    pool = fake_pool(n_pages, hk, hkv.FP32)
+    f = wl.make_forest(parent, ntok, leaves, np.arange(n_pages, dtype=np.int32))
     plan = hkv.hkv_decode_plan_create(pool, f.nodes, f.node_pages, f.req_leaf, hq, hkv.PLAN_HOST_ONLY)
     assert hkv.hkv_decode_plan_workspace_bytes(plan) == 528 * n_req * hq * shares
     hkv.hkv_decode_plan_destroy(plan)
