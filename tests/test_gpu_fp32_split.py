@@ -124,6 +124,7 @@ def test_values_that_must_not_spread(gpu, hq, hk, what):  # noqa: F811
     rest = np.ones(hq, dtype=bool)
     rest[bad] = False
     if rest.any():
-        exp, exp_l = exact_row(K, V, q, hq, keep)
+        with np.errstate(invalid="ignore"):   # (the bad rows too)
+            exp, exp_l = exact_row(K, V, q, hq, keep)
         check_close_fp32(got[rest], exp[rest], what)
         assert np.abs(got_l[rest] - exp_l[rest]).max() <= 1e-4
